@@ -64,9 +64,9 @@ __global__ __launch_bounds__(256) void bwd_prep_kernel(BwdArgs a) {
 
 
 // dK/dV kernel: 8 wavefronts in two groups of four. Two forms share the code below.
-// WIDE (the plain, half precision and padded instantiations): 256 keys per workgroup, wavefront
+// WIDE (every instantiation but the mask's): 256 keys per workgroup, wavefront
 // v owns keys 32*v.. and visits every tile; see the comment at `if constexpr (WIDE)`.
-// Otherwise (dropout, mask: their extra registers leave no room for K_j in registers, and K_j
+// Otherwise (mask: its extra registers leave no room for K_j in registers, and K_j
 // plus V_j of 256 keys do not fit in LDS): 128 keys per workgroup, wavefront (kg, grp) owns
 // keys 32*kg.. of the column block; the groups take the 32*QTW-row query tiles alternately
 // (group = tile index mod 2) and accumulate partial dK_j^T, dV_j^T over their own tiles.
@@ -94,8 +94,8 @@ __global__ __launch_bounds__(256) void bwd_prep_kernel(BwdArgs a) {
 // distinct operand.
 constexpr int kDkdvAhead = 4;  // how many MFMAs ahead the LDS operands are requested (3 where K_j takes the registers)
 // keys per workgroup of the dK/dV kernel instantiation (the launch needs it for the grid)
-constexpr bool dkdv_wide(int D, bool dropout, bool mask) { return !dropout && !mask; }
-constexpr int dkdv_block_keys(int D, bool dropout, bool mask) { return dkdv_wide(D, dropout, mask) ? 256 : 128; }
+constexpr bool dkdv_wide(bool mask) { return !mask; }
+constexpr int dkdv_block_keys(bool mask) { return dkdv_wide(mask) ? 256 : 128; }
 //
 // PAD: head dimension p.d below the tile width D, rows padded with zeros on chip (see the
 // forward kernel); only the first p.d columns of dK, dV are stored.
@@ -119,10 +119,10 @@ __global__ __launch_bounds__(512) void bwd_dkdv_kernel(BwdArgs a) {
   static_assert(DH == D || (PAD && DH % 32 == 0 && DH < D), "a narrower product width is for padded head dimensions");
   static_assert(!MASK || (!DROPOUT && !PAD), "the mask variant is built for the plain kernel");
   static_assert(!LOCAL || (!CAUSAL && !DROPOUT && !PAD && !MASK), "the window variant is built for the plain kernel");
-  constexpr bool KREG = !MASK && !DROPOUT;  // K_j operands of the wavefront's 32 keys in registers
-  constexpr bool VREG = D == 64 && !MASK && !DROPOUT;  // at d = 64 V_j's as well
-  constexpr bool WIDE = dkdv_wide(D, DROPOUT, MASK);
-  constexpr int BC = dkdv_block_keys(D, DROPOUT, MASK);  // keys per workgroup
+  constexpr bool KREG = !MASK;  // K_j operands of the wavefront's 32 keys in registers
+  constexpr bool VREG = D == 64 && !MASK;  // at d = 64 V_j's as well
+  constexpr bool WIDE = dkdv_wide(MASK);
+  constexpr int BC = dkdv_block_keys(MASK);  // keys per workgroup
   constexpr int QTW = D == 128 ? 1 : 2;  // 32-row query tiles per wavefront per step
   constexpr int BR = 32 * QTW;          // query rows of one tile
   constexpr int KS = DH / 16, DT = DH / 32;
@@ -301,6 +301,7 @@ __global__ __launch_bounds__(512) void bwd_dkdv_kernel(BwdArgs a) {
   // them, and with them for the copies in flight.
   float lraw = 0.f, draw = 0.f;
   bool stat_ok = false;
+  const float d_factor = DROPOUT ? 1.f - (float)p.drop_thr * (1.f / 256.f) : 1.f;  // (see phase_v)
   TileLoader<D, BR, 4, PAD> qloader;  // Q_i and dO_i tiles have the same shape and row pitch
   qloader.init(qstride, kg, lane, dh / 8);
   auto issue_loads = [&](const Cursor& c) {
@@ -333,7 +334,7 @@ __global__ __launch_bounds__(512) void bwd_dkdv_kernel(BwdArgs a) {
       // D is stored negated: it is the initial value of the dP accumulator (line 14).
       // (mask: a row left without keys has L = -inf and, like a row past the end, P = 0)
       *(float*)(smem + LS_OFF + o) = stat_ok && !((MASK || LOCAL) && lraw == -INFINITY) ? lraw * kLog2e : INFINITY;
-      *(float*)(smem + DV_OFF + o) = stat_ok ? -draw : 0.f;
+      *(float*)(smem + DV_OFF + o) = stat_ok ? -draw * d_factor : 0.f;
     }
   };
 
@@ -377,7 +378,7 @@ __global__ __launch_bounds__(512) void bwd_dkdv_kernel(BwdArgs a) {
         const float l = a.LSE[si_], dd = a.Dvec[si_];
         const int o = (c.slot * BR + tid - t * BR) * 4;
         *(float*)(smem + LS_OFF + o) = ok && !((MASK || LOCAL) && l == -INFINITY) ? l * kLog2e : INFINITY;
-        *(float*)(smem + DV_OFF + o) = ok ? -dd : 0.f;
+        *(float*)(smem + DV_OFF + o) = ok ? -dd * d_factor : 0.f;
       }
       advance(c, 1);
     }
@@ -519,20 +520,27 @@ __global__ __launch_bounds__(512) void bwd_dkdv_kernel(BwdArgs a) {
       }
       if constexpr (DROPOUT) {
         // dP = keep o (dO V^T) / (1 - p), then dS = P o (dP - D) with the true P; afterwards P
-        // itself is masked for dV += P_drop^T dO (its 1 / (1 - p) goes into the final scaling)
+        // itself is masked for dV += P_drop^T dO. The factor 1 / (1 - p) of all three goes into the
+        // final scaling: (1 - p) dS = P o (keep o (dO V^T) - (1 - p) D), the factor being on D in LDS.
+        // A hash covers four consecutive keys of one query, here four neighbouring lanes, and a lane
+        // holds four consecutive queries in four registers: lane i of a quad hashes query i of each
+        // four and the quad exchanges the words, one hash per four entries instead of one per entry.
+        // (The integer multiplies of a hash per entry were the longest part of the phase: fp16, d = 64,
+        // 4 x 1777 tokens, 16 heads: 227 us for the kernel with them in its 128-key form, 150 us now.)
         const uint32_t hq_key = p.drop_seed ^ (uint32_t)(s * p.Hq + c.hq) * kDropHead;
-        const uint32_t base = (uint32_t)(key >> 2) * kDropCol + hq_key;
-        const int sh = 8 * (key & 3);
+        const int quad = lane & 3;  // = key & 3
+        const uint32_t base = (uint32_t)(key >> 2) * kDropCol + hq_key + (uint32_t)(r0 + 4 * hh + quad) * kDropRow;
+        const uint32_t byte_mask = 255u << (8 * quad), byte_thr = p.drop_thr << (8 * quad);
 #pragma unroll
         for (int r4 = 0; r4 < 4; ++r4) {
           const f32x4 Dn = *(const f32x4*)(smem + DV_OFF + stat_off + (32 * tq + 8 * r4 + 4 * hh) * 4);
+          const uint32_t x = drop_mix(base + (uint32_t)(8 * r4) * kDropRow);
 #pragma unroll
           for (int u = 0; u < 4; ++u) {
             const int e = 4 * r4 + u;
-            const uint32_t x = drop_mix(base + (uint32_t)(r0 + acc_row(e, hh)) * kDropRow);
-            const bool kept = ((x >> sh) & 255u) >= p.drop_thr;
-            const float pe = S[tq][e], dpe = kept ? dP[tq][e] * p.drop_rp : 0.f;
-            dP[tq][e] = pe * (dpe + Dn[u]);  // Dn = -D
+            const bool kept = (quad_lane(x, u) & byte_mask) >= byte_thr;
+            const float pe = S[tq][e];
+            dP[tq][e] = pe * ((kept ? dP[tq][e] : 0.f) + Dn[u]);  // Dn = -D (1 - p)
             S[tq][e] = kept ? pe : 0.f;
           }
         }
@@ -800,8 +808,8 @@ __global__ __launch_bounds__(512) void bwd_dkdv_kernel(BwdArgs a) {
       const long kvoff = ((si.tok0k + key0) * p.Hkv + g) * dh;
       int ln = lane;  // recomputed here: nothing of the staging addresses is to live across the main loop
       asm volatile("" : "+v"(ln));
-      store_tiles_via_lds<DT, F16>(stg, dKt, p.scale, a.dK + kvoff, (long)p.Hkv * dh, nk - key0, dh, ln);
-      store_tiles_via_lds<DT, F16>(stg, dVt, 1.f, a.dV + kvoff, (long)p.Hkv * dh, nk - key0, dh, ln);
+      store_tiles_via_lds<DT, F16>(stg, dKt, DROPOUT ? p.scale * p.drop_rp : p.scale, a.dK + kvoff, (long)p.Hkv * dh, nk - key0, dh, ln);
+      store_tiles_via_lds<DT, F16>(stg, dVt, DROPOUT ? p.drop_rp : 1.f, a.dV + kvoff, (long)p.Hkv * dh, nk - key0, dh, ln);
     }
     return;
   }
@@ -856,7 +864,7 @@ __global__ __launch_bounds__(512) void bwd_dkdv_kernel(BwdArgs a) {
     __syncthreads();
     if (grp == 0 && key_ok) {
       __bf16* dst = (which == 0 ? a.dK : a.dV) + ((si.tok0k + key) * p.Hkv + g) * dh + 4 * hh;
-      const float mul = which == 0 ? sc : (DROPOUT ? p.drop_rp : 1.f);
+      const float mul = which == 0 ? sc : 1.f;
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
@@ -1078,6 +1086,7 @@ __global__ __launch_bounds__(512) void bwd_dq_kernel(BwdArgs a) {
   touch(Dq);
   wait_vmem();
   lds_barrier();
+  if (DROPOUT) Dq *= 1.f - (float)p.drop_thr * (1.f / 256.f);
 #pragma unroll
   for (int r = 0; r < 16; ++r) negD[r] = NEGD ? -Dq : 0.f;
 
@@ -1187,13 +1196,13 @@ __global__ __launch_bounds__(512) void bwd_dq_kernel(BwdArgs a) {
           if (c > lim_row || (LOCAL && c < lo_row)) S[kt][r] = 0.f;
         }
       }
-      if constexpr (DROPOUT) {  // dP = keep o (dO V^T) / (1 - p)
+      if constexpr (DROPOUT) {  // dP = keep o (dO V^T) / (1 - p), the factor left to the final scaling: Dq is (1 - p) D
 #pragma unroll
         for (int q4 = 0; q4 < 4; ++q4) {  // registers 4 q4 .. 4 q4 + 3: keys col0 + 32 kt + 8 q4 + 4 hh + 0..3
           const uint32_t x = drop_mix(drop_lane + (uint32_t)(col0 / 4 + 8 * kt + 2 * q4) * kDropCol);
 #pragma unroll
           for (int u = 0; u < 4; ++u)
-            dP[kt][4 * q4 + u] = ((x >> (8 * u)) & 255u) >= p.drop_thr ? dP[kt][4 * q4 + u] * p.drop_rp : 0.f;
+            dP[kt][4 * q4 + u] = ((x >> (8 * u)) & 255u) >= p.drop_thr ? dP[kt][4 * q4 + u] : 0.f;
         }
       }
 #pragma unroll
@@ -1257,7 +1266,7 @@ __global__ __launch_bounds__(512) void bwd_dq_kernel(BwdArgs a) {
     if constexpr (DT % 2 == 0) {
 #pragma unroll
       for (int half = 0; half < 2; ++half)
-        store_rows_via_lds<DT / 2, F16>(stg, &dQt[half * (DT / 2)], p.scale, op + half * (DH / 2), ostride, n - wrow0,
+        store_rows_via_lds<DT / 2, F16>(stg, &dQt[half * (DT / 2)], DROPOUT ? p.scale * p.drop_rp : p.scale, op + half * (DH / 2), ostride, n - wrow0,
                                         dh - half * (DH / 2), ln);
     } else {  // (an odd number of 32-column tiles: one at a time)
 #pragma unroll
@@ -1310,8 +1319,7 @@ static hipError_t launch_bwd_d(const BwdArgs& a, int causal, int stages, hipStre
   }
   if (stages & 2) {
     // keys per workgroup differ between the instantiations
-    const bool special = a.p.mask || a.p.drop_thr;
-    const int bck = special ? dkdv_block_keys(D, true, true) : dkdv_block_keys(D, false, false);
+    const int bck = dkdv_block_keys(a.p.mask != nullptr);
     dim3 grid(grid_size((a.p.Nk + bck - 1) / bck, a.p.Hkv * a.p.nseq));
     bool done = false;
     {

@@ -227,6 +227,16 @@ __device__ __forceinline__ uint32_t drop_mix(uint32_t x) {
   return x;
 }
 
+// The value that lane u of this lane's quad (four neighbouring lanes) holds; u is a constant after unrolling.
+__device__ __forceinline__ uint32_t quad_lane(uint32_t x, int u) {
+  switch (u) {
+    case 0: return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x00, 0xf, 0xf, true);
+    case 1: return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x55, 0xf, 0xf, true);
+    case 2: return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0xaa, 0xf, 0xf, true);
+    default: return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0xff, 0xf, 0xf, true);
+  }
+}
+
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 __device__ __forceinline__ float fast_log2(float x) { return __builtin_amdgcn_logf(x); }
 

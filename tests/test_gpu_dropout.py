@@ -93,6 +93,14 @@ def test_kept_fraction_seen_through_the_output():
         assert np.max(np.abs(pu.to_f64(O[0, :, h, 0]) - want)) <= 2 * pu.bf16_ulp(float(want.max()))
 
 
+@pytest.mark.parametrize("Nq,Nk,d,causal", [(31, 255, 64, False), (64, 256, 128, True), (257, 257, 64, True),
+                                            (33, 511, 128, False), (513, 513, 128, True), (1, 769, 64, False)])
+def test_lengths_around_the_256_key_blocks_of_the_backward(Nq, Nk, d, causal):
+    """The dK/dV kernel's 256-key blocks under dropout: a last block of 1, 255 or 256 keys, row tiles with
+    a single row, wavefronts whose keys lie past the end or above every row."""
+    check_dropout(inputs.make_cross(B=1, Nq=Nq, Nk=Nk, Hq=4, Hkv=2, d=d, causal=causal, seed=6300 + Nk), 0.1, seed=0x256)
+
+
 @pytest.mark.parametrize("causal", [False, True])
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 @pytest.mark.parametrize("d,Hq,Hkv", [(64, 2, 2), (128, 4, 2)])

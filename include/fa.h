@@ -503,7 +503,8 @@ int fa_splitkv_fwd(const void* Q, const void* K, const void* V, void* O, float* 
  *     any sequence may have (FA_ERR_SHAPE otherwise). Entries past a sequence's last page are never
  *     read; the entries that are read must name pages inside the pools (not checked).
  * The key sequence of every (sequence, key/value head) is split over num_splits workgroups as in
- * fa_splitkv_fwd: same workspace (fa_splitkv_fwd_workspace_bytes), limits (d in {64, 128},
+ * fa_splitkv_fwd (fewer, where a sequence is much shorter than Nk): same workspace
+ * (fa_splitkv_fwd_workspace_bytes), limits (d in {64, 128},
  * bfloat16, 1 <= num_splits <= FA_SPLITKV_MAX_SPLITS) and errors. Nothing is written to the caches.
  */
 int fa_kvcache_fwd(const void* Q, const void* Kcache, const void* Vcache, const int32_t* seqlens_k,

@@ -131,20 +131,23 @@ __global__ __launch_bounds__(512)
   if (!bc.valid) return;
   const int split = SPLIT ? bc.blk % nsplit : 0;
   const int rowblk = SPLIT ? bc.blk / nsplit : nblk - 1 - bc.blk;  // not split: longest causal rows first
-  const int s = bc.seq;
+  const int s = SPLIT ? cache_sequence(a, bc.seq) : bc.seq;  // (uneven cache lengths: longest first)
   const SeqInfo si = seq_info(p, s);
-  int nk_ = si.nk;
-  if (SPLIT && a.seqlens_k) {  // a key/value cache filled up to a length of its own per sequence
-    const int len = a.seqlens_k[s];
-    nk_ = len < 0 ? 0 : (len < p.Nk ? len : p.Nk);
-  }
-  const int n = si.n, nk = nk_;  // query rows, key rows
+  const int n = si.n, nk = SPLIT && a.seqlens_k ? cache_length(a, s) : si.nk;  // query rows, key rows
   const int off = nk - n;          // position of query 0 among the keys (causal alignment)
   const int nrows = SPLIT ? n * p.G : n;  // rows of the (packed) row dimension
   const int i0 = rowblk * BR;
-  if (i0 >= nrows || nk == 0) return;  // (a sequence without keys: see keyless_rows_kernel, fwd_merge_kernel)
   const int g = SPLIT ? bc.head : bc.head / p.G;
   const int dh = PAD ? p.d : D;  // row length in memory
+  if (SPLIT && nk == 0 && nsplit == 1) {  // an empty cache and no merge to come: O = 0, L = -inf
+    for (int i = tid; i < BR * (D / 8); i += 512) {
+      const int pr = i0 + i / (D / 8), q = pr / p.G, hq = g * p.G + pr % p.G;
+      if (pr >= nrows) break;
+      *(u32x4*)(a.O + ((si.tok0 + q) * p.Hq + hq) * D + 8 * (i % (D / 8))) = (u32x4){0, 0, 0, 0};
+      if (i % (D / 8) == 0) a.LSE[s * p.lse_seq_stride + (long)hq * p.lse_head_stride + q] = -INFINITY;
+    }
+  }
+  if (i0 >= nrows || nk == 0) return;  // (a sequence without keys: see keyless_rows_kernel, fwd_merge_kernel)
   const long kstride = (long)p.Hkv * dh;
   const __bf16* Kb = a.K + (si.tok0k * p.Hkv + g) * dh;
   const __bf16* Vb = a.V + (si.tok0k * p.Hkv + g) * dh;
@@ -184,8 +187,10 @@ __global__ __launch_bounds__(512)
   // column blocks the workgroup visits: all of them, or (causal) those not entirely above the diagonal
   // (split: this workgroup's share jb .. of them)
   const int ncol_all = (nk + BC - 1) / BC;
-  const int per_split = (ncol_all + nsplit - 1) / nsplit;
+  const int per_split = SPLIT ? split_share_blocks(ncol_all, (p.Nk + BC - 1) / BC, nsplit) : ncol_all;
+  const bool direct = SPLIT && per_split >= ncol_all;  // a single share: O and LSE are written here
   int jb = split * per_split;
+  if (SPLIT && split > 0 && jb >= ncol_all) return;  // the sequence has fewer shares (the merge knows how many)
   int ncol = jb + per_split < ncol_all ? jb + per_split : ncol_all;
   const int wl = LOCAL ? p.win_left : -1, wr = LOCAL ? p.win_right : -1;  // window bounds (negative: none)
   if (CAUSAL || LOCAL) {
@@ -197,7 +202,7 @@ __global__ __launch_bounds__(512)
     }
     if (LOCAL && wl >= 0 && i0 + off > wl) jb = (i0 + off - wl) / BC;  // the first block the first row sees
   }
-  if (SPLIT && jb >= ncol) {  // this share holds no key that the workgroup's rows see: L = -inf says so to the merge
+  if (SPLIT && !direct && jb >= ncol) {  // this share holds no key that the workgroup's rows see: L = -inf says so to the merge
     if (row_ok && hh == 0)
       a.Lpart[(long)split * p.total_tokens * p.Hq + s * p.lse_seq_stride + h * p.lse_head_stride + row] = -INFINITY;
     return;
@@ -543,7 +548,7 @@ __global__ __launch_bounds__(512)
 
   // ---- epilogue: O = diag(l)^-1 O, L = m + log l (Algorithm 1, lines 12-15)
   const float lsum = sum_with_partner32(l);
-  if (SPLIT) {  // partial result of this share of the keys, float32; no visible key: O = 0, L = -inf
+  if (SPLIT && !direct) {  // partial result of this share of the keys, float32; no visible key: O = 0, L = -inf
     const float inv = lsum > 0.f ? 1.0f / lsum : 0.f;
     if (row_ok) {
       const long tok = si.tok0 + row;
@@ -564,7 +569,7 @@ __global__ __launch_bounds__(512)
     return;
   }
   // (mask, window: a row without any key ends with l = 0: O = 0, L = -inf)
-  const float inv = (MASK || LOCAL) && !(lsum > 0.f) ? 0.f : (DROPOUT ? p.drop_rp : 1.0f) / lsum;
+  const float inv = GUARD && !(lsum > 0.f) ? 0.f : (DROPOUT ? p.drop_rp : 1.0f) / lsum;
   {
     // O through the ring slot that neither holds a block still in use nor receives one of the
     // copies issued past the last block (those fill the three slots after block ncol - 1)
@@ -574,7 +579,18 @@ __global__ __launch_bounds__(512)
     const long ostride = (long)p.Hq * dh;
     int ln = lane;  // recomputed here: nothing of the staging addresses is to live across the main loop
     asm volatile("" : "+v"(ln));
-    if constexpr (DT % 2 == 0) {
+    if constexpr (SPLIT) {  // packed rows: query * G + head of the group
+      __bf16* o0 = a.O + (si.tok0 * p.Hq + g * p.G) * D;
+#pragma unroll
+      for (int half = 0; half < 2; ++half)
+        store_rows_via_lds<DT / 2, F16>(
+            stg, &O[half * (DT / 2)], inv,
+            [&](int r) {
+              const int q = (prow0 + r) / p.G;
+              return o0 + ((long)q * p.Hq + (prow0 + r - q * p.G)) * D + half * (DH / 2);
+            },
+            nrows - prow0, D / 2, ln);
+    } else if constexpr (DT % 2 == 0) {
 #pragma unroll
       for (int half = 0; half < 2; ++half) {
         store_rows_via_lds<DT / 2, F16>(stg, &O[half * (DT / 2)], inv, op + half * (DH / 2), ostride, n - prow0,
@@ -585,10 +601,10 @@ __global__ __launch_bounds__(512)
       for (int dt = 0; dt < DT; ++dt)
         store_rows_via_lds<1, F16>(stg, &O[dt], inv, op + 32 * dt, ostride, n - prow0, dh - 32 * dt, ln);
     }
-    if (row < n && hh == 0)
+    if ((SPLIT ? row_ok : row < n) && hh == 0)
       a.LSE[s * p.lse_seq_stride + h * p.lse_head_stride + (p.cu_seqlens ? si.tok0 : 0) + row] =
           MASK    ? (lsum > 0.f ? m + fast_log2(lsum) * kLn2 : -INFINITY)
-          : LOCAL ? (lsum > 0.f ? m * p.scale + fast_log2(lsum) * kLn2 : -INFINITY)
+          : GUARD ? (lsum > 0.f ? m * p.scale + fast_log2(lsum) * kLn2 : -INFINITY)
                   : m * p.scale + fast_log2(lsum) * kLn2;
   }
 }
@@ -904,8 +920,9 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   else run_items(std::integral_constant<int, 1>{});
 }
 
-// Combine the partial results of the key shares: one thread per 4 output elements.
-template <int D, bool F16>
+// Combine the partial results of the key shares: one thread per 4 output elements. DECODE: the shares are
+// those of fwd_decode_kernel (always nsplit), otherwise those of the split kernel.
+template <int D, bool F16, bool DECODE>
 __global__ __launch_bounds__(256) void fwd_merge_kernel(FwdArgs a) {
   constexpr int TPR = D / 4;  // threads per (token, head) row
   const Problem& p = a.p;
@@ -918,10 +935,16 @@ __global__ __launch_bounds__(256) void fwd_merge_kernel(FwdArgs a) {
   const long b = tok / p.N, q = tok - b * p.N;
   const long li = b * p.lse_seq_stride + (long)h * p.lse_head_stride + q;
   // (a cache without keys: the split kernel wrote nothing for this sequence)
-  const bool keyless = a.seqlens_k && a.seqlens_k[b] <= 0;
+  const int ncol = ((a.seqlens_k ? cache_length(a, b) : p.Nk) + 63) / 64;
+  int nshare = a.nsplit;
+  if (!DECODE) {
+    const int per = split_share_blocks(ncol, (p.Nk + 63) / 64, a.nsplit);
+    nshare = (ncol + per - 1) / per;
+    if (nshare == 1) return;  // the split kernel wrote O and LSE
+  }
   float mx = -INFINITY;
-  if (!keyless)
-    for (int k = 0; k < a.nsplit; ++k) mx = fmaxf(mx, a.Lpart[(long)k * nrows + li]);
+  if (ncol > 0)
+    for (int k = 0; k < nshare; ++k) mx = fmaxf(mx, a.Lpart[(long)k * nrows + li]);
   if (mx == -INFINITY) {  // no share holds a key that this row sees: P = 0, so O = 0 and L = -inf
     *(u32x2*)(a.O + r * D + 4 * c) = (u32x2){0u, 0u};
     if (c == 0) a.LSE[li] = -INFINITY;
@@ -929,7 +952,7 @@ __global__ __launch_bounds__(256) void fwd_merge_kernel(FwdArgs a) {
   }
   float z = 0.f;
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  for (int k = 0; k < a.nsplit; ++k) {
+  for (int k = 0; k < nshare; ++k) {
     const float lp = a.Lpart[(long)k * nrows + li];
     if (lp == -INFINITY) continue;  // a share without keys for this row (it may have written no partial O at all)
     const float wgt = __expf(lp - mx);
@@ -970,9 +993,9 @@ template <int D, bool F16>
 static hipError_t launch_fwd_d(const FwdArgs& a, int causal, hipStream_t st) {
   dim3 block(512);
   if (a.nsplit > 0) {
-    if (a.p.N * a.p.G <= 32) {  // one row tile per key/value head: the wavefronts divide the keys (fa_decode.hip)
+    const bool decode = a.p.N * a.p.G <= 32;  // one row tile per key/value head: the wavefronts divide the keys (fa_decode.hip)
+    if (decode) {
       if (hipError_t e = launch_fwd_decode(a, D, causal, st)) return e;
-      if (a.nsplit == 1) return hipSuccess;  // (a single share: that kernel has written O and LSE itself)
     } else {
       const int nblk = (a.p.N * a.p.G + 255) / 256;
       dim3 grid(grid_size(nblk * a.nsplit, a.p.Hkv * a.p.nseq));
@@ -980,9 +1003,12 @@ static hipError_t launch_fwd_d(const FwdArgs& a, int causal, hipStream_t st) {
       else hipLaunchKernelGGL((fwd_kernel<D, false, true, F16>), grid, block, 0, st, a);
       if (hipError_t e = hipGetLastError()) return e;
     }
+    if (a.nsplit == 1) return hipSuccess;  // (a single share: the kernel has written O and LSE itself)
     constexpr int RPB = 256 / (D / 4);
     const long nrows = (long)a.p.total_tokens * a.p.Hq;
-    hipLaunchKernelGGL((fwd_merge_kernel<D, F16>), dim3((unsigned)((nrows + RPB - 1) / RPB)), dim3(256), 0, st, a);
+    const dim3 mgrid((unsigned)((nrows + RPB - 1) / RPB));
+    if (decode) hipLaunchKernelGGL((fwd_merge_kernel<D, F16, true>), mgrid, dim3(256), 0, st, a);
+    else hipLaunchKernelGGL((fwd_merge_kernel<D, F16, false>), mgrid, dim3(256), 0, st, a);
     return hipGetLastError();
   }
   dim3 grid(grid_size((a.p.N + 255) / 256, a.p.Hq * a.p.nseq));

@@ -25,6 +25,51 @@ struct FwdArgs {
   int page_log2, table_stride;
 };
 
+// Keys of sequence s in a cache with lengths of its own (a.seqlens_k is set).
+__device__ __forceinline__ int cache_length(const FwdArgs& a, int s) {
+  const int len = a.seqlens_k[s];
+  return len < 0 ? 0 : (len < a.p.Nk ? len : a.p.Nk);
+}
+
+// Sequences of uneven cache lengths are handed out longest first: the workgroups of an XCD take
+// their (sequence, head) pairs in launch order, and a long sequence that starts last leaves the
+// other compute units idle at the end. The sequence index of the launch order is therefore read as a
+// RANK, and the sequence of that rank (by length, ties by index) is found here: lane c counts the
+// sequences that come before candidate c. Done by every wavefront for itself (a few hundred scalar
+// loads that hit L2); batches of more than kRankMax sequences keep the launch order.
+constexpr int kRankMax = 128;
+__device__ __forceinline__ int cache_sequence(const FwdArgs& a, int rank) {
+  const int nseq = a.p.nseq, lane = threadIdx.x & 63;
+  if (!a.seqlens_k || nseq <= 1 || nseq > kRankMax) return rank;
+  int found = 0;
+  for (int c0 = 0; c0 < nseq; c0 += 64) {
+    const int c = c0 + lane;
+    const int lc = c < nseq ? cache_length(a, c) : -1;
+    int before = 0;
+    for (int j = 0; j < nseq; ++j) {
+      const int lj = __builtin_amdgcn_readfirstlane(cache_length(a, j));
+      before += (lj > lc || (lj == lc && j < c)) ? 1 : 0;
+    }
+    const unsigned long long hit = __builtin_amdgcn_ballot_w64(c < nseq && before == rank);
+    if (hit) found = c0 + __builtin_ctzll(hit);
+  }
+  return __builtin_amdgcn_readfirstlane(found);
+}
+
+// Shares of the row-block split kernel, in blocks of 64 keys: a sequence of `ncol` blocks is cut into at
+// most nsplit equal shares, the same number for every length (shares of one size, of which a short
+// sequence gets fewer, measured 5-15% slower at two shares: longest-first order then no longer goes by
+// the work of a share), but not into shares of under kSplitMinBlocks blocks unless those of a full cache
+// (cap_blocks) are that short: their start-up and partial results cost more than they even out. A
+// sequence of one share needs no merge: the split kernel writes its O and LSE and fwd_merge_kernel passes
+// its rows over.
+constexpr int kSplitMinBlocks = 16;
+__host__ __device__ inline int split_share_blocks(int ncol, int cap_blocks, int nsplit) {
+  const int per = (ncol + nsplit - 1) / nsplit, full = (cap_blocks + nsplit - 1) / nsplit;
+  const int least = full < kSplitMinBlocks ? full : kSplitMinBlocks;
+  return per < least ? least : per;
+}
+
 struct BwdArgs {
   Problem p;
   const __bf16* Q;

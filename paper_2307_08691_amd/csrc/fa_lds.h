@@ -175,9 +175,10 @@ __device__ __forceinline__ void landed(T& x) {
 // wavefront-private LDS buffer `stg` (32 * 64 * NT bytes, chunks XOR-ed so that neither side
 // conflicts) turns it into whole rows: a quarter of the write requests. Rows >= nrows and columns >=
 // ncols (a multiple of 8) are not stored. Needs no barrier: only this wavefront touches `stg`.
-template <int NT, bool F16>
-__device__ __forceinline__ void store_rows_via_lds(char* stg, const f32x16* acc, float mul, __bf16* g, long gstride,
-                                                   int nrows, int ncols, int lane) {
+// (row_at(r): where row r < nrows begins)
+template <int NT, bool F16, class RowAt>
+__device__ __forceinline__ void store_rows_via_lds(char* stg, const f32x16* acc, float mul, RowAt row_at, int nrows,
+                                                   int ncols, int lane) {
   constexpr int SROW = 64 * NT;      // bytes per staged row
   constexpr int CPR = SROW / 16;     // 16-byte chunks per row
   constexpr int RPB = 256 / SROW;    // rows per 256 bytes (one pass over the banks)
@@ -199,8 +200,13 @@ __device__ __forceinline__ void store_rows_via_lds(char* stg, const f32x16* acc,
   for (int u = 0; u < 32 / RPI; ++u) {
     const int row = RPI * u + rr;
     const u32x4 v = *(const u32x4*)(stg + row * SROW + 16 * (c ^ ((row / RPB) & (CPR - 1))));
-    if (row < nrows && 8 * c < ncols) *(u32x4*)(g + row * gstride + 8 * c) = v;
+    if (row < nrows && 8 * c < ncols) *(u32x4*)(row_at(row) + 8 * c) = v;
   }
+}
+template <int NT, bool F16>
+__device__ __forceinline__ void store_rows_via_lds(char* stg, const f32x16* acc, float mul, __bf16* g, long gstride,
+                                                   int nrows, int ncols, int lane) {
+  store_rows_via_lds<NT, F16>(stg, acc, mul, [&](int row) { return g + row * gstride; }, nrows, ncols, lane);
 }
 
 // The same for NT tiles where NT need not be a power of two (three tiles: one at a time).

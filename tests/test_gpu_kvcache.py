@@ -181,6 +181,16 @@ def test_row_counts_around_the_decode_kernel_limit(Nq, Hq, Hkv, d, causal):
     check_contiguous(draw(18600 + Nq + Hq + d, len(lens), Nq, cap, Hq, Hkv, d), lens, causal, 7)
 
 
+@pytest.mark.parametrize("num_splits", [1, 2, 3])
+@pytest.mark.parametrize("d", [64, 128])
+def test_sequences_of_one_and_of_several_shares_in_the_row_block_kernel(d, num_splits):
+    """The row-block kernel writes O and LSE itself for a sequence that one share covers (at most 1024
+    keys here) and leaves partial results for the others: 1024 and 1025 keys, an empty cache, fewer
+    keys than queries (rows without a key), a full cache; three heads per key/value head in the rows."""
+    lens = [1025, 3000, 30, 0, 1024, 2049, 1]
+    check_contiguous(draw(18650 + d, len(lens), 90, 3000, 6, 2, d), lens, True, num_splits)
+
+
 @pytest.mark.parametrize("B", [2, 64, 128, 129])
 def test_many_sequences_with_equal_and_uneven_lengths(B):
     """The decode kernel hands up to 128 sequences out longest first (a rank per workgroup, ties by

@@ -150,19 +150,14 @@ __global__ __launch_bounds__(512) void bwd_dkdv_kernel(BwdArgs a) {
   const int kgi = WIDE ? v : kg;  // which 32 keys of the block this wavefront owns
   const int gtid = tid & 255;  // thread index inside the group
   const int lq = lane & 31, hh = lane >> 5;
-  const BlockCoord bc = block_coord<CAUSAL>((p.Nk + BC - 1) / BC, p.Hkv, p.nseq);  // causal: block 0 is the longest
+  const BlockCoord bc = key_block_coord<CAUSAL>(p, BC);
   if (!bc.valid) return;
   const int g = bc.head, s = bc.seq;
   const SeqInfo si = seq_info(p, s);
   const int n = si.n, nk = si.nk;  // query rows, key rows
   const int off = nk - n;          // position of query 0 among the keys (causal alignment)
-  // Causal: a key block's work grows with the number of rows below it, so the launch order (block 0
-  // first) is the longest-first order when block indices count from the END of the longest possible
-  // sequence: a shorter sequence of a ragged batch owns the last of them, and its blocks are handed out
-  // among the equally long remainders of the longer ones instead of ahead of them.
-  const int jblk = CAUSAL ? bc.blk - ((p.Nk + BC - 1) / BC - (nk + BC - 1) / BC) : bc.blk;
-  if (jblk < 0) return;
-  const int j0 = jblk * BC;
+  if (bc.blk < 0) return;
+  const int j0 = bc.blk * BC;
   if (j0 >= nk) return;
   const int dh = PAD ? p.d : D;  // row length in memory
   const long qstride = (long)p.Hq * dh, kstride = (long)p.Hkv * dh;
@@ -918,16 +913,15 @@ __global__ __launch_bounds__(512) void bwd_dq_kernel(BwdArgs a) {
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int grp = w >> 2;  // 0: matrix phase on even phases, 1: on odd phases
   const int lq = lane & 31, hh = lane >> 5;
-  const int nblk = (p.N + BR - 1) / BR;
-  const BlockCoord bc = block_coord<CAUSAL>(nblk, p.Hq, p.nseq, p.G);
+  const BlockCoord bc = row_block_coord<CAUSAL>(p, BR);
   if (!bc.valid) return;
-  const int rowblk = nblk - 1 - bc.blk;  // longest causal rows first
+  const int rowblk = bc.blk;
   const int h = bc.head, s = bc.seq;
   const SeqInfo si = seq_info(p, s);
   const int n = si.n, nk = si.nk, off = nk - n;  // query rows, key rows, position of query 0
   const int i0 = rowblk * BR;
   if (i0 >= n || nk == 0) return;  // (a sequence without keys: dQ = 0 comes from keyless_rows_kernel)
-  const int g = h / p.G;
+  const int g = __builtin_amdgcn_readfirstlane(h / p.G);
   const int dh = PAD ? p.d : D;  // row length in memory
   const long kstride = (long)p.Hkv * dh;
   const __bf16* Kb = a.K + (si.tok0k * p.Hkv + g) * dh;

@@ -56,10 +56,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lq = lane & 31, hh = lane >> 5;
-  const int nblk = (p.N + BR - 1) / BR;
-  const BlockCoord bc = block_coord<CAUSAL>(nblk, p.Hq, p.nseq, p.G);
+  const BlockCoord bc = row_block_coord<CAUSAL>(p, BR);
   if (!bc.valid) return;
-  const int rowblk = nblk - 1 - bc.blk;  // longest causal rows first
+  const int rowblk = bc.blk;
   const int h = bc.head, s = bc.seq;
   const SeqInfo si = seq_info(p, s);
   const int n = si.n, nk = si.nk, off = nk - n;
@@ -284,10 +283,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lq = lane & 31, hh = lane >> 5;
-  const int nblk = (p.N + BR - 1) / BR;
-  const BlockCoord bc = block_coord<CAUSAL>(nblk, p.Hq, p.nseq, p.G);
+  const BlockCoord bc = row_block_coord<CAUSAL>(p, BR);
   if (!bc.valid) return;
-  const int rowblk = nblk - 1 - bc.blk;
+  const int rowblk = bc.blk;
   const int h = bc.head, s = bc.seq;
   const SeqInfo si = seq_info(p, s);
   const int n = si.n, nk = si.nk, off = nk - n;
@@ -447,8 +445,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lq = lane & 31, hh = lane >> 5;
-  const BlockCoord bc = block_coord<CAUSAL>((p.Nk + BC - 1) / BC, p.Hkv, p.nseq);  // causal: block 0 is the longest
-  if (!bc.valid) return;
+  const BlockCoord bc = key_block_coord<CAUSAL>(p, BC);
+  if (!bc.valid || bc.blk < 0) return;
   const int g = bc.head, s = bc.seq;
   const SeqInfo si = seq_info(p, s);
   const int n = si.n, nk = si.nk, off = nk - n;

@@ -127,17 +127,17 @@ __global__ __launch_bounds__(512)
   const int lq = lane & 31, hh = lane >> 5;
   const int nsplit = SPLIT ? a.nsplit : 1;
   const int nblk = ((SPLIT ? p.N * p.G : p.N) + BR - 1) / BR;
-  const BlockCoord bc = block_coord<CAUSAL && !SPLIT>(nblk * nsplit, SPLIT ? p.Hkv : p.Hq, p.nseq, SPLIT ? 1 : p.G);
+  const BlockCoord bc = SPLIT ? block_coord<false>(nblk * nsplit, p.Hkv, p.nseq) : row_block_coord<CAUSAL>(p, BR);
   if (!bc.valid) return;
   const int split = SPLIT ? bc.blk % nsplit : 0;
-  const int rowblk = SPLIT ? bc.blk / nsplit : nblk - 1 - bc.blk;  // not split: longest causal rows first
+  const int rowblk = SPLIT ? bc.blk / nsplit : bc.blk;
   const int s = SPLIT ? cache_sequence(a, bc.seq) : bc.seq;  // (uneven cache lengths: longest first)
   const SeqInfo si = seq_info(p, s);
   const int n = si.n, nk = SPLIT && a.seqlens_k ? cache_length(a, s) : si.nk;  // query rows, key rows
   const int off = nk - n;          // position of query 0 among the keys (causal alignment)
   const int nrows = SPLIT ? n * p.G : n;  // rows of the (packed) row dimension
   const int i0 = rowblk * BR;
-  const int g = SPLIT ? bc.head : bc.head / p.G;
+  const int g = SPLIT ? bc.head : __builtin_amdgcn_readfirstlane(bc.head / p.G);
   const int dh = PAD ? p.d : D;  // row length in memory
   if (SPLIT && nk == 0 && nsplit == 1) {  // an empty cache and no merge to come: O = 0, L = -inf
     for (int i = tid; i < BR * (D / 8); i += 512) {

@@ -73,6 +73,36 @@ def test_packed_ragged_batch(d, Hq, Hkv, causal):
     check(prob)
 
 
+# (number of sequences, longest, Hq, Hkv, d): 16 and 130 query heads x sequences per XCD with gaps on every
+# level, head counts that are no multiple of 8, one pair per XCD and fewer, more pairs than the kernels number
+# without gaps (264 per XCD, for the row blocks only and for both), one length for all, an empty batch entry
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("nseq,longest,Hq,Hkv,d", [(16, 900, 8, 2, 128), (65, 300, 16, 8, 64), (7, 1100, 6, 3, 64),
+                                                   (3, 1025, 2, 1, 128), (33, 270, 64, 8, 64), (132, 260, 16, 16, 64),
+                                                   (5, 400, 4, 2, 256), (9, 520, 4, 4, 96)])
+def test_ragged_batches_are_covered_without_gaps(nseq, longest, Hq, Hkv, d, causal):
+    """Every row of every sequence is computed exactly once whatever order the blocks are handed out in."""
+    rng = np.random.default_rng(9100 + nseq)
+    lens = rng.integers(0, longest + 1, nseq)
+    lens[nseq // 2], lens[0] = longest, 0
+    prob = inputs.make_varlen(lens, Hq=Hq, Hkv=Hkv, d=d, causal=causal, seed=9200 + nseq)
+    Q, K, V, dO = (pu.to_gpu(x, prob.dtype) for x in (prob.Q, prob.K, prob.V, prob.dO))
+    cu, mx = torch.from_numpy(prob.cu_seqlens.astype(np.int32)).cuda(), min(longest + 300, int(lens.sum()))
+    bad = lambda x: torch.full_like(x, float("nan"))
+    O, L = binding.fa_varlen_fwd(Q, K, V, cu, mx, prob.scale, causal, O=bad(Q),
+                                 LSE=torch.full((Hq, Q.shape[0]), float("nan"), device="cuda"))
+    grads = binding.fa_varlen_bwd(Q, K, V, O, dO, L, cu, mx, prob.scale, causal, dQ=bad(Q), dK=bad(K), dV=bad(V))
+    for s in range(nseq):
+        a, e = int(prob.cu_seqlens[s]), int(prob.cu_seqlens[s + 1])
+        if a == e:
+            continue
+        q, k, v, g = (x[a:e].unsqueeze(0).contiguous() for x in (Q, K, V, dO))
+        o, l = binding.fa_fwd(q, k, v, prob.scale, causal)
+        want = (o, l) + binding.fa_bwd(q, k, v, o, g, l, prob.scale, causal)
+        for name, x, y in zip(("O", "LSE", "dQ", "dK", "dV"), (O[a:e], L[:, a:e]) + tuple(t[a:e] for t in grads), want):
+            assert torch.equal(x, y[0]), f"{name} of sequence {s} ({e - a} tokens)"
+
+
 def test_packed_ragged_equals_dense_calls_bitwise():
     """A packed batch of equal lengths must reproduce the dense entry point bit for bit
     (every output is deterministic)."""

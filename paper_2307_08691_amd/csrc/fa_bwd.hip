@@ -109,12 +109,15 @@ constexpr int dkdv_block_keys(bool mask) { return dkdv_wide(mask) ? 256 : 128; }
 // LOCAL: sliding window (see the forward kernel). The workgroup visits only the row tiles whose
 // window reaches its 256 keys, a wavefront computes only on those that reach its own 32 keys
 // (leading and trailing tiles are sat out), and the element mask is applied on the tiles that
-// straddle an edge of the band.
+// straddle an edge of the band. A window (kWindow) leaves a wavefront one contiguous run of tiles and so
+// keeps the plain loops; a block-sparse pattern (kBlocks) needs a loop of its own, with two barriers a
+// tile and operands one MFMA ahead (window of 1024, N = 8192, 32 heads of 128, MI355X: 357 us through the
+// pattern's loop, 302 us through the plain ones).
 //
 // DH (PAD only): the head dimension rounded up to a multiple of 32; the products run over the
 // first DH columns of the D-wide tiles only (see the forward kernel).
-template <int D, bool CAUSAL, bool F16, bool DROPOUT = false, bool PAD = false, bool MASK = false, bool LOCAL = false,
-          int DH = D>
+template <int D, bool CAUSAL, bool F16, bool DROPOUT = false, bool PAD = false, bool MASK = false,
+          int LOCAL = kNoPattern, int DH = D>
 __global__ __launch_bounds__(512) void bwd_dkdv_kernel(BwdArgs a) {
   static_assert(DH == D || (PAD && DH % 32 == 0 && DH < D), "a narrower product width is for padded head dimensions");
   static_assert(!MASK || (!DROPOUT && !PAD), "the mask variant is built for the plain kernel");
@@ -134,9 +137,9 @@ __global__ __launch_bounds__(512) void bwd_dkdv_kernel(BwdArgs a) {
   constexpr int TILEB = BR * ROWB, BUFB = 2 * TILEB;  // one Q_i (or dO_i) tile; one ring slot = Q_i | dO_i
   constexpr int LS_OFF = QDO_OFF + RING * BUFB;       // [slot][row] floats
   constexpr int DV_OFF = LS_OFF + RING * BR * 4;
-  constexpr int BITS_OFF = DV_OFF + RING * BR * 4;  // LOCAL: one activity bitmap per wavefront (over the tiles in its range)
-  constexpr int LIST_OFF = BITS_OFF + 8 * 8 * kPatternWords;  // LOCAL: the tiles the workgroup visits, four bytes each
-  constexpr int SMEM = LOCAL ? LIST_OFF + 4 * 64 * kPatternWords : BITS_OFF;
+  constexpr int BITS_OFF = DV_OFF + RING * BR * 4;  // kBlocks: one activity bitmap per wavefront (over the tiles in its range)
+  constexpr int LIST_OFF = BITS_OFF + 8 * 8 * kPatternWords;  // kBlocks: the tiles the workgroup visits, four bytes each
+  constexpr int SMEM = LOCAL == kBlocks ? LIST_OFF + 4 * 64 * kPatternWords : BITS_OFF;
   static_assert(VT_OFF + BC * ROWB <= 65536 && BUFB <= 32768, "immediate offsets must fit 16 bits");
   static_assert(WIDE || 4 * DT * 16 * 64 * 4 <= RING * BUFB, "the final reduction reuses the ring");
   static_assert(SMEM <= 160 * 1024, "LDS of one compute unit");
@@ -235,11 +238,11 @@ __global__ __launch_bounds__(512) void bwd_dkdv_kernel(BwdArgs a) {
   // here for every t. The workgroup then visits only the tiles that some wavefront has a bit for:
   // every wavefront compacts the union of the eight bitmaps into the same list, so neither copies
   // nor phases are spent on a tile that the pattern removes from all 256 keys.
-  const bool sparse = LOCAL && p.bmask != nullptr;
+  constexpr bool sparse = LOCAL == kBlocks;
   const unsigned* visit = (const unsigned*)(smem + LIST_OFF);
   int Tv = T;  // tiles the workgroup visits
   bool listed = false;  // the visit follows the list
-  if (LOCAL && sparse) {
+  if constexpr (sparse) {
     unsigned long long* bits = (unsigned long long*)(smem + BITS_OFF) + v * kPatternWords;
     const uint8_t* bm0 = p.bmask + s * p.bmask_bs + (long)((j0 + 32 * kgi < nk ? j0 + 32 * kgi : nk - 1) >> p.bmask_log2);
     for (int q = 0; q * 64 < T; q += 4) {  // (four words a round: their loads are in flight together)
@@ -277,9 +280,9 @@ __global__ __launch_bounds__(512) void bwd_dkdv_kernel(BwdArgs a) {
   // The list entry of the tile at position t of the visit (past its end: the last one). Lane l keeps
   // entry win_base + l, so that a lookup is a lane read; step t asks for positions t .. t + 3.
   int win_base = 0;
-  unsigned win = LOCAL && listed ? visit[lane] : 0u;
+  unsigned win = sparse && listed ? visit[lane] : 0u;
   auto tile_no = [&](int t) {
-    if (!(LOCAL && listed)) return (unsigned)t;
+    if (!(sparse && listed)) return (unsigned)t;
     const int tc = t < Tv ? t : Tv - 1;
     if (tc < 0) return 0u;
     if ((unsigned)(tc - win_base) >= 64u) {
@@ -361,7 +364,7 @@ __global__ __launch_bounds__(512) void bwd_dkdv_kernel(BwdArgs a) {
   {
     Cursor c = tile0;
     for (int t = 0; t < (WIDE ? 2 : 3) && t < Tv; ++t) {
-      if (LOCAL && listed) c = cursor_at(tile_no(t), t);
+      if (sparse && listed) c = cursor_at(tile_no(t), t);
       const long first = c.qoff - (long)c.it * BR * qstride;  // row 0 of this head
       char* dst = smem + QDO_OFF + c.slot * BUFB;
       tile_load_async<D, BR, 8, PAD>(dst, a.Q + first, qstride, c.it * BR, n - 1, v, lane, dh / 8);
@@ -424,8 +427,8 @@ __global__ __launch_bounds__(512) void bwd_dkdv_kernel(BwdArgs a) {
   }
   constexpr int NM = QTW * 2 * KS;   // S and dP: 16 MFMAs
   constexpr int NM2 = QTW * 4 * DT;  // dV and dK: 16 MFMAs
-  // (mask, window / pattern: a shorter prefetch, their bookkeeping needs the registers)
-  constexpr int AH = MASK ? (D == 128 ? 1 : 2) : LOCAL && D == 128 ? 1 : (KREG && D == 128 ? 3 : kDkdvAhead);
+  // (mask, pattern: a shorter prefetch, their bookkeeping needs the registers)
+  constexpr int AH = MASK ? (D == 128 ? 1 : 2) : sparse && D == 128 ? 1 : (KREG && D == 128 ? 3 : kDkdvAhead);
   // MASK: this lane's entries of M for the wavefront's next tile (raw 16-bit elements), row by row
   uint32_t mraw[MASK ? QTW * 16 : 1];
   auto issue_mask_loads = [&](const Cursor& c) {
@@ -638,15 +641,14 @@ __global__ __launch_bounds__(512) void bwd_dkdv_kernel(BwdArgs a) {
     // the two wavefronts of a SIMD change phase together, and without it a matrix phase that ends
     // early runs on into the vector phase (see the forward kernel).
     advance(ld, 2);
-    if constexpr (LOCAL) {
-      // (the window / pattern instantiation keeps both barriers of a tile: group 1 one phase behind group 0)
+    if constexpr (sparse) {
+      // (the pattern instantiation keeps both barriers of a tile: group 1 one phase behind group 0)
       if (grp == 1) lds_barrier();
-      // Window and block-sparse pattern: tile by tile, over the tiles the workgroup visits.
+      // Block-sparse pattern: tile by tile, over the tiles the workgroup visits.
       const unsigned long long* bits = (const unsigned long long*)(smem + BITS_OFF) + v * kPatternWords;
       int word_q = -1;
       unsigned long long word = 0;
       auto active = [&](int t) {  // t: a tile's number in the full order
-        if (!sparse) return t >= skip && t < t_stop;
         if ((t >> 6) != word_q) {
           word_q = t >> 6;
           word = bits[word_q];
@@ -728,6 +730,8 @@ __global__ __launch_bounds__(512) void bwd_dkdv_kernel(BwdArgs a) {
       // The loops are written out once per group: which of the two barriers a group executes is then
       // fixed in the code (as a run-time condition on both of them the compiler's output failed its own
       // verification, and as lambdas generic in the group the accumulators ended up in memory).
+      // (window: after its last tile, t_end - 1, a wavefront only keeps up with the copies and the barriers)
+      const int t_end = LOCAL ? t_stop : T;
       auto vector_work = [&](int t, bool do_v, bool loads) {  // a vector phase without its barrier
         if (loads && t + 2 < T) {
           issue_loads(ld);
@@ -747,13 +751,13 @@ __global__ __launch_bounds__(512) void bwd_dkdv_kernel(BwdArgs a) {
           lds_barrier();
           advance(cur, 1);
         }
-        if (t < T) {
+        if (t < t_end) {
           __builtin_amdgcn_s_setprio(2);
           mfma_stream<NM, AH, 2>([&](int i) { return load_m(cur, i); }, mma_m);
           end_matrix_work();
           vector_work(t, true, true);
           lds_barrier();
-          for (++t; t < T; ++t) {
+          for (++t; t < t_end; ++t) {
             prev = cur;
             advance(cur, 1);
             fused_stream();
@@ -765,6 +769,12 @@ __global__ __launch_bounds__(512) void bwd_dkdv_kernel(BwdArgs a) {
           __builtin_amdgcn_s_setprio(2);
           mfma_stream_run<NM2, AH, 2>(pre, [&](int i) { return load_m2(prev, i); }, mma_m2);
         }
+        if (LOCAL)
+          for (; t < T; ++t) {
+            end_matrix_work();
+            vector_work(t, false, true);
+            lds_barrier();
+          }
         end_matrix_work();
         lds_barrier();  // (none was executed for the last matrix phase)
       } else {  // barrier after the matrix phase
@@ -774,12 +784,12 @@ __global__ __launch_bounds__(512) void bwd_dkdv_kernel(BwdArgs a) {
           vector_work(t, false, false);
           advance(cur, 1);
         }
-        if (t < T) {
+        if (t < t_end) {
           __builtin_amdgcn_s_setprio(2);
           mfma_stream<NM, AH, 2>([&](int i) { return load_m(cur, i); }, mma_m);
           end_matrix_phase();
           vector_work(t, true, false);
-          for (++t; t < T; ++t) {
+          for (++t; t < t_end; ++t) {
             prev = cur;
             advance(cur, 1);
             fused_stream();
@@ -790,6 +800,11 @@ __global__ __launch_bounds__(512) void bwd_dkdv_kernel(BwdArgs a) {
           __builtin_amdgcn_s_setprio(2);
           mfma_stream_run<NM2, AH, 2>(pre, [&](int i) { return load_m2(prev, i); }, mma_m2);
         }
+        if (LOCAL)
+          for (; t < T; ++t) {
+            end_matrix_phase();
+            vector_work(t, false, false);
+          }
         end_matrix_phase();
       }
     }
@@ -890,7 +905,7 @@ __global__ __launch_bounds__(512) void bwd_dkdv_kernel(BwdArgs a) {
 // dO_i operands it holds anyway and one pass over its O_i rows, and writes it for the dK/dV kernel,
 // which then runs after this one: the whole backward without the separate D pre-pass.
 // DH (PAD only): the narrower product width of a padded head dimension (see the forward kernel).
-template <int D, bool CAUSAL, bool F16, bool DROPOUT = false, bool PAD = false, bool MASK = false, bool LOCAL = false,
+template <int D, bool CAUSAL, bool F16, bool DROPOUT = false, bool PAD = false, bool MASK = false, int LOCAL = kNoPattern,
           bool OWN_D = false, int DH = D>
 __global__ __launch_bounds__(512) void bwd_dq_kernel(BwdArgs a) {
   static_assert(DH == D || (PAD && DH % 32 == 0 && DH < D), "a narrower product width is for padded head dimensions");
@@ -903,10 +918,10 @@ __global__ __launch_bounds__(512) void bwd_dq_kernel(BwdArgs a) {
   constexpr int MASKB = 32 * BC * 2;             // one wavefront's piece of M for one block
   constexpr int MPW = MASK ? MASKB / 1024 : 0;  // copies per wavefront per block
 
-  // (LOCAL: behind the ring, one activity bitmap per wavefront and the list of the key blocks that
+  // (kBlocks: behind the ring, one activity bitmap per wavefront and the list of the key blocks that
   // the workgroup visits, as in the forward kernel)
   constexpr int BITSB = 8 * 8 * kPatternWords, LISTB = 2 * 64 * kPatternWords;
-  __shared__ __attribute__((aligned(1024))) char smem[RING * BUFB + (MASK ? 8 * MASKB : 0) + (LOCAL ? BITSB + LISTB : 0)];
+  __shared__ __attribute__((aligned(1024))) char smem[RING * BUFB + (MASK ? 8 * MASKB : 0) + (LOCAL == kBlocks ? BITSB + LISTB : 0)];
 
   const Problem& p = a.p;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -973,10 +988,10 @@ __global__ __launch_bounds__(512) void bwd_dq_kernel(BwdArgs a) {
   // that any of the eight bitmaps keeps, which is what the workgroup walks (see the forward kernel)
   const unsigned long long* pattern_bits = (const unsigned long long*)(smem + RING * BUFB) + w * kPatternWords;
   const unsigned short* visit = (const unsigned short*)(smem + RING * BUFB + BITSB);
-  const bool sparse = LOCAL && p.bmask != nullptr;
+  constexpr bool sparse = LOCAL == kBlocks;
   int tb = jb, tend = ncol;  // positions of the walk; position t stands for block t unless the pattern thins the walk
   bool listed = false;       // the walk follows the list
-  if (LOCAL && sparse) {
+  if constexpr (sparse) {
     const int r0 = wrow0 < n ? wrow0 : n - 1;
     const uint8_t* bm_row = p.bmask + s * p.bmask_bs + h * p.bmask_hs + (long)(r0 >> p.bmask_log2) * p.bmask_cols;
     for (int q = jb >> 6; q * 64 < ncol; q += 4) {  // (four words a round: their loads are in flight together)
@@ -1016,7 +1031,7 @@ __global__ __launch_bounds__(512) void bwd_dq_kernel(BwdArgs a) {
   }
   // the block at position t (past the end of the walk: any block; its tiles are copied and never read)
   auto blk = [&](int t) {
-    if (!(LOCAL && listed)) return t;
+    if (!(sparse && listed)) return t;
     const int tc = t < tend ? t : tend - 1;
     return tc < 0 ? 0 : __builtin_amdgcn_readfirstlane((int)visit[tc]);
   };
@@ -1302,7 +1317,8 @@ static hipError_t launch_bwd_d(const BwdArgs& a, int causal, int stages, hipStre
       if (causal) hipLaunchKernelGGL((bwd_dq_kernel<D, true, F16, true, false, false, false, true>), qgrid, dim3(512), 0, st, a);
       else hipLaunchKernelGGL((bwd_dq_kernel<D, false, F16, true, false, false, false, true>), qgrid, dim3(512), 0, st, a);
     } else {
-      hipLaunchKernelGGL((bwd_dq_kernel<D, false, F16, false, false, false, true, true>), qgrid, dim3(512), 0, st, a);
+      if (a.p.bmask) hipLaunchKernelGGL((bwd_dq_kernel<D, false, F16, false, false, false, kBlocks, true>), qgrid, dim3(512), 0, st, a);
+      else hipLaunchKernelGGL((bwd_dq_kernel<D, false, F16, false, false, false, kWindow, true>), qgrid, dim3(512), 0, st, a);
     }
     if ((e = hipGetLastError()) != hipSuccess) return e;
     stages = 2;
@@ -1318,7 +1334,8 @@ static hipError_t launch_bwd_d(const BwdArgs& a, int causal, int stages, hipStre
     bool done = false;
     {
       if (a.p.win_left >= 0 || a.p.win_right >= 0 || a.p.bmask) {  // sliding window, block-sparse pattern
-        hipLaunchKernelGGL((bwd_dkdv_kernel<D, false, F16, false, false, false, true>), grid, dim3(512), 0, st, a);
+        if (a.p.bmask) hipLaunchKernelGGL((bwd_dkdv_kernel<D, false, F16, false, false, false, kBlocks>), grid, dim3(512), 0, st, a);
+        else hipLaunchKernelGGL((bwd_dkdv_kernel<D, false, F16, false, false, false, kWindow>), grid, dim3(512), 0, st, a);
         done = true;
       } else
       if (a.p.mask) {
@@ -1355,7 +1372,8 @@ static hipError_t launch_bwd_d(const BwdArgs& a, int causal, int stages, hipStre
     bool done = false;
     {
       if (a.p.win_left >= 0 || a.p.win_right >= 0 || a.p.bmask) {  // sliding window, block-sparse pattern
-        hipLaunchKernelGGL((bwd_dq_kernel<D, false, F16, false, false, false, true>), grid, dim3(512), 0, st, a);
+        if (a.p.bmask) hipLaunchKernelGGL((bwd_dq_kernel<D, false, F16, false, false, false, kBlocks>), grid, dim3(512), 0, st, a);
+        else hipLaunchKernelGGL((bwd_dq_kernel<D, false, F16, false, false, false, kWindow>), grid, dim3(512), 0, st, a);
         done = true;
       } else
       if (a.p.mask) {

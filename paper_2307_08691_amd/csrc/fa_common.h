@@ -60,6 +60,8 @@ struct Problem {
   long bmask_bs, bmask_hs;
   int bmask_cols, bmask_log2;
 };
+// the LOCAL template parameter of the kernels: nothing, a sliding window, a block-sparse pattern (perhaps with a window)
+constexpr int kNoPattern = 0, kWindow = 1, kBlocks = 2;
 constexpr int kPatternWords = 64;  // 64-bit words of a wavefront's activity bitmap in LDS: 4096 blocks or tiles
 
 struct SeqInfo {

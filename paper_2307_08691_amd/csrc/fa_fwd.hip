@@ -96,11 +96,11 @@ __device__ __forceinline__ float max3(float a, float b, float c) { return __buil
 // over the first DH columns: D = 128 with DH = 96 does three quarters of the matrix work of the
 // full width, D = 64 with DH = 32 half.
 template <int D, bool CAUSAL, bool SPLIT, bool F16, bool DROPOUT = false, bool PAD = false, bool MASK = false,
-          bool LOCAL = false, int DH = D>
+          int LOCAL = kNoPattern, int DH = D>
 __global__ __launch_bounds__(512)
-    __attribute__((amdgpu_waves_per_eu(fwd_two_per_cu(D, DROPOUT, MASK || LOCAL) ? 4 : 2, fwd_two_per_cu(D, DROPOUT, MASK || LOCAL) ? 4 : 2))) void
+    __attribute__((amdgpu_waves_per_eu(fwd_two_per_cu(D, DROPOUT, MASK || LOCAL == kBlocks) ? 4 : 2, fwd_two_per_cu(D, DROPOUT, MASK || LOCAL == kBlocks) ? 4 : 2))) void
     fwd_kernel(FwdArgs a) {
-  constexpr bool TWO = fwd_two_per_cu(D, DROPOUT, MASK || LOCAL);
+  constexpr bool TWO = fwd_two_per_cu(D, DROPOUT, MASK || LOCAL == kBlocks);
   static_assert(!LOCAL || (!CAUSAL && !SPLIT && !DROPOUT && !PAD && !MASK), "the window variant is built for the plain kernel");
   constexpr int AHEAD_QK = TWO ? 1 : kFwdAheadQK, AHEAD_PV = TWO ? 1 : kFwdAheadPV;
   static_assert(!MASK || (!SPLIT && !DROPOUT && !PAD), "the mask variant is built for the plain kernel");
@@ -114,11 +114,11 @@ __global__ __launch_bounds__(512)
   constexpr int MASKB = 32 * BC * 2;             // one wavefront's piece of M for one block
   constexpr int MPW = MASK ? MASKB / 1024 : 0;  // copies per wavefront per block
 
-  // (LOCAL: behind the ring, one bitmap of kPatternWords 64-bit words per wavefront: which key blocks
+  // (kBlocks: behind the ring, one bitmap of kPatternWords 64-bit words per wavefront: which key blocks
   // the block-sparse pattern leaves to its rows; behind them the list of the key blocks that it
   // leaves to any row of the workgroup, two bytes each)
   constexpr int BITSB = 8 * 8 * kPatternWords, LISTB = 2 * 64 * kPatternWords;
-  __shared__ __attribute__((aligned(1024))) char smem[RING * BUFB + (MASK ? 8 * MASKB : 0) + (LOCAL ? BITSB + LISTB : 0)];
+  __shared__ __attribute__((aligned(1024))) char smem[RING * BUFB + (MASK ? 8 * MASKB : 0) + (LOCAL == kBlocks ? BITSB + LISTB : 0)];
 
   const Problem& p = a.p;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -218,10 +218,10 @@ __global__ __launch_bounds__(512)
   // neither copies nor phases are spent on a block that the pattern removes from all 256 rows.
   const unsigned long long* pattern_bits = (const unsigned long long*)(smem + RING * BUFB) + w * kPatternWords;
   const unsigned short* visit = (const unsigned short*)(smem + RING * BUFB + BITSB);
-  const bool sparse = LOCAL && p.bmask != nullptr;
+  constexpr bool sparse = LOCAL == kBlocks;
   int tb = jb, tend = ncol;  // positions of the walk; position t stands for block t unless the pattern thins the walk
   bool listed = false;       // the walk follows the list
-  if (LOCAL && sparse) {
+  if constexpr (sparse) {
     const int r0 = prow0 < n ? prow0 : n - 1;
     const uint8_t* bm_row = p.bmask + s * p.bmask_bs + bc.head * p.bmask_hs + (long)(r0 >> p.bmask_log2) * p.bmask_cols;
     for (int q = jb >> 6; q * 64 < ncol; q += 4) {  // (four words a round: their loads are in flight together)
@@ -261,7 +261,7 @@ __global__ __launch_bounds__(512)
   }
   // the block at position t (past the end of the walk: any block; its tiles are copied and never read)
   auto blk = [&](int t) {
-    if (!(LOCAL && listed)) return t;
+    if (!(sparse && listed)) return t;
     const int tc = t < tend ? t : tend - 1;
     return tc < 0 ? 0 : __builtin_amdgcn_readfirstlane((int)visit[tc]);
   };
@@ -430,7 +430,7 @@ __global__ __launch_bounds__(512)
     // rounded into the operand registers of the second product; the row sum is taken from the
     // float32 exponentials, not from their bf16 roundings: rows that see only a few keys would
     // otherwise miss the 1e-3 bound on L. On the fast path S itself stays intact.
-    constexpr bool FAST = !GUARD && !(PAD && TWO);  // (see below)
+    constexpr bool FAST = !(TWO && (PAD || SPLIT));  // (see below)
     float rs0, rs1;
     auto exponentials = [&](float ref) {
       rs0 = rs1 = 0.f;
@@ -465,10 +465,10 @@ __global__ __launch_bounds__(512)
     // is the maximum of the block found, the reference advanced to it, O and l rescaled, and the
     // exponentials taken again. After the first few blocks that is rare: the fast path saves the
     // 16 three-way maxima, the exchange with the partner lane and the comparison per block.
-    // The first block of a row (m = -inf) always takes the second path, and so do the
-    // instantiations in which a row may still have seen no key (split keys, elementwise mask)
-    // and the one that has no registers left to keep S beside the exponentials.
-    bool advance = !FAST || t == tb;
+    // The first block of a row always takes the second path, and where a row may still have seen no key
+    // (GUARD: m = -inf) every block until it has; so do the instantiations that have no registers
+    // left to keep S beside the exponentials.
+    bool advance = !FAST || t == tb || (GUARD && __builtin_amdgcn_ballot_w64(m == -INFINITY) != 0);
     if (!advance) {
       exponentials(m * cs);
       advance = __builtin_amdgcn_ballot_w64(rs0 + rs1 > (float)(1 << (F16 ? kFwdLazyLog2Half : kFwdLazyLog2Bf16))) != 0;
@@ -487,7 +487,7 @@ __global__ __launch_bounds__(512)
       // finite from the first block on and exp2(-inf) = 0 covers the start (not so with split
       // keys or a mask: GUARD). Without the fast path the reference is advanced only when some
       // row's maximum outgrew it by a factor 2^kFwdLazyLog2.
-      if (FAST || __builtin_amdgcn_ballot_w64((m_new - m) * cs > (float)(F16 ? kFwdLazyLog2Half : kFwdLazyLog2Bf16)) != 0) {
+      if (FAST ? !GUARD || __builtin_amdgcn_ballot_w64(m_new > m) != 0 : __builtin_amdgcn_ballot_w64((m_new - m) * cs > (float)(F16 ? kFwdLazyLog2Half : kFwdLazyLog2Bf16)) != 0) {
         // (split, mask: a row that has still seen no key has m = m_new = -inf and nothing to rescale)
         const float alpha = GUARD && m_new == -INFINITY ? 1.f : fast_exp2((m - m_new) * cs);
         l *= alpha;
@@ -1018,7 +1018,8 @@ static hipError_t launch_fwd_d(const FwdArgs& a, int causal, hipStream_t st) {
     return hipGetLastError();
   }
   if (a.p.win_left >= 0 || a.p.win_right >= 0 || a.p.bmask) {  // sliding window, block-sparse pattern (the entry points keep everything else away from them)
-    hipLaunchKernelGGL((fwd_kernel<D, false, false, F16, false, false, false, true>), grid, block, 0, st, a);
+    if (a.p.bmask) hipLaunchKernelGGL((fwd_kernel<D, false, false, F16, false, false, false, kBlocks>), grid, block, 0, st, a);
+    else hipLaunchKernelGGL((fwd_kernel<D, false, false, F16, false, false, false, kWindow>), grid, block, 0, st, a);
     return hipGetLastError();
   }
   if (a.p.d != D) {  // padded head dimension (the entry points keep dropout away from it)

@@ -37,9 +37,9 @@ __device__ __forceinline__ int swz_off(int row, int chunk) { return row * ROWB +
 // copies (it cannot tell the ring buffers apart), which serialises the prefetch. The
 // kernels order these copies themselves with wait_vmem*() + barriers. M0 holds the LDS
 // base for the duration of the instruction only; the compiler keeps no value live in M0.
-__device__ __forceinline__ unsigned lds_address(const void* p) {
-  return (unsigned)(size_t)(__attribute__((address_space(3))) const char*)p;
-}
+// (the LDS offset is the low half of a generic LDS address; a cast to the LDS address space would do the same
+// behind a test for the null pointer)
+__device__ __forceinline__ unsigned lds_address(const void* p) { return (unsigned)(size_t)p; }
 __device__ __forceinline__ void dma16(const void* gaddr, const void* lds) {
   asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(gaddr),
                "s"(__builtin_amdgcn_readfirstlane(lds_address(lds)))

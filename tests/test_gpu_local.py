@@ -26,7 +26,7 @@ def window_mask_gpu(nq, nk, left, right):
     return torch.where(vis, 0.0, float("-inf"))[None, None]
 
 
-def check_local(prob, left, right):
+def check_local(prob, left, right, standard=True):
     Q, K, V, dO = (pu.to_gpu(x, prob.dtype) for x in (prob.Q, prob.K, prob.V, prob.dO))
     O, L = binding.fa_local_fwd(Q, K, V, prob.scale, left, right)
     dQ, dK, dV = binding.fa_local_bwd(Q, K, V, O, dO, L, prob.scale, left, right)
@@ -39,8 +39,17 @@ def check_local(prob, left, right):
     ref = pu.reference_batch(Q, K, V, dO, prob.scale, False, M=window_mask_gpu(prob.N, prob.keys, left, right))
     pu.judge(f"window ({left},{right}) {pu.describe(prob)}",
              {nm: pu.to_f64(t) for nm, t in (("O", O), ("LSE", L), ("dQ", dQ), ("dK", dK), ("dV", dV))}, exp, ref,
-             dtype=prob.dtype, d=prob.d)
+             standard=standard, dtype=prob.dtype, d=prob.d)
     return O, L, dQ, dK, dV
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("left,right", [(40, 0), (300, 0), (5, 200), (-1, 40)])
+def test_windows_with_widely_spread_scores(left, right, d):
+    """Scores of tens of bits: the reference of the running softmax advances again and again, in rows
+    that have seen keys and in rows whose window has only just begun."""
+    prob = inputs.make_dense(B=1, N=700, Hq=2, Hkv=2, d=d, causal=False, seed=16900 + left + right, qk_mult=5.0)
+    check_local(prob, left, right, standard=False)
 
 
 @pytest.mark.parametrize("d", [64, 128])

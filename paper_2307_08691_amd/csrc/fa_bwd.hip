@@ -97,6 +97,8 @@ constexpr int kDkdvAhead = 4;  // how many MFMAs ahead the LDS operands are requ
 constexpr bool dkdv_wide(bool mask) { return !mask; }
 constexpr int dkdv_block_keys(bool mask) { return dkdv_wide(mask) ? 256 : 128; }
 //
+// NW = 4: a workgroup of 128 keys, the four wavefronts of group 0 alone (see small_workgroups).
+//
 // PAD: head dimension p.d below the tile width D, rows padded with zeros on chip (see the
 // forward kernel); only the first p.d columns of dK, dV are stored.
 //
@@ -117,15 +119,17 @@ constexpr int dkdv_block_keys(bool mask) { return dkdv_wide(mask) ? 256 : 128; }
 // DH (PAD only): the head dimension rounded up to a multiple of 32; the products run over the
 // first DH columns of the D-wide tiles only (see the forward kernel).
 template <int D, bool CAUSAL, bool F16, bool DROPOUT = false, bool PAD = false, bool MASK = false,
-          int LOCAL = kNoPattern, int DH = D>
-__global__ __launch_bounds__(512) void bwd_dkdv_kernel(BwdArgs a) {
+          int LOCAL = kNoPattern, int DH = D, int NW = 8>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 128 ? NW / 4 : 2, D == 128 ? NW / 4 : 2))) void
+    bwd_dkdv_kernel(BwdArgs a) {
   static_assert(DH == D || (PAD && DH % 32 == 0 && DH < D), "a narrower product width is for padded head dimensions");
   static_assert(!MASK || (!DROPOUT && !PAD), "the mask variant is built for the plain kernel");
   static_assert(!LOCAL || (!CAUSAL && !DROPOUT && !PAD && !MASK), "the window variant is built for the plain kernel");
   constexpr bool KREG = !MASK;  // K_j operands of the wavefront's 32 keys in registers
   constexpr bool VREG = D == 64 && !MASK;  // at d = 64 V_j's as well
   constexpr bool WIDE = dkdv_wide(MASK);
-  constexpr int BC = dkdv_block_keys(MASK);  // keys per workgroup
+  static_assert(NW == 8 || (NW == 4 && WIDE && LOCAL != kBlocks), "the small workgroup is the plain kernel's group 0");
+  constexpr int BC = NW == 4 ? 128 : dkdv_block_keys(MASK);  // keys per workgroup
   constexpr int QTW = D == 128 ? 1 : 2;  // 32-row query tiles per wavefront per step
   constexpr int BR = 32 * QTW;          // query rows of one tile
   constexpr int KS = DH / 16, DT = DH / 32;
@@ -164,7 +168,7 @@ __global__ __launch_bounds__(512) void bwd_dkdv_kernel(BwdArgs a) {
   if (j0 >= nk) return;
   const int dh = PAD ? p.d : D;  // row length in memory
   const long qstride = (long)p.Hq * dh, kstride = (long)p.Hkv * dh;
-  if (PAD) lds_zero<512>(smem, SMEM);
+  if (PAD) lds_zero<64 * NW>(smem, SMEM);
 
   const float c2 = p.scale_log2e;
   const int nrt = (n + BR - 1) / BR;         // row tiles of the sequence
@@ -340,9 +344,9 @@ __global__ __launch_bounds__(512) void bwd_dkdv_kernel(BwdArgs a) {
   //      read from there, or from registers, see Kf / Vf below); tiles 0..2 are requested up
   //      front by all wavefronts
   if (K_IN_LDS)
-    tile_load_async<D, BC, 8, PAD>(smem + KT_OFF, a.K + (si.tok0k * p.Hkv + g) * dh, kstride, j0, nk - 1, v, lane, dh / 8);
+    tile_load_async<D, BC, NW, PAD>(smem + KT_OFF, a.K + (si.tok0k * p.Hkv + g) * dh, kstride, j0, nk - 1, v, lane, dh / 8);
   if (V_IN_LDS)
-    tile_load_async<D, BC, 8, PAD>(smem + VT_OFF, a.V + (si.tok0k * p.Hkv + g) * dh, kstride, j0, nk - 1, v, lane, dh / 8);
+    tile_load_async<D, BC, NW, PAD>(smem + VT_OFF, a.V + (si.tok0k * p.Hkv + g) * dh, kstride, j0, nk - 1, v, lane, dh / 8);
   // this lane's key column, and (WIDE) its K_j / V_j operands straight from memory: the 8
   // elements 16 ks + 8 hh .. of the key's row are exactly what lane (lq, hh) feeds to MFMA ks
   const int key = j0 + 32 * kgi + lq;
@@ -367,9 +371,9 @@ __global__ __launch_bounds__(512) void bwd_dkdv_kernel(BwdArgs a) {
       if (sparse && listed) c = cursor_at(tile_no(t), t);
       const long first = c.qoff - (long)c.it * BR * qstride;  // row 0 of this head
       char* dst = smem + QDO_OFF + c.slot * BUFB;
-      tile_load_async<D, BR, 8, PAD>(dst, a.Q + first, qstride, c.it * BR, n - 1, v, lane, dh / 8);
-      tile_load_async<D, BR, 8, PAD>(dst + TILEB, a.dO + first, qstride, c.it * BR, n - 1, v, lane, dh / 8);
-      if (tid >= t * BR && tid < (t + 1) * BR) {  // 3 * BR <= 512 threads
+      tile_load_async<D, BR, NW, PAD>(dst, a.Q + first, qstride, c.it * BR, n - 1, v, lane, dh / 8);
+      tile_load_async<D, BR, NW, PAD>(dst + TILEB, a.dO + first, qstride, c.it * BR, n - 1, v, lane, dh / 8);
+      if (tid >= t * BR && tid < (t + 1) * BR) {  // (one row of these tiles per thread)
         const int row = c.it * BR + tid - t * BR;
         const bool ok = row < n;
         const long si_ = stat_base + (long)c.hq * p.lse_head_stride + (ok ? row : n - 1);
@@ -743,7 +747,7 @@ __global__ __launch_bounds__(512) void bwd_dkdv_kernel(BwdArgs a) {
           mfma_stream_begin<NM2, AH, 2>(pre, [&](int i) { return load_m2(cur, i); });
         }
       };
-      if (grp == 0) {  // barrier after the vector phase; this group requests the tiles
+      if (NW == 4 || grp == 0) {  // barrier after the vector phase; this group requests the tiles
         int t = 0;
         for (; t < skip; ++t) {
           end_matrix_work();
@@ -812,7 +816,7 @@ __global__ __launch_bounds__(512) void bwd_dkdv_kernel(BwdArgs a) {
     // ---- write dK_j, dV_j (line 18); dK carries the scaling. The ring is idle now (no copy is
     // requested past the last tile): each wavefront stages its rows there and stores whole rows.
     {
-      static_assert(RING * BUFB >= 8 * 32 * ROWB, "the ring holds one 32-key tile per wavefront");
+      static_assert(RING * BUFB >= NW * 32 * ROWB, "the ring holds one 32-key tile per wavefront");
       char* stg = smem + QDO_OFF + v * (32 * ROWB);
       const int key0 = j0 + 32 * kgi;
       const long kvoff = ((si.tok0k + key0) * p.Hkv + g) * dh;
@@ -906,12 +910,13 @@ __global__ __launch_bounds__(512) void bwd_dkdv_kernel(BwdArgs a) {
 // which then runs after this one: the whole backward without the separate D pre-pass.
 // DH (PAD only): the narrower product width of a padded head dimension (see the forward kernel).
 template <int D, bool CAUSAL, bool F16, bool DROPOUT = false, bool PAD = false, bool MASK = false, int LOCAL = kNoPattern,
-          bool OWN_D = false, int DH = D>
-__global__ __launch_bounds__(512) void bwd_dq_kernel(BwdArgs a) {
+          bool OWN_D = false, int DH = D, int NW = 8>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2))) void bwd_dq_kernel(BwdArgs a) {
   static_assert(DH == D || (PAD && DH % 32 == 0 && DH < D), "a narrower product width is for padded head dimensions");
   static_assert(!MASK || (!DROPOUT && !PAD), "the mask variant is built for the plain kernel");
   static_assert(!LOCAL || (!CAUSAL && !DROPOUT && !PAD && !MASK), "the window variant is built for the plain kernel");
-  constexpr int BR = 256, BC = 64, RING = 4;
+  static_assert(NW == 8 || (NW == 4 && !MASK && LOCAL != kBlocks), "the small workgroup is the plain kernel's group 0");
+  constexpr int BR = 32 * NW, BC = 64, RING = 4;
   constexpr int KS = DH / 16, DT = DH / 32;
   constexpr int ROWB = 2 * D;
   constexpr int TILEB = BC * ROWB, BUFB = 2 * TILEB;  // one buffer = K_j | V_j
@@ -941,7 +946,7 @@ __global__ __launch_bounds__(512) void bwd_dq_kernel(BwdArgs a) {
   const long kstride = (long)p.Hkv * dh;
   const __bf16* Kb = a.K + (si.tok0k * p.Hkv + g) * dh;
   const __bf16* Vb = a.V + (si.tok0k * p.Hkv + g) * dh;
-  if (PAD) lds_zero<512>(smem, RING * BUFB);
+  if (PAD) lds_zero<64 * NW>(smem, RING * BUFB);
 
   // ---- Q_i, dO_i operands and L_i, D_i of this lane's query row: registers for the whole kernel
   const int wrow0 = i0 + 32 * w;
@@ -1040,10 +1045,11 @@ __global__ __launch_bounds__(512) void bwd_dq_kernel(BwdArgs a) {
   // own vector phase (see the forward kernel)
   TileLoader<D, BC, 4, PAD> loader;
   loader.init(kstride, w & 3, lane, dh / 8);
-  constexpr int TPW = TileLoader<D, BC, 4, PAD>::PER;
+  constexpr int TPW = (NW == 4 ? 2 : 1) * TileLoader<D, BC, 4, PAD>::PER;  // (four wavefronts bring in both tiles)
   auto issue_tile = [&](int t) {  // the block at position t of the walk
     char* dst = smem + (t % RING) * BUFB + (grp == 0 ? TILEB : 0);
     loader.load(dst, grp == 0 ? Vb : Kb, kstride, blk(t) * BC, nk - 1, w & 3, lane);
+    if (NW == 4) loader.load(dst - TILEB, Kb, kstride, blk(t) * BC, nk - 1, w & 3, lane);
   };
   char* mbuf = smem + RING * BUFB + w * MASKB;
   const __bf16* Mb = MASK ? p.mask + s * p.mask_bs + h * p.mask_hs : nullptr;
@@ -1240,7 +1246,7 @@ __global__ __launch_bounds__(512) void bwd_dq_kernel(BwdArgs a) {
 
   // phases: see the forward kernel (j counts positions of the walk; one barrier per block, the one
   // between a group's matrix and vector phase is left out as in the forward kernel's one-workgroup form)
-  if (grp == 0) {
+  if (NW == 4 || grp == 0) {
     for (int j = tb; j <= tend; ++j) {
       matrix_phase(j);
       issue_tile(j + 2);
@@ -1285,8 +1291,31 @@ __global__ __launch_bounds__(512) void bwd_dq_kernel(BwdArgs a) {
   }
 }
 
+// Whether the four-wavefront form of a backward kernel is taken: workgroups of 128 rows (keys) instead of 256, the
+// program of the eight-wavefront form's group 0; at d = 64 two of them fit on a compute unit.
+//  * The whole grid of small workgroups fits the 256 compute units at once (MI355X, backward, from the larger to the
+//    smaller form in both kernels at d = 64: 1 x 512, 8 heads: 35 -> 30 us; 1 x 4096, 8 heads: 170 -> 153; 2 x 1000,
+//    16 heads 55 -> 49; at d = 128 the dK/dV kernel alone: 1 x 1531, 32 heads on 8: 287 -> 262; the dQ kernel
+//    does not gain there).
+//  * `two` (two fit on a compute unit) and there are many of them: where blocks of 256 would be mostly padding
+//    (16 x 300, 32 heads, no mask: 107 -> 86 us), and in the causal dK/dV kernel (`short_too`), whose 128-key blocks
+//    also start closer to the diagonal, up to 4096 keys (16k tokens, N = 512: 304 -> 284 us, 2048: 584 -> 572,
+//    4096: 980 -> 975, 8192: 1779 -> 1807).
+static bool small_workgroups(int n, int pairs, bool short_too, bool two = true) {
+  const long small = (long)((n + 127) / 128) * pairs, large = (long)((n + 255) / 256) * pairs;
+  if (small <= 256) return true;
+  if (!two) return false;
+  if (short_too && n <= 4096) return true;
+  return large >= 512 && 2 * large * 5 >= 6 * small;
+}
+
 template <int D, bool F16>
-static hipError_t launch_bwd_d(const BwdArgs& a, int causal, int stages, hipStream_t st) {
+static hipError_t launch_bwd_d(BwdArgs a, int causal, int stages, hipStream_t st) {
+  // The dQ kernel reads Q, K, V, O that the forward pass has just streamed through the last-level cache (256 MB) and
+  // the dK/dV kernel most of them again: it goes through the pairs from the last to the first and finds the
+  // newest there first, and so does the dK/dV kernel after it (16k tokens, 32 heads of 64, MI355X, backward: N = 256
+  // 250 -> 235 us, N = 512 without the mask 337 -> 326 us, N >= 1024 -1% .. 0).
+  a.p.pairs_back = 1;
   const long nrows = (long)a.p.total_tokens * a.p.Hq;
   constexpr int RPB = 256 / (D / 8);
   constexpr int DN = D == 128 ? 96 : 32;  // the narrower product width of this tile width (padded head dimensions)
@@ -1296,7 +1325,15 @@ static hipError_t launch_bwd_d(const BwdArgs& a, int causal, int stages, hipStre
   const bool plain = !a.p.mask && !a.p.drop_thr && !a.p.bmask && a.p.win_left < 0 && a.p.win_right < 0;
   if (stages == 7 && plain) {
     dim3 qgrid(grid_size((a.p.N + 255) / 256, a.p.Hq * a.p.nseq));
-    if (a.p.d != D && a.p.d <= DN) {
+    bool small = false;
+    if constexpr (D == 64) {
+      small = a.p.d == D && small_workgroups(a.p.N, a.p.Hq * a.p.nseq, false);
+      const dim3 sgrid(grid_size((a.p.N + 127) / 128, a.p.Hq * a.p.nseq));
+      if (small && causal) hipLaunchKernelGGL((bwd_dq_kernel<D, true, F16, false, false, false, kNoPattern, true, D, 4>), sgrid, dim3(256), 0, st, a);
+      else if (small) hipLaunchKernelGGL((bwd_dq_kernel<D, false, F16, false, false, false, kNoPattern, true, D, 4>), sgrid, dim3(256), 0, st, a);
+    }
+    if (small) {
+    } else if (a.p.d != D && a.p.d <= DN) {
       if (causal) hipLaunchKernelGGL((bwd_dq_kernel<D, true, F16, false, true, false, false, true, DN>), qgrid, dim3(512), 0, st, a);
       else hipLaunchKernelGGL((bwd_dq_kernel<D, false, F16, false, true, false, false, true, DN>), qgrid, dim3(512), 0, st, a);
     } else if (a.p.d != D) {
@@ -1330,6 +1367,13 @@ static hipError_t launch_bwd_d(const BwdArgs& a, int causal, int stages, hipStre
   if (stages & 2) {
     // keys per workgroup differ between the instantiations
     const int bck = dkdv_block_keys(a.p.mask != nullptr);
+    a.p.pairs_back = 0;
+    if (a.p.d == D && plain && small_workgroups(a.p.Nk, a.p.Hkv * a.p.nseq, D == 64 && causal, D == 64)) {
+      const dim3 sgrid(grid_size((a.p.Nk + 127) / 128, a.p.Hkv * a.p.nseq));
+      if (causal) hipLaunchKernelGGL((bwd_dkdv_kernel<D, true, F16, false, false, false, kNoPattern, D, 4>), sgrid, dim3(256), 0, st, a);
+      else hipLaunchKernelGGL((bwd_dkdv_kernel<D, false, F16, false, false, false, kNoPattern, D, 4>), sgrid, dim3(256), 0, st, a);
+      return hipGetLastError();
+    }
     dim3 grid(grid_size((a.p.Nk + bck - 1) / bck, a.p.Hkv * a.p.nseq));
     bool done = false;
     {

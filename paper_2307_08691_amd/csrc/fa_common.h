@@ -59,6 +59,7 @@ struct Problem {
   const uint8_t* bmask;
   long bmask_bs, bmask_hs;
   int bmask_cols, bmask_log2;
+  int pairs_back;  // set by a launch: hand the (head, sequence) pairs out from the last to the first (see launch_bwd_d)
 };
 // the LOCAL template parameter of the kernels: nothing, a sliding window, a block-sparse pattern (perhaps with a window)
 constexpr int kNoPattern = 0, kWindow = 1, kBlocks = 2;
@@ -115,7 +116,7 @@ __host__ __device__ inline unsigned grid_size(int nblk, int pairs) {
 // distance of nheads / group pairs. With a multiple of 8 key/value heads they then land on the
 // same XCD, whose L2 holds the group's K and V once instead of every XCD holding them all.
 template <bool WORK_SORTED>
-__device__ __forceinline__ BlockCoord block_coord(int nblk, int nheads, int nseq, int group = 1) {
+__device__ __forceinline__ BlockCoord block_coord(int nblk, int nheads, int nseq, int group = 1, int back = 0) {
   const int L = blockIdx.x;
   const int x = L % kXcds, k = L / kXcds;
   const int ppx = gridDim.x / (kXcds * nblk);  // pairs per XCD
@@ -128,6 +129,7 @@ __device__ __forceinline__ BlockCoord block_coord(int nblk, int nheads, int nseq
     c.blk = k % nblk;
     pl = k / nblk;
   }
+  if (back) pl = ppx - 1 - pl;
   const int pr = pl * kXcds + x;
   const int hp = pr % nheads, nkv = nheads / group;
   c.head = (hp % nkv) * group + hp / nkv;
@@ -241,7 +243,7 @@ __device__ __forceinline__ BlockCoord row_block_coord(const Problem& p, int rows
     const RaggedCoord r = ragged_coord<CAUSAL>(p.cu_seqlens, rows, nblk, p.Hq, p.nseq, p.G);
     c = {CAUSAL ? r.left - 1 : r.blk, r.head, r.seq, r.valid};
   } else {
-    c = block_coord<CAUSAL>(nblk, p.Hq, p.nseq, p.G);
+    c = block_coord<CAUSAL>(nblk, p.Hq, p.nseq, p.G, p.pairs_back);
     c.blk = nblk - 1 - c.blk;
   }
   return scalar_coord(c);

@@ -120,6 +120,23 @@ def test_packed_ragged_equals_dense_calls_bitwise():
     assert torch.equal(dense["dQ"].reshape(600, 4, 128), rag["dQ"])
 
 
+# (lengths on either side of the 128- and 256-row blocks; 36 sequences x 8 heads fill more than 256 workgroups
+# of either size, one sequence does not)
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("N,Hq,Hkv,d", [(128, 8, 8, 64), (129, 8, 8, 64), (256, 8, 8, 64), (257, 8, 4, 64), (385, 8, 8, 64),
+                                        (640, 8, 8, 64), (129, 8, 8, 128), (300, 16, 8, 128)])
+def test_small_and_large_workgroups_agree_bitwise(N, Hq, Hkv, d, causal):
+    """The form of the backward kernels is chosen by the size of the grid; a sequence's results do not depend on it."""
+    prob = inputs.make_dense(B=36, N=N, Hq=Hq, Hkv=Hkv, d=d, causal=causal, seed=9300 + N)
+    Q, K, V, dO = (pu.to_gpu(x, prob.dtype) for x in (prob.Q, prob.K, prob.V, prob.dO))
+    O, L = binding.fa_fwd(Q, K, V, prob.scale, causal)
+    grads = binding.fa_bwd(Q, K, V, O, dO, L, prob.scale, causal)
+    for s in (0, 17, 35):
+        alone = binding.fa_bwd(*(x[s:s + 1].contiguous() for x in (Q, K, V, O, dO, L)), prob.scale, causal)
+        for name, x, y in zip(("dQ", "dK", "dV"), grads, alone):
+            assert torch.equal(x[s], y[0]), name
+
+
 @pytest.mark.parametrize("d", [64, 128])
 def test_every_output_is_bit_reproducible(d):
     """No output is accumulated by atomic adds (dQ comes from a row-block pass of its own instead

@@ -58,9 +58,10 @@ constexpr int kFwdChainMaxN = 1024;
 // 16 wavefronts do, i.e. with at most 128 registers each. Two resident workgroups overlap one's
 // start-up (Q and the first tiles: one memory latency) and epilogue with the other's loop,
 // which a single workgroup per compute unit cannot: 10% faster at N = 8192, 27% at N = 512.
-// The price is the shortest operand prefetch (one MFMA ahead). Not for dropout (more
-// registers) or the elementwise mask (more LDS).
-constexpr bool fwd_two_per_cu(int D, bool dropout, bool mask) { return D == 64 && !dropout && !mask; }
+// The price is the shortest operand prefetch (one MFMA ahead), and for dropout the softmax path
+// without row maxima, whose second copy of the scores does not fit (fp16, 4 x 1777 tokens, 16 heads, MI355X:
+// 109 -> 98 us all the same). Not for the elementwise mask (more LDS).
+constexpr bool fwd_two_per_cu(int D, bool mask) { return D == 64 && !mask; }
 
 __device__ __forceinline__ float max3(float a, float b, float c) { return __builtin_fmaxf(__builtin_fmaxf(a, b), c); }
 
@@ -98,9 +99,9 @@ __device__ __forceinline__ float max3(float a, float b, float c) { return __buil
 template <int D, bool CAUSAL, bool SPLIT, bool F16, bool DROPOUT = false, bool PAD = false, bool MASK = false,
           int LOCAL = kNoPattern, int DH = D>
 __global__ __launch_bounds__(512)
-    __attribute__((amdgpu_waves_per_eu(fwd_two_per_cu(D, DROPOUT, MASK || LOCAL == kBlocks) ? 4 : 2, fwd_two_per_cu(D, DROPOUT, MASK || LOCAL == kBlocks) ? 4 : 2))) void
+    __attribute__((amdgpu_waves_per_eu(fwd_two_per_cu(D, MASK || LOCAL == kBlocks) ? 4 : 2, fwd_two_per_cu(D, MASK || LOCAL == kBlocks) ? 4 : 2))) void
     fwd_kernel(FwdArgs a) {
-  constexpr bool TWO = fwd_two_per_cu(D, DROPOUT, MASK || LOCAL == kBlocks);
+  constexpr bool TWO = fwd_two_per_cu(D, MASK || LOCAL == kBlocks);
   static_assert(!LOCAL || (!CAUSAL && !SPLIT && !DROPOUT && !PAD && !MASK), "the window variant is built for the plain kernel");
   constexpr int AHEAD_QK = TWO ? 1 : kFwdAheadQK, AHEAD_PV = TWO ? 1 : kFwdAheadPV;
   static_assert(!MASK || (!SPLIT && !DROPOUT && !PAD), "the mask variant is built for the plain kernel");
@@ -430,7 +431,7 @@ __global__ __launch_bounds__(512)
     // rounded into the operand registers of the second product; the row sum is taken from the
     // float32 exponentials, not from their bf16 roundings: rows that see only a few keys would
     // otherwise miss the 1e-3 bound on L. On the fast path S itself stays intact.
-    constexpr bool FAST = !(TWO && (PAD || SPLIT));  // (see below)
+    constexpr bool FAST = !(TWO && (PAD || SPLIT || DROPOUT));  // (see below)
     float rs0, rs1;
     auto exponentials = [&](float ref) {
       rs0 = rs1 = 0.f;

@@ -808,26 +808,35 @@ FA_SPLITKV_MAX_SPLITS = 128
 def splitkv_default_splits(B, Hq, Hkv, Nq, Nk, ragged: bool = False) -> int:
     """About one workgroup per compute unit, and at least 8 blocks of 64 keys per share (measured:
     more, shorter shares cost more in prologues and in the merge than they gain in parallelism).
-    ragged (a cache with a length of its own per sequence, Nk the capacity; the kernels hand the sequences
-    out longest first): the same for up to 128 sequences in decoding shapes (measured on 64 sequences
-    of 1 .. 8192 keys: 1 share 5.0 TB/s, 4 shares 4.3, 16 shares 2.5). With more query rows than
-    that, sequences of different lengths want half as many workgroups again as there are compute units,
-    and at least 16 blocks per share (d = 128, 32 heads on 8, lengths up to 8192; us at 1 / 2 / 3 / 4 / 8
-    shares: 4 x 512 queries, 256 workgroups per share: 191 / 158 / 166 / 187 / 212; 8 x 128, 128
-    workgroups: 177 / 110 / 87 / 95 / 115; 8 x 1000, 1024 workgroups: 408 / 568 / 583 / 732 / 816, float32
-    partial results and the merge being what a share costs). One sequence has equal shares, and they
-    should fill the compute units once (1 x 512, 64 workgroups: 4 shares 80, 6 shares 101). In batches
-    of more than 128 sequences, which keep the launch order, decoding shapes take about eight workgroups per
-    compute unit (64 sequences in launch order: 4 shares 3.7 TB/s, 1 share 2.6, 16 shares 2.9)."""
-    rows = Nq * (Hq // Hkv)
-    units = B * Hkv * ((rows + 255) // 256)
+    ragged (a cache with a length of its own per sequence, Nk the capacity): the same for up to 128
+    sequences in decoding shapes, where the decode kernel hands the sequences out longest first
+    (measured on 64 sequences of 1 .. 8192 keys: 1 share 5.0 TB/s, 4 shares 4.3, 16 shares 2.5);
+    otherwise about eight workgroups per compute unit and at least 16 blocks per share of a full
+    cache, since more, shorter shares then even the load out (same batch in launch order: 4 shares
+    3.7 TB/s, 1 share 2.6, 16 shares 2.9). (fa_kvcache_fwd takes no more than this many.)"""
+    units = B * Hkv * ((Nq * (Hq // Hkv) + 255) // 256)
     blocks = (Nk + 63) // 64
-    least, want = 8, 256
-    if ragged and rows > 32:
-        least, want = 16, 384 if B > 1 else 256
-    elif ragged and B > 128:
-        least, want = 16, 2048
-    return max(1, min(FA_SPLITKV_MAX_SPLITS, blocks // least, -(-want // units)))
+    if ragged and not (B <= 128 and Nq * (Hq // Hkv) <= 32):
+        return max(1, min(FA_SPLITKV_MAX_SPLITS, blocks // 16, -(-2048 // units)))
+    return max(1, min(FA_SPLITKV_MAX_SPLITS, blocks // 8, -(-256 // units)))
+
+
+def _cache_splits(B, Hq, Hkv, Nq, Nk, ragged: bool) -> int:
+    """Shares of fa_kvcache_fwd when the caller names none: splitkv_default_splits, but fewer where more than 32
+    query rows meet caches with lengths of their own (the row-block kernel; longest sequence first). Sequences of
+    different lengths then want half as many workgroups again as there are compute units, and shares of at
+    least 16 blocks (d = 128, 32 heads on 8, lengths up to 8192; us at 1 / 2 / 3 / 4 / 8 shares: 4 x 512
+    queries, 256 workgroups per share: 191 / 158 / 166 / 187 / 212; 8 x 128, 128 workgroups:
+    177 / 110 / 87 / 95 / 115; 8 x 1000, 1024 workgroups: 408 / 568 / 583 / 732 / 816, float32 partial
+    results and the merge being what a share costs). One sequence has equal shares, and they should fill the
+    compute units once (1 x 512, 64 workgroups: 4 shares 80, 6 shares 101). Never more than
+    splitkv_default_splits: a workspace sized by that is large enough."""
+    rows = Nq * (Hq // Hkv)
+    if not ragged or rows <= 32:
+        return splitkv_default_splits(B, Hq, Hkv, Nq, Nk, ragged)
+    units = B * Hkv * ((rows + 255) // 256)
+    want = 384 if B > 1 else 256
+    return max(1, min(FA_SPLITKV_MAX_SPLITS, (Nk + 63) // 64 // 16, -(-want // units)))
 
 
 def fa_splitkv_fwd(Q, K, V, scale: float, causal: bool, num_splits: int = 0, O=None, LSE=None, workspace=None):
@@ -877,7 +886,7 @@ def fa_kvcache_fwd(Q, Kcache, Vcache, scale: float, causal: bool, seqlens_k=None
         _need(seqlens_k, "seqlens_k", torch.int32, (x.B,), x.dev)
     x.q_shape, x.l_shape = (x.B, x.Nq, x.Hq, x.d), (x.B, x.Hq, x.Nq)
     if num_splits <= 0:
-        num_splits = splitkv_default_splits(x.B, x.Hq, x.Hkv, x.Nq, x.Nk, ragged=seqlens_k is not None)
+        num_splits = _cache_splits(x.B, x.Hq, x.Hkv, x.Nq, x.Nk, seqlens_k is not None)
     O, LSE = _fwd_outputs(x, O, LSE)
     ws = _workspace(workspace, fa_splitkv_fwd_workspace_bytes(x.B, x.Hq, x.Nq, x.d, num_splits), x.dev)
     _check(fa_kvcache_fwd_raw(_ptr(Q), _ptr(Kcache), _ptr(Vcache), _ptr(seqlens_k) if seqlens_k is not None else 0,

@@ -64,7 +64,7 @@ __global__ __launch_bounds__(256) void bwd_prep_kernel(BwdArgs a) {
 
 
 // dK/dV kernel: 8 wavefronts in two groups of four. Two forms share the code below.
-// WIDE (every instantiation but the mask's): 256 keys per workgroup, wavefront
+// WIDE (every instantiation but the mask's and SHARED): 256 keys per workgroup, wavefront
 // v owns keys 32*v.. and visits every tile; see the comment at `if constexpr (WIDE)`.
 // Otherwise (mask: its extra registers leave no room for K_j in registers, and K_j
 // plus V_j of 256 keys do not fit in LDS): 128 keys per workgroup, wavefront (kg, grp) owns
@@ -94,10 +94,12 @@ __global__ __launch_bounds__(256) void bwd_prep_kernel(BwdArgs a) {
 // distinct operand.
 constexpr int kDkdvAhead = 4;  // how many MFMAs ahead the LDS operands are requested (3 where K_j takes the registers)
 // keys per workgroup of the dK/dV kernel instantiation (the launch needs it for the grid)
-constexpr bool dkdv_wide(bool mask) { return !mask; }
-constexpr int dkdv_block_keys(bool mask) { return dkdv_wide(mask) ? 256 : 128; }
+constexpr int dkdv_block_keys(bool mask) { return mask ? 128 : 256; }
 //
 // NW = 4: a workgroup of 128 keys, the four wavefronts of group 0 alone (see small_workgroups).
+//
+// SHARED (dropout at d = 128 on small grids): the form that is not WIDE. Its two groups halve the chain of row
+// tiles that a block of keys stands for, which is what the time is where every workgroup is resident at once.
 //
 // PAD: head dimension p.d below the tile width D, rows padded with zeros on chip (see the
 // forward kernel); only the first p.d columns of dK, dV are stored.
@@ -119,17 +121,17 @@ constexpr int dkdv_block_keys(bool mask) { return dkdv_wide(mask) ? 256 : 128; }
 // DH (PAD only): the head dimension rounded up to a multiple of 32; the products run over the
 // first DH columns of the D-wide tiles only (see the forward kernel).
 template <int D, bool CAUSAL, bool F16, bool DROPOUT = false, bool PAD = false, bool MASK = false,
-          int LOCAL = kNoPattern, int DH = D, int NW = 8>
+          int LOCAL = kNoPattern, int DH = D, int NW = 8, bool SHARED = false>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 128 ? NW / 4 : 2, D == 128 ? NW / 4 : 2))) void
     bwd_dkdv_kernel(BwdArgs a) {
   static_assert(DH == D || (PAD && DH % 32 == 0 && DH < D), "a narrower product width is for padded head dimensions");
   static_assert(!MASK || (!DROPOUT && !PAD), "the mask variant is built for the plain kernel");
   static_assert(!LOCAL || (!CAUSAL && !DROPOUT && !PAD && !MASK), "the window variant is built for the plain kernel");
-  constexpr bool KREG = !MASK;  // K_j operands of the wavefront's 32 keys in registers
+  constexpr bool KREG = !MASK && !SHARED;  // K_j operands of the wavefront's 32 keys in registers
   constexpr bool VREG = D == 64 && !MASK;  // at d = 64 V_j's as well
-  constexpr bool WIDE = dkdv_wide(MASK);
+  constexpr bool WIDE = !MASK && !SHARED;
   static_assert(NW == 8 || (NW == 4 && WIDE && LOCAL != kBlocks), "the small workgroup is the plain kernel's group 0");
-  constexpr int BC = NW == 4 ? 128 : dkdv_block_keys(MASK);  // keys per workgroup
+  constexpr int BC = NW == 4 || SHARED ? 128 : dkdv_block_keys(MASK);  // keys per workgroup
   constexpr int QTW = D == 128 ? 1 : 2;  // 32-row query tiles per wavefront per step
   constexpr int BR = 32 * QTW;          // query rows of one tile
   constexpr int KS = DH / 16, DT = DH / 32;
@@ -865,7 +867,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 12
 
   // ---- combine the two groups' partial sums and write dK_j, dV_j (line 18); dK carries the scaling
   float* red = (float*)(smem + QDO_OFF);  // 4 * DT * 16 * 64 floats, free after the loop
-  const float sc = p.scale;
+  const float rp = DROPOUT ? p.drop_rp : 1.f;
 #pragma unroll
   for (int which = 0; which < 2; ++which) {
     f32x16* accs = which == 0 ? dKt : dVt;
@@ -878,7 +880,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 12
     __syncthreads();
     if (grp == 0 && key_ok) {
       __bf16* dst = (which == 0 ? a.dK : a.dV) + ((si.tok0k + key) * p.Hkv + g) * dh + 4 * hh;
-      const float mul = which == 0 ? sc : 1.f;
+      const float mul = which == 0 ? p.scale * rp : rp;
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
@@ -1322,7 +1324,8 @@ static hipError_t launch_bwd_d(BwdArgs a, int causal, int stages, hipStream_t st
   hipError_t e = hipSuccess;
   // The whole backward on the plain paths (no dropout, mask, window or pattern): two launches. The
   // dQ kernel goes first and computes D on the way, the dK/dV kernel follows and reads it.
-  const bool plain = !a.p.mask && !a.p.drop_thr && !a.p.bmask && a.p.win_left < 0 && a.p.win_right < 0;
+  const bool optionless = !a.p.mask && !a.p.bmask && a.p.win_left < 0 && a.p.win_right < 0;
+  const bool plain = optionless && !a.p.drop_thr, drop = optionless && a.p.drop_thr;
   if (stages == 7 && plain) {
     dim3 qgrid(grid_size((a.p.N + 255) / 256, a.p.Hq * a.p.nseq));
     bool small = false;
@@ -1368,8 +1371,29 @@ static hipError_t launch_bwd_d(BwdArgs a, int causal, int stages, hipStream_t st
     // keys per workgroup differ between the instantiations
     const int bck = dkdv_block_keys(a.p.mask != nullptr);
     a.p.pairs_back = 0;
-    if (a.p.d == D && plain && small_workgroups(a.p.Nk, a.p.Hkv * a.p.nseq, D == 64 && causal, D == 64)) {
-      const dim3 sgrid(grid_size((a.p.Nk + 127) / 128, a.p.Hkv * a.p.nseq));
+    const dim3 sgrid(grid_size((a.p.Nk + 127) / 128, a.p.Hkv * a.p.nseq));
+    // Dropout at d = 64 takes the four-wavefront form by the same rule (bfloat16, 14 x 353
+    // causal, 8 heads on 4, forward + backward: 66.6 us in blocks of 256 keys, 61.5 so).
+    // At d = 128 it takes the SHARED form while a grid of large (causal) or of small workgroups is resident at
+    // once (forward + backward, from blocks of 256 keys or four wavefronts: 1 x 500 causal, 8 heads: 76.5 -> 72.0 us;
+    // 1 x 1531, 16 heads on 8: 241 -> 205; 4 x 513, 16 heads: 87 -> 80; on larger grids the wide form gains:
+    // 4 x 1000 causal, 32 heads, from 128-key blocks to 256: 264 -> 228, 1 x 3000, 16 heads, no mask: 433 -> 363).
+    if constexpr (D == 128) {
+      const long blocks = (long)((a.p.Nk + (causal ? 255 : 127)) / (causal ? 256 : 128)) * a.p.Hkv * a.p.nseq;
+      if (drop && blocks <= 256) {
+        if (causal) hipLaunchKernelGGL((bwd_dkdv_kernel<D, true, F16, true, false, false, kNoPattern, D, 8, true>), sgrid, dim3(512), 0, st, a);
+        else hipLaunchKernelGGL((bwd_dkdv_kernel<D, false, F16, true, false, false, kNoPattern, D, 8, true>), sgrid, dim3(512), 0, st, a);
+        return hipGetLastError();
+      }
+    }
+    if (a.p.d == D && (plain || (drop && D == 64)) && small_workgroups(a.p.Nk, a.p.Hkv * a.p.nseq, D == 64 && causal, D == 64)) {
+      if constexpr (D == 64) {
+        if (drop) {
+          if (causal) hipLaunchKernelGGL((bwd_dkdv_kernel<D, true, F16, true, false, false, kNoPattern, D, 4>), sgrid, dim3(256), 0, st, a);
+          else hipLaunchKernelGGL((bwd_dkdv_kernel<D, false, F16, true, false, false, kNoPattern, D, 4>), sgrid, dim3(256), 0, st, a);
+          return hipGetLastError();
+        }
+      }
       if (causal) hipLaunchKernelGGL((bwd_dkdv_kernel<D, true, F16, false, false, false, kNoPattern, D, 4>), sgrid, dim3(256), 0, st, a);
       else hipLaunchKernelGGL((bwd_dkdv_kernel<D, false, F16, false, false, false, kNoPattern, D, 4>), sgrid, dim3(256), 0, st, a);
       return hipGetLastError();

@@ -101,6 +101,29 @@ def test_lengths_around_the_256_key_blocks_of_the_backward(Nq, Nk, d, causal):
     check_dropout(inputs.make_cross(B=1, Nq=Nq, Nk=Nk, Hq=4, Hkv=2, d=d, causal=causal, seed=6300 + Nk), 0.1, seed=0x256)
 
 
+# (36 sequences x 8 heads fill more than 256 workgroups of 128 or 256 keys, one sequence does not; under the causal rule
+# d = 64 takes the small form up to 4096 keys either way)
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("N,Hq,Hkv,d", [(127, 8, 8, 64), (129, 8, 8, 64), (256, 8, 4, 64), (385, 8, 8, 64), (129, 8, 8, 128),
+                                        (300, 16, 8, 128)])
+def test_small_and_large_workgroups_of_the_backward_drop_the_same_entries(N, Hq, Hkv, d, causal):
+    """The form of the dK/dV kernel is chosen by the size of the grid; the first sequence's results (its hash does not
+    depend on the batch) are the same in a batch and alone, and alone they match the oracle. At d = 128 the small
+    form adds dK and dV in two halves: float32 sums that differ by their own rounding end in the same 16-bit value
+    or its neighbour (2^-7 of the value apart at most; values near zero are held to the sums' rounding instead)."""
+    prob = inputs.make_dense(B=36, N=N, Hq=Hq, Hkv=Hkv, d=d, causal=causal, seed=6400 + N)
+    Q, K, V, dO = (pu.to_gpu(x, prob.dtype) for x in (prob.Q, prob.K, prob.V, prob.dO))
+    O, L = binding.fa_dropout_fwd(Q, K, V, prob.scale, causal, 0.2, 77)
+    grads = binding.fa_dropout_bwd(Q, K, V, O, dO, L, prob.scale, causal, 0.2, 77)
+    alone = binding.fa_dropout_bwd(*(x[:1].contiguous() for x in (Q, K, V, O, dO, L)), prob.scale, causal, 0.2, 77)
+    for name, x, y in zip(("dQ", "dK", "dV"), grads, alone):
+        if d == 64 or name == "dQ":
+            assert torch.equal(x[0], y[0]), name
+        else:
+            torch.testing.assert_close(x[0].float(), y[0].float(), rtol=2.0 ** -7, atol=1e-4)
+    check_dropout(inputs.make_dense(B=1, N=N, Hq=Hq, Hkv=Hkv, d=d, causal=causal, seed=6500 + N), 0.2, seed=77)
+
+
 @pytest.mark.parametrize("causal", [False, True])
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 @pytest.mark.parametrize("d,Hq,Hkv", [(64, 2, 2), (128, 4, 2)])

@@ -821,7 +821,7 @@ def splitkv_default_splits(B, Hq, Hkv, Nq, Nk, ragged: bool = False) -> int:
     return max(1, min(FA_SPLITKV_MAX_SPLITS, blocks // 8, -(-256 // units)))
 
 
-def _cache_splits(B, Hq, Hkv, Nq, Nk, ragged: bool) -> int:
+def _cache_splits(B, Hq, Hkv, Nq, Nk, d, ragged: bool) -> int:
     """Shares of fa_kvcache_fwd when the caller names none: splitkv_default_splits, but fewer where more than 32
     query rows meet caches with lengths of their own (the row-block kernel; longest sequence first). Sequences of
     different lengths then want half as many workgroups again as there are compute units, and shares of at
@@ -829,14 +829,17 @@ def _cache_splits(B, Hq, Hkv, Nq, Nk, ragged: bool) -> int:
     queries, 256 workgroups per share: 191 / 158 / 166 / 187 / 212; 8 x 128, 128 workgroups:
     177 / 110 / 87 / 95 / 115; 8 x 1000, 1024 workgroups: 408 / 568 / 583 / 732 / 816, float32 partial
     results and the merge being what a share costs). One sequence has equal shares, and they should fill the
-    compute units once (1 x 512, 64 workgroups: 4 shares 80, 6 shares 101). Never more than
-    splitkv_default_splits: a workspace sized by that is large enough."""
+    compute units once (1 x 512, 64 workgroups: 4 shares 80, 6 shares 101). At d = 64 two workgroups share a
+    compute unit, and as many shares as fit there at once are best (same heads, us at 2 / 3 / 4 / 5 / 8 shares: 4 x 233
+    on up to 10752 keys, 128 workgroups per share: 124 / 118 / 99 / 100 / 105; 8 x 128: 99 / 84 / 73 / 85 / 97;
+    1 x 512: 98 / 75 / 63 / 73 / 62; 2 x 700, 16 heads, 96 workgroups: 178 / 144 / 122 / 108 / 116 and 6 shares
+    137). Never more than splitkv_default_splits: a workspace sized by that is large enough."""
     rows = Nq * (Hq // Hkv)
     if not ragged or rows <= 32:
         return splitkv_default_splits(B, Hq, Hkv, Nq, Nk, ragged)
     units = B * Hkv * ((rows + 255) // 256)
-    want = 384 if B > 1 else 256
-    return max(1, min(FA_SPLITKV_MAX_SPLITS, (Nk + 63) // 64 // 16, -(-want // units)))
+    want = 512 // units if d == 64 else -(-(384 if B > 1 else 256) // units)
+    return max(1, min(FA_SPLITKV_MAX_SPLITS, (Nk + 63) // 64 // 16, want))
 
 
 def fa_splitkv_fwd(Q, K, V, scale: float, causal: bool, num_splits: int = 0, O=None, LSE=None, workspace=None):
@@ -886,7 +889,7 @@ def fa_kvcache_fwd(Q, Kcache, Vcache, scale: float, causal: bool, seqlens_k=None
         _need(seqlens_k, "seqlens_k", torch.int32, (x.B,), x.dev)
     x.q_shape, x.l_shape = (x.B, x.Nq, x.Hq, x.d), (x.B, x.Hq, x.Nq)
     if num_splits <= 0:
-        num_splits = _cache_splits(x.B, x.Hq, x.Hkv, x.Nq, x.Nk, seqlens_k is not None)
+        num_splits = _cache_splits(x.B, x.Hq, x.Hkv, x.Nq, x.Nk, x.d, seqlens_k is not None)
     O, LSE = _fwd_outputs(x, O, LSE)
     ws = _workspace(workspace, fa_splitkv_fwd_workspace_bytes(x.B, x.Hq, x.Nq, x.d, num_splits), x.dev)
     _check(fa_kvcache_fwd_raw(_ptr(Q), _ptr(Kcache), _ptr(Vcache), _ptr(seqlens_k) if seqlens_k is not None else 0,

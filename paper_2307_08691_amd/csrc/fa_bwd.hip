@@ -1311,67 +1311,87 @@ static bool small_workgroups(int n, int pairs, bool short_too, bool two = true) 
   return large >= 512 && 2 * large * 5 >= 6 * small;
 }
 
-template <int D, bool F16>
-static hipError_t launch_bwd_d(BwdArgs a, int causal, int stages, hipStream_t st) {
-  // The dQ kernel reads Q, K, V, O that the forward pass has just streamed through the last-level cache (256 MB) and
-  // the dK/dV kernel most of them again: it goes through the pairs from the last to the first and finds the
-  // newest there first, and so does the dK/dV kernel after it (16k tokens, 32 heads of 64, MI355X, backward: N = 256
-  // 250 -> 235 us, N = 512 without the mask 337 -> 326 us, N >= 1024 -1% .. 0).
-  a.p.pairs_back = 1;
-  const long nrows = (long)a.p.total_tokens * a.p.Hq;
-  constexpr int RPB = 256 / (D / 8);
-  constexpr int DN = D == 128 ? 96 : 32;  // the narrower product width of this tile width (padded head dimensions)
-  hipError_t e = hipSuccess;
-  // The whole backward on the plain paths (no dropout, mask, window or pattern): two launches. The
-  // dQ kernel goes first and computes D on the way, the dK/dV kernel follows and reads it.
-  const bool optionless = !a.p.mask && !a.p.bmask && a.p.win_left < 0 && a.p.win_right < 0;
-  const bool plain = optionless && !a.p.drop_thr, drop = optionless && a.p.drop_thr;
-  if (stages == 7 && plain) {
-    dim3 qgrid(grid_size((a.p.N + 255) / 256, a.p.Hq * a.p.nseq));
-    bool small = false;
-    if constexpr (D == 64) {
-      small = a.p.d == D && small_workgroups(a.p.N, a.p.Hq * a.p.nseq, false);
-      const dim3 sgrid(grid_size((a.p.N + 127) / 128, a.p.Hq * a.p.nseq));
-      if (small && causal) hipLaunchKernelGGL((bwd_dq_kernel<D, true, F16, false, false, false, kNoPattern, true, D, 4>), sgrid, dim3(256), 0, st, a);
-      else if (small) hipLaunchKernelGGL((bwd_dq_kernel<D, false, F16, false, false, false, kNoPattern, true, D, 4>), sgrid, dim3(256), 0, st, a);
+static bool windowed(const Problem& p) { return p.win_left >= 0 || p.win_right >= 0; }
+// the narrower product width of a tile width (padded head dimensions)
+constexpr int dn_of(int D) { return D == 128 ? 96 : 32; }
+
+// The dQ kernel. OWN_D: it sums D on the way (the whole backward, with every option); otherwise the pre-pass has (the
+// separate stages, which have no options).
+template <int D, bool F16, bool OWN_D>
+static hipError_t launch_dq(const BwdArgs& a, int causal, hipStream_t st) {
+  constexpr int DN = dn_of(D);
+  const int pairs = a.p.Hq * a.p.nseq;
+  const dim3 grid(grid_size((a.p.N + 255) / 256, pairs)), block(512);
+  if constexpr (OWN_D) {
+    if (a.p.bmask || windowed(a.p)) {  // sliding window, block-sparse pattern
+      if (a.p.bmask) hipLaunchKernelGGL((bwd_dq_kernel<D, false, F16, false, false, false, kBlocks, true>), grid, block, 0, st, a);
+      else hipLaunchKernelGGL((bwd_dq_kernel<D, false, F16, false, false, false, kWindow, true>), grid, block, 0, st, a);
+      return hipGetLastError();
     }
-    if (small) {
-    } else if (a.p.d != D && a.p.d <= DN) {
-      if (causal) hipLaunchKernelGGL((bwd_dq_kernel<D, true, F16, false, true, false, false, true, DN>), qgrid, dim3(512), 0, st, a);
-      else hipLaunchKernelGGL((bwd_dq_kernel<D, false, F16, false, true, false, false, true, DN>), qgrid, dim3(512), 0, st, a);
-    } else if (a.p.d != D) {
-      if (causal) hipLaunchKernelGGL((bwd_dq_kernel<D, true, F16, false, true, false, false, true>), qgrid, dim3(512), 0, st, a);
-      else hipLaunchKernelGGL((bwd_dq_kernel<D, false, F16, false, true, false, false, true>), qgrid, dim3(512), 0, st, a);
-    } else {
-      if (causal) hipLaunchKernelGGL((bwd_dq_kernel<D, true, F16, false, false, false, false, true>), qgrid, dim3(512), 0, st, a);
-      else hipLaunchKernelGGL((bwd_dq_kernel<D, false, F16, false, false, false, false, true>), qgrid, dim3(512), 0, st, a);
-    }
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    stages = 2;  // what remains: the dK/dV kernel
-  } else if (stages == 7 && a.p.d == D) {  // sliding window or block-sparse pattern, mask, dropout: the same two launches
-    dim3 qgrid(grid_size((a.p.N + 255) / 256, a.p.Hq * a.p.nseq));
     if (a.p.mask) {
-      if (causal) hipLaunchKernelGGL((bwd_dq_kernel<D, true, F16, false, false, true, false, true>), qgrid, dim3(512), 0, st, a);
-      else hipLaunchKernelGGL((bwd_dq_kernel<D, false, F16, false, false, true, false, true>), qgrid, dim3(512), 0, st, a);
-    } else if (a.p.drop_thr) {
-      if (causal) hipLaunchKernelGGL((bwd_dq_kernel<D, true, F16, true, false, false, false, true>), qgrid, dim3(512), 0, st, a);
-      else hipLaunchKernelGGL((bwd_dq_kernel<D, false, F16, true, false, false, false, true>), qgrid, dim3(512), 0, st, a);
-    } else {
-      if (a.p.bmask) hipLaunchKernelGGL((bwd_dq_kernel<D, false, F16, false, false, false, kBlocks, true>), qgrid, dim3(512), 0, st, a);
-      else hipLaunchKernelGGL((bwd_dq_kernel<D, false, F16, false, false, false, kWindow, true>), qgrid, dim3(512), 0, st, a);
+      if (causal) hipLaunchKernelGGL((bwd_dq_kernel<D, true, F16, false, false, true, kNoPattern, true>), grid, block, 0, st, a);
+      else hipLaunchKernelGGL((bwd_dq_kernel<D, false, F16, false, false, true, kNoPattern, true>), grid, block, 0, st, a);
+      return hipGetLastError();
     }
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    stages = 2;
+    if (a.p.drop_thr) {  // (the entry points keep dropout away from padded head dimensions)
+      if (causal) hipLaunchKernelGGL((bwd_dq_kernel<D, true, F16, true, false, false, kNoPattern, true>), grid, block, 0, st, a);
+      else hipLaunchKernelGGL((bwd_dq_kernel<D, false, F16, true, false, false, kNoPattern, true>), grid, block, 0, st, a);
+      return hipGetLastError();
+    }
   }
-  if (stages & 1) {
-    hipLaunchKernelGGL((bwd_prep_kernel<D, F16>), dim3((unsigned)((nrows + RPB - 1) / RPB)), dim3(256), 0, st, a);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+  if (a.p.d != D && a.p.d <= DN) {
+    if (causal) hipLaunchKernelGGL((bwd_dq_kernel<D, true, F16, false, true, false, kNoPattern, OWN_D, DN>), grid, block, 0, st, a);
+    else hipLaunchKernelGGL((bwd_dq_kernel<D, false, F16, false, true, false, kNoPattern, OWN_D, DN>), grid, block, 0, st, a);
+    return hipGetLastError();
   }
-  if (stages & 2) {
-    // keys per workgroup differ between the instantiations
-    const int bck = dkdv_block_keys(a.p.mask != nullptr);
-    a.p.pairs_back = 0;
-    const dim3 sgrid(grid_size((a.p.Nk + 127) / 128, a.p.Hkv * a.p.nseq));
+  if (a.p.d != D) {
+    if (causal) hipLaunchKernelGGL((bwd_dq_kernel<D, true, F16, false, true, false, kNoPattern, OWN_D>), grid, block, 0, st, a);
+    else hipLaunchKernelGGL((bwd_dq_kernel<D, false, F16, false, true, false, kNoPattern, OWN_D>), grid, block, 0, st, a);
+    return hipGetLastError();
+  }
+  if constexpr (D == 64) {
+    if (small_workgroups(a.p.N, pairs, false)) {
+      const dim3 sgrid(grid_size((a.p.N + 127) / 128, pairs));
+      if (causal) hipLaunchKernelGGL((bwd_dq_kernel<D, true, F16, false, false, false, kNoPattern, OWN_D, D, 4>), sgrid, dim3(256), 0, st, a);
+      else hipLaunchKernelGGL((bwd_dq_kernel<D, false, F16, false, false, false, kNoPattern, OWN_D, D, 4>), sgrid, dim3(256), 0, st, a);
+      return hipGetLastError();
+    }
+  }
+  if (causal) hipLaunchKernelGGL((bwd_dq_kernel<D, true, F16, false, false, false, kNoPattern, OWN_D>), grid, block, 0, st, a);
+  else hipLaunchKernelGGL((bwd_dq_kernel<D, false, F16, false, false, false, kNoPattern, OWN_D>), grid, block, 0, st, a);
+  return hipGetLastError();
+}
+
+// The dK/dV kernel.
+template <int D, bool F16>
+static hipError_t launch_dkdv(const BwdArgs& a, int causal, hipStream_t st) {
+  constexpr int DN = dn_of(D);
+  const int pairs = a.p.Hkv * a.p.nseq;
+  const int bck = dkdv_block_keys(a.p.mask != nullptr);  // keys per workgroup differ between the instantiations
+  const dim3 grid(grid_size((a.p.Nk + bck - 1) / bck, pairs)), block(512);
+  const dim3 sgrid(grid_size((a.p.Nk + 127) / 128, pairs));
+  if (a.p.bmask || windowed(a.p)) {  // sliding window, block-sparse pattern
+    if (a.p.bmask) hipLaunchKernelGGL((bwd_dkdv_kernel<D, false, F16, false, false, false, kBlocks>), grid, block, 0, st, a);
+    else hipLaunchKernelGGL((bwd_dkdv_kernel<D, false, F16, false, false, false, kWindow>), grid, block, 0, st, a);
+    return hipGetLastError();
+  }
+  if (a.p.mask) {
+    if (causal) hipLaunchKernelGGL((bwd_dkdv_kernel<D, true, F16, false, false, true>), grid, block, 0, st, a);
+    else hipLaunchKernelGGL((bwd_dkdv_kernel<D, false, F16, false, false, true>), grid, block, 0, st, a);
+    return hipGetLastError();
+  }
+  if (a.p.d != D && a.p.d <= DN) {
+    if (causal) hipLaunchKernelGGL((bwd_dkdv_kernel<D, true, F16, false, true, false, kNoPattern, DN>), grid, block, 0, st, a);
+    else hipLaunchKernelGGL((bwd_dkdv_kernel<D, false, F16, false, true, false, kNoPattern, DN>), grid, block, 0, st, a);
+    return hipGetLastError();
+  }
+  if (a.p.d != D) {
+    if (causal) hipLaunchKernelGGL((bwd_dkdv_kernel<D, true, F16, false, true>), grid, block, 0, st, a);
+    else hipLaunchKernelGGL((bwd_dkdv_kernel<D, false, F16, false, true>), grid, block, 0, st, a);
+    return hipGetLastError();
+  }
+  const bool small = small_workgroups(a.p.Nk, pairs, D == 64 && causal, D == 64);
+  if (a.p.drop_thr) {
     // Dropout at d = 64 takes the four-wavefront form by the same rule (bfloat16, 14 x 353
     // causal, 8 heads on 4, forward + backward: 66.6 us in blocks of 256 keys, 61.5 so).
     // At d = 128 it takes the SHARED form while a grid of large (causal) or of small workgroups is resident at
@@ -1379,101 +1399,54 @@ static hipError_t launch_bwd_d(BwdArgs a, int causal, int stages, hipStream_t st
     // 1 x 1531, 16 heads on 8: 241 -> 205; 4 x 513, 16 heads: 87 -> 80; on larger grids the wide form gains:
     // 4 x 1000 causal, 32 heads, from 128-key blocks to 256: 264 -> 228, 1 x 3000, 16 heads, no mask: 433 -> 363).
     if constexpr (D == 128) {
-      const long blocks = (long)((a.p.Nk + (causal ? 255 : 127)) / (causal ? 256 : 128)) * a.p.Hkv * a.p.nseq;
-      if (drop && blocks <= 256) {
-        if (causal) hipLaunchKernelGGL((bwd_dkdv_kernel<D, true, F16, true, false, false, kNoPattern, D, 8, true>), sgrid, dim3(512), 0, st, a);
-        else hipLaunchKernelGGL((bwd_dkdv_kernel<D, false, F16, true, false, false, kNoPattern, D, 8, true>), sgrid, dim3(512), 0, st, a);
+      const long blocks = (long)((a.p.Nk + (causal ? 255 : 127)) / (causal ? 256 : 128)) * pairs;
+      if (blocks <= 256) {
+        if (causal) hipLaunchKernelGGL((bwd_dkdv_kernel<D, true, F16, true, false, false, kNoPattern, D, 8, true>), sgrid, block, 0, st, a);
+        else hipLaunchKernelGGL((bwd_dkdv_kernel<D, false, F16, true, false, false, kNoPattern, D, 8, true>), sgrid, block, 0, st, a);
         return hipGetLastError();
       }
-    }
-    if (a.p.d == D && (plain || (drop && D == 64)) && small_workgroups(a.p.Nk, a.p.Hkv * a.p.nseq, D == 64 && causal, D == 64)) {
-      if constexpr (D == 64) {
-        if (drop) {
-          if (causal) hipLaunchKernelGGL((bwd_dkdv_kernel<D, true, F16, true, false, false, kNoPattern, D, 4>), sgrid, dim3(256), 0, st, a);
-          else hipLaunchKernelGGL((bwd_dkdv_kernel<D, false, F16, true, false, false, kNoPattern, D, 4>), sgrid, dim3(256), 0, st, a);
-          return hipGetLastError();
-        }
-      }
-      if (causal) hipLaunchKernelGGL((bwd_dkdv_kernel<D, true, F16, false, false, false, kNoPattern, D, 4>), sgrid, dim3(256), 0, st, a);
-      else hipLaunchKernelGGL((bwd_dkdv_kernel<D, false, F16, false, false, false, kNoPattern, D, 4>), sgrid, dim3(256), 0, st, a);
+    } else if (small) {
+      if (causal) hipLaunchKernelGGL((bwd_dkdv_kernel<D, true, F16, true, false, false, kNoPattern, D, 4>), sgrid, dim3(256), 0, st, a);
+      else hipLaunchKernelGGL((bwd_dkdv_kernel<D, false, F16, true, false, false, kNoPattern, D, 4>), sgrid, dim3(256), 0, st, a);
       return hipGetLastError();
     }
-    dim3 grid(grid_size((a.p.Nk + bck - 1) / bck, a.p.Hkv * a.p.nseq));
-    bool done = false;
-    {
-      if (a.p.win_left >= 0 || a.p.win_right >= 0 || a.p.bmask) {  // sliding window, block-sparse pattern
-        if (a.p.bmask) hipLaunchKernelGGL((bwd_dkdv_kernel<D, false, F16, false, false, false, kBlocks>), grid, dim3(512), 0, st, a);
-        else hipLaunchKernelGGL((bwd_dkdv_kernel<D, false, F16, false, false, false, kWindow>), grid, dim3(512), 0, st, a);
-        done = true;
-      } else
-      if (a.p.mask) {
-        if (causal) hipLaunchKernelGGL((bwd_dkdv_kernel<D, true, F16, false, false, true>), grid, dim3(512), 0, st, a);
-        else hipLaunchKernelGGL((bwd_dkdv_kernel<D, false, F16, false, false, true>), grid, dim3(512), 0, st, a);
-        done = true;
-      }
-    }
-    if (done) {
-    } else if (a.p.d != D) {  // padded head dimension (the entry points keep dropout away from it)
-      if (a.p.d <= DN) {
-        if (causal) hipLaunchKernelGGL((bwd_dkdv_kernel<D, true, F16, false, true, false, false, DN>), grid, dim3(512), 0, st, a);
-        else hipLaunchKernelGGL((bwd_dkdv_kernel<D, false, F16, false, true, false, false, DN>), grid, dim3(512), 0, st, a);
-      } else {
-        if (causal) hipLaunchKernelGGL((bwd_dkdv_kernel<D, true, F16, false, true>), grid, dim3(512), 0, st, a);
-        else hipLaunchKernelGGL((bwd_dkdv_kernel<D, false, F16, false, true>), grid, dim3(512), 0, st, a);
-      }
-      done = true;
-    }
-    {
-      if (!done && a.p.drop_thr) {
-        if (causal) hipLaunchKernelGGL((bwd_dkdv_kernel<D, true, F16, true>), grid, dim3(512), 0, st, a);
-        else hipLaunchKernelGGL((bwd_dkdv_kernel<D, false, F16, true>), grid, dim3(512), 0, st, a);
-        done = true;
-      }
-    }
-    if (done) {
-    } else if (causal) hipLaunchKernelGGL((bwd_dkdv_kernel<D, true, F16>), grid, dim3(512), 0, st, a);
-    else hipLaunchKernelGGL((bwd_dkdv_kernel<D, false, F16>), grid, dim3(512), 0, st, a);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+    if (causal) hipLaunchKernelGGL((bwd_dkdv_kernel<D, true, F16, true>), grid, block, 0, st, a);
+    else hipLaunchKernelGGL((bwd_dkdv_kernel<D, false, F16, true>), grid, block, 0, st, a);
+    return hipGetLastError();
   }
-  if (stages & 4) {
-    dim3 grid(grid_size((a.p.N + 255) / 256, a.p.Hq * a.p.nseq));
-    bool done = false;
-    {
-      if (a.p.win_left >= 0 || a.p.win_right >= 0 || a.p.bmask) {  // sliding window, block-sparse pattern
-        if (a.p.bmask) hipLaunchKernelGGL((bwd_dq_kernel<D, false, F16, false, false, false, kBlocks>), grid, dim3(512), 0, st, a);
-        else hipLaunchKernelGGL((bwd_dq_kernel<D, false, F16, false, false, false, kWindow>), grid, dim3(512), 0, st, a);
-        done = true;
-      } else
-      if (a.p.mask) {
-        if (causal) hipLaunchKernelGGL((bwd_dq_kernel<D, true, F16, false, false, true>), grid, dim3(512), 0, st, a);
-        else hipLaunchKernelGGL((bwd_dq_kernel<D, false, F16, false, false, true>), grid, dim3(512), 0, st, a);
-        done = true;
-      }
-    }
-    if (done) {
-    } else if (a.p.d != D) {
-      if (a.p.d <= DN) {
-        if (causal) hipLaunchKernelGGL((bwd_dq_kernel<D, true, F16, false, true, false, false, false, DN>), grid, dim3(512), 0, st, a);
-        else hipLaunchKernelGGL((bwd_dq_kernel<D, false, F16, false, true, false, false, false, DN>), grid, dim3(512), 0, st, a);
-      } else {
-        if (causal) hipLaunchKernelGGL((bwd_dq_kernel<D, true, F16, false, true>), grid, dim3(512), 0, st, a);
-        else hipLaunchKernelGGL((bwd_dq_kernel<D, false, F16, false, true>), grid, dim3(512), 0, st, a);
-      }
-      done = true;
-    }
-    {
-      if (!done && a.p.drop_thr) {
-        if (causal) hipLaunchKernelGGL((bwd_dq_kernel<D, true, F16, true>), grid, dim3(512), 0, st, a);
-        else hipLaunchKernelGGL((bwd_dq_kernel<D, false, F16, true>), grid, dim3(512), 0, st, a);
-        done = true;
-      }
-    }
-    if (done) {
-    } else if (causal) hipLaunchKernelGGL((bwd_dq_kernel<D, true, F16>), grid, dim3(512), 0, st, a);
-    else hipLaunchKernelGGL((bwd_dq_kernel<D, false, F16>), grid, dim3(512), 0, st, a);
-    e = hipGetLastError();
+  if (small) {
+    if (causal) hipLaunchKernelGGL((bwd_dkdv_kernel<D, true, F16, false, false, false, kNoPattern, D, 4>), sgrid, dim3(256), 0, st, a);
+    else hipLaunchKernelGGL((bwd_dkdv_kernel<D, false, F16, false, false, false, kNoPattern, D, 4>), sgrid, dim3(256), 0, st, a);
+    return hipGetLastError();
   }
-  return e;
+  if (causal) hipLaunchKernelGGL((bwd_dkdv_kernel<D, true, F16>), grid, block, 0, st, a);
+  else hipLaunchKernelGGL((bwd_dkdv_kernel<D, false, F16>), grid, block, 0, st, a);
+  return hipGetLastError();
+}
+
+template <int D, bool F16>
+static hipError_t launch_bwd_d(BwdArgs a, int causal, int stages, hipStream_t st) {
+  // The dQ kernel reads Q, K, V, O that the forward pass has just streamed through the last-level cache (256 MB):
+  // it goes through the pairs from the last to the first and finds the newest there first (16k tokens, 32 heads of 64,
+  // MI355X, backward: N = 256 250 -> 235 us, N = 512 without the mask 337 -> 326 us, N >= 1024 -1% .. 0).
+  a.p.pairs_back = 1;
+  // The whole backward is two launches: the dQ kernel goes first and computes D on the way, the dK/dV kernel
+  // follows and reads it.
+  if (stages == 7) {
+    if (hipError_t e = launch_dq<D, F16, true>(a, causal, st)) return e;
+    return launch_dkdv<D, F16>(a, causal, st);
+  }
+  if (stages & 1) {
+    const long nrows = (long)a.p.total_tokens * a.p.Hq;
+    constexpr int RPB = 256 / (D / 8);
+    hipLaunchKernelGGL((bwd_prep_kernel<D, F16>), dim3((unsigned)((nrows + RPB - 1) / RPB)), dim3(256), 0, st, a);
+    if (hipError_t e = hipGetLastError()) return e;
+  }
+  if (stages & 2)
+    if (hipError_t e = launch_dkdv<D, F16>(a, causal, st)) return e;
+  if (stages & 4)
+    if (hipError_t e = launch_dq<D, F16, false>(a, causal, st)) return e;
+  return hipSuccess;
 }
 
 hipError_t launch_bwd(const BwdArgs& a, int d, int causal, int stages, hipStream_t st) {

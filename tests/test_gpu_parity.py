@@ -137,6 +137,31 @@ def test_small_and_large_workgroups_agree_bitwise(N, Hq, Hkv, d, causal):
             assert torch.equal(x[s], y[0]), name
 
 
+# (the grids on which each form of the two kernels is chosen: every small one, the small dK/dV form beside the large dQ
+# form, both large ones; a padded head dimension and d = 256)
+@pytest.mark.parametrize("order", [(1, 6), (1, 2, 4), (1, 4, 2), (3, 4), (5, 2)])
+@pytest.mark.parametrize("B,N,Hq,Hkv,d,causal", [(1, 257, 4, 2, 64, True), (1, 257, 4, 2, 64, False), (1, 300, 4, 2, 128, True),
+                                                 (1, 300, 4, 4, 128, False), (36, 256, 8, 8, 64, True),
+                                                 (36, 256, 8, 8, 64, False), (40, 256, 8, 8, 128, True),
+                                                 (1, 200, 2, 1, 96, True), (1, 200, 2, 1, 256, True)])
+def test_any_split_of_the_backward_into_stages(B, N, Hq, Hkv, d, causal, order):
+    """fa_bwd_stages runs whatever subset of the three stages it is asked for: the pre-pass first and the two
+    kernels together, apart or in either order write all of dQ, dK and dV. (fa_bwd sums D inside the dQ kernel,
+    in another order than the pre-pass: float32 rounding apart, so the 16-bit results differ by at most a
+    rounding, a unit in the last place at the tensor's largest magnitude.)"""
+    prob = inputs.make_dense(B=B, N=N, Hq=Hq, Hkv=Hkv, d=d, causal=causal, seed=9400 + N + d)
+    Q, K, V, dO = (pu.to_gpu(x, prob.dtype) for x in (prob.Q, prob.K, prob.V, prob.dO))
+    O, L = binding.fa_fwd(Q, K, V, prob.scale, causal)
+    want = binding.fa_bwd(Q, K, V, O, dO, L, prob.scale, causal)
+    got = [torch.full_like(x, float("nan")) for x in (Q, K, V)]
+    ws = torch.empty(binding.fa_bwd_workspace_bytes(B, Hq, Hkv, N, d), dtype=torch.uint8, device="cuda")
+    for stages in order:
+        binding.fa_bwd_stages(Q, K, V, O, dO, L, prob.scale, causal, stages, *got, ws)
+    for name, x, y in zip(("dQ", "dK", "dV"), got, want):
+        assert torch.isfinite(x).all(), f"{name} not written"
+        assert pu.maxdiff(pu.to_f64(x), pu.to_f64(y)) <= pu.ulp(pu.maxabs(pu.to_f64(y))), name
+
+
 @pytest.mark.parametrize("d", [64, 128])
 def test_every_output_is_bit_reproducible(d):
     """No output is accumulated by atomic adds (dQ comes from a row-block pass of its own instead

@@ -72,7 +72,6 @@ fa::Problem make_problem(const int32_t* cu, int nseq, int N, int Nk, int Hq, int
   p.bmask = nullptr;
   p.bmask_bs = p.bmask_hs = 0;
   p.bmask_cols = p.bmask_log2 = 0;
-  p.pairs_back = 0;
   p.cu_seqlens = cu;
   p.cu_seqlens_k = cu_k;
   p.nseq = nseq;

@@ -120,13 +120,16 @@ constexpr int dkdv_block_keys(bool mask) { return mask ? 128 : 256; }
 //
 // DH (PAD only): the head dimension rounded up to a multiple of 32; the products run over the
 // first DH columns of the D-wide tiles only (see the forward kernel).
+//
+// RAGGED: a packed batch (p.cu_seqlens); see row_block_coord.
 template <int D, bool CAUSAL, bool F16, bool DROPOUT = false, bool PAD = false, bool MASK = false,
-          int LOCAL = kNoPattern, int DH = D, int NW = 8, bool SHARED = false>
+          int LOCAL = kNoPattern, int DH = D, int NW = 8, bool SHARED = false, bool RAGGED = false>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 128 ? NW / 4 : 2, D == 128 ? NW / 4 : 2))) void
     bwd_dkdv_kernel(BwdArgs a) {
   static_assert(DH == D || (PAD && DH % 32 == 0 && DH < D), "a narrower product width is for padded head dimensions");
   static_assert(!MASK || (!DROPOUT && !PAD), "the mask variant is built for the plain kernel");
   static_assert(!LOCAL || (!CAUSAL && !DROPOUT && !PAD && !MASK), "the window variant is built for the plain kernel");
+  static_assert(!RAGGED || (!MASK && LOCAL != kBlocks), "no entry point packs these batches");
   constexpr bool KREG = !MASK && !SHARED;  // K_j operands of the wavefront's 32 keys in registers
   constexpr bool VREG = D == 64 && !MASK;  // at d = 64 V_j's as well
   constexpr bool WIDE = !MASK && !SHARED;
@@ -159,13 +162,12 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 12
   const int kgi = WIDE ? v : kg;  // which 32 keys of the block this wavefront owns
   const int gtid = tid & 255;  // thread index inside the group
   const int lq = lane & 31, hh = lane >> 5;
-  const BlockCoord bc = key_block_coord<CAUSAL>(p, BC);
+  const BlockCoord bc = key_block_coord<CAUSAL, RAGGED>(p, BC);
   if (!bc.valid) return;
   const int g = bc.head, s = bc.seq;
   const SeqInfo si = seq_info(p, s);
   const int n = si.n, nk = si.nk;  // query rows, key rows
   const int off = nk - n;          // position of query 0 among the keys (causal alignment)
-  if (bc.blk < 0) return;
   const int j0 = bc.blk * BC;
   if (j0 >= nk) return;
   const int dh = PAD ? p.d : D;  // row length in memory
@@ -910,13 +912,15 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 12
 // OWN_D: the kernel computes D_i = rowsum(dO_i o O_i) (line 4) of its own rows itself, from the
 // dO_i operands it holds anyway and one pass over its O_i rows, and writes it for the dK/dV kernel,
 // which then runs after this one: the whole backward without the separate D pre-pass.
-// DH (PAD only): the narrower product width of a padded head dimension (see the forward kernel).
+// DH (PAD only): the narrower product width of a padded head dimension (see the forward kernel). RAGGED: a packed
+// batch. The pairs are taken from the last to the first: see launch_bwd_d.
 template <int D, bool CAUSAL, bool F16, bool DROPOUT = false, bool PAD = false, bool MASK = false, int LOCAL = kNoPattern,
-          bool OWN_D = false, int DH = D, int NW = 8>
+          bool OWN_D = false, int DH = D, int NW = 8, bool RAGGED = false>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2))) void bwd_dq_kernel(BwdArgs a) {
   static_assert(DH == D || (PAD && DH % 32 == 0 && DH < D), "a narrower product width is for padded head dimensions");
   static_assert(!MASK || (!DROPOUT && !PAD), "the mask variant is built for the plain kernel");
   static_assert(!LOCAL || (!CAUSAL && !DROPOUT && !PAD && !MASK), "the window variant is built for the plain kernel");
+  static_assert(!RAGGED || (!MASK && LOCAL != kBlocks), "no entry point packs these batches");
   static_assert(NW == 8 || (NW == 4 && !MASK && LOCAL != kBlocks), "the small workgroup is the plain kernel's group 0");
   constexpr int BR = 32 * NW, BC = 64, RING = 4;
   constexpr int KS = DH / 16, DT = DH / 32;
@@ -935,7 +939,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int grp = w >> 2;  // 0: matrix phase on even phases, 1: on odd phases
   const int lq = lane & 31, hh = lane >> 5;
-  const BlockCoord bc = row_block_coord<CAUSAL>(p, BR);
+  const BlockCoord bc = row_block_coord<CAUSAL, RAGGED, true>(p, BR);
   if (!bc.valid) return;
   const int rowblk = bc.blk;
   const int h = bc.head, s = bc.seq;
@@ -1316,16 +1320,16 @@ static bool windowed(const Problem& p) { return p.win_left >= 0 || p.win_right >
 constexpr int dn_of(int D) { return D == 128 ? 96 : 32; }
 
 // The dQ kernel. OWN_D: it sums D on the way (the whole backward, with every option); otherwise the pre-pass has (the
-// separate stages, which have no options).
-template <int D, bool F16, bool OWN_D>
+// separate stages, which have no options). RAGGED: a.p.cu_seqlens is set (the stages and the two patterns of the mask
+// are for dense batches).
+template <int D, bool F16, bool OWN_D, bool RAGGED>
 static hipError_t launch_dq(const BwdArgs& a, int causal, hipStream_t st) {
   constexpr int DN = dn_of(D);
   const int pairs = a.p.Hq * a.p.nseq;
   const dim3 grid(grid_size((a.p.N + 255) / 256, pairs)), block(512);
-  if constexpr (OWN_D) {
-    if (a.p.bmask || windowed(a.p)) {  // sliding window, block-sparse pattern
-      if (a.p.bmask) hipLaunchKernelGGL((bwd_dq_kernel<D, false, F16, false, false, false, kBlocks, true>), grid, block, 0, st, a);
-      else hipLaunchKernelGGL((bwd_dq_kernel<D, false, F16, false, false, false, kWindow, true>), grid, block, 0, st, a);
+  if constexpr (OWN_D && !RAGGED) {
+    if (a.p.bmask) {  // block-sparse pattern (perhaps with a window)
+      hipLaunchKernelGGL((bwd_dq_kernel<D, false, F16, false, false, false, kBlocks, true>), grid, block, 0, st, a);
       return hipGetLastError();
     }
     if (a.p.mask) {
@@ -1333,61 +1337,72 @@ static hipError_t launch_dq(const BwdArgs& a, int causal, hipStream_t st) {
       else hipLaunchKernelGGL((bwd_dq_kernel<D, false, F16, false, false, true, kNoPattern, true>), grid, block, 0, st, a);
       return hipGetLastError();
     }
+  }
+  if constexpr (OWN_D) {
+    if (windowed(a.p)) {
+      hipLaunchKernelGGL((bwd_dq_kernel<D, false, F16, false, false, false, kWindow, true, D, 8, RAGGED>), grid, block, 0, st, a);
+      return hipGetLastError();
+    }
     if (a.p.drop_thr) {  // (the entry points keep dropout away from padded head dimensions)
-      if (causal) hipLaunchKernelGGL((bwd_dq_kernel<D, true, F16, true, false, false, kNoPattern, true>), grid, block, 0, st, a);
-      else hipLaunchKernelGGL((bwd_dq_kernel<D, false, F16, true, false, false, kNoPattern, true>), grid, block, 0, st, a);
+      if (causal) hipLaunchKernelGGL((bwd_dq_kernel<D, true, F16, true, false, false, kNoPattern, true, D, 8, RAGGED>), grid, block, 0, st, a);
+      else hipLaunchKernelGGL((bwd_dq_kernel<D, false, F16, true, false, false, kNoPattern, true, D, 8, RAGGED>), grid, block, 0, st, a);
       return hipGetLastError();
     }
   }
   if (a.p.d != D && a.p.d <= DN) {
-    if (causal) hipLaunchKernelGGL((bwd_dq_kernel<D, true, F16, false, true, false, kNoPattern, OWN_D, DN>), grid, block, 0, st, a);
-    else hipLaunchKernelGGL((bwd_dq_kernel<D, false, F16, false, true, false, kNoPattern, OWN_D, DN>), grid, block, 0, st, a);
+    if (causal) hipLaunchKernelGGL((bwd_dq_kernel<D, true, F16, false, true, false, kNoPattern, OWN_D, DN, 8, RAGGED>), grid, block, 0, st, a);
+    else hipLaunchKernelGGL((bwd_dq_kernel<D, false, F16, false, true, false, kNoPattern, OWN_D, DN, 8, RAGGED>), grid, block, 0, st, a);
     return hipGetLastError();
   }
   if (a.p.d != D) {
-    if (causal) hipLaunchKernelGGL((bwd_dq_kernel<D, true, F16, false, true, false, kNoPattern, OWN_D>), grid, block, 0, st, a);
-    else hipLaunchKernelGGL((bwd_dq_kernel<D, false, F16, false, true, false, kNoPattern, OWN_D>), grid, block, 0, st, a);
+    if (causal) hipLaunchKernelGGL((bwd_dq_kernel<D, true, F16, false, true, false, kNoPattern, OWN_D, D, 8, RAGGED>), grid, block, 0, st, a);
+    else hipLaunchKernelGGL((bwd_dq_kernel<D, false, F16, false, true, false, kNoPattern, OWN_D, D, 8, RAGGED>), grid, block, 0, st, a);
     return hipGetLastError();
   }
   if constexpr (D == 64) {
     if (small_workgroups(a.p.N, pairs, false)) {
       const dim3 sgrid(grid_size((a.p.N + 127) / 128, pairs));
-      if (causal) hipLaunchKernelGGL((bwd_dq_kernel<D, true, F16, false, false, false, kNoPattern, OWN_D, D, 4>), sgrid, dim3(256), 0, st, a);
-      else hipLaunchKernelGGL((bwd_dq_kernel<D, false, F16, false, false, false, kNoPattern, OWN_D, D, 4>), sgrid, dim3(256), 0, st, a);
+      if (causal) hipLaunchKernelGGL((bwd_dq_kernel<D, true, F16, false, false, false, kNoPattern, OWN_D, D, 4, RAGGED>), sgrid, dim3(256), 0, st, a);
+      else hipLaunchKernelGGL((bwd_dq_kernel<D, false, F16, false, false, false, kNoPattern, OWN_D, D, 4, RAGGED>), sgrid, dim3(256), 0, st, a);
       return hipGetLastError();
     }
   }
-  if (causal) hipLaunchKernelGGL((bwd_dq_kernel<D, true, F16, false, false, false, kNoPattern, OWN_D>), grid, block, 0, st, a);
-  else hipLaunchKernelGGL((bwd_dq_kernel<D, false, F16, false, false, false, kNoPattern, OWN_D>), grid, block, 0, st, a);
+  if (causal) hipLaunchKernelGGL((bwd_dq_kernel<D, true, F16, false, false, false, kNoPattern, OWN_D, D, 8, RAGGED>), grid, block, 0, st, a);
+  else hipLaunchKernelGGL((bwd_dq_kernel<D, false, F16, false, false, false, kNoPattern, OWN_D, D, 8, RAGGED>), grid, block, 0, st, a);
   return hipGetLastError();
 }
 
 // The dK/dV kernel.
-template <int D, bool F16>
+template <int D, bool F16, bool RAGGED>
 static hipError_t launch_dkdv(const BwdArgs& a, int causal, hipStream_t st) {
   constexpr int DN = dn_of(D);
   const int pairs = a.p.Hkv * a.p.nseq;
   const int bck = dkdv_block_keys(a.p.mask != nullptr);  // keys per workgroup differ between the instantiations
   const dim3 grid(grid_size((a.p.Nk + bck - 1) / bck, pairs)), block(512);
   const dim3 sgrid(grid_size((a.p.Nk + 127) / 128, pairs));
-  if (a.p.bmask || windowed(a.p)) {  // sliding window, block-sparse pattern
-    if (a.p.bmask) hipLaunchKernelGGL((bwd_dkdv_kernel<D, false, F16, false, false, false, kBlocks>), grid, block, 0, st, a);
-    else hipLaunchKernelGGL((bwd_dkdv_kernel<D, false, F16, false, false, false, kWindow>), grid, block, 0, st, a);
-    return hipGetLastError();
+  if constexpr (!RAGGED) {
+    if (a.p.bmask) {  // block-sparse pattern (perhaps with a window)
+      hipLaunchKernelGGL((bwd_dkdv_kernel<D, false, F16, false, false, false, kBlocks>), grid, block, 0, st, a);
+      return hipGetLastError();
+    }
+    if (a.p.mask) {
+      if (causal) hipLaunchKernelGGL((bwd_dkdv_kernel<D, true, F16, false, false, true>), grid, block, 0, st, a);
+      else hipLaunchKernelGGL((bwd_dkdv_kernel<D, false, F16, false, false, true>), grid, block, 0, st, a);
+      return hipGetLastError();
+    }
   }
-  if (a.p.mask) {
-    if (causal) hipLaunchKernelGGL((bwd_dkdv_kernel<D, true, F16, false, false, true>), grid, block, 0, st, a);
-    else hipLaunchKernelGGL((bwd_dkdv_kernel<D, false, F16, false, false, true>), grid, block, 0, st, a);
+  if (windowed(a.p)) {
+    hipLaunchKernelGGL((bwd_dkdv_kernel<D, false, F16, false, false, false, kWindow, D, 8, false, RAGGED>), grid, block, 0, st, a);
     return hipGetLastError();
   }
   if (a.p.d != D && a.p.d <= DN) {
-    if (causal) hipLaunchKernelGGL((bwd_dkdv_kernel<D, true, F16, false, true, false, kNoPattern, DN>), grid, block, 0, st, a);
-    else hipLaunchKernelGGL((bwd_dkdv_kernel<D, false, F16, false, true, false, kNoPattern, DN>), grid, block, 0, st, a);
+    if (causal) hipLaunchKernelGGL((bwd_dkdv_kernel<D, true, F16, false, true, false, kNoPattern, DN, 8, false, RAGGED>), grid, block, 0, st, a);
+    else hipLaunchKernelGGL((bwd_dkdv_kernel<D, false, F16, false, true, false, kNoPattern, DN, 8, false, RAGGED>), grid, block, 0, st, a);
     return hipGetLastError();
   }
   if (a.p.d != D) {
-    if (causal) hipLaunchKernelGGL((bwd_dkdv_kernel<D, true, F16, false, true>), grid, block, 0, st, a);
-    else hipLaunchKernelGGL((bwd_dkdv_kernel<D, false, F16, false, true>), grid, block, 0, st, a);
+    if (causal) hipLaunchKernelGGL((bwd_dkdv_kernel<D, true, F16, false, true, false, kNoPattern, D, 8, false, RAGGED>), grid, block, 0, st, a);
+    else hipLaunchKernelGGL((bwd_dkdv_kernel<D, false, F16, false, true, false, kNoPattern, D, 8, false, RAGGED>), grid, block, 0, st, a);
     return hipGetLastError();
   }
   const bool small = small_workgroups(a.p.Nk, pairs, D == 64 && causal, D == 64);
@@ -1401,41 +1416,45 @@ static hipError_t launch_dkdv(const BwdArgs& a, int causal, hipStream_t st) {
     if constexpr (D == 128) {
       const long blocks = (long)((a.p.Nk + (causal ? 255 : 127)) / (causal ? 256 : 128)) * pairs;
       if (blocks <= 256) {
-        if (causal) hipLaunchKernelGGL((bwd_dkdv_kernel<D, true, F16, true, false, false, kNoPattern, D, 8, true>), sgrid, block, 0, st, a);
-        else hipLaunchKernelGGL((bwd_dkdv_kernel<D, false, F16, true, false, false, kNoPattern, D, 8, true>), sgrid, block, 0, st, a);
+        if (causal) hipLaunchKernelGGL((bwd_dkdv_kernel<D, true, F16, true, false, false, kNoPattern, D, 8, true, RAGGED>), sgrid, block, 0, st, a);
+        else hipLaunchKernelGGL((bwd_dkdv_kernel<D, false, F16, true, false, false, kNoPattern, D, 8, true, RAGGED>), sgrid, block, 0, st, a);
         return hipGetLastError();
       }
     } else if (small) {
-      if (causal) hipLaunchKernelGGL((bwd_dkdv_kernel<D, true, F16, true, false, false, kNoPattern, D, 4>), sgrid, dim3(256), 0, st, a);
-      else hipLaunchKernelGGL((bwd_dkdv_kernel<D, false, F16, true, false, false, kNoPattern, D, 4>), sgrid, dim3(256), 0, st, a);
+      if (causal) hipLaunchKernelGGL((bwd_dkdv_kernel<D, true, F16, true, false, false, kNoPattern, D, 4, false, RAGGED>), sgrid, dim3(256), 0, st, a);
+      else hipLaunchKernelGGL((bwd_dkdv_kernel<D, false, F16, true, false, false, kNoPattern, D, 4, false, RAGGED>), sgrid, dim3(256), 0, st, a);
       return hipGetLastError();
     }
-    if (causal) hipLaunchKernelGGL((bwd_dkdv_kernel<D, true, F16, true>), grid, block, 0, st, a);
-    else hipLaunchKernelGGL((bwd_dkdv_kernel<D, false, F16, true>), grid, block, 0, st, a);
+    if (causal) hipLaunchKernelGGL((bwd_dkdv_kernel<D, true, F16, true, false, false, kNoPattern, D, 8, false, RAGGED>), grid, block, 0, st, a);
+    else hipLaunchKernelGGL((bwd_dkdv_kernel<D, false, F16, true, false, false, kNoPattern, D, 8, false, RAGGED>), grid, block, 0, st, a);
     return hipGetLastError();
   }
   if (small) {
-    if (causal) hipLaunchKernelGGL((bwd_dkdv_kernel<D, true, F16, false, false, false, kNoPattern, D, 4>), sgrid, dim3(256), 0, st, a);
-    else hipLaunchKernelGGL((bwd_dkdv_kernel<D, false, F16, false, false, false, kNoPattern, D, 4>), sgrid, dim3(256), 0, st, a);
+    if (causal) hipLaunchKernelGGL((bwd_dkdv_kernel<D, true, F16, false, false, false, kNoPattern, D, 4, false, RAGGED>), sgrid, dim3(256), 0, st, a);
+    else hipLaunchKernelGGL((bwd_dkdv_kernel<D, false, F16, false, false, false, kNoPattern, D, 4, false, RAGGED>), sgrid, dim3(256), 0, st, a);
     return hipGetLastError();
   }
-  if (causal) hipLaunchKernelGGL((bwd_dkdv_kernel<D, true, F16>), grid, block, 0, st, a);
-  else hipLaunchKernelGGL((bwd_dkdv_kernel<D, false, F16>), grid, block, 0, st, a);
+  if (causal) hipLaunchKernelGGL((bwd_dkdv_kernel<D, true, F16, false, false, false, kNoPattern, D, 8, false, RAGGED>), grid, block, 0, st, a);
+  else hipLaunchKernelGGL((bwd_dkdv_kernel<D, false, F16, false, false, false, kNoPattern, D, 8, false, RAGGED>), grid, block, 0, st, a);
   return hipGetLastError();
 }
 
+// The dQ kernel reads Q, K, V, O that the forward pass has just streamed through the last-level cache (256 MB):
+// it goes through the pairs from the last to the first and finds the newest there first (16k tokens, 32 heads of 64,
+// MI355X, backward: N = 256 250 -> 235 us, N = 512 without the mask 337 -> 326 us, N >= 1024 -1% .. 0).
 template <int D, bool F16>
-static hipError_t launch_bwd_d(BwdArgs a, int causal, int stages, hipStream_t st) {
-  // The dQ kernel reads Q, K, V, O that the forward pass has just streamed through the last-level cache (256 MB):
-  // it goes through the pairs from the last to the first and finds the newest there first (16k tokens, 32 heads of 64,
-  // MI355X, backward: N = 256 250 -> 235 us, N = 512 without the mask 337 -> 326 us, N >= 1024 -1% .. 0).
-  a.p.pairs_back = 1;
+static hipError_t launch_bwd_d(const BwdArgs& a, int causal, int stages, hipStream_t st) {
   // The whole backward is two launches: the dQ kernel goes first and computes D on the way, the dK/dV kernel
   // follows and reads it.
-  if (stages == 7) {
-    if (hipError_t e = launch_dq<D, F16, true>(a, causal, st)) return e;
-    return launch_dkdv<D, F16>(a, causal, st);
+  if (stages == 7 && a.p.cu_seqlens) {
+    if (hipError_t e = launch_dq<D, F16, true, true>(a, causal, st)) return e;
+    return launch_dkdv<D, F16, true>(a, causal, st);
   }
+  if (stages == 7) {
+    if (hipError_t e = launch_dq<D, F16, true, false>(a, causal, st)) return e;
+    return launch_dkdv<D, F16, false>(a, causal, st);
+  }
+  // one stage or two (dense batches only)
   if (stages & 1) {
     const long nrows = (long)a.p.total_tokens * a.p.Hq;
     constexpr int RPB = 256 / (D / 8);
@@ -1443,9 +1462,9 @@ static hipError_t launch_bwd_d(BwdArgs a, int causal, int stages, hipStream_t st
     if (hipError_t e = hipGetLastError()) return e;
   }
   if (stages & 2)
-    if (hipError_t e = launch_dkdv<D, F16>(a, causal, st)) return e;
+    if (hipError_t e = launch_dkdv<D, F16, false>(a, causal, st)) return e;
   if (stages & 4)
-    if (hipError_t e = launch_dq<D, F16, false>(a, causal, st)) return e;
+    if (hipError_t e = launch_dq<D, F16, false, false>(a, causal, st)) return e;
   return hipSuccess;
 }
 

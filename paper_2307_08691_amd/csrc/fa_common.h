@@ -59,7 +59,6 @@ struct Problem {
   const uint8_t* bmask;
   long bmask_bs, bmask_hs;
   int bmask_cols, bmask_log2;
-  int pairs_back;  // set by a launch: hand the (head, sequence) pairs out from the last to the first (see launch_bwd_d)
 };
 // the LOCAL template parameter of the kernels: nothing, a sliding window, a block-sparse pattern (perhaps with a window)
 constexpr int kNoPattern = 0, kWindow = 1, kBlocks = 2;
@@ -115,8 +114,9 @@ __host__ __device__ inline unsigned grid_size(int nblk, int pairs) {
 // that size): heads are handed out so that the heads of one group follow each other at a
 // distance of nheads / group pairs. With a multiple of 8 key/value heads they then land on the
 // same XCD, whose L2 holds the group's K and V once instead of every XCD holding them all.
-template <bool WORK_SORTED>
-__device__ __forceinline__ BlockCoord block_coord(int nblk, int nheads, int nseq, int group = 1, int back = 0) {
+// BACK: the pairs from the last to the first (see launch_bwd_d).
+template <bool WORK_SORTED, bool BACK = false>
+__device__ __forceinline__ BlockCoord block_coord(int nblk, int nheads, int nseq, int group = 1) {
   const int L = blockIdx.x;
   const int x = L % kXcds, k = L / kXcds;
   const int ppx = gridDim.x / (kXcds * nblk);  // pairs per XCD
@@ -129,7 +129,7 @@ __device__ __forceinline__ BlockCoord block_coord(int nblk, int nheads, int nseq
     c.blk = k % nblk;
     pl = k / nblk;
   }
-  if (back) pl = ppx - 1 - pl;
+  if (BACK) pl = ppx - 1 - pl;
   const int pr = pl * kXcds + x;
   const int hp = pr % nheads, nkv = nheads / group;
   c.head = (hp % nkv) * group + hp / nkv;
@@ -223,10 +223,7 @@ __device__ __forceinline__ RaggedCoord ragged_coord(const int32_t* cu, int rows,
   r.valid = true;
   return r;
 }
-// (expected false where it is asked: short dense batches feel the instructions they have to jump over)
-__device__ __forceinline__ bool ragged_order(const Problem& p, int nblk) {
-  return p.cu_seqlens && (int)(gridDim.x / (kXcds * nblk)) <= 64 * kRaggedChunks;
-}
+__device__ __forceinline__ bool ragged_order(int nblk) { return (int)(gridDim.x / (kXcds * nblk)) <= 64 * kRaggedChunks; }
 
 // (through the first lane: the compiler would keep the coordinates, and all that follows from them, per lane)
 __device__ __forceinline__ BlockCoord scalar_coord(BlockCoord c) {
@@ -235,36 +232,37 @@ __device__ __forceinline__ BlockCoord scalar_coord(BlockCoord c) {
 }
 
 // Which block of `rows` query rows (heaviest first) of which query head a workgroup takes; blk counts from row 0.
-template <bool CAUSAL>
+// RAGGED (p.cu_seqlens is set) is a parameter of the instantiation, not asked here: short dense batches, whose time is
+// the chain of one workgroup, feel the search even as code that they jump over.
+template <bool CAUSAL, bool RAGGED, bool BACK = false>
 __device__ __forceinline__ BlockCoord row_block_coord(const Problem& p, int rows) {
   const int nblk = (p.N + rows - 1) / rows;
-  BlockCoord c;
-  if (__builtin_expect(ragged_order(p, nblk), 0)) {
+  if (RAGGED && ragged_order(nblk)) {
     const RaggedCoord r = ragged_coord<CAUSAL>(p.cu_seqlens, rows, nblk, p.Hq, p.nseq, p.G);
-    c = {CAUSAL ? r.left - 1 : r.blk, r.head, r.seq, r.valid};
-  } else {
-    c = block_coord<CAUSAL>(nblk, p.Hq, p.nseq, p.G, p.pairs_back);
-    c.blk = nblk - 1 - c.blk;
+    return scalar_coord({CAUSAL ? r.left - 1 : r.blk, r.head, r.seq, r.valid});
   }
-  return scalar_coord(c);
+  BlockCoord c = block_coord<CAUSAL, BACK>(nblk, p.Hq, p.nseq, p.G);
+  c.blk = nblk - 1 - c.blk;
+  return c;
 }
 // Which block of `keys` keys of which key/value head; blk counts from key 0, under the causal rule the
 // heaviest block. A block's work then grows with the number of rows below it, not with its index: in
 // block_coord's order (batches with very many pairs) block indices therefore count from the END of the
-// longest possible sequence, and blk < 0 stands for a block that a shorter one does not have.
-template <bool CAUSAL>
+// longest possible sequence, and the blocks that a shorter one does not have are not valid.
+template <bool CAUSAL, bool RAGGED>
 __device__ __forceinline__ BlockCoord key_block_coord(const Problem& p, int keys) {
   const int nblk = (p.Nk + keys - 1) / keys;
-  BlockCoord c;
-  if (__builtin_expect(ragged_order(p, nblk), 0)) {
+  if (RAGGED && ragged_order(nblk)) {
     const RaggedCoord r =
         ragged_coord<CAUSAL>(p.cu_seqlens_k ? p.cu_seqlens_k : p.cu_seqlens, keys, nblk, p.Hkv, p.nseq, 1);
-    c = {CAUSAL ? r.blocks - r.left : r.blk, r.head, r.seq, r.valid};
-  } else {
-    c = block_coord<CAUSAL>(nblk, p.Hkv, p.nseq);
-    if (CAUSAL && p.cu_seqlens && c.valid) c.blk -= nblk - (seq_info(p, c.seq).nk + keys - 1) / keys;
+    return scalar_coord({CAUSAL ? r.blocks - r.left : r.blk, r.head, r.seq, r.valid});
   }
-  return scalar_coord(c);
+  BlockCoord c = block_coord<CAUSAL>(nblk, p.Hkv, p.nseq);
+  if (CAUSAL && RAGGED && c.valid) {
+    c.blk -= nblk - (seq_info(p, c.seq).nk + keys - 1) / keys;
+    c.valid = c.blk >= 0;
+  }
+  return c;
 }
 
 // D = A(32 x 16) * B(16 x 32) + C on one wavefront, 16-bit inputs, fp32 accumulate.

@@ -45,7 +45,7 @@ struct LaneAddr {
 // ---------------------------------------------------------------------------------------------
 // Forward (Algorithm 1). Wavefront w owns rows 32 w .. 32 w + 31 of a 128-row block; key blocks
 // of 64. LDS: three stages of K_j (left | right half, 16 KiB each) and two of V_j.
-template <bool CAUSAL, bool F16>
+template <bool CAUSAL, bool F16, bool RAGGED>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void fwd256_kernel(FwdArgs a) {
   constexpr int D = 256, BR = 128, BC = 64, KS = D / 16, DT = D / 32;
   constexpr int HALFB = BC * kRowB, TILEB = 2 * HALFB;  // one K_j or V_j: left | right
@@ -56,7 +56,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lq = lane & 31, hh = lane >> 5;
-  const BlockCoord bc = row_block_coord<CAUSAL>(p, BR);
+  const BlockCoord bc = row_block_coord<CAUSAL, RAGGED>(p, BR);
   if (!bc.valid) return;
   const int rowblk = bc.blk;
   const int h = bc.head, s = bc.seq;
@@ -257,23 +257,27 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
         m * p.scale + fast_log2(lsum) * kLn2;
 }
 
-hipError_t launch_fwd256(const FwdArgs& a, int causal, hipStream_t st) {
+template <bool RAGGED>  // a.p.cu_seqlens is set
+static hipError_t launch_fwd256_d(const FwdArgs& a, int causal, hipStream_t st) {
   dim3 grid(grid_size((a.p.N + 127) / 128, a.p.Hq * a.p.nseq)), block(256);
   if (a.p.f16) {
-    if (causal) hipLaunchKernelGGL((fwd256_kernel<true, true>), grid, block, 0, st, a);
-    else hipLaunchKernelGGL((fwd256_kernel<false, true>), grid, block, 0, st, a);
+    if (causal) hipLaunchKernelGGL((fwd256_kernel<true, true, RAGGED>), grid, block, 0, st, a);
+    else hipLaunchKernelGGL((fwd256_kernel<false, true, RAGGED>), grid, block, 0, st, a);
   } else {
-    if (causal) hipLaunchKernelGGL((fwd256_kernel<true, false>), grid, block, 0, st, a);
-    else hipLaunchKernelGGL((fwd256_kernel<false, false>), grid, block, 0, st, a);
+    if (causal) hipLaunchKernelGGL((fwd256_kernel<true, false, RAGGED>), grid, block, 0, st, a);
+    else hipLaunchKernelGGL((fwd256_kernel<false, false, RAGGED>), grid, block, 0, st, a);
   }
   return hipGetLastError();
+}
+hipError_t launch_fwd256(const FwdArgs& a, int causal, hipStream_t st) {
+  return a.p.cu_seqlens ? launch_fwd256_d<true>(a, causal, st) : launch_fwd256_d<false>(a, causal, st);
 }
 
 // ---------------------------------------------------------------------------------------------
 // dQ (Algorithm 2, lines 10-15 for one row block): the forward kernel's skeleton. Wavefront w owns
 // rows 32 w .. of a 128-row block with Q_i, dO_i, L_i, D_i in registers; per key block S^T and
 // dP^T = V_j dO_i^T, then P and dS, then dQ_i^T += K_j^T dS^T with K_j^T from transposing reads.
-template <bool CAUSAL, bool F16>
+template <bool CAUSAL, bool F16, bool RAGGED>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void dq256_kernel(BwdArgs a) {
   constexpr int D = 256, BR = 128, BC = 64, KS = D / 16, DT = D / 32;
   constexpr int HALFB = BC * kRowB, STAGEB = 4 * HALFB;
@@ -283,7 +287,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lq = lane & 31, hh = lane >> 5;
-  const BlockCoord bc = row_block_coord<CAUSAL>(p, BR);
+  const BlockCoord bc = row_block_coord<CAUSAL, RAGGED>(p, BR);
   if (!bc.valid) return;
   const int rowblk = bc.blk;
   const int h = bc.head, s = bc.seq;
@@ -434,7 +438,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 // dK_j^T, dV_j^T accumulators in registers (384 of them). It walks the query heads of the group
 // and, per head, the 32-row tiles Q_i | dO_i (left and right halves, 8 KiB each) that are not
 // entirely above the diagonal; L_i and -D_i of the tile's rows sit beside them in LDS.
-template <bool CAUSAL, bool F16>
+template <bool CAUSAL, bool F16, bool RAGGED>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void dkdv256_kernel(BwdArgs a) {
   constexpr int D = 256, BC = 128, BR = 32, KS = D / 16, DT = D / 32;
   constexpr int HALFB = BR * kRowB, STAGEB = 4 * HALFB;  // Q left | Q right | dO left | dO right
@@ -445,8 +449,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lq = lane & 31, hh = lane >> 5;
-  const BlockCoord bc = key_block_coord<CAUSAL>(p, BC);
-  if (!bc.valid || bc.blk < 0) return;
+  const BlockCoord bc = key_block_coord<CAUSAL, RAGGED>(p, BC);
+  if (!bc.valid) return;
   const int g = bc.head, s = bc.seq;
   const SeqInfo si = seq_info(p, s);
   const int n = si.n, nk = si.nk, off = nk - n;
@@ -610,31 +614,35 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   }
 }
 
-hipError_t launch_bwd256(const BwdArgs& a, int causal, int stages, hipStream_t st) {
+template <bool RAGGED>
+static hipError_t launch_bwd256_d(const BwdArgs& a, int causal, int stages, hipStream_t st) {
   hipError_t e = hipSuccess;
   if (stages & 2) {
     dim3 grid(grid_size((a.p.Nk + 127) / 128, a.p.Hkv * a.p.nseq)), block(256);
     if (a.p.f16) {
-      if (causal) hipLaunchKernelGGL((dkdv256_kernel<true, true>), grid, block, 0, st, a);
-      else hipLaunchKernelGGL((dkdv256_kernel<false, true>), grid, block, 0, st, a);
+      if (causal) hipLaunchKernelGGL((dkdv256_kernel<true, true, RAGGED>), grid, block, 0, st, a);
+      else hipLaunchKernelGGL((dkdv256_kernel<false, true, RAGGED>), grid, block, 0, st, a);
     } else {
-      if (causal) hipLaunchKernelGGL((dkdv256_kernel<true, false>), grid, block, 0, st, a);
-      else hipLaunchKernelGGL((dkdv256_kernel<false, false>), grid, block, 0, st, a);
+      if (causal) hipLaunchKernelGGL((dkdv256_kernel<true, false, RAGGED>), grid, block, 0, st, a);
+      else hipLaunchKernelGGL((dkdv256_kernel<false, false, RAGGED>), grid, block, 0, st, a);
     }
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   if (stages & 4) {
     dim3 grid(grid_size((a.p.N + 127) / 128, a.p.Hq * a.p.nseq)), block(256);
     if (a.p.f16) {
-      if (causal) hipLaunchKernelGGL((dq256_kernel<true, true>), grid, block, 0, st, a);
-      else hipLaunchKernelGGL((dq256_kernel<false, true>), grid, block, 0, st, a);
+      if (causal) hipLaunchKernelGGL((dq256_kernel<true, true, RAGGED>), grid, block, 0, st, a);
+      else hipLaunchKernelGGL((dq256_kernel<false, true, RAGGED>), grid, block, 0, st, a);
     } else {
-      if (causal) hipLaunchKernelGGL((dq256_kernel<true, false>), grid, block, 0, st, a);
-      else hipLaunchKernelGGL((dq256_kernel<false, false>), grid, block, 0, st, a);
+      if (causal) hipLaunchKernelGGL((dq256_kernel<true, false, RAGGED>), grid, block, 0, st, a);
+      else hipLaunchKernelGGL((dq256_kernel<false, false, RAGGED>), grid, block, 0, st, a);
     }
     e = hipGetLastError();
   }
   return e;
+}
+hipError_t launch_bwd256(const BwdArgs& a, int causal, int stages, hipStream_t st) {
+  return a.p.cu_seqlens ? launch_bwd256_d<true>(a, causal, stages, st) : launch_bwd256_d<false>(a, causal, stages, st);
 }
 
 }  // namespace fa

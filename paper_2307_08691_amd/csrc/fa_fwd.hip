@@ -96,13 +96,16 @@ __device__ __forceinline__ float max3(float a, float b, float c) { return __buil
 // width D (row pitch, swizzle and copies are those of the full tile), but the products only run
 // over the first DH columns: D = 128 with DH = 96 does three quarters of the matrix work of the
 // full width, D = 64 with DH = 32 half.
+//
+// RAGGED: a packed batch (p.cu_seqlens); see row_block_coord.
 template <int D, bool CAUSAL, bool SPLIT, bool F16, bool DROPOUT = false, bool PAD = false, bool MASK = false,
-          int LOCAL = kNoPattern, int DH = D>
+          int LOCAL = kNoPattern, int DH = D, bool RAGGED = false>
 __global__ __launch_bounds__(512)
     __attribute__((amdgpu_waves_per_eu(fwd_two_per_cu(D, MASK || LOCAL == kBlocks) ? 4 : 2, fwd_two_per_cu(D, MASK || LOCAL == kBlocks) ? 4 : 2))) void
     fwd_kernel(FwdArgs a) {
   constexpr bool TWO = fwd_two_per_cu(D, MASK || LOCAL == kBlocks);
   static_assert(!LOCAL || (!CAUSAL && !SPLIT && !DROPOUT && !PAD && !MASK), "the window variant is built for the plain kernel");
+  static_assert(!RAGGED || (!SPLIT && !MASK && LOCAL != kBlocks), "no entry point packs these batches");
   constexpr int AHEAD_QK = TWO ? 1 : kFwdAheadQK, AHEAD_PV = TWO ? 1 : kFwdAheadPV;
   static_assert(!MASK || (!SPLIT && !DROPOUT && !PAD), "the mask variant is built for the plain kernel");
   constexpr int BR = 256, BC = 64, RING = 4;
@@ -128,7 +131,7 @@ __global__ __launch_bounds__(512)
   const int lq = lane & 31, hh = lane >> 5;
   const int nsplit = SPLIT ? a.nsplit : 1;
   const int nblk = ((SPLIT ? p.N * p.G : p.N) + BR - 1) / BR;
-  const BlockCoord bc = SPLIT ? block_coord<false>(nblk * nsplit, p.Hkv, p.nseq) : row_block_coord<CAUSAL>(p, BR);
+  const BlockCoord bc = SPLIT ? block_coord<false>(nblk * nsplit, p.Hkv, p.nseq) : row_block_coord<CAUSAL, RAGGED>(p, BR);
   if (!bc.valid) return;
   const int split = SPLIT ? bc.blk % nsplit : 0;
   const int rowblk = SPLIT ? bc.blk / nsplit : bc.blk;
@@ -990,63 +993,72 @@ hipError_t launch_keyless_rows(const Problem& p, __bf16* out, float* lse, hipStr
   return hipGetLastError();
 }
 
+// Few query rows against many keys: the keys split over workgroups, the shares merged.
 template <int D, bool F16>
+static hipError_t launch_fwd_split(const FwdArgs& a, int causal, hipStream_t st) {
+  const dim3 block(512);
+  const bool decode = a.p.N * a.p.G <= 32;  // one row tile per key/value head: the wavefronts divide the keys (fa_decode.hip)
+  if (decode) {
+    if (hipError_t e = launch_fwd_decode(a, D, causal, st)) return e;
+  } else {
+    const int nblk = (a.p.N * a.p.G + 255) / 256;
+    dim3 grid(grid_size(nblk * a.nsplit, a.p.Hkv * a.p.nseq));
+    if (causal) hipLaunchKernelGGL((fwd_kernel<D, true, true, F16>), grid, block, 0, st, a);
+    else hipLaunchKernelGGL((fwd_kernel<D, false, true, F16>), grid, block, 0, st, a);
+    if (hipError_t e = hipGetLastError()) return e;
+  }
+  if (a.nsplit == 1) return hipSuccess;  // (a single share: the kernel has written O and LSE itself)
+  constexpr int RPB = 256 / (D / 4);
+  const long nrows = (long)a.p.total_tokens * a.p.Hq;
+  const dim3 mgrid((unsigned)((nrows + RPB - 1) / RPB));
+  if (decode) hipLaunchKernelGGL((fwd_merge_kernel<D, F16, true>), mgrid, dim3(256), 0, st, a);
+  else hipLaunchKernelGGL((fwd_merge_kernel<D, F16, false>), mgrid, dim3(256), 0, st, a);
+  return hipGetLastError();
+}
+
+// RAGGED: a.p.cu_seqlens is set.
+template <int D, bool F16, bool RAGGED>
 static hipError_t launch_fwd_d(const FwdArgs& a, int causal, hipStream_t st) {
-  dim3 block(512);
-  if (a.nsplit > 0) {
-    const bool decode = a.p.N * a.p.G <= 32;  // one row tile per key/value head: the wavefronts divide the keys (fa_decode.hip)
-    if (decode) {
-      if (hipError_t e = launch_fwd_decode(a, D, causal, st)) return e;
-    } else {
-      const int nblk = (a.p.N * a.p.G + 255) / 256;
-      dim3 grid(grid_size(nblk * a.nsplit, a.p.Hkv * a.p.nseq));
-      if (causal) hipLaunchKernelGGL((fwd_kernel<D, true, true, F16>), grid, block, 0, st, a);
-      else hipLaunchKernelGGL((fwd_kernel<D, false, true, F16>), grid, block, 0, st, a);
-      if (hipError_t e = hipGetLastError()) return e;
+  const dim3 grid(grid_size((a.p.N + 255) / 256, a.p.Hq * a.p.nseq)), block(512);
+  if constexpr (!RAGGED) {  // the entry points keep everything else away from the elementwise mask and the block-sparse pattern
+    if (a.p.mask) {
+      if (causal) hipLaunchKernelGGL((fwd_kernel<D, true, false, F16, false, false, true>), grid, block, 0, st, a);
+      else hipLaunchKernelGGL((fwd_kernel<D, false, false, F16, false, false, true>), grid, block, 0, st, a);
+      return hipGetLastError();
     }
-    if (a.nsplit == 1) return hipSuccess;  // (a single share: the kernel has written O and LSE itself)
-    constexpr int RPB = 256 / (D / 4);
-    const long nrows = (long)a.p.total_tokens * a.p.Hq;
-    const dim3 mgrid((unsigned)((nrows + RPB - 1) / RPB));
-    if (decode) hipLaunchKernelGGL((fwd_merge_kernel<D, F16, true>), mgrid, dim3(256), 0, st, a);
-    else hipLaunchKernelGGL((fwd_merge_kernel<D, F16, false>), mgrid, dim3(256), 0, st, a);
-    return hipGetLastError();
+    if (a.p.bmask) {
+      hipLaunchKernelGGL((fwd_kernel<D, false, false, F16, false, false, false, kBlocks>), grid, block, 0, st, a);
+      return hipGetLastError();
+    }
   }
-  dim3 grid(grid_size((a.p.N + 255) / 256, a.p.Hq * a.p.nseq));
-  if (a.p.mask) {  // the entry points keep everything else away from it
-    if (causal) hipLaunchKernelGGL((fwd_kernel<D, true, false, F16, false, false, true>), grid, block, 0, st, a);
-    else hipLaunchKernelGGL((fwd_kernel<D, false, false, F16, false, false, true>), grid, block, 0, st, a);
-    return hipGetLastError();
-  }
-  if (a.p.win_left >= 0 || a.p.win_right >= 0 || a.p.bmask) {  // sliding window, block-sparse pattern (the entry points keep everything else away from them)
-    if (a.p.bmask) hipLaunchKernelGGL((fwd_kernel<D, false, false, F16, false, false, false, kBlocks>), grid, block, 0, st, a);
-    else hipLaunchKernelGGL((fwd_kernel<D, false, false, F16, false, false, false, kWindow>), grid, block, 0, st, a);
+  if (a.p.win_left >= 0 || a.p.win_right >= 0) {  // (dropout and padded head dimensions are kept away from the window)
+    hipLaunchKernelGGL((fwd_kernel<D, false, false, F16, false, false, false, kWindow, D, RAGGED>), grid, block, 0, st, a);
     return hipGetLastError();
   }
   if (a.p.d != D) {  // padded head dimension (the entry points keep dropout away from it)
     constexpr int DN = D == 128 ? 96 : 32;  // the narrower product width of this tile width
     if (a.p.d <= DN) {
-      if (causal) hipLaunchKernelGGL((fwd_kernel<D, true, false, F16, false, true, false, false, DN>), grid, block, 0, st, a);
-      else hipLaunchKernelGGL((fwd_kernel<D, false, false, F16, false, true, false, false, DN>), grid, block, 0, st, a);
+      if (causal) hipLaunchKernelGGL((fwd_kernel<D, true, false, F16, false, true, false, kNoPattern, DN, RAGGED>), grid, block, 0, st, a);
+      else hipLaunchKernelGGL((fwd_kernel<D, false, false, F16, false, true, false, kNoPattern, DN, RAGGED>), grid, block, 0, st, a);
     } else {
-      if (causal) hipLaunchKernelGGL((fwd_kernel<D, true, false, F16, false, true>), grid, block, 0, st, a);
-      else hipLaunchKernelGGL((fwd_kernel<D, false, false, F16, false, true>), grid, block, 0, st, a);
+      if (causal) hipLaunchKernelGGL((fwd_kernel<D, true, false, F16, false, true, false, kNoPattern, D, RAGGED>), grid, block, 0, st, a);
+      else hipLaunchKernelGGL((fwd_kernel<D, false, false, F16, false, true, false, kNoPattern, D, RAGGED>), grid, block, 0, st, a);
     }
     return hipGetLastError();
   }
   if (a.p.drop_thr) {
-    if (causal) hipLaunchKernelGGL((fwd_kernel<D, true, false, F16, true>), grid, block, 0, st, a);
-    else hipLaunchKernelGGL((fwd_kernel<D, false, false, F16, true>), grid, block, 0, st, a);
+    if (causal) hipLaunchKernelGGL((fwd_kernel<D, true, false, F16, true, false, false, kNoPattern, D, RAGGED>), grid, block, 0, st, a);
+    else hipLaunchKernelGGL((fwd_kernel<D, false, false, F16, true, false, false, kNoPattern, D, RAGGED>), grid, block, 0, st, a);
     return hipGetLastError();
   }
-  if constexpr (D == 128) {
+  if constexpr (D == 128 && !RAGGED) {
     // chained items (fwd_chain_kernel): dense batches of short sequences (at most 16 key blocks:
     // +15% at N = 512; from N = 2048 on the start-up no longer matters and the fixed assignment
     // of items loses against the hardware's dynamic one, -5% at N = 8192 under the mask) whose
     // items split evenly over the XCDs and into chains of even length, with at least one
     // workgroup left per compute unit
     const int pairs = a.p.Hq * a.p.nseq, nblk = (a.p.N + 255) / 256;
-    if (!a.p.cu_seqlens && pairs % kXcds == 0 && a.p.N >= 256 && a.p.Nk >= a.p.N && a.p.Nk <= kFwdChainMaxN) {
+    if (pairs % kXcds == 0 && a.p.N >= 256 && a.p.Nk >= a.p.N && a.p.Nk <= kFwdChainMaxN) {
       const int items = pairs / kXcds * nblk;  // per XCD
       int chain = items % 8 == 0 ? 8 : items % 4 == 0 ? 4 : items % 2 == 0 ? 2 : 1;
       while (chain > 1 && items / chain < 32) chain /= 2;
@@ -1058,17 +1070,23 @@ static hipError_t launch_fwd_d(const FwdArgs& a, int causal, hipStream_t st) {
       }
     }
   }
-  if (causal) hipLaunchKernelGGL((fwd_kernel<D, true, false, F16>), grid, block, 0, st, a);
-  else hipLaunchKernelGGL((fwd_kernel<D, false, false, F16>), grid, block, 0, st, a);
+  if (causal) hipLaunchKernelGGL((fwd_kernel<D, true, false, F16, false, false, false, kNoPattern, D, RAGGED>), grid, block, 0, st, a);
+  else hipLaunchKernelGGL((fwd_kernel<D, false, false, F16, false, false, false, kNoPattern, D, RAGGED>), grid, block, 0, st, a);
   return hipGetLastError();
+}
+
+template <int D, bool F16>
+static hipError_t launch_fwd_w(const FwdArgs& a, int causal, hipStream_t st) {
+  if (a.nsplit > 0) return launch_fwd_split<D, F16>(a, causal, st);
+  return a.p.cu_seqlens ? launch_fwd_d<D, F16, true>(a, causal, st) : launch_fwd_d<D, F16, false>(a, causal, st);
 }
 
 hipError_t launch_fwd(const FwdArgs& a, int d, int causal, hipStream_t st) {
   if (hipError_t e = launch_keyless_rows(a.p, a.O, a.LSE, st)) return e;
   if (d == 256) return launch_fwd256(a, causal, st);
   // tile width: the head dimension padded up to 64 or 128
-  if (a.p.f16) return d <= 64 ? launch_fwd_d<64, true>(a, causal, st) : launch_fwd_d<128, true>(a, causal, st);
-  return d <= 64 ? launch_fwd_d<64, false>(a, causal, st) : launch_fwd_d<128, false>(a, causal, st);
+  if (a.p.f16) return d <= 64 ? launch_fwd_w<64, true>(a, causal, st) : launch_fwd_w<128, true>(a, causal, st);
+  return d <= 64 ? launch_fwd_w<64, false>(a, causal, st) : launch_fwd_w<128, false>(a, causal, st);
 }
 
 }  // namespace fa

@@ -141,9 +141,22 @@ def touched_in_flight(lines):
     return loads, bad
 
 
-def test_registers_of_loads_in_flight_are_left_alone():
-    kernels = kernel_assembly("fa_fwd.hip")
-    chained = {k: v for k, v in kernels.items() if "fwd_chain_kernel" in k}
+@pytest.fixture(scope="module")
+def forward_assembly():
+    return kernel_assembly("fa_fwd.hip")
+
+
+def test_only_the_instantiations_for_packed_batches_search_for_their_block(forward_assembly):
+    """The search of a packed batch's launch order (recognisable by the wavefront-wide sum) costs a short dense call
+    1-2% even as code that is jumped over, so it is compiled into the RAGGED instantiations only."""
+    kernels = {k: "row_bcast" in "\n".join(v) for k, v in forward_assembly.items() if "fwd_kernel" in k}
+    ragged = {k for k in kernels if k.endswith("ELb1EEEvNS_7FwdArgsE")}  # the last template parameter
+    assert len(ragged) >= 18 and len(kernels) - len(ragged) >= 26
+    assert {k for k, searches in kernels.items() if searches} == ragged
+
+
+def test_registers_of_loads_in_flight_are_left_alone(forward_assembly):
+    chained = {k: v for k, v in forward_assembly.items() if "fwd_chain_kernel" in k}
     assert len(chained) == 4
     for name, lines in chained.items():
         loads, bad = touched_in_flight(lines)

@@ -66,6 +66,7 @@ fa::Problem make_problem(const int32_t* cu, int nseq, int N, int Nk, int Hq, int
   p.drop_thr = 0;
   p.drop_seed = 0;
   p.drop_rp = 1.f;
+  p.drop_log2 = 0.f;
   p.mask = nullptr;
   p.mask_bs = p.mask_hs = p.mask_rs = 0;
   p.win_left = p.win_right = -1;
@@ -101,6 +102,7 @@ int set_dropout(fa::Problem& p, float p_drop, uint64_t seed) {
   p.drop_thr = (uint32_t)t;
   p.drop_seed = (uint32_t)seed ^ ((uint32_t)(seed >> 32) * 0x27D4EB2Fu);
   p.drop_rp = 256.f / (256.f - (float)t);
+  p.drop_log2 = 8.f - log2f(256.f - (float)t);
   return FA_OK;
 }
 

@@ -307,7 +307,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 12
   // them, and with them for the copies in flight.
   float lraw = 0.f, draw = 0.f;
   bool stat_ok = false;
-  const float d_factor = DROPOUT ? 1.f - (float)p.drop_thr * (1.f / 256.f) : 1.f;  // (see phase_v)
+  const float d_factor = DROPOUT ? 1.f - (float)p.drop_thr * (1.f / 256.f) : 1.f, l_less = DROPOUT ? p.drop_log2 : 0.f;  // (see phase_v)
   TileLoader<D, BR, 4, PAD> qloader;  // Q_i and dO_i tiles have the same shape and row pitch
   qloader.init(qstride, kg, lane, dh / 8);
   auto issue_loads = [&](const Cursor& c) {
@@ -339,7 +339,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 12
       // L in the exponent's base; rows past the end get L = +inf so that P = exp2(. - inf) = 0.
       // D is stored negated: it is the initial value of the dP accumulator (line 14).
       // (mask: a row left without keys has L = -inf and, like a row past the end, P = 0)
-      *(float*)(smem + LS_OFF + o) = stat_ok && !((MASK || LOCAL) && lraw == -INFINITY) ? lraw * kLog2e : INFINITY;
+      *(float*)(smem + LS_OFF + o) = stat_ok && !((MASK || LOCAL) && lraw == -INFINITY) ? lraw * kLog2e - l_less : INFINITY;
       *(float*)(smem + DV_OFF + o) = stat_ok ? -draw * d_factor : 0.f;
     }
   };
@@ -383,7 +383,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 12
         const long si_ = stat_base + (long)c.hq * p.lse_head_stride + (ok ? row : n - 1);
         const float l = a.LSE[si_], dd = a.Dvec[si_];
         const int o = (c.slot * BR + tid - t * BR) * 4;
-        *(float*)(smem + LS_OFF + o) = ok && !((MASK || LOCAL) && l == -INFINITY) ? l * kLog2e : INFINITY;
+        *(float*)(smem + LS_OFF + o) = ok && !((MASK || LOCAL) && l == -INFINITY) ? l * kLog2e - l_less : INFINITY;
         *(float*)(smem + DV_OFF + o) = ok ? -dd * d_factor : 0.f;
       }
       advance(c, 1);
@@ -525,9 +525,11 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 12
         for (int r = 0; r < 16; ++r) S[tq][r] = kc <= acc_row(r, 0) && (!LOCAL || acc_row(r, 0) <= kb) ? S[tq][r] : 0.f;
       }
       if constexpr (DROPOUT) {
-        // dP = keep o (dO V^T) / (1 - p), then dS = P o (dP - D) with the true P; afterwards P
-        // itself is masked for dV += P_drop^T dO. The factor 1 / (1 - p) of all three goes into the
-        // final scaling: (1 - p) dS = P o (keep o (dO V^T) - (1 - p) D), the factor being on D in LDS.
+        // dP = keep o (dO V^T) / (1 - p), dS = P o (dP - D) and dV += (keep o P / (1 - p))^T dO. The statistics
+        // in LDS carry the factor: L is less by log2(1 / (1 - p)), so that S holds P / (1 - p), and D is (1 - p) D:
+        // dS = P / (1 - p) o (keep o (dO V^T) - (1 - p) D). (Left to the final scaling of the three gradients
+        // the factor would make P and dS smaller before they are rounded to 16 bits, in half precision
+        // subnormal sooner; as a factor of dP's entries it costs the phase up to 4%.)
         // A hash covers four consecutive keys of one query, here four neighbouring lanes, and a lane
         // holds four consecutive queries in four registers: lane i of a quad hashes query i of each
         // four and the quad exchanges the words, one hash per four entries instead of one per entry.
@@ -546,7 +548,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 12
             const int e = 4 * r4 + u;
             const bool kept = (quad_lane(x, u) & byte_mask) >= byte_thr;
             const float pe = S[tq][e];
-            dP[tq][e] = pe * ((kept ? dP[tq][e] : 0.f) + Dn[u]);  // Dn = -D (1 - p)
+            dP[tq][e] = pe * ((kept ? dP[tq][e] : 0.f) + Dn[u]);  // Dn = -(1 - p) D
             S[tq][e] = kept ? pe : 0.f;
           }
         }
@@ -826,8 +828,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 12
       const long kvoff = ((si.tok0k + key0) * p.Hkv + g) * dh;
       int ln = lane;  // recomputed here: nothing of the staging addresses is to live across the main loop
       asm volatile("" : "+v"(ln));
-      store_tiles_via_lds<DT, F16>(stg, dKt, DROPOUT ? p.scale * p.drop_rp : p.scale, a.dK + kvoff, (long)p.Hkv * dh, nk - key0, dh, ln);
-      store_tiles_via_lds<DT, F16>(stg, dVt, DROPOUT ? p.drop_rp : 1.f, a.dV + kvoff, (long)p.Hkv * dh, nk - key0, dh, ln);
+      store_tiles_via_lds<DT, F16>(stg, dKt, p.scale, a.dK + kvoff, (long)p.Hkv * dh, nk - key0, dh, ln);
+      store_tiles_via_lds<DT, F16>(stg, dVt, 1.f, a.dV + kvoff, (long)p.Hkv * dh, nk - key0, dh, ln);
     }
     return;
   }
@@ -869,7 +871,6 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 12
 
   // ---- combine the two groups' partial sums and write dK_j, dV_j (line 18); dK carries the scaling
   float* red = (float*)(smem + QDO_OFF);  // 4 * DT * 16 * 64 floats, free after the loop
-  const float rp = DROPOUT ? p.drop_rp : 1.f;
 #pragma unroll
   for (int which = 0; which < 2; ++which) {
     f32x16* accs = which == 0 ? dKt : dVt;
@@ -882,7 +883,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 12
     __syncthreads();
     if (grp == 0 && key_ok) {
       __bf16* dst = (which == 0 ? a.dK : a.dV) + ((si.tok0k + key) * p.Hkv + g) * dh + 4 * hh;
-      const float mul = which == 0 ? p.scale * rp : rp;
+      const float mul = which == 0 ? p.scale : 1.f;
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
@@ -972,7 +973,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
     }
   }
   const long stat = s * p.lse_seq_stride + (long)h * p.lse_head_stride + (p.cu_seqlens ? si.tok0 : 0) + rowc;
-  float Lq = row < n ? a.LSE[stat] * kLog2e : INFINITY;  // rows past the end: P = 0
+  // (dropout: S then holds P / (1 - p), and D_i is scaled by 1 - p below: see the dK/dV kernel) rows past the end: P = 0
+  float Lq = row < n ? a.LSE[stat] * kLog2e - (DROPOUT ? p.drop_log2 : 0.f) : INFINITY;
   if ((MASK || LOCAL) && Lq == -INFINITY) Lq = INFINITY;  // a row that the mask (the pattern) left without keys: P = 0
 
   f32x16 dQt[DT];
@@ -1217,7 +1219,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
           if (c > lim_row || (LOCAL && c < lo_row)) S[kt][r] = 0.f;
         }
       }
-      if constexpr (DROPOUT) {  // dP = keep o (dO V^T) / (1 - p), the factor left to the final scaling: Dq is (1 - p) D
+      if constexpr (DROPOUT) {  // dP = keep o (dO V^T) / (1 - p), the factor being in S and in Dq
 #pragma unroll
         for (int q4 = 0; q4 < 4; ++q4) {  // registers 4 q4 .. 4 q4 + 3: keys col0 + 32 kt + 8 q4 + 4 hh + 0..3
           const uint32_t x = drop_mix(drop_lane + (uint32_t)(col0 / 4 + 8 * kt + 2 * q4) * kDropCol);
@@ -1287,7 +1289,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
     if constexpr (DT % 2 == 0) {
 #pragma unroll
       for (int half = 0; half < 2; ++half)
-        store_rows_via_lds<DT / 2, F16>(stg, &dQt[half * (DT / 2)], DROPOUT ? p.scale * p.drop_rp : p.scale, op + half * (DH / 2), ostride, n - wrow0,
+        store_rows_via_lds<DT / 2, F16>(stg, &dQt[half * (DT / 2)], p.scale, op + half * (DH / 2), ostride, n - wrow0,
                                         dh - half * (DH / 2), ln);
     } else {  // (an odd number of 32-column tiles: one at a time)
 #pragma unroll

@@ -40,7 +40,7 @@ struct Problem {
   // dropout on P (drop_thr = 0: none): an entry is kept when its byte of the hash is >= drop_thr
   uint32_t drop_thr;          // round(256 p), 1 .. 255
   uint32_t drop_seed;         // (seed mod 2^32) xor (seed >> 32) * 0x27D4EB2F
-  float drop_rp;              // 1 / (1 - drop_thr / 256)
+  float drop_rp, drop_log2;   // 1 / (1 - drop_thr / 256) and its base-2 logarithm
   // elementwise mask added to the scaled scores (nullptr: none): bfloat16, finite or -inf,
   // element (s, h, r, c) at mask[s * mask_bs + h * mask_hs + r * mask_rs + c]; a stride of 0
   // shares the mask over sequences or heads; mask_rs >= Nk rounded up to 8, a multiple of 8

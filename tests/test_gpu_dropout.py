@@ -101,6 +101,17 @@ def test_lengths_around_the_256_key_blocks_of_the_backward(Nq, Nk, d, causal):
     check_dropout(inputs.make_cross(B=1, Nq=Nq, Nk=Nk, Hq=4, Hkv=2, d=d, causal=causal, seed=6300 + Nk), 0.1, seed=0x256)
 
 
+@pytest.mark.parametrize("p_drop", [0.9, 255 / 256])
+@pytest.mark.parametrize("Nq,Nk,d", [(200, 512, 64), (200, 512, 128), (512, 512, 64)])
+def test_half_precision_gradients_at_a_high_probability(Nq, Nk, d, p_drop):
+    """An output gradient of 2^-12: the entries of dS are subnormal half-precision numbers, spaced by 2^-24, as those of the
+    reference are; rounded without their factor 1 / (1 - p) they would be spaced by that much more (a float64 model of
+    the rounding: dQ off by 3.0e-7 and 2.1e-6 at p = 0.9, by 5e-7 and 5e-5 at 255/256)."""
+    prob = inputs.make_cross(B=1, Nq=Nq, Nk=Nk, Hq=2, Hkv=2, d=d, causal=False, seed=6700 + Nq + d, dtype="f16")
+    prob.dO = inputs.f32_to_f16_bits(orc.widen_f16(prob.dO).astype(np.float32) / 4096)
+    check_dropout(prob, p_drop, seed=0xBEEF)
+
+
 # (36 sequences x 8 heads fill more than 256 workgroups of 128 or 256 keys, one sequence does not; under the causal rule
 # d = 64 takes the small form up to 4096 keys either way)
 @pytest.mark.parametrize("causal", [False, True])

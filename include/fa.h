@@ -208,7 +208,11 @@ int fa_cross_bwd_f16(const void* Q, const void* K, const void* V, const void* O,
  *     keep = byte (key mod 4) of x  >=  round(256 * p_drop)       (threshold capped at 255)
  * so the effective drop probability is a multiple of 1/256, and 1 / (1 - p) uses that
  * multiple. 0 <= p_drop < 1, otherwise FA_ERR_SHAPE; a threshold of 0 runs the plain kernels.
- * Workspace: fa_cross_bwd_workspace_bytes.
+ * Workspace: fa_cross_bwd_workspace_bytes. All outputs are bit-reproducible. Unlike those of the
+ * plain entry points, dK and dV at d = 128 are not independent of the batch a sequence is in: on
+ * grids that fit the GPU at once a key's float32 sum is taken in two halves, on larger ones in a
+ * single chain, so a 16-bit entry may come out as its neighbour (O, LSE, dQ and d = 64 are
+ * independent of it).
  */
 int fa_dropout_fwd(const void* Q, const void* K, const void* V, void* O, float* LSE,
                    int B, int Hq, int Hkv, int Nq, int Nk, int d, float scale, int causal,
@@ -225,7 +229,8 @@ int fa_dropout_bwd(const void* Q, const void* K, const void* V, const void* O, c
  * the head index of the generator is bh = sequence * Hq + head, query and key are counted from
  * the start of their sequence, so a ragged batch of equal lengths drops exactly what the dense
  * batch drops). Layouts, arguments and workspace as for fa_varlen_fwd / fa_varlen_bwd
- * (fa_varlen_bwd_workspace_bytes); d in {64, 128}; bfloat16 elements.
+ * (fa_varlen_bwd_workspace_bytes); d in {64, 128}; bfloat16 elements. dK and dV at d = 128 depend
+ * on the batch as said at fa_dropout_bwd.
  */
 int fa_varlen_dropout_fwd(const void* Q, const void* K, const void* V, void* O, float* LSE,
                           const int32_t* cu_seqlens, int nseq, int total_tokens, int max_seqlen,

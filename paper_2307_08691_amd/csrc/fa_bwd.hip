@@ -1309,6 +1309,9 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
 //    (16 x 300, 32 heads, no mask: 107 -> 86 us), and in the causal dK/dV kernel (`short_too`), whose 128-key blocks
 //    also start closer to the diagonal, up to 4096 keys (16k tokens, N = 512: 304 -> 284 us, 2048: 584 -> 572,
 //    4096: 980 -> 975, 8192: 1779 -> 1807).
+// The plain kernels have the form, and dropout's dK/dV kernel at d = 64. Dropout's dQ kernel, windows, masks, patterns
+// and padded head dimensions keep blocks of 256 rows on small grids too: no small form of theirs has been measured, and each
+// would be another instantiation per element type and causal flag.
 static bool small_workgroups(int n, int pairs, bool short_too, bool two = true) {
   const long small = (long)((n + 127) / 128) * pairs, large = (long)((n + 255) / 256) * pairs;
   if (small <= 256) return true;

@@ -812,8 +812,11 @@ def splitkv_default_splits(B, Hq, Hkv, Nq, Nk, ragged: bool = False) -> int:
     sequences in decoding shapes, where the decode kernel hands the sequences out longest first
     (measured on 64 sequences of 1 .. 8192 keys: 1 share 5.0 TB/s, 4 shares 4.3, 16 shares 2.5);
     otherwise about eight workgroups per compute unit and at least 16 blocks per share of a full
-    cache, since more, shorter shares then even the load out (same batch in launch order: 4 shares
-    3.7 TB/s, 1 share 2.6, 16 shares 2.9). (fa_kvcache_fwd takes no more than this many.)"""
+    cache: what evened the load out while the row-block kernel kept the launch order (same batch:
+    4 shares 3.7 TB/s, 1 share 2.6, 16 shares 2.9). That kernel goes longest first now and fa_kvcache_fwd,
+    when it is left the choice (num_splits = 0), takes as many shares as _cache_splits says: never
+    more than these, so a workspace sized by this function is large enough, but usually fewer and
+    faster (4 x 512 queries on caches of up to 8192 keys: 8 here, 212 us; 2 there, 158 us)."""
     units = B * Hkv * ((Nq * (Hq // Hkv) + 255) // 256)
     blocks = (Nk + 63) // 64
     if ragged and not (B <= 128 and Nq * (Hq // Hkv) <= 32):

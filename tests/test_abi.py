@@ -221,6 +221,25 @@ def test_split_key_entry_point_rejects_bad_arguments():
     assert binding.splitkv_default_splits(200, 32, 8, 1, 8192, ragged=True) == 2
 
 
+def test_default_shares_of_cache_attention_fit_the_public_workspace():
+    """fa_kvcache_fwd's own rule: the public one where lengths are equal or the query rows fit the decode kernel, never
+    more than it elsewhere, so a workspace sized by splitkv_default_splits is always large enough."""
+    public, own = binding.splitkv_default_splits, binding._cache_splits
+    for B in (1, 2, 3, 4, 7, 8, 16, 33, 64, 128, 129, 300):
+        for Hq, Hkv in ((1, 1), (4, 4), (8, 1), (32, 8), (32, 32), (64, 8)):
+            for Nq in (1, 2, 8, 33, 70, 128, 233, 512, 1000, 4096):
+                for Nk in (1, 64, 65, 700, 1024, 2048, 8191, 8192, 10752, 131072):
+                    for d in (64, 128):
+                        n, most = own(B, Hq, Hkv, Nq, Nk, d, True), public(B, Hq, Hkv, Nq, Nk, ragged=True)
+                        assert 1 <= n <= most <= binding.FA_SPLITKV_MAX_SPLITS, (B, Hq, Hkv, Nq, Nk, d)
+                        assert Nq * (Hq // Hkv) > 32 or n == most
+                        assert own(B, Hq, Hkv, Nq, Nk, d, False) == public(B, Hq, Hkv, Nq, Nk)
+    assert own(4, 32, 8, 512, 8192, 128, True) == 2
+    assert own(8, 32, 8, 128, 8192, 128, True) == 3
+    assert own(1, 32, 8, 512, 8192, 128, True) == 4
+    assert own(4, 32, 8, 233, 10752, 64, True) == 4
+
+
 def test_window_pattern_cache_fp8_and_mask_gradient_entry_points_reject_bad_arguments():
     def local(Nq=64, Nk=64, d=128, left=10, right=0, Q=P):
         return binding.fa_local_fwd_raw(Q, P, P, P, P, 1, 4, 2, Nq, Nk, d, 0.1, left, right, 0)

@@ -116,8 +116,18 @@ def check_splitkv(prob, num_splits):
     O, L = binding.fa_splitkv_fwd(Q, K, V, prob.scale, prob.causal, num_splits)
     torch.cuda.synchronize()
     pu.judge(f"split keys {pu.describe(prob)} shares={num_splits}", {"O": pu.to_f64(O), "LSE": pu.to_f64(L)},
-             pu.run_oracle(prob, backward=False), pu.run_reference(prob, backward=False), d=prob.d)
+             pu.run_oracle(prob, backward=False), pu.run_reference(prob, backward=False), standard=pu.is_standard(prob), d=prob.d)
     return O, L
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("num_splits", [1, 3])
+@pytest.mark.parametrize("Hq,Hkv,d", [(2, 2, 64), (2, 2, 128), (32, 1, 128)])
+def test_split_keys_with_widely_spread_scores(Hq, Hkv, d, num_splits, causal):
+    """Scores of tens of bits: the reference of each share's running softmax advances again and again, and the shares
+    are merged over references that lie far apart."""
+    prob = inputs.make_dense(B=1, N=900, Hq=Hq, Hkv=Hkv, d=d, causal=causal, seed=3750 + d, qk_mult=5.0)
+    check_splitkv(prob, num_splits)
 
 
 @pytest.mark.parametrize("causal", [False, True])

@@ -35,7 +35,7 @@ def reference(Q, K_of, V_of, lens, scale, causal, Hq, Hkv):
     return out
 
 
-def check_contiguous(prob, lens, causal, num_splits):
+def check_contiguous(prob, lens, causal, num_splits, standard=True):
     Q, Kc, Vc = (pu.to_gpu(x) for x in (prob.Q, prob.K, prob.V))
     cap = Kc.shape[1]
     for b, n in enumerate(lens):  # what lies past a sequence's length is not part of it
@@ -48,7 +48,7 @@ def check_contiguous(prob, lens, causal, num_splits):
     eO, eL = orc.kvcache_forward(Qf, Kf, Vf, prob.scale, causal, np.asarray(lens))
     ref = reference(Q, lambda b: Kc[b, :lens[b]], lambda b: Vc[b, :lens[b]], lens, prob.scale, causal, prob.Hq, prob.Hkv)
     pu.judge(f"cache {lens} of {cap} Nq{prob.N} H{prob.Hq}/{prob.Hkv} d{prob.d} {'c' if causal else 'f'} x{num_splits}",
-             {"O": pu.to_f64(O), "LSE": pu.to_f64(L)}, {"O": eO, "LSE": eL}, ref, d=prob.d)
+             {"O": pu.to_f64(O), "LSE": pu.to_f64(L)}, {"O": eO, "LSE": eL}, ref, standard=standard, d=prob.d)
     return O, L
 
 
@@ -108,8 +108,7 @@ def test_paged_cache(Nq, Hq, Hkv, d, num_splits, page, causal):
     pu.judge(f"paged cache page {page} Nq{Nq} H{Hq}/{Hkv} d{d} {'c' if causal else 'f'} x{num_splits}",
              {"O": pu.to_f64(O), "LSE": pu.to_f64(L)}, {"O": eO, "LSE": eL}, ref, d=d)
     # the same keys in one slab per sequence: the same arithmetic in the same order
-    O2, L2 = binding.fa_kvcache_fwd(Q, Kc, Vc, prob.scale, causal, seqlens_k=sl,
-                                    num_splits=num_splits or binding.splitkv_default_splits(len(lens), Hq, Hkv, Nq, cap, ragged=True))
+    O2, L2 = binding.fa_kvcache_fwd(Q, Kc, Vc, prob.scale, causal, seqlens_k=sl, num_splits=num_splits)
     torch.cuda.synchronize()
     assert torch.equal(O, O2) and torch.equal(L, L2)
 
@@ -189,6 +188,15 @@ def test_sequences_of_one_and_of_several_shares_in_the_row_block_kernel(d, num_s
     keys than queries (rows without a key), a full cache; three heads per key/value head in the rows."""
     lens = [1025, 3000, 30, 0, 1024, 2049, 1]
     check_contiguous(draw(18650 + d, len(lens), 90, 3000, 6, 2, d), lens, True, num_splits)
+
+
+@pytest.mark.parametrize("Nq,Hq,Hkv,d", [(90, 6, 2, 64), (90, 6, 2, 128), (2, 8, 2, 128)])
+def test_caches_with_widely_spread_scores(Nq, Hq, Hkv, d):
+    """Scores of tens of bits in the row-block and in the decode kernel: one share and several, rows without a key."""
+    lens = [1025, 3000, 30, 0, 2049]
+    prob = inputs.make_dense(B=len(lens), N=3000, Hq=Hq, Hkv=Hkv, d=d, causal=False, seed=18660 + d, qk_mult=5.0)
+    prob.Q, prob.N, prob.Nk = prob.Q[:, :Nq].copy(), Nq, 3000
+    check_contiguous(prob, lens, True, 2, standard=False)
 
 
 @pytest.mark.parametrize("B", [2, 64, 128, 129])

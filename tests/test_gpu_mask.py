@@ -37,7 +37,7 @@ def mask_to_gpu(bits, dtype="bf16"):
     return M
 
 
-def check_mask(prob, mbits, fwd_only=False):
+def check_mask(prob, mbits, fwd_only=False, standard=True):
     Q, K, V, dO = (pu.to_gpu(x, prob.dtype) for x in (prob.Q, prob.K, prob.V, prob.dO))
     M = mask_to_gpu(mbits, prob.dtype)
     O, L = binding.fa_mask_fwd(Q, K, V, M, prob.scale, prob.causal)
@@ -54,7 +54,7 @@ def check_mask(prob, mbits, fwd_only=False):
     Bm, Hm, Nq, Nk = mbits.shape
     ref = pu.reference_batch(Q, K, V, dO, prob.scale, prob.causal, backward=not fwd_only, M=M[:, :, :, :Nk])
     res = pu.judge(f"mask {pu.describe(prob)} shared {Bm}x{Hm}", {k: pu.to_f64(v) for k, v in got.items()}, exp, ref,
-                   dtype=prob.dtype, d=prob.d)
+                   standard=standard, dtype=prob.dtype, d=prob.d)
     return {k: v[0] for k, v in res.items()}
 
 
@@ -65,6 +65,16 @@ def check_mask(prob, mbits, fwd_only=False):
 def test_masked_self_attention(N, kind, d, causal):
     prob = inputs.make_dense(B=2, N=N, Hq=2, Hkv=2, d=d, causal=causal, seed=9000 + N)
     check_mask(prob, make_mask(9100 + N, 2, 2, N, N, kind))
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("kind", ["bias", "mixed", "dead"])
+def test_masks_with_widely_spread_scores(kind, d, causal):
+    """Scores of tens of bits: the reference of the running softmax advances again and again, in rows that have
+    seen keys and in rows whose keys were all removed so far."""
+    prob = inputs.make_dense(B=1, N=700, Hq=2, Hkv=2, d=d, causal=causal, seed=9070 + d, qk_mult=5.0)
+    check_mask(prob, make_mask(9080 + d, 1, 2, 700, 700, kind), standard=False)
 
 
 @pytest.mark.parametrize("causal", [False, True])

@@ -95,10 +95,61 @@ def test_kept_fraction_seen_through_the_output():
 
 @pytest.mark.parametrize("Nq,Nk,d,causal", [(31, 255, 64, False), (64, 256, 128, True), (257, 257, 64, True),
                                             (33, 511, 128, False), (513, 513, 128, True), (1, 769, 64, False)])
-def test_lengths_around_the_256_key_blocks_of_the_backward(Nq, Nk, d, causal):
+def test_lengths_around_the_blocks_of_the_backward_on_small_grids(Nq, Nk, d, causal):
+    """The dK/dV kernel's 128-key blocks that small grids take under dropout: a last block of 1, 127 or 128 keys, row
+    tiles with a single row, wavefronts whose keys lie past the end or above every row."""
+    check_dropout(inputs.make_cross(B=1, Nq=Nq, Nk=Nk, Hq=4, Hkv=2, d=d, causal=causal, seed=6300 + Nk), 0.1, seed=0x256)
+
+
+def check_dropout_units(prob, p_drop, seed, units):
+    """check_dropout on whole (sequence b, key/value head g) units of a larger dense batch."""
+    Q, K, V, dO = (pu.to_gpu(x, prob.dtype) for x in (prob.Q, prob.K, prob.V, prob.dO))
+    got = run(prob, p_drop, seed)
+    widen = orc.widen_f16 if prob.dtype == "f16" else orc.widen_bf16
+    thr = orc.dropout_threshold(p_drop)
+    G = prob.Hq // prob.Hkv
+    for t in got.values():
+        assert torch.isfinite(t.float()).all()
+    for (b, g) in units:
+        k, v = widen(prob.K[b, :, g]), widen(prob.V[b, :, g])
+        exp = {"O": [], "LSE": [], "dQ": [], "dK": np.zeros_like(k), "dV": np.zeros_like(v)}
+        ref = {"O": [], "LSE": [], "dQ": [], "dK": np.zeros_like(k), "dV": np.zeros_like(v)}
+        hs = slice(g * G, (g + 1) * G)
+        for h in range(g * G, (g + 1) * G):
+            keep = orc.dropout_keep(seed, b * prob.Hq + h, prob.N, prob.keys, thr)
+            q, do = widen(prob.Q[b, :, h]), widen(prob.dO[b, :, h])
+            o, lse, _ = orc.head_forward_dropout(q, k, v, prob.scale, prob.causal, keep, thr)
+            dq, dk, dv = orc.head_backward_dropout(q, k, v, do, prob.scale, prob.causal, keep, thr)
+            r = pu.reference_head(Q[b, :, h], K[b, :, g], V[b, :, g], dO[b, :, h], prob.scale, prob.causal,
+                                  keep=torch.from_numpy(keep).cuda(), rp=256.0 / (256.0 - thr))
+            for nm, x in (("O", o), ("LSE", lse), ("dQ", dq), ("dK", dk), ("dV", dv)):
+                for to, value in ((exp, x), (ref, r[nm])):
+                    if nm in ("dK", "dV"):
+                        to[nm] += value
+                    else:
+                        to[nm].append(value)
+        for nm in ("O", "LSE", "dQ"):
+            exp[nm], ref[nm] = np.stack(exp[nm]), np.stack(ref[nm])
+        part = {"O": pu.to_f64(got["O"][b, :, hs]).transpose(1, 0, 2), "LSE": pu.to_f64(got["LSE"][b, hs]),
+                "dQ": pu.to_f64(got["dQ"][b, :, hs]).transpose(1, 0, 2), "dK": pu.to_f64(got["dK"][b, :, g]),
+                "dV": pu.to_f64(got["dV"][b, :, g])}
+        pu.judge(f"dropout p={p_drop} unit (b={b}, g={g}) {pu.describe(prob)}", part, exp, ref, standard=False, dtype=prob.dtype,
+                 d=prob.d)
+
+
+# (136 key/value heads over all sequences, 8 where the sequences are long: more than 256 workgroups, so the blocks are of
+# 256 keys; at d = 64 with the mask that takes more than 4096 keys as well)
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("B,Nq,Nk,Hq,Hkv,d,causal", [
+    (17, 100, 257, 8, 8, 64, False), (17, 33, 511, 16, 8, 64, False), (17, 1, 512, 8, 8, 64, False),
+    (17, 100, 257, 8, 8, 128, False), (17, 33, 511, 16, 8, 128, False), (17, 1, 512, 8, 8, 128, False),
+    (17, 257, 257, 8, 8, 128, True), (17, 100, 511, 16, 8, 128, True), (17, 512, 512, 8, 8, 128, True),
+    (1, 4097, 4097, 8, 8, 64, True), (1, 100, 4351, 16, 8, 64, True), (2, 65, 4352, 4, 4, 64, True)])
+def test_lengths_around_the_256_key_blocks_of_the_backward(B, Nq, Nk, Hq, Hkv, d, causal, dtype):
     """The dK/dV kernel's 256-key blocks under dropout: a last block of 1, 255 or 256 keys, row tiles with
     a single row, wavefronts whose keys lie past the end or above every row."""
-    check_dropout(inputs.make_cross(B=1, Nq=Nq, Nk=Nk, Hq=4, Hkv=2, d=d, causal=causal, seed=6300 + Nk), 0.1, seed=0x256)
+    prob = inputs.make_cross(B=B, Nq=Nq, Nk=Nk, Hq=Hq, Hkv=Hkv, d=d, causal=causal, seed=6800 + Nk, dtype=dtype)
+    check_dropout_units(prob, 0.1, 0x256, [(0, 0), (B - 1, Hkv - 1)])
 
 
 @pytest.mark.parametrize("p_drop", [0.9, 255 / 256])

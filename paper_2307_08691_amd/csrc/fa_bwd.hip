@@ -1459,18 +1459,21 @@ static hipError_t launch_bwd_d(const BwdArgs& a, int causal, int stages, hipStre
     if (hipError_t e = launch_dq<D, F16, true, false>(a, causal, st)) return e;
     return launch_dkdv<D, F16, false>(a, causal, st);
   }
-  // one stage or two (dense batches only)
-  if (stages & 1) {
-    const long nrows = (long)a.p.total_tokens * a.p.Hq;
-    constexpr int RPB = 256 / (D / 8);
-    hipLaunchKernelGGL((bwd_prep_kernel<D, F16>), dim3((unsigned)((nrows + RPB - 1) / RPB)), dim3(256), 0, st, a);
-    if (hipError_t e = hipGetLastError()) return e;
+  if constexpr (F16) {
+    return hipErrorInvalidValue;
+  } else {  // one stage or two (fa_bwd_stages: dense batches in bfloat16)
+    if (stages & 1) {
+      const long nrows = (long)a.p.total_tokens * a.p.Hq;
+      constexpr int RPB = 256 / (D / 8);
+      hipLaunchKernelGGL((bwd_prep_kernel<D, F16>), dim3((unsigned)((nrows + RPB - 1) / RPB)), dim3(256), 0, st, a);
+      if (hipError_t e = hipGetLastError()) return e;
+    }
+    if (stages & 2)
+      if (hipError_t e = launch_dkdv<D, F16, false>(a, causal, st)) return e;
+    if (stages & 4)
+      if (hipError_t e = launch_dq<D, F16, false, false>(a, causal, st)) return e;
+    return hipSuccess;
   }
-  if (stages & 2)
-    if (hipError_t e = launch_dkdv<D, F16, false>(a, causal, st)) return e;
-  if (stages & 4)
-    if (hipError_t e = launch_dq<D, F16, false, false>(a, causal, st)) return e;
-  return hipSuccess;
 }
 
 hipError_t launch_bwd(const BwdArgs& a, int d, int causal, int stages, hipStream_t st) {

@@ -34,7 +34,7 @@ import numpy as np
 
 from oracle import attention_oracle as orc
 from paper_2307_08691_amd import binding
-from paper_2307_08691_amd.inputs import AttnProblem
+from paper_2307_08691_amd.inputs import AttnProblem, make_varlen
 
 # Absolute bounds against the float64 oracle for 16-bit inputs drawn from N(0,1).
 TOL_O = 2e-2
@@ -298,6 +298,14 @@ def run_reference(prob: AttnProblem, backward: bool = True):
     Q, K, V, dO = (to_gpu(x, prob.dtype) for x in (prob.Q, prob.K, prob.V, prob.dO))
     return reference_batch(Q, K, V, dO, prob.scale, prob.causal, backward,
                            cu_q=prob.cu_seqlens if prob.varlen else None)
+
+
+def large_varlen(d, causal, seed, dtype="bf16") -> AttnProblem:
+    """A ragged batch small enough for the oracle whose grids (sized by the longest sequence) hold more than 256 workgroups of
+    256 rows or keys: the kernels take their largest form, in the causal dK/dV kernel at d = 64 past 4096 keys."""
+    short = [257, 1, 100, 0, 511, 64, 300, 31, 129, 256, 513, 2, 128, 33, 255]
+    longest, Hkv = (4150, 1) if d == 64 and causal else (1100, 4)
+    return make_varlen(short[:7] + [longest] + short[7:], Hq=2 * Hkv, Hkv=Hkv, d=d, causal=causal, seed=seed, dtype=dtype)
 
 
 def check(prob: AttnProblem, backward: bool = True):

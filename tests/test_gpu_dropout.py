@@ -192,12 +192,25 @@ def test_small_and_large_workgroups_of_the_backward_drop_the_same_entries(N, Hq,
 def test_ragged_batches_with_dropout(d, Hq, Hkv, causal, dtype):
     """fa_varlen_dropout_fwd / bwd against the oracle's ragged dropout: the generator counts rows and
     columns from the start of each sequence and uses sequence * Hq + head as its head index."""
-    prob = inputs.make_varlen([100, 257, 1, 31, 300], Hq=Hq, Hkv=Hkv, d=d, causal=causal, seed=6100 + d, dtype=dtype)
+    check_ragged_dropout(inputs.make_varlen([100, 257, 1, 31, 300], Hq=Hq, Hkv=Hkv, d=d, causal=causal, seed=6100 + d, dtype=dtype))
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("d", [64, 128])
+def test_ragged_batches_with_dropout_on_large_grids(d, causal, dtype):
+    """The same where the dK/dV kernel has blocks of 256 keys (more than 256 workgroups; past 4096 keys at d = 64 with
+    the mask)."""
+    check_ragged_dropout(pu.large_varlen(d=d, causal=causal, seed=6900 + d, dtype=dtype))
+
+
+def check_ragged_dropout(prob):
+    causal, dtype, Hq, Hkv, d = prob.causal, prob.dtype, prob.Hq, prob.Hkv, prob.d
     Q, K, V, dO = (pu.to_gpu(x, dtype) for x in (prob.Q, prob.K, prob.V, prob.dO))
-    cu = torch.from_numpy(prob.cu_seqlens.astype(np.int32)).cuda()
+    cu, longest = torch.from_numpy(prob.cu_seqlens.astype(np.int32)).cuda(), int(prob.seqlens.max())
     p_drop, seed = 0.25, 0x1234567890ABCDEF
-    O, L = binding.fa_varlen_dropout_fwd(Q, K, V, cu, 300, prob.scale, causal, p_drop, seed)
-    dQ, dK, dV = binding.fa_varlen_dropout_bwd(Q, K, V, O, dO, L, cu, 300, prob.scale, causal, p_drop, seed)
+    O, L = binding.fa_varlen_dropout_fwd(Q, K, V, cu, longest, prob.scale, causal, p_drop, seed)
+    dQ, dK, dV = binding.fa_varlen_dropout_bwd(Q, K, V, O, dO, L, cu, longest, prob.scale, causal, p_drop, seed)
     torch.cuda.synchronize()
     widen = orc.widen_f16 if dtype == "f16" else orc.widen_bf16
     Qf, Kf, Vf, dOf = (widen(x) for x in (prob.Q, prob.K, prob.V, prob.dO))

@@ -70,7 +70,8 @@ def test_ragged_batches_with_two_lengths_in_half_precision(causal):
 
 
 @pytest.mark.parametrize("causal", [False, True])
-@pytest.mark.parametrize("Nq,Nk,Hq,Hkv,d,splits", [(1, 1000, 8, 2, 128, 3), (5, 700, 4, 4, 64, 2), (70, 4097, 8, 1, 128, 0)])
+@pytest.mark.parametrize("Nq,Nk,Hq,Hkv,d,splits", [(1, 1000, 8, 2, 128, 3), (5, 700, 4, 4, 64, 2), (70, 4097, 8, 1, 128, 0),
+                                                   (70, 700, 4, 2, 64, 3)])
 def test_split_keys_and_the_key_value_cache_in_half_precision(Nq, Nk, Hq, Hkv, d, splits, causal):
     prob = inputs.make_cross(B=3, Nq=Nq, Nk=Nk, Hq=Hq, Hkv=Hkv, d=d, causal=causal, seed=5500 + Nq, dtype="f16")
     Q, K, V = (pu.to_gpu(x, "f16") for x in (prob.Q, prob.K, prob.V))
@@ -89,6 +90,13 @@ def test_split_keys_and_the_key_value_cache_in_half_precision(Nq, Nk, Hq, Hkv, d
     ref2 = cache_reference(Q, lambda b: K[b, :lens[b]], lambda b: V[b, :lens[b]], lens, prob.scale, causal, Hq, Hkv)
     pu.judge(f"cache f16 {lens} {pu.describe(prob)}", {"O": pu.to_f64(O2), "LSE": pu.to_f64(L2)}, {"O": eO2, "LSE": eL2}, ref2,
              dtype="f16", d=d)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_half_precision_on_large_grids_without_the_mask(d):
+    """17 sequences of 8 heads: more than 256 workgroups, both backward kernels in their forms of eight wavefronts."""
+    prob = inputs.make_cross(B=17, Nq=257, Nk=257, Hq=8, Hkv=8, d=d, causal=False, seed=5450 + d, dtype="f16")
+    check_units(prob, pu.run_hip(prob), [(0, 0), (16, 7)])
 
 
 def test_half_precision_outputs_are_half_precision_roundings():

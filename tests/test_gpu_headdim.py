@@ -39,6 +39,20 @@ def test_packed_ragged_batches(d, causal):
     check(prob)
 
 
+# (32 and 96 or less: the narrower product width of a tile; 48, 104: all of it; 256: kernels of their own)
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("d", [32, 48, 104, 256])
+def test_packed_ragged_batches_at_every_product_width(d, dtype, causal):
+    check(inputs.make_varlen([100, 257, 1, 0, 31, 515], Hq=4, Hkv=2, d=d, causal=causal, seed=5650 + d, dtype=dtype))
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("d", [32, 48, 96, 104])
+def test_half_precision_at_every_product_width(d, causal):
+    check(inputs.make_cross(B=2, Nq=300, Nk=300, Hq=4, Hkv=2, d=d, causal=causal, seed=5660 + d, dtype="f16"))
+
+
 @pytest.mark.parametrize("d", [32, 96])
 def test_packed_ragged_batches_with_two_lengths(d):
     lq, lk = [1, 70, 0, 300], [257, 70, 33, 515]

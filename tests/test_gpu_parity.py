@@ -103,6 +103,14 @@ def test_ragged_batches_are_covered_without_gaps(nseq, longest, Hq, Hkv, d, caus
             assert torch.equal(x, y[0]), f"{name} of sequence {s} ({e - a} tokens)"
 
 
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("d", [64, 128])
+def test_packed_ragged_batches_on_large_grids(d, dtype, causal):
+    """More workgroups than compute units: both backward kernels in their forms of eight wavefronts."""
+    check(pu.large_varlen(d=d, causal=causal, seed=9370 + d, dtype=dtype))
+
+
 def test_packed_ragged_equals_dense_calls_bitwise():
     """A packed batch of equal lengths must reproduce the dense entry point bit for bit
     (every output is deterministic)."""
@@ -170,12 +178,14 @@ def test_forms_of_the_backward_agree_bitwise(B, part, N, Hq, Hkv, causal, dq, dk
 
 
 # (the grids on which each form of the two kernels is chosen: every small one, the small dK/dV form beside the large dQ
-# form, both large ones; a padded head dimension and d = 256)
+# form, both large ones; every product width of a padded head dimension and d = 256)
 @pytest.mark.parametrize("order", [(1, 6), (1, 2, 4), (1, 4, 2), (3, 4), (5, 2)])
 @pytest.mark.parametrize("B,N,Hq,Hkv,d,causal", [(1, 257, 4, 2, 64, True), (1, 257, 4, 2, 64, False), (1, 300, 4, 2, 128, True),
                                                  (1, 300, 4, 4, 128, False), (36, 256, 8, 8, 64, True),
                                                  (36, 256, 8, 8, 64, False), (40, 256, 8, 8, 128, True),
-                                                 (1, 200, 2, 1, 96, True), (1, 200, 2, 1, 256, True)])
+                                                 (1, 200, 2, 1, 96, True), (1, 200, 2, 1, 96, False), (1, 200, 2, 1, 32, True),
+                                                 (1, 200, 2, 1, 32, False), (1, 200, 2, 1, 48, True), (1, 200, 2, 1, 48, False),
+                                                 (1, 200, 2, 1, 104, True), (1, 200, 2, 1, 104, False), (1, 200, 2, 1, 256, True)])
 def test_any_split_of_the_backward_into_stages(B, N, Hq, Hkv, d, causal, order):
     """fa_bwd_stages runs whatever subset of the three stages it is asked for: the pre-pass first and the two
     kernels together, apart or in either order write all of dQ, dK and dV. (fa_bwd sums D inside the dQ kernel,

@@ -58,12 +58,12 @@ PEAK_HBM_GBS = 8000.0      # MI355X HBM3E peak
 # the kernel sources are the ones they were measured on (`sources`: kernel_sources_id() at the time
 # of the measurement); otherwise `traffic` is null and the stale figure moves to `traffic_recorded`.
 MEASURED_TRAFFIC = {
-    "sources": "aa63587ade56",
-    "d128_n8k_causal": {"fwd_kernel": 657936517, "bwd_dkdv_kernel": 862384831, "bwd_dq_kernel": 736812614},
-    "sweep_d128_n8192_full": {"fwd_kernel": 269806409, "bwd_dkdv_kernel": 405186020, "bwd_dq_kernel": 338038522},
-    "sweep_d64_n8192_causal": {"fwd_kernel": 873743558, "bwd_dkdv_kernel": 883456292, "bwd_dq_kernel": 831791357},
-    "decode_b8_on_8k": {"fwd_decode_kernel": 269316633},
-    "decode_paged_b64_to_8k": {"fwd_decode_kernel": 1019765575},
+    "sources": "1275c74f5718",
+    "d128_n8k_causal": {"fwd_kernel": 687892647, "bwd_dkdv_kernel": 900573335, "bwd_dq_kernel": 755300878},
+    "sweep_d128_n8192_full": {"fwd_kernel": 269782498, "bwd_dkdv_kernel": 405144627, "bwd_dq_kernel": 337872473},
+    "sweep_d64_n8192_causal": {"fwd_kernel": 885046153, "bwd_dkdv_kernel": 882182574, "bwd_dq_kernel": 831279353},
+    "decode_b8_on_8k": {"fwd_decode_kernel": 269298586},
+    "decode_paged_b64_to_8k": {"fwd_decode_kernel": 1019798805},
 }
 
 

@@ -1479,12 +1479,11 @@ static hipError_t launch_bwd_d(const BwdArgs& a, int causal, int stages, hipStre
 hipError_t launch_bwd(const BwdArgs& a, int d, int causal, int stages, hipStream_t st) {
   if (stages & 4)
     if (hipError_t e = launch_keyless_rows(a.p, a.dQ, nullptr, st)) return e;
-  if (d == 256) {  // the D pre-pass is the generic one, the two kernels live in fa_d256.hip
-    if (stages & 1) {
+  if (d == 256) {  // (the two kernels live in fa_d256.hip)
+    if (stages != 7 && (stages & 1)) {  // the D pre-pass is the generic one
       const long nrows = (long)a.p.total_tokens * a.p.Hq;
       constexpr int RPB = 256 / (256 / 8);
-      if (a.p.f16) hipLaunchKernelGGL((bwd_prep_kernel<256, true>), dim3((unsigned)((nrows + RPB - 1) / RPB)), dim3(256), 0, st, a);
-      else hipLaunchKernelGGL((bwd_prep_kernel<256, false>), dim3((unsigned)((nrows + RPB - 1) / RPB)), dim3(256), 0, st, a);
+      hipLaunchKernelGGL((bwd_prep_kernel<256, false>), dim3((unsigned)((nrows + RPB - 1) / RPB)), dim3(256), 0, st, a);
       if (hipError_t e = hipGetLastError()) return e;
     }
     return launch_bwd256(a, causal, stages, st);

@@ -4,6 +4,9 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+#include <utility>
+
 namespace fa {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
@@ -279,6 +282,58 @@ __device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
   else
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+}
+
+// The same product with the registers of its accumulator and of B chosen by hand, for kernels of one wavefront per SIMD:
+// the 512 registers of a wavefront are two files of 256, vector and accumulation registers (VGPR, AGPR); an MFMA takes its
+// accumulator from either and vector instructions only see the first. Left to itself the compiler keeps EVERY
+// accumulator in the second and copies scores back and forth for the softmax, or moves the long-lived accumulators
+// from one file to the other around every branch (d = 256 dQ kernel: 432 register copies beside 96 MFMAs).
+//   mfma32_agpr     C in AGPRs, B in VGPRs            mfma32_vgpr_ab  C in VGPRs, B in AGPRs
+//   mfma32_vgpr     C in VGPRs, B in VGPRs            (FIRST: C starts from zero)
+// Inline assembly is opaque to the compiler's hazard recogniser, so the callers keep the rules: two wait states between a
+// vector instruction that writes an operand and the MFMA, and settled() between the last MFMA on an accumulator and a
+// vector instruction that touches it, unless two other MFMAs lie between (tests/test_kernel_resources.py walks
+// the compiler's output for both).
+template <bool F16>
+__device__ __forceinline__ void mfma32_agpr(f32x16& c, bf16x8 a, bf16x8 b) {
+  if constexpr (F16) asm volatile("v_mfma_f32_32x32x16_f16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
+  else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
+}
+template <bool F16, bool FIRST>
+__device__ __forceinline__ void mfma32_vgpr_ab(f32x16& c, bf16x8 a, bf16x8 b) {
+  if constexpr (F16 && FIRST) asm volatile("v_mfma_f32_32x32x16_f16 %0, %1, %2, 0" : "=&v"(c) : "v"(a), "a"(b));
+  else if constexpr (F16) asm volatile("v_mfma_f32_32x32x16_f16 %0, %1, %2, %0" : "+v"(c) : "v"(a), "a"(b));
+  else if constexpr (FIRST) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(c) : "v"(a), "a"(b));
+  else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(a), "a"(b));
+}
+template <bool F16, bool FIRST>
+__device__ __forceinline__ void mfma32_vgpr(f32x16& c, bf16x8 a, bf16x8 b) {
+  if constexpr (F16 && FIRST) asm volatile("v_mfma_f32_32x32x16_f16 %0, %1, %2, 0" : "=&v"(c) : "v"(a), "v"(b));
+  else if constexpr (F16) asm volatile("v_mfma_f32_32x32x16_f16 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b));
+  else if constexpr (FIRST) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(c) : "v"(a), "v"(b));
+  else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b));
+}
+// (an MFMA of 8 passes needs 12 wait states before its result may be touched)
+__device__ __forceinline__ void settled(f32x16& a) { asm volatile("s_nop 15" : "+v"(a)); }
+__device__ __forceinline__ void settled(f32x16& a, f32x16& b) { asm volatile("s_nop 15" : "+v"(a), "+v"(b)); }
+// (as operands of ONE statement: a copy of an accumulator that the compiler makes then stands on the right side of the wait)
+__device__ __forceinline__ void agpr_settled(f32x16 (&c)[8]) {
+  asm volatile("s_nop 15" : "+a"(c[0]), "+a"(c[1]), "+a"(c[2]), "+a"(c[3]), "+a"(c[4]), "+a"(c[5]), "+a"(c[6]), "+a"(c[7]));
+}
+// Before a stream of MFMAs: the accumulators are in the registers that it uses.
+__device__ __forceinline__ void agpr_ready(f32x16 (&c)[8]) {
+  asm volatile("s_nop 1" : "+a"(c[0]), "+a"(c[1]), "+a"(c[2]), "+a"(c[3]), "+a"(c[4]), "+a"(c[5]), "+a"(c[6]), "+a"(c[7]));
+}
+
+// f(integral_constant<int, 0>) .. f(integral_constant<int, N - 1>): loops that have to be unrolled whatever their size
+template <class F, int... I>
+__device__ __forceinline__ void static_for_each(F f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, class F>
+__device__ __forceinline__ void static_for(F f) {
+  static_for_each(f, std::make_integer_sequence<int, N>{});
 }
 
 // Row of the 32 x 32 accumulator tile that register r of lane-half hh holds.

@@ -4,10 +4,14 @@
 // operands another 64 to 128, so a wavefront needs the whole register file of its SIMD (512
 // registers, one wavefront per SIMD): workgroups of FOUR wavefronts, 128 query rows (forward,
 // dQ) or 128 keys (dK/dV) each, and no second wavefront on the SIMD to run the softmax
-// while the first one multiplies. The backward loops are plain: wait for the tile, barrier,
-// products, P and dS, products, barrier, with the next tile in flight meanwhile (two LDS
-// stages); the forward kernel interleaves the exponentials of one block with the MFMAs of its
-// neighbours inside its single instruction stream.
+// while the first one multiplies. Every kernel is therefore ONE instruction stream in which the vector work of a block
+// stands between MFMAs that do not need it (the order of the source, held by scheduling fences), with one barrier
+// per block. What bounds such a stream is first the number of its instructions (a wavefront alone on its SIMD issues one in
+// about five cycles: six beside an MFMA of 32), then the chip's power: at N = 8192 without the mask the forward kernel
+// keeps the matrix pipe busy 59% of the cycles at 1.73 GHz. Accumulators and operands are placed in the two register
+// files by hand (mfma32_agpr and its kin, fa_common.h). Measured (MI355X, bfloat16, 16k tokens in 8 heads, us, plain
+// loops around the builtin product -> these): forward N = 2048 causal 179 -> 154, N = 8192 without the mask 1111 -> 944;
+// backward 581 -> 521 (25 of them the D pre-pass, now inside the dQ kernel) and 3575 -> 3284.
 //
 // A 256-wide tile is kept in LDS as two 128-wide halves side by side (columns 0..127 and
 // 128..255 of every row), each in the swizzled layout of fa_lds.h, so the operand addressing
@@ -22,7 +26,72 @@ namespace {
 
 constexpr int kHalf = 128;          // columns of one half tile
 constexpr int kRowB = 2 * kHalf;    // its row bytes
-constexpr int kLazyLog2 = 8;        // see FA_FWD_LAZY_LOG2 in fa_fwd.hip
+constexpr int kLazyLog2Half = 8, kLazyLog2Bf16 = 20;  // see kFwdLazyLog2Half in fa_fwd.hip
+
+// Copies of a 256-wide tile of ROWS rows (left | right half) by NW wavefronts: one wavefront instruction fetches four rows of a
+// half tile. The lane offsets of an interior tile are computed once; at the end of a sequence rows past the last repeat it.
+template <int ROWS, int NW>
+struct TileCopier {
+  static constexpr int PER = ROWS / 4 / NW, COPIES = 2 * PER, HALFB = ROWS * kRowB;
+  unsigned voff[PER], rowb, cbyte;
+  int crow, wave;
+  struct Plan {
+    const __bf16* base;
+    unsigned off[PER];
+  };
+  __device__ __forceinline__ void init(long gstride, int w, int lane) {
+    wave = w;
+    crow = 4 * w + (lane >> 4);
+    cbyte = 16u * ((lane & 15) ^ swz<kRowB>(crow));  // (4 NW rows further on the swizzle is the same)
+    static_assert(NW == 4, "");
+    rowb = (unsigned)gstride * 2u;
+#pragma unroll
+    for (int u = 0; u < PER; ++u) voff[u] = (unsigned)(crow + 4 * NW * u) * rowb + cbyte;
+  }
+  __device__ __forceinline__ Plan plan(const __bf16* base, int last) const {
+    Plan t;
+    t.base = base;
+#pragma unroll
+    for (int u = 0; u < PER; ++u) t.off[u] = voff[u];
+    if (last < ROWS - 1) {
+      asm volatile("; keep this a branch" ::);
+#pragma unroll
+      for (int u = 0; u < PER; ++u) t.off[u] = (unsigned)(crow + 4 * NW * u < last ? crow + 4 * NW * u : last) * rowb + cbyte;
+    }
+    return t;
+  }
+  template <int Q>
+  __device__ __forceinline__ void copy(const Plan& t, char* dst) const {
+    constexpr int u = Q >> 1, half = Q & 1;
+    dma16_uniform(t.base + half * kHalf, t.off[u], dst + half * HALFB + (wave + NW * u) * 1024);
+  }
+};
+
+// LDS operands of a stream of MFMAs, requested in pairs two pairs ahead. The second of a pair is requested first, so that the
+// wait in front of the pair's first MFMA covers both: one wait per two MFMAs. (A wavefront alone on its SIMD issues
+// one instruction in about five cycles, six beside an MFMA of 32: every instruction of the loop counts.)
+struct OperandRing {
+  static constexpr int PAIRS = 3;
+  bf16x8 x[2 * PAIRS];
+  template <int P, class LoadF>
+  __device__ __forceinline__ void pair(LoadF load) {
+    x[2 * (P % PAIRS) + 1] = load(std::integral_constant<int, 2 * P + 1>{});
+    x[2 * (P % PAIRS)] = load(std::integral_constant<int, 2 * P>{});
+  }
+  template <class LoadF>
+  __device__ __forceinline__ void begin(LoadF load) {
+    pair<0>(load);
+    pair<1>(load);
+  }
+  template <int I, int N, class LoadF>  // before MFMA I of N (even)
+  __device__ __forceinline__ void advance(LoadF load) {
+    if constexpr (I % 2 == 0 && I + 4 < N) pair<I / 2 + 2>(load);
+  }
+  template <class IC>
+  __device__ __forceinline__ bf16x8 at(IC) const {
+    return x[IC::value % (2 * PAIRS)];
+  }
+};
 
 __device__ __forceinline__ float max3f(float a, float b, float c) { return __builtin_fmaxf(__builtin_fmaxf(a, b), c); }
 
@@ -92,146 +161,196 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   }
   if (ncol < 1) ncol = 1;  // (more queries than keys is only allowed without the mask)
 
-  TileLoader<kHalf, BC, 4, false> loader;
-  loader.init(kstride, w, lane, kHalf / 8);
-  // One wavefront per SIMD has to overlap its own matrix and vector work: iteration j issues
-  // the MFMAs of O^T += V_{j-1}^T P_{j-1}^T and of S_{j+1}^T while it takes the exponentials of block j
-  // (whose maximum it has found just before): one basic block in which the two kinds of
-  // instruction alternate in source order, held there by scheduling fences.
-  //
-  // Copies: iteration j requests V_j (two LDS stages; read in iteration j + 1) and K_{j+3}
-  // (three stages; read in iteration j + 2), always the same number of copies, past the end too
-  // (rows are clamped, the data is never used), so that the waits can count.
-  constexpr int CPT = 2 * TileLoader<kHalf, BC, 4, false>::PER;  // copies per wavefront and tile
-  auto issue_k = [&](int j) {
-    char* st = smem + (j % KSTAGES) * TILEB;
-#pragma unroll
-    for (int half = 0; half < 2; ++half) loader.load(st + half * HALFB, Kb + half * kHalf, kstride, j * BC, nk - 1, w, lane);
+  TileCopier<BC, 4> copier;
+  copier.init(kstride, w, lane);
+  constexpr int CPT = TileCopier<BC, 4>::COPIES;  // copies per wavefront and tile
+  auto k_stage = [&](int j) { return smem + (j % KSTAGES) * TILEB; };
+  auto v_stage = [&](int j) { return smem + V_OFF + (j & 1) * TILEB; };
+  // (blocks past the end fetch the last one again, never read, so that the waits can count)
+  auto plan = [&](const __bf16* rows, int j) {
+    const int jc = j < ncol_all ? j : ncol_all - 1;
+    return copier.plan(rows + (long)jc * BC * kstride, nk - 1 - jc * BC);
   };
-  auto issue_v = [&](int j) {
-    char* st = smem + V_OFF + (j & 1) * TILEB;
+  static_for<3>([&](auto T) {
+    const auto tc = plan(Kb, T.value);
+    static_for<CPT>([&](auto Q) { copier.template copy<Q.value>(tc, k_stage(T.value)); });
+  });
 #pragma unroll
-    for (int half = 0; half < 2; ++half) loader.load(st + half * HALFB, Vb + half * kHalf, kstride, j * BC, nk - 1, w, lane);
-  };
-  issue_k(0);
-  issue_k(1);
-  issue_k(2);
-  // (iteration 0 multiplies a P of zeros with whatever the V stage of "block -1" holds: zeros)
-  for (int o = tid * 16; o < TILEB; o += 256 * 16) *(u32x4*)(smem + V_OFF + TILEB + o) = (u32x4){0, 0, 0, 0};
-#pragma unroll
-  for (int ks = 0; ks < KS; ++ks) touch(Qf[ks]);
+  for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+a"(Qf[ks]));  // (MFMAs take them from there)
 
   LaneAddr la;
   la.init(lane);
   const float c2 = p.scale_log2e;
   const int lim_row = CAUSAL ? (row + off < nk - 1 ? row + off : nk - 1) : nk - 1;
-  f32x16 Sc[2], Sn[2];   // scores of the current block (turned into P in place) and of the next
+  f32x16 S[2];           // scores of the current block
   bf16x8 Pp[2][2];       // P of the previous block, rounded: the operand of its O update
-#pragma unroll
-  for (int kt = 0; kt < 2; ++kt) Pp[kt][0] = Pp[kt][1] = (bf16x8){0};
-  auto k_operand = [&](int st, int i) {
-    const int ks = i >> 1;
-    return lds_b128(smem, ((la.zrow + st + (ks >> 3) * HALFB) ^ (32 * (ks & 7))) + (i & 1) * 32 * kRowB);
+  auto k_operand = [&](int st, int i) {  // all of tile 0 (keys 0 .. 31), then of tile 1
+    const int ks = i % KS;
+    return lds_b128(smem, ((la.zrow + st + (ks >> 3) * HALFB) ^ (32 * (ks & 7))) + (i / KS) * 32 * kRowB);
   };
   auto v_operand = [&](int vst, int i) {
     const int dt = i >> 2, ro = (16 * (i & 3)) * kRowB;
     const int vb = vst + (dt >> 2) * HALFB;
     return lds_tr_pair(smem, ((la.zcol[0] + vb) ^ (64 * (dt & 3))) + ro, ((la.zcol[1] + vb) ^ (64 * (dt & 3))) + ro);
   };
-
-  wait_vmem_upto<2 * CPT>();
-  lds_barrier();  // K_0 has landed
-  Sc[0] = Sc[1] = (f32x16){0};
-  mfma_stream<2 * KS, 4, 1>([&](int i) { return k_operand(0, i); },
-                            [&](int i, bf16x8 x) { Sc[i & 1] = mfma32<F16>(x, Qf[i >> 1], Sc[i & 1]); });
-  lds_barrier();  // K_0 has been read by everyone (and the zeros above are in place)
-
-  for (int j = 0; j < ncol; ++j) {
-    issue_v(j);
-    issue_k(j + 3);  // in flight, oldest first: .. K_{j+1}, V_{j-1} | K_{j+2}, V_j, K_{j+3}
-    // ---- the maximum of block j and the reference it is measured against (line 9)
+  auto mask = [&](int j) {  // entries above the diagonal and columns past the end
     const int col0 = j * BC;
     if ((CAUSAL && col0 + BC - 1 > prow0 + off) || col0 + BC > nk) {
       const int lim = lim_row - col0 - 4 * hh;
 #pragma unroll
       for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) Sc[kt][r] = 32 * kt + acc_row(r, 0) > lim ? -INFINITY : Sc[kt][r];
+        for (int r = 0; r < 16; ++r) S[kt][r] = 32 * kt + acc_row(r, 0) > lim ? -INFINITY : S[kt][r];
     }
-    float mx = max3f(Sc[0][0], Sc[0][1], Sc[1][0]);
+  };
+  auto row_maximum = [&]() {
+    float mx = max3f(S[0][0], S[0][1], S[1][0]);
 #pragma unroll
-    for (int r = 2; r < 16; r += 2) mx = max3f(mx, Sc[0][r], Sc[0][r + 1]);
-    mx = max3f(mx, Sc[1][1], Sc[1][2]);
-    mx = fmaxf(mx, Sc[1][3]);
+    for (int r = 2; r < 16; r += 2) mx = max3f(mx, S[0][r], S[0][r + 1]);
+    mx = max3f(mx, S[1][1], S[1][2]);
+    mx = fmaxf(mx, S[1][3]);
 #pragma unroll
-    for (int r = 4; r < 16; r += 2) mx = max3f(mx, Sc[1][r], Sc[1][r + 1]);
-    mx = max_with_partner32(mx);
-    const float m_new = fmaxf(m, mx);
-    // (lazy: the reference only moves when some row outgrew it by 2^kLazyLog2; O then is rescaled
-    // AFTER this iteration's MFMAs, which still add a block measured against the old reference)
-    const bool moved = __builtin_amdgcn_ballot_w64((m_new - m) * c2 > (float)kLazyLog2) != 0;
-    float alpha = 1.f;
-    if (moved) {
-      alpha = fast_exp2((m - m_new) * c2);
+    for (int r = 4; r < 16; r += 2) mx = max3f(mx, S[1][r], S[1][r + 1]);
+    return max_with_partner32(mx);
+  };
+
+  // S_0
+  wait_vmem_upto<2 * CPT>();
+  lds_barrier();  // K_0 has landed
+  {
+    const int kst = 0;
+    OperandRing ring;
+    ring.begin([&](auto I) { return k_operand(kst, I.value); });
+    static_for<2 * KS>([&](auto I) {
+      constexpr int i = I.value;
+      ring.template advance<i, 2 * KS>([&](auto J) { return k_operand(kst, J.value); });
+      mfma32_vgpr_ab<F16, i % KS == 0>(S[i / KS], ring.at(I), Qf[i % KS]);
+      __builtin_amdgcn_sched_barrier(0);
+    });
+  }
+  settled(S[0], S[1]);
+  mask(0);
+  m = row_maximum();
+
+  // One wavefront per SIMD has to overlap its own matrix and vector work. Iteration j:
+  //   O^T += V_{j-1}^T P_{j-1}^T (line 10)     with the exponentials of block j between the MFMAs (line 9)
+  //   S_{j+1}^T = K_{j+1} Q_i^T (line 8)       with the tile copies between them
+  // in source order, held there by scheduling fences. The exponentials are taken against the reference m as it stands
+  // and checked afterwards, as in fwd_kernel (fa_fwd.hip): the row maximum is found only if they outgrew it.
+  // One barrier per iteration: it says that K_{j+1} and V_{j-1} have landed everywhere and that everyone has read
+  // K_j and V_{j-2}, whose stages this iteration's copies (K_{j+3}, V_j) take.
+  auto iteration = [&](int j, auto PV, auto NEXT) {
+    constexpr bool pv = decltype(PV)::value, next = decltype(NEXT)::value;
+    wait_vmem_upto<CPT>();  // everything but K_{j+2}
+    lds_barrier();
+    const int vst = V_OFF + ((j + 1) & 1) * TILEB, kst = ((j + 1) % KSTAGES) * TILEB;
+    constexpr int NPV = 4 * DT, NS = 2 * KS;
+    bf16x8 Pn[2][2];
+    float rs0 = 0.f, rs1 = 0.f;
+    const float mc = m * c2;
+    OperandRing ring;
+    if constexpr (pv) ring.begin([&](auto I) { return v_operand(vst, I.value); });
+    else if constexpr (next) ring.begin([&](auto I) { return k_operand(kst, I.value); });
+    if constexpr (pv) agpr_ready(O);
+    u32x4 pw;
+    float e0 = 0.f, e1 = 0.f;
+    // (a slot consumes the exponential of the slot before it: the result of v_exp_f32 is not ready for the next instruction)
+    auto consume = [&](auto E) {
+      constexpr int e = decltype(E)::value, kt = e / 16, r = e % 16;
+      if constexpr (r & 1) {
+        rs1 += e1;
+        pw[(r >> 1) & 3] = pack2<F16>(e0, e1);
+        if constexpr ((r & 7) == 7) Pn[kt][r >> 3] = __builtin_bit_cast(bf16x8, pw);
+      } else {
+        rs0 += e0;
+      }
+    };
+    static_for<NPV>([&](auto I) {
+      constexpr int i = I.value;
+      if constexpr (pv) {
+        if constexpr (next) ring.template advance<i, NPV + NS>([&](auto J) { if constexpr (J.value < NPV) return v_operand(vst, J.value); else return k_operand(kst, J.value - NPV); });
+        else ring.template advance<i, NPV>([&](auto J) { return v_operand(vst, J.value); });
+        mfma32_agpr<F16>(O[i >> 2], ring.at(I), Pp[(i >> 1) & 1][i & 1]);
+      }
+      {
+        constexpr int kt = i / 16, r = i % 16;
+        float x = __builtin_fmaf(S[kt][r], c2, -mc);
+        asm volatile("" : "+v"(x));  // (ties the exponential to this place)
+        if constexpr (i > 0) consume(std::integral_constant<int, i - 1>{});
+        float& ex = (r & 1) ? e1 : e0;
+        ex = fast_exp2(x);
+        asm volatile("" : "+v"(ex));
+      }
+      if constexpr (pv) __builtin_amdgcn_sched_barrier(0);  // keep this order: the two kinds of work alternate
+    });
+    consume(std::integral_constant<int, NPV - 1>{});
+    asm volatile("" ::: "memory");  // (the operands requested for the next stream are not to be requested later)
+    if (__builtin_amdgcn_ballot_w64(rs0 + rs1 > (float)(1 << (F16 ? kLazyLog2Half : kLazyLog2Bf16))) != 0) {
+      const float m_new = fmaxf(m, row_maximum());
+      const float alpha = fast_exp2((m - m_new) * c2);
       l *= alpha;
       m = m_new;
-    }
-    const float mc = m * c2;
-    wait_vmem_upto<3 * CPT>();
-    lds_barrier();  // K_{j+1} and V_{j-1} have landed
-    // ---- one basic block: 64 MFMAs (O^T += V_{j-1}^T P_{j-1}^T, line 10; S_{j+1}^T = K_{j+1} Q_i^T, line 8)
-    //      with the exponentials of block j between them
-    {
-      const int vst = V_OFF + ((j + 1) & 1) * TILEB, kst = ((j + 1) % KSTAGES) * TILEB;
-      constexpr int NPV = 4 * DT, NS = 2 * KS, AH = 3;
-      bf16x8 ring[AH];
-      auto operand = [&](int i) { return i < NPV ? v_operand(vst, i) : k_operand(kst, i - NPV); };
+      if constexpr (pv) {
+        agpr_settled(O);
 #pragma unroll
-      for (int i = 0; i < AH; ++i) ring[i] = operand(i);
-      __builtin_amdgcn_sched_barrier(0);
-      Sn[0] = Sn[1] = (f32x16){0};
-      float rs0 = 0.f, rs1 = 0.f;
+        for (int dt = 0; dt < DT; ++dt) {
 #pragma unroll
-      for (int i = 0; i < NPV + NS; ++i) {
-        const bf16x8 cur = ring[i % AH];
-        if (i + AH < NPV + NS) ring[i % AH] = operand(i + AH);
-        if (i < NPV) {
-          O[i >> 2] = mfma32<F16>(cur, Pp[(i >> 1) & 1][i & 1], O[i >> 2]);
-        } else {
-          const int k = i - NPV;
-          Sn[k & 1] = mfma32<F16>(cur, Qf[k >> 1], Sn[k & 1]);
+          for (int r = 0; r < 16; ++r) O[dt][r] *= alpha;
+          asm volatile("" : "+a"(O[dt]));
         }
-        {  // one exponential of block j behind every second MFMA
-          const int e = i / 2, kt = e / 16, r = e % 16;
-          if (i & 1) {
-            // (the two empty statements tie the exponential to this place: instruction selection
-            // would otherwise sink all of them behind the last MFMA, next to their uses)
-            float x = Sc[kt][r];
-            asm volatile("" : "+v"(x));
-            float ex = fast_exp2(__builtin_fmaf(x, c2, -mc));
-            asm volatile("" : "+v"(ex));
-            Sc[kt][r] = ex;
-            if (r & 1) rs1 += ex;
-            else rs0 += ex;
-          }
-        }
-        __builtin_amdgcn_sched_barrier(0);  // keep this order: the two kinds of work alternate
       }
-      l += rs0 + rs1;
+      rs0 = rs1 = 0.f;
+#pragma unroll
+      for (int kt = 0; kt < 2; ++kt) {
+        f32x16 E;
+#pragma unroll
+        for (int r = 0; r < 16; r += 2) {
+          E[r] = fast_exp2(__builtin_fmaf(S[kt][r], c2, -m * c2));
+          E[r + 1] = fast_exp2(__builtin_fmaf(S[kt][r + 1], c2, -m * c2));
+          rs0 += E[r];
+          rs1 += E[r + 1];
+        }
+        Pn[kt][0] = pack8<F16>(E, 0);
+        Pn[kt][1] = pack8<F16>(E, 1);
+      }
     }
-    if (moved) {
-#pragma unroll
-      for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) O[dt][r] *= alpha;
+    l += rs0 + rs1;
+    if constexpr (next) {
+      char* vdst = v_stage(j);
+      char* kdst = k_stage(j + 3);
+      const auto vc = plan(Vb, j), kc = plan(Kb, j + 3);
+      static_for<NS>([&](auto I) {
+        constexpr int i = I.value;
+        if constexpr (pv) ring.template advance<NPV + i, NPV + NS>([&](auto J) { return k_operand(kst, J.value - NPV); });
+        else ring.template advance<i, NS>([&](auto J) { return k_operand(kst, J.value); });
+        mfma32_vgpr_ab<F16, i % KS == 0>(S[i / KS], ring.at(std::integral_constant<int, pv ? NPV + i : i>{}), Qf[i % KS]);
+        if constexpr (i % 2 == 0) {
+          constexpr int q = i / 2;
+          if constexpr (q < CPT) copier.template copy<q>(vc, vdst);
+          else copier.template copy<q - CPT>(kc, kdst);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      });
+      settled(S[0], S[1]);
+      mask(j + 1);
+    } else {
+      const auto vc = plan(Vb, j);
+      static_for<CPT>([&](auto Q) { copier.template copy<Q.value>(vc, v_stage(j)); });
     }
 #pragma unroll
     for (int kt = 0; kt < 2; ++kt) {
-      Pp[kt][0] = pack8<F16>(Sc[kt], 0);
-      Pp[kt][1] = pack8<F16>(Sc[kt], 1);
-      Sc[kt] = Sn[kt];
+      Pp[kt][0] = Pn[kt][0];
+      Pp[kt][1] = Pn[kt][1];
     }
-    lds_barrier();  // K_{j+1} and V_{j-1} have been read by everyone: their stages may be overwritten
+  };
+  constexpr std::true_type yes{};
+  constexpr std::false_type no{};
+  if (ncol > 1) {
+    iteration(0, no, yes);
+    for (int j = 1; j < ncol - 1; ++j) iteration(j, yes, yes);
+    iteration(ncol - 1, yes, no);
+  } else {
+    iteration(0, no, no);
   }
 
   // ---- the last block's O update
@@ -239,9 +358,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   lds_barrier();
   {
     const int vst = V_OFF + ((ncol - 1) & 1) * TILEB;
-    mfma_stream<4 * DT, 3, 2>([&](int i) { return v_operand(vst, i); },
-                              [&](int i, bf16x8 x) { O[i >> 2] = mfma32<F16>(x, Pp[(i >> 1) & 1][i & 1], O[i >> 2]); });
+    OperandRing ring;
+    ring.begin([&](auto I) { return v_operand(vst, I.value); });
+    agpr_ready(O);
+    static_for<4 * DT>([&](auto I) {
+      constexpr int i = I.value;
+      ring.template advance<i, 4 * DT>([&](auto J) { return v_operand(vst, J.value); });
+      mfma32_agpr<F16>(O[i >> 2], ring.at(I), Pp[(i >> 1) & 1][i & 1]);
+      __builtin_amdgcn_sched_barrier(0);
+    });
   }
+  agpr_settled(O);
   lds_barrier();
 
   // ---- epilogue (lines 12-15): whole rows through LDS, see store_rows_via_lds
@@ -277,11 +404,12 @@ hipError_t launch_fwd256(const FwdArgs& a, int causal, hipStream_t st) {
 // dQ (Algorithm 2, lines 10-15 for one row block): the forward kernel's skeleton. Wavefront w owns
 // rows 32 w .. of a 128-row block with Q_i, dO_i, L_i, D_i in registers; per key block S^T and
 // dP^T = V_j dO_i^T, then P and dS, then dQ_i^T += K_j^T dS^T with K_j^T from transposing reads.
-template <bool CAUSAL, bool F16, bool RAGGED>
+template <bool CAUSAL, bool F16, bool OWN_D, bool RAGGED>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void dq256_kernel(BwdArgs a) {
   constexpr int D = 256, BR = 128, BC = 64, KS = D / 16, DT = D / 32;
-  constexpr int HALFB = BC * kRowB, STAGEB = 4 * HALFB;
-  __shared__ __attribute__((aligned(1024))) char smem[2 * STAGEB];
+  constexpr int HALFB = BC * kRowB, TILEB = 2 * HALFB;  // one K_j or V_j: left | right
+  constexpr int KSTAGES = 3, V_OFF = KSTAGES * TILEB;     // K_j: three stages, V_j: two (160 KiB in all)
+  __shared__ __attribute__((aligned(1024))) char smem[V_OFF + 2 * TILEB];
 
   const Problem& p = a.p;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -313,7 +441,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   }
   const long stat = s * p.lse_seq_stride + (long)h * p.lse_head_stride + (p.cu_seqlens ? si.tok0 : 0) + rowc;
   const float Lq = row < n ? a.LSE[stat] * kLog2e : INFINITY;  // rows past the end: P = 0
-  const float Dq = a.Dvec[stat];
   f32x16 dQt[DT];
 #pragma unroll
   for (int dt = 0; dt < DT; ++dt) dQt[dt] = (f32x16){0};
@@ -327,104 +454,154 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   }
   if (ncol < 1) ncol = 1;
 
-  TileLoader<kHalf, BC, 4, false> loader;
-  loader.init(kstride, w, lane, kHalf / 8);
-  constexpr int CPB = 4 * TileLoader<kHalf, BC, 4, false>::PER;
-  auto issue_block = [&](int j) {
-    char* st = smem + (j & 1) * STAGEB;
-#pragma unroll
-    for (int half = 0; half < 2; ++half) {
-      loader.load(st + half * HALFB, Kb + half * kHalf, kstride, j * BC, nk - 1, w, lane);
-      loader.load(st + (2 + half) * HALFB, Vb + half * kHalf, kstride, j * BC, nk - 1, w, lane);
-    }
+  TileCopier<BC, 4> copier;
+  copier.init(kstride, w, lane);
+  constexpr int CPT = TileCopier<BC, 4>::COPIES;  // copies per wavefront and tile
+  auto k_stage = [&](int j) { return smem + (j % KSTAGES) * TILEB; };
+  auto v_stage = [&](int j) { return smem + V_OFF + (j & 1) * TILEB; };
+  // (blocks past the end fetch the last one again)
+  auto plan = [&](const __bf16* rows, int j) {
+    const int jc = j < ncol_all ? j : ncol_all - 1;
+    return copier.plan(rows + (long)jc * BC * kstride, nk - 1 - jc * BC);
   };
-  issue_block(0);
-#pragma unroll
-  for (int ks = 0; ks < KS; ++ks) {
-    touch(Qf[ks]);
-    touch(dOf[ks]);
+  {
+    const auto k0 = plan(Kb, 0), v0 = plan(Vb, 0), k1 = plan(Kb, 1);
+    static_for<CPT>([&](auto Q) { copier.template copy<Q.value>(k0, k_stage(0)); });
+    static_for<CPT>([&](auto Q) { copier.template copy<Q.value>(v0, v_stage(0)); });
+    static_for<CPT>([&](auto Q) { copier.template copy<Q.value>(k1, k_stage(1)); });
   }
+  float Dq;
+  if constexpr (OWN_D) {  // D_i = rowsum(dO_i o O_i) (line 4), see bwd_dq_kernel in fa_bwd.hip
+    const __bf16* op = a.O + ((si.tok0 + rowc) * p.Hq + h) * D + 8 * hh;
+    float part = 0.f;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      const bf16x8 o = *(const bf16x8*)(op + 16 * ks);
+#pragma unroll
+      for (int t = 0; t < 8; ++t) part += widen<F16>(o, t) * widen<F16>(dOf[ks], t);
+    }
+    Dq = sum_with_partner32(part);
+    if (row < n && hh == 0) a.Dvec[stat] = Dq;
+  } else {
+    Dq = a.Dvec[stat];
+  }
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+a"(Qf[ks]), "+a"(dOf[ks]));  // (MFMAs take them from there)
   touch(Lq);
   touch(Dq);
 
   LaneAddr la;
   la.init(lane);
   const float c2 = p.scale_log2e;
-  const int wrow_last = prow0 + 31 + off;
   const int lim_row = CAUSAL ? (row + off < nk - 1 ? row + off : nk - 1) : nk - 1;
-  f32x16 S[2], dP[2];
+  f32x16 S[2], Sn[2], dP[2];
   bf16x8 dSf[2][2];
-
-  for (int j = 0; j < ncol; ++j) {
-    if (j + 1 < ncol) {
-      issue_block(j + 1);
-      wait_vmem_upto<CPB>();
-    } else {
-      wait_vmem();
-    }
-    lds_barrier();
-    if (!CAUSAL || j * BC <= wrow_last) {
-      const int st = (j & 1) * STAGEB;
-      // ---- S^T = K_j Q_i^T (line 10)
-      S[0] = S[1] = dP[0] = dP[1] = (f32x16){0};
-      mfma_stream<2 * KS, 4, 1>(
-          [&](int i) {
-            const int ks = i >> 1;
-            return lds_b128(smem, ((la.zrow + st + (ks >> 3) * HALFB) ^ (32 * (ks & 7))) + (i & 1) * 32 * kRowB);
-          },
-          [&](int i, bf16x8 x) { S[i & 1] = mfma32<F16>(x, Qf[i >> 1], S[i & 1]); });
-      // ---- dP^T = V_j dO_i^T (line 13) with P = exp(S - L) (line 11) between its MFMAs (one
-      //      instruction stream per SIMD has to overlap its own matrix and vector work)
-      {
-        constexpr int AH = 4;
-        bf16x8 ring[AH];
-        auto operand = [&](int i) {
-          const int ks = i >> 1;
-          return lds_b128(smem, ((la.zrow + st + 2 * HALFB + (ks >> 3) * HALFB) ^ (32 * (ks & 7))) + (i & 1) * 32 * kRowB);
-        };
-#pragma unroll
-        for (int i = 0; i < AH; ++i) ring[i] = operand(i);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int i = 0; i < 2 * KS; ++i) {
-          const bf16x8 cur = ring[i % AH];
-          if (i + AH < 2 * KS) ring[i % AH] = operand(i + AH);
-          dP[i & 1] = mfma32<F16>(cur, dOf[i >> 1], dP[i & 1]);
-          float x = S[i >> 4][i & 15];  // (tied in place, see the forward kernel)
-          asm volatile("" : "+v"(x));
-          float ex = fast_exp2(__builtin_fmaf(x, c2, -Lq));
-          asm volatile("" : "+v"(ex));
-          S[i >> 4][i & 15] = ex;
-          __builtin_amdgcn_sched_barrier(0);
-        }
-      }
-      // ---- dS = P o (dP - D) (line 14)
-      const int col0 = j * BC;
-      const bool need_mask = (CAUSAL && col0 + BC - 1 > prow0 + off) || (col0 + BC > nk);
-#pragma unroll
-      for (int kt = 0; kt < 2; ++kt) {
-        if (need_mask) {
-#pragma unroll
-          for (int r = 0; r < 16; ++r)
-            if (col0 + 32 * kt + acc_row(r, hh) > lim_row) S[kt][r] = 0.f;
-        }
-#pragma unroll
-        for (int r = 0; r < 16; ++r) dP[kt][r] = S[kt][r] * (dP[kt][r] - Dq);
-        dSf[kt][0] = pack8<F16>(dP[kt], 0);
-        dSf[kt][1] = pack8<F16>(dP[kt], 1);
-      }
-      // ---- dQ_i^T += K_j^T dS^T (line 15)
-      mfma_stream<4 * DT, 3, 2>(
-          [&](int i) {
-            const int dt = i >> 2, ro = (16 * (i & 3)) * kRowB;
-            const int kb = st + (dt >> 2) * HALFB;
-            return lds_tr_pair(smem, ((la.zcol[0] + kb) ^ (64 * (dt & 3))) + ro, ((la.zcol[1] + kb) ^ (64 * (dt & 3))) + ro);
-          },
-          [&](int i, bf16x8 x) { dQt[i >> 2] = mfma32<F16>(x, dSf[(i >> 1) & 1][i & 1], dQt[i >> 2]); });
-    }
-    lds_barrier();
+  auto row_operand = [&](int st, int i) {  // of K_j or V_j: all of tile 0 (keys 0 .. 31), then of tile 1
+    const int ks = i % KS;
+    return lds_b128(smem, ((la.zrow + st + (ks >> 3) * HALFB) ^ (32 * (ks & 7))) + (i / KS) * 32 * kRowB);
+  };
+  auto col_operand = [&](int st, int i) {  // of K_j^T
+    const int dt = i >> 2, ro = (16 * (i & 3)) * kRowB, kb = st + (dt >> 2) * HALFB;
+    return lds_tr_pair(smem, ((la.zcol[0] + kb) ^ (64 * (dt & 3))) + ro, ((la.zcol[1] + kb) ^ (64 * (dt & 3))) + ro);
+  };
+  // S_0
+  wait_vmem();
+  lds_barrier();
+  {
+    OperandRing ring;
+    ring.begin([&](auto I) { return row_operand(0, I.value); });
+    static_for<2 * KS>([&](auto I) {
+      constexpr int i = I.value;
+      ring.template advance<i, 2 * KS>([&](auto J) { return row_operand(0, J.value); });
+      mfma32_vgpr_ab<F16, i % KS == 0>(S[i / KS], ring.at(I), Qf[i % KS]);
+      __builtin_amdgcn_sched_barrier(0);
+    });
   }
+  settled(S[0], S[1]);
 
+  // One wavefront per SIMD has to overlap its own matrix and vector work. Iteration j:
+  //   dP_j^T = V_j dO_i^T (line 13)           with P_j = exp(S_j - L) (line 11) and the tile copies between the MFMAs
+  //   S_{j+1}^T = K_{j+1} Q_i^T (line 10)     with dS_j = P_j o (dP_j - D) (line 14)
+  //   dQ_i^T += K_j^T dS_j^T (line 15)        with the registers of S_{j+1} taking the place of S_j's
+  // in source order, held there by scheduling fences. One barrier per iteration: V_j and K_{j+1} have landed everywhere, and
+  // everyone has read V_{j-1} and K_{j-1}, whose stages this iteration's copies (V_{j+1}, K_{j+2}) take.
+  auto iteration = [&](int j, auto NEXT) {
+    constexpr bool next = decltype(NEXT)::value;
+    if (j > 0) {
+      wait_vmem();
+      lds_barrier();
+    }
+    const int kst = (j % KSTAGES) * TILEB, knst = ((j + 1) % KSTAGES) * TILEB, vst = V_OFF + (j & 1) * TILEB;
+    constexpr int NA = 2 * KS, NB = next ? 2 * KS : 0, NC = 4 * DT, N = NA + NB + NC;
+    auto operand = [&](auto J) {
+      constexpr int i = decltype(J)::value;
+      if constexpr (i < NA) return row_operand(vst, i);
+      else if constexpr (i < NA + NB) return row_operand(knst, i - NA);
+      else return col_operand(kst, i - NA - NB);
+    };
+    const auto vc = plan(Vb, j + 1), kc = plan(Kb, j + 2);
+    char *vdst = v_stage(j + 1), *kdst = k_stage(j + 2);
+    OperandRing ring;
+    ring.begin(operand);
+    static_for<NA>([&](auto I) {
+      constexpr int i = I.value;
+      ring.template advance<i, N>(operand);
+      mfma32_vgpr_ab<F16, i % KS == 0>(dP[i / KS], ring.at(I), dOf[i % KS]);
+      float x = __builtin_fmaf(S[i >> 4][i & 15], c2, -Lq);
+      asm volatile("" : "+v"(x));  // (the empty statements tie the exponential to this place)
+      float ex = fast_exp2(x);
+      asm volatile("" : "+v"(ex));
+      S[i >> 4][i & 15] = ex;
+      if constexpr (next && i % 2 == 1) {
+        constexpr int q = i / 2;
+        if constexpr (q < CPT) copier.template copy<q>(vc, vdst);
+        else copier.template copy<q - CPT>(kc, kdst);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    });
+    const int col0 = j * BC;
+    asm volatile("" ::: "memory");  // (the operands requested for the next stream are not to be requested later)
+    if ((CAUSAL && col0 + BC - 1 > prow0 + off) || (col0 + BC > nk)) {
+      asm volatile("; keep this a branch" ::);
+#pragma unroll
+      for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          if (col0 + 32 * kt + acc_row(r, hh) > lim_row) S[kt][r] = 0.f;
+    }
+    if constexpr (!next) settled(dP[0], dP[1]);
+    u32x4 pw;
+    static_for<2 * KS>([&](auto I) {
+      constexpr int i = I.value, kt = i >> 4, r = i & 15;
+      if constexpr (next) {
+        ring.template advance<NA + i, N>(operand);
+        mfma32_vgpr_ab<F16, i % KS == 0>(Sn[i / KS], ring.at(std::integral_constant<int, NA + i>{}), Qf[i % KS]);
+      }
+      float ds = S[kt][r] * (dP[kt][r] - Dq);
+      asm volatile("" : "+v"(ds));
+      dP[kt][r] = ds;
+      if constexpr (r & 1) pw[(r >> 1) & 3] = pack2<F16>(dP[kt][r - 1], ds);
+      if constexpr ((r & 7) == 7) dSf[kt][r >> 3] = __builtin_bit_cast(bf16x8, pw);
+      if constexpr (next) __builtin_amdgcn_sched_barrier(0);
+    });
+    agpr_ready(dQt);
+    static_for<NC>([&](auto I) {
+      constexpr int i = I.value;
+      ring.template advance<NA + NB + i, N>(operand);
+      mfma32_agpr<F16>(dQt[i >> 2], ring.at(std::integral_constant<int, NA + NB + i>{}), dSf[(i >> 1) & 1][i & 1]);
+      if constexpr (next) asm volatile("v_mov_b32 %0, %1" : "=v"(S[i >> 4][i & 15]) : "v"(Sn[i >> 4][i & 15]));
+      __builtin_amdgcn_sched_barrier(0);
+    });
+  };
+  if (ncol > 1) {
+    for (int j = 0; j < ncol - 1; ++j) iteration(j, std::true_type{});
+    agpr_settled(dQt);  // (where the two paths meet the compiler may move the accumulators)
+  }
+  iteration(ncol - 1, std::false_type{});
+
+  wait_vmem();
+  agpr_settled(dQt);
+  lds_barrier();
   char* stg = smem + w * (32 * kRowB);
   __bf16* op = a.dQ + ((si.tok0 + prow0) * p.Hq + h) * D;
 #pragma unroll
@@ -442,7 +619,8 @@ template <bool CAUSAL, bool F16, bool RAGGED>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void dkdv256_kernel(BwdArgs a) {
   constexpr int D = 256, BC = 128, BR = 32, KS = D / 16, DT = D / 32;
   constexpr int HALFB = BR * kRowB, STAGEB = 4 * HALFB;  // Q left | Q right | dO left | dO right
-  constexpr int LS_OFF = 2 * STAGEB, DV_OFF = LS_OFF + 2 * BR * 4, SMEM = DV_OFF + 2 * BR * 4;
+  constexpr int RING = 3;  // tiles in LDS
+  constexpr int LS_OFF = RING * STAGEB, DV_OFF = LS_OFF + RING * BR * 4, SMEM = DV_OFF + RING * BR * 4;
   __shared__ __attribute__((aligned(1024))) char smem[SMEM < 4 * 32 * kRowB ? 4 * 32 * kRowB : SMEM];
 
   const Problem& p = a.p;
@@ -483,128 +661,195 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   // tile t = (head g G + t / per_head, row tile i_first + t % per_head)
   float lraw = 0.f, draw = 0.f;
   bool stat_ok = false;
-  // (tiles are requested in order: the head and row tile of the next request are carried along, and
-  // the per-lane offsets of an interior tile are computed once, so that a request costs a scalar base
-  // address and the copy instructions; only the last row tile of a sequence clamps its rows)
-  TileLoader<kHalf, BR, 4, false> qloader;
-  qloader.init(qstride, w, lane, kHalf / 8);
-  int next_hq = g * p.G, next_it = i_first;
-  auto issue_tile = [&](int t) {
+  // (tiles are requested in order: the head and row tile of the next request are carried along; past the last tile it is
+  // requested again, never read)
+  TileCopier<BR, 4> copier;
+  copier.init(qstride, w, lane);
+  constexpr int CPT = TileCopier<BR, 4>::COPIES;  // copies per wavefront of Q_i, as many of dO_i
+  int next_hq = g * p.G, next_it = i_first, next_t = 0;
+  struct Request {
+    typename TileCopier<BR, 4>::Plan q, o;
+    char* dst;
+  };
+  auto request = [&]() {  // the next tile's copies (to be issued) and its statistics (on their way)
     const int hq = next_hq, it = next_it;
-    if (++next_it == nrt) {
+    Request r;
+    r.dst = smem + (next_t % RING) * STAGEB;
+    if (next_t < T - 1 && ++next_it == nrt) {
       next_it = i_first;
       ++next_hq;
     }
-    char* st = smem + (t & 1) * STAGEB;
-    const long head0 = (si.tok0 * p.Hq + hq) * D;  // row 0 of this head
-#pragma unroll
-    for (int half = 0; half < 2; ++half) {
-      qloader.load(st + half * HALFB, a.Q + head0 + half * kHalf, qstride, it * BR, n - 1, w, lane);
-      qloader.load(st + (2 + half) * HALFB, a.dO + head0 + half * kHalf, qstride, it * BR, n - 1, w, lane);
-    }
+    ++next_t;
+    const long first = ((si.tok0 + (long)it * BR) * p.Hq + hq) * D;
+    r.q = copier.plan(a.Q + first, n - 1 - it * BR);
+    r.o = copier.plan(a.dO + first, n - 1 - it * BR);
     if (tid < BR) {
-      const int r = it * BR + tid;
-      stat_ok = r < n;
-      const long si_ = stat_base + (long)hq * p.lse_head_stride + (stat_ok ? r : n - 1);
+      const int row = it * BR + tid;
+      stat_ok = row < n;
+      const long si_ = stat_base + (long)hq * p.lse_head_stride + (stat_ok ? row : n - 1);
       lraw = a.LSE[si_];
       draw = a.Dvec[si_];
     }
+    return r;
   };
-  if (T > 0) issue_tile(0);
-#pragma unroll
-  for (int ks = 0; ks < KS; ++ks) {
-    touch(Kf[ks]);
-    touch(Vf[ks]);
-  }
-
-  LaneAddr la;
-  la.init(lane);
-  f32x16 S, dP;
-  bf16x8 Pf[2], dSf[2];
-
-  int cur_it = i_first;  // row tile of tile t
-  for (int t = 0; t < T; ++t) {
-    wait_vmem();  // tile t and its statistics have arrived
+  auto commit_stats = [&](int t) {
     touch(lraw);
     touch(draw);
     if (tid < BR) {
       // L in the exponent's base; rows past the end get L = +inf so that P = 0. D is stored
       // negated: it is the initial value of the dP accumulator (line 14).
-      *(float*)(smem + LS_OFF + ((t & 1) * BR + tid) * 4) = stat_ok ? lraw * kLog2e : INFINITY;
-      *(float*)(smem + DV_OFF + ((t & 1) * BR + tid) * 4) = stat_ok ? -draw : 0.f;
+      *(float*)(smem + LS_OFF + ((t % RING) * BR + tid) * 4) = stat_ok ? lraw * kLog2e : INFINITY;
+      *(float*)(smem + DV_OFF + ((t % RING) * BR + tid) * 4) = stat_ok ? -draw : 0.f;
     }
-    lds_barrier();
-    if (t + 1 < T) issue_tile(t + 1);  // into the other stage, which everyone left at the last barrier
-    const int st = (t & 1) * STAGEB;
-    const int r0 = cur_it * BR;  // first query row of the tile
-    if (++cur_it == nrt) cur_it = i_first;
-    // ---- S = Q_i K_j^T (line 10)
-    S = (f32x16){0};
-    mfma_stream<KS, 4, 1>(
-        [&](int i) { return lds_b128(smem, (la.zrow + st + (i >> 3) * HALFB) ^ (32 * (i & 7))); },
-        [&](int i, bf16x8 x) { S = mfma32<F16>(x, Kf[i], S); });
-    // ---- dP - D = dO_i V_j^T - D (lines 13, 14; -D is where the accumulator starts) with
-    //      P = exp(S - L) (line 11) between its MFMAs: one instruction stream per SIMD has to
-    //      overlap its own matrix and vector work (see the forward kernel)
-    f32x4 Lv[4];
+  };
+  LaneAddr la;
+  la.init(lane);
+  f32x16 S, dP;
+  f32x4 Lv[4];
+  bf16x8 Pf[2], dSf[2];
+  auto row_operand = [&](int st, int i) { return lds_b128(smem, (la.zrow + st + (i >> 3) * HALFB) ^ (32 * (i & 7))); };
+  auto col_operand = [&](int st, int i) {  // dt = i / 2, contraction half i % 2
+    const int dt = i >> 1, qoff = st + (dt >> 2) * HALFB + 16 * (i & 1) * kRowB;
+    return lds_tr_pair(smem, (la.zcol[0] + qoff) ^ (64 * (dt & 3)), (la.zcol[1] + qoff) ^ (64 * (dt & 3)));
+  };
+  auto load_stats = [&](int t) {  // dP starts from -D_i (line 14)
 #pragma unroll
     for (int r4 = 0; r4 < 4; ++r4) {
-      const f32x4 Dn = *(const f32x4*)(smem + DV_OFF + ((t & 1) * BR + 8 * r4 + 4 * hh) * 4);
-      Lv[r4] = *(const f32x4*)(smem + LS_OFF + ((t & 1) * BR + 8 * r4 + 4 * hh) * 4);
+      const f32x4 Dn = *(const f32x4*)(smem + DV_OFF + ((t % RING) * BR + 8 * r4 + 4 * hh) * 4);
+      Lv[r4] = *(const f32x4*)(smem + LS_OFF + ((t % RING) * BR + 8 * r4 + 4 * hh) * 4);
 #pragma unroll
       for (int u = 0; u < 4; ++u) dP[4 * r4 + u] = Dn[u];
     }
-    {
-      constexpr int AH = 4;
-      bf16x8 ring[AH];
-      auto operand = [&](int i) { return lds_b128(smem, (la.zrow + st + 2 * HALFB + (i >> 3) * HALFB) ^ (32 * (i & 7))); };
+  };
+  if (T > 0) {
 #pragma unroll
-      for (int i = 0; i < AH; ++i) ring[i] = operand(i);
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int i = 0; i < KS; ++i) {
-        const bf16x8 cur = ring[i % AH];
-        if (i + AH < KS) ring[i % AH] = operand(i + AH);
-        dP = mfma32<F16>(cur, Vf[i], dP);
-        float x = S[i];  // (tied in place, see the forward kernel)
-        asm volatile("" : "+v"(x));
-        float ex = fast_exp2(__builtin_fmaf(x, c2, -Lv[i >> 2][i & 3]));
-        asm volatile("" : "+v"(ex));
-        S[i] = ex;
-        __builtin_amdgcn_sched_barrier(0);
-      }
+    for (int t = 0; t < 2; ++t) {
+      const Request r = request();
+      static_for<CPT>([&](auto Q) { copier.template copy<Q.value>(r.q, r.dst); });
+      static_for<CPT>([&](auto Q) { copier.template copy<Q.value>(r.o, r.dst + 2 * HALFB); });
+      commit_stats(t);
     }
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      touch(Kf[ks]);
+      touch(Vf[ks]);
+    }
+    wait_vmem();
+    lds_barrier();
+    {
+      OperandRing ring;
+      ring.begin([&](auto I) { return row_operand(0, I.value); });
+      static_for<KS>([&](auto I) {
+        constexpr int i = I.value;
+        ring.template advance<i, KS>([&](auto J) { return row_operand(0, J.value); });
+        mfma32_vgpr<F16, i == 0>(S, ring.at(I), Kf[i]);
+        __builtin_amdgcn_sched_barrier(0);
+      });
+    }
+    load_stats(0);
+    settled(S);
+  }
+
+  // One wavefront per SIMD has to overlap its own matrix and vector work. Iteration t:
+  //   dP_t - D = dO_i V_j^T - D (line 13)   with P_t = exp(S_t - L) (line 11) between the MFMAs
+  //   dV_j^T += dO_i^T P_t (line 12)        with dS_t = P_t o (dP_t - D) (line 14)
+  //   S_{t+1} = Q_{i'} K_j^T (line 10)      with the copies of tile t + 2
+  //   dK_j^T += Q_i^T dS_t (line 16)        with the statistics of tile t + 1
+  // in source order, held there by scheduling fences. One barrier per iteration: tile t + 1 has landed everywhere, and
+  // everyone has read tile t - 1, whose place this iteration's copies take.
+  int cur_it = i_first;  // row tile of tile t
+  auto iteration = [&](int t, auto NEXT) {
+    constexpr bool next = decltype(NEXT)::value;
+    if (t > 0) {
+      wait_vmem();
+      commit_stats(t + 1);
+      lds_barrier();
+    }
+    const int st = (t % RING) * STAGEB, nst = ((t + 1) % RING) * STAGEB;
+    const int r0 = cur_it * BR;  // first query row of the tile
+    if (++cur_it == nrt) cur_it = i_first;
+    constexpr int NA = KS, NV = 2 * DT, NB = next ? KS : 0, NK = 2 * DT, N = NA + NV + NB + NK;
+    auto operand = [&](auto J) {
+      constexpr int i = decltype(J)::value;
+      if constexpr (i < NA) return row_operand(st + 2 * HALFB, i);
+      else if constexpr (i < NA + NV) return col_operand(st + 2 * HALFB, i - NA);
+      else if constexpr (i < NA + NV + NB) return row_operand(nst, i - NA - NV);
+      else return col_operand(st, i - NA - NV - NB);
+    };
+    OperandRing ring;
+    ring.begin(operand);
+    static_for<NA>([&](auto I) {
+      constexpr int i = I.value;
+      ring.template advance<i, N>(operand);
+      mfma32_vgpr<F16, false>(dP, ring.at(I), Vf[i]);
+      float x = __builtin_fmaf(S[i], c2, -Lv[i >> 2][i & 3]);
+      asm volatile("" : "+v"(x));  // (the empty statements tie the exponential to this place)
+      float ex = fast_exp2(x);
+      asm volatile("" : "+v"(ex));
+      S[i] = ex;
+      __builtin_amdgcn_sched_barrier(0);
+    });
+    asm volatile("" ::: "memory");  // (the operands requested for the next stream are not to be requested later)
     if ((CAUSAL && key0 + 31 > r0 + off) || j0 + BC > nk) {
+      asm volatile("; keep this a branch" ::);
       // visible: key < nk and (causal) key <= r0 + off + row of the tile, row = acc_row(r, hh)
       const int kc = key_ok ? (CAUSAL ? key - (r0 + off) - 4 * hh : -1) : 0x7fffffff;
 #pragma unroll
       for (int r = 0; r < 16; ++r) S[r] = kc <= acc_row(r, 0) ? S[r] : 0.f;
     }
-#pragma unroll
-    for (int r = 0; r < 16; ++r) dP[r] *= S[r];
-#pragma unroll
-    for (int s2 = 0; s2 < 2; ++s2) {
-      Pf[s2] = pack8<F16>(S, s2);
-      dSf[s2] = pack8<F16>(dP, s2);
-    }
-    // ---- dV_j^T += dO_i^T P (line 12), dK_j^T += Q_i^T dS (line 16)
-    mfma_stream<4 * DT, 3, 2>(
-        [&](int i) {
-          const int k = i >> 1, dt = k >> 1, s2 = k & 1;
-          const int qoff = st + ((i & 1) ? 2 : 0) * HALFB + (dt >> 2) * HALFB + 16 * s2 * kRowB;
-          return lds_tr_pair(smem, (la.zcol[0] + qoff) ^ (64 * (dt & 3)), (la.zcol[1] + qoff) ^ (64 * (dt & 3)));
-        },
-        [&](int i, bf16x8 x) {
-          const int k = i >> 1, dt = k >> 1, s2 = k & 1;
-          if (i & 1) dVt[dt] = mfma32<F16>(x, Pf[s2], dVt[dt]);
-          else dKt[dt] = mfma32<F16>(x, dSf[s2], dKt[dt]);
+    Pf[0] = pack8<F16>(S, 0);
+    Pf[1] = pack8<F16>(S, 1);
+    asm volatile("" : "+v"(Pf[0]), "+v"(Pf[1]));
+    agpr_ready(dVt);
+    u32x4 pw;
+    static_for<NV>([&](auto I) {
+      constexpr int i = I.value;
+      ring.template advance<NA + i, N>(operand);
+      mfma32_agpr<F16>(dVt[i >> 1], ring.at(std::integral_constant<int, NA + i>{}), Pf[i & 1]);
+      // (the first entries of dP after the MFMAs above have had time to finish)
+      if constexpr (i % 2 == 1) {
+        static_for<2>([&](auto U) {
+          constexpr int r = i - 1 + U.value;
+          float ds = dP[r] * S[r];
+          asm volatile("" : "+v"(ds));
+          dP[r] = ds;
+          if constexpr (r & 1) pw[(r >> 1) & 3] = pack2<F16>(dP[r - 1], ds);
+          if constexpr ((r & 7) == 7) dSf[r >> 3] = __builtin_bit_cast(bf16x8, pw);
         });
-    lds_barrier();  // the tile has been read by everyone
-  }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    });
+    if constexpr (next) {
+      const Request r = request();
+      static_for<NB>([&](auto I) {
+        constexpr int i = I.value;
+        ring.template advance<NA + NV + i, N>(operand);
+        mfma32_vgpr<F16, i == 0>(S, ring.at(std::integral_constant<int, NA + NV + i>{}), Kf[i]);
+        if constexpr (i % 2 == 0) {
+          constexpr int q = i / 2;
+          if constexpr (q < CPT) copier.template copy<q>(r.q, r.dst);
+          else copier.template copy<q - CPT>(r.o, r.dst + 2 * HALFB);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      });
+    }
+    agpr_ready(dKt);
+    static_for<NK>([&](auto I) {
+      constexpr int i = I.value;
+      ring.template advance<NA + NV + NB + i, N>(operand);
+      mfma32_agpr<F16>(dKt[i >> 1], ring.at(std::integral_constant<int, NA + NV + NB + i>{}), dSf[i & 1]);
+      if constexpr (next && i == NK - 4) load_stats(t + 1);
+      __builtin_amdgcn_sched_barrier(0);
+    });
+  };
+  for (int t = 0; t < T - 1; ++t) iteration(t, std::true_type{});
+  if (T > 0) iteration(T - 1, std::false_type{});
 
-  // ---- write dK_j, dV_j (line 18); dK carries the scaling
   wait_vmem();
+  agpr_settled(dKt);
+  agpr_settled(dVt);
   lds_barrier();
+  // ---- write dK_j, dV_j (line 18); dK carries the scaling
   char* stg = smem + w * (32 * kRowB);
   const long kvoff = ((si.tok0k + key0) * p.Hkv + g) * D;
 #pragma unroll
@@ -615,34 +860,37 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 }
 
 template <bool RAGGED>
-static hipError_t launch_bwd256_d(const BwdArgs& a, int causal, int stages, hipStream_t st) {
-  hipError_t e = hipSuccess;
-  if (stages & 2) {
-    dim3 grid(grid_size((a.p.Nk + 127) / 128, a.p.Hkv * a.p.nseq)), block(256);
-    if (a.p.f16) {
-      if (causal) hipLaunchKernelGGL((dkdv256_kernel<true, true, RAGGED>), grid, block, 0, st, a);
-      else hipLaunchKernelGGL((dkdv256_kernel<false, true, RAGGED>), grid, block, 0, st, a);
-    } else {
-      if (causal) hipLaunchKernelGGL((dkdv256_kernel<true, false, RAGGED>), grid, block, 0, st, a);
-      else hipLaunchKernelGGL((dkdv256_kernel<false, false, RAGGED>), grid, block, 0, st, a);
-    }
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+static hipError_t launch_dkdv256(const BwdArgs& a, int causal, hipStream_t st) {
+  dim3 grid(grid_size((a.p.Nk + 127) / 128, a.p.Hkv * a.p.nseq)), block(256);
+  if (a.p.f16) {
+    if (causal) hipLaunchKernelGGL((dkdv256_kernel<true, true, RAGGED>), grid, block, 0, st, a);
+    else hipLaunchKernelGGL((dkdv256_kernel<false, true, RAGGED>), grid, block, 0, st, a);
+  } else {
+    if (causal) hipLaunchKernelGGL((dkdv256_kernel<true, false, RAGGED>), grid, block, 0, st, a);
+    else hipLaunchKernelGGL((dkdv256_kernel<false, false, RAGGED>), grid, block, 0, st, a);
   }
-  if (stages & 4) {
-    dim3 grid(grid_size((a.p.N + 127) / 128, a.p.Hq * a.p.nseq)), block(256);
-    if (a.p.f16) {
-      if (causal) hipLaunchKernelGGL((dq256_kernel<true, true, RAGGED>), grid, block, 0, st, a);
-      else hipLaunchKernelGGL((dq256_kernel<false, true, RAGGED>), grid, block, 0, st, a);
-    } else {
-      if (causal) hipLaunchKernelGGL((dq256_kernel<true, false, RAGGED>), grid, block, 0, st, a);
-      else hipLaunchKernelGGL((dq256_kernel<false, false, RAGGED>), grid, block, 0, st, a);
-    }
-    e = hipGetLastError();
-  }
-  return e;
+  return hipGetLastError();
+}
+template <bool F16, bool OWN_D, bool RAGGED>
+static hipError_t launch_dq256(const BwdArgs& a, int causal, hipStream_t st) {
+  dim3 grid(grid_size((a.p.N + 127) / 128, a.p.Hq * a.p.nseq)), block(256);
+  if (causal) hipLaunchKernelGGL((dq256_kernel<true, F16, OWN_D, RAGGED>), grid, block, 0, st, a);
+  else hipLaunchKernelGGL((dq256_kernel<false, F16, OWN_D, RAGGED>), grid, block, 0, st, a);
+  return hipGetLastError();
+}
+template <bool RAGGED>
+static hipError_t launch_bwd256_whole(const BwdArgs& a, int causal, hipStream_t st) {
+  // (the dQ kernel sums D on the way, the dK/dV kernel reads it)
+  if (hipError_t e = a.p.f16 ? launch_dq256<true, true, RAGGED>(a, causal, st) : launch_dq256<false, true, RAGGED>(a, causal, st)) return e;
+  return launch_dkdv256<RAGGED>(a, causal, st);
 }
 hipError_t launch_bwd256(const BwdArgs& a, int causal, int stages, hipStream_t st) {
-  return a.p.cu_seqlens ? launch_bwd256_d<true>(a, causal, stages, st) : launch_bwd256_d<false>(a, causal, stages, st);
+  if (stages == 7) return a.p.cu_seqlens ? launch_bwd256_whole<true>(a, causal, st) : launch_bwd256_whole<false>(a, causal, st);
+  if (a.p.cu_seqlens || a.p.f16) return hipErrorInvalidValue;  // (one stage or two: fa_bwd_stages, dense batches in bfloat16)
+  if (stages & 2)
+    if (hipError_t e = launch_dkdv256<false>(a, causal, st)) return e;
+  if (stages & 4) return launch_dq256<false, false, false>(a, causal, st);
+  return hipSuccess;
 }
 
 }  // namespace fa

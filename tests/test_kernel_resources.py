@@ -177,3 +177,131 @@ def test_the_in_flight_check_sees_a_planted_copy():
     ]
     loads, bad = touched_in_flight(lines)
     assert len(loads) == 1 and len(bad) == 1 and "v20" in bad[0][1]
+
+
+# ---- MFMAs written as inline assembly (mfma32_agpr and its kin): the compiler does not know them for MFMAs, so its hazard
+# recogniser inserts no wait states around them. Two rules have to hold in its output, along every path:
+#  * an operand or accumulator of such an MFMA is not written by a vector instruction in the two wait states before it;
+#  * its accumulator is not touched by anything but another MFMA that accumulates into exactly the same registers for 12
+#    wait states (a product of 8 passes; the next MFMA cannot issue before those 8 passes are over).
+
+def whole_assembly(source):
+    """kernel -> all lines up to its end (kernel_assembly stops at the first s_endpgm)."""
+    cmd = [fa_build.hipcc(), *[f for f in fa_build.FLAGS if f not in ("-shared", "-fPIC")], "--cuda-device-only", "-S",
+           "-o", "-", os.path.join(fa_build.CSRC, source)]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-2000:]
+    kernels, body = {}, None
+    for line in r.stdout.splitlines():
+        m = re.match(r"^(_Z\w+):", line)
+        if m:
+            body = kernels.setdefault(m.group(1), [])
+        elif line.startswith(".Lfunc_end"):
+            body = None
+        elif body is not None:
+            body.append(line)
+    return kernels
+
+
+def registers(text, files="va"):
+    regs = set()
+    for m in re.finditer(r"\b([va])\[(\d+):(\d+)\]", text):
+        regs.update((m.group(1), r) for r in range(int(m.group(2)), int(m.group(3)) + 1))
+    for m in re.finditer(r"\b([va])(\d+)\b", text):
+        regs.add((m.group(1), int(m.group(2))))
+    return {r for r in regs if r[0] in files}
+
+
+def mfma_hazards(lines):
+    """(MFMAs in inline assembly, [(line, offending line)]) for one kernel's assembly."""
+    code = []  # (text, in inline assembly); labels kept
+    in_asm = False
+    for l in lines:
+        t = l.strip()
+        if t.startswith(";;#ASMSTART"):
+            in_asm = True
+        elif t.startswith(";;#ASMEND"):
+            in_asm = False
+        elif re.match(r"^\.LBB\w+:", t):
+            code.append((t.split(":")[0] + ":", False))
+        elif t and not t.startswith((";", ".")):
+            code.append((t.split(";")[0].strip(), in_asm))
+    labels = {t[:-1]: i for i, (t, _) in enumerate(code) if t.endswith(":")}
+
+    def successors(i):
+        t = code[i][0]
+        if t.startswith("s_endpgm"):
+            return []
+        m = re.match(r"s_(c?branch\w*)\s+(\.LBB\w+)", t)
+        if m:
+            return [labels[m.group(2)]] + ([i + 1] if m.group(1).startswith("cbranch") else [])
+        return [i + 1]
+
+    def states(t):  # wait states that an instruction stands for
+        m = re.match(r"s_nop (\d+)", t)
+        return 0 if t.endswith(":") else int(m.group(1)) + 1 if m else 1
+
+    mfmas, bad = 0, []
+    for i, (t, in_asm) in enumerate(code):
+        if t.startswith("v_mfma") and in_asm:
+            mfmas += 1
+            dst = registers(t.split(",")[0])
+            todo, seen = [(j, 0) for j in successors(i)], set()
+            while todo:
+                j, at = todo.pop()
+                if at >= 12 or j >= len(code) or (j, at) in seen:
+                    continue
+                seen.add((j, at))
+                u = code[j][0]
+                if u.startswith("v_mfma"):
+                    at = max(at, 8 * (1 + at // 8))  # the unit takes the next product when the 8 passes are over
+                    ops = [registers(x) for x in u.split(None, 1)[1].split(",")]
+                    if (ops[1] | ops[2]) & dst or (ops[0] & dst and ops[0] != dst) or (ops[3] & dst and ops[3] != dst):
+                        bad.append((t, u))
+                    if ops[0] == dst:
+                        continue  # (checked from there)
+                elif registers(u) & dst:
+                    bad.append((t, u))
+                todo.extend((k, at + states(u)) for k in successors(j))
+        elif t.startswith("v_") and not t.startswith("v_mfma"):
+            dst = registers(t.split(",")[0])
+            todo = [(j, 0) for j in successors(i)]
+            while todo:
+                j, at = todo.pop()
+                if at >= 2 or j >= len(code):
+                    continue
+                u, u_asm = code[j]
+                if u.startswith("v_mfma"):
+                    if u_asm and registers(u) & dst:
+                        bad.append((t, u))
+                    continue
+                todo.extend((k, at + states(u)) for k in successors(j))
+    return mfmas, bad
+
+
+def test_hand_placed_products_keep_their_wait_states():
+    seen = 0
+    for name, lines in whole_assembly("fa_d256.hip").items():
+        mfmas, bad = mfma_hazards(lines)
+        seen += mfmas > 0
+        assert not bad, (name, bad[:5])
+    assert seen >= 18  # forward, dK/dV and dQ kernels
+
+
+@pytest.mark.parametrize("between,caught", [
+    (["v_add_f32_e32 v1, v2, v3"], True), (["s_nop 15"], False), (["s_nop 9"], True),
+    (["v_mfma_f32_32x32x16_bf16 a[16:31], v[40:43], v[44:47], a[16:31]"], True),
+    (["v_mfma_f32_32x32x16_bf16 a[16:31], v[40:43], v[44:47], a[16:31]"] * 2, False),
+    (["s_cbranch_scc1 .LBB0_2", "s_nop 15", ".LBB0_2:"], True)])
+def test_the_wait_state_check_sees_a_planted_read(between, caught):
+    lines = [";;#ASMSTART", "v_mfma_f32_32x32x16_bf16 a[0:15], v[32:35], v[36:39], a[0:15]", ";;#ASMEND", *between,
+             "v_accvgpr_read_b32 v20, a9", "s_endpgm"]
+    mfmas, bad = mfma_hazards(lines)
+    assert mfmas == 1 and bool(bad) == caught
+
+
+def test_the_wait_state_check_sees_a_planted_write():
+    for gap, caught in (([], True), (["s_nop 0"], True), (["s_nop 1"], False)):
+        lines = ["v_mov_b32_e32 v33, v1", *gap, ";;#ASMSTART", "v_mfma_f32_32x32x16_bf16 a[0:15], v[32:35], v[36:39], a[0:15]",
+                 ";;#ASMEND", "s_endpgm"]
+        assert bool(mfma_hazards(lines)[1]) == caught

@@ -317,6 +317,11 @@ __device__ __forceinline__ void mfma32_vgpr(f32x16& c, bf16x8 a, bf16x8 b) {
 // (an MFMA of 8 passes needs 12 wait states before its result may be touched)
 __device__ __forceinline__ void settled(f32x16& a) { asm volatile("s_nop 15" : "+v"(a)); }
 __device__ __forceinline__ void settled(f32x16& a, f32x16& b) { asm volatile("s_nop 15" : "+v"(a), "+v"(b)); }
+template <int N>
+__device__ __forceinline__ void settled(f32x16 (&c)[N]) {
+  if constexpr (N == 2) asm volatile("s_nop 15" : "+v"(c[0]), "+v"(c[1]));
+  else asm volatile("s_nop 15" : "+v"(c[0]), "+v"(c[1]), "+v"(c[2]), "+v"(c[3]));
+}
 // (as operands of ONE statement: a copy of an accumulator that the compiler makes then stands on the right side of the wait)
 __device__ __forceinline__ void agpr_settled(f32x16 (&c)[8]) {
   asm volatile("s_nop 15" : "+a"(c[0]), "+a"(c[1]), "+a"(c[2]), "+a"(c[3]), "+a"(c[4]), "+a"(c[5]), "+a"(c[6]), "+a"(c[7]));

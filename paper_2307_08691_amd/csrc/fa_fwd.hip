@@ -27,7 +27,7 @@
 // K_j and V_j travel HBM -> LDS directly (no registers), two blocks ahead, into a
 // ring of four swizzled (unpadded) buffers shared by all eight wavefronts.
 //
-// Two kernels: fwd_kernel (every option: split keys, half precision, dropout, padded head
+// Two kernels here (small grids without options: fa_stream.hip): fwd_kernel (every option: split keys, half precision, dropout, padded head
 // dimension, elementwise mask) and fwd_chain_kernel (d = 128, short dense sequences: several
 // row blocks per workgroup, each one's start-up hidden behind the previous one's last blocks).
 #include <type_traits>
@@ -1016,6 +1016,22 @@ static hipError_t launch_fwd_split(const FwdArgs& a, int causal, hipStream_t st)
   return hipGetLastError();
 }
 
+// Whether the plain forward pass takes the four-wavefront form (fa_stream.hip) with its blocks of 128 rows. Same bits; the line is
+// where it was measured to win (MI355X, bfloat16, us from 256-row blocks to 128-row ones):
+//  * one block of 128 rows or less: the other half of a 256-row block is padding (128 x 128, 8 heads of 128: 41.9 -> 24.8).
+//  * causal: up to 512 workgroups of 128 rows, two per compute unit (1 x 1024, 64 heads of 128: 512 workgroups, 30.0 -> 26.5;
+//    5 x 1024, 16 heads: 640, 31.9 -> 32.5); at d = 64 up to 768 (6 x 1024, 16 heads: 27.3 -> 24.5; 8 x 1024: 1024,
+//    29.7 -> 29.1, 16 x 256, 32 heads: 1024, 18.0 -> 18.2).
+//  * without the mask all chains are equally long: up to 256 workgroups, one per compute unit (1 x 1024, 32 heads of 128:
+//    26.5 -> 22.0; 3 x 1024, 16 heads: 384, 30.5 -> 33.4), and from 513 to 768, where 256-row blocks need a second
+//    round for a few (5 x 1024, 16 heads: 58.0 -> 50.9; 6 x 1024: 768, 60.8 -> 54.8; 8 x 1024: 1024, 65.9 -> 69.9).
+static bool stream_form(int d, int causal, int n, int pairs) {
+  const long small = (long)((n + 127) / 128) * pairs;
+  if (n <= 128) return true;
+  if (causal) return small <= (d == 64 ? 768 : 512);
+  return small <= 256 || (small > 512 && small <= 768);
+}
+
 // RAGGED: a.p.cu_seqlens is set.
 template <int D, bool F16, bool RAGGED>
 static hipError_t launch_fwd_d(const FwdArgs& a, int causal, hipStream_t st) {
@@ -1051,6 +1067,7 @@ static hipError_t launch_fwd_d(const FwdArgs& a, int causal, hipStream_t st) {
     else hipLaunchKernelGGL((fwd_kernel<D, false, false, F16, true, false, false, kNoPattern, D, RAGGED>), grid, block, 0, st, a);
     return hipGetLastError();
   }
+  if (stream_form(D, causal, a.p.N, a.p.Hq * a.p.nseq)) return launch_fwd_stream(a, D, causal, st);
   if constexpr (D == 128 && !RAGGED) {
     // chained items (fwd_chain_kernel): dense batches of short sequences (at most 16 key blocks:
     // +15% at N = 512; from N = 2048 on the start-up no longer matters and the fixed assignment

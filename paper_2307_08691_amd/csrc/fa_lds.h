@@ -263,4 +263,30 @@ __device__ __forceinline__ void mfma_stream(LoadF load, MmaF mma) {
   mfma_stream_run<N, AHEAD, READS>(ring, load, mma);
 }
 
+// LDS operands of a stream of MFMAs, requested in pairs two pairs ahead. The second of a pair is requested first, so that the
+// wait in front of the pair's first MFMA covers both: one wait per two MFMAs. (A wavefront alone on its SIMD issues
+// one instruction in about five cycles, six beside an MFMA of 32: every instruction of the loop counts.)
+struct OperandRing {
+  static constexpr int PAIRS = 3;
+  bf16x8 x[2 * PAIRS];
+  template <int P, class LoadF>
+  __device__ __forceinline__ void pair(LoadF load) {
+    x[2 * (P % PAIRS) + 1] = load(std::integral_constant<int, 2 * P + 1>{});
+    x[2 * (P % PAIRS)] = load(std::integral_constant<int, 2 * P>{});
+  }
+  template <class LoadF>
+  __device__ __forceinline__ void begin(LoadF load) {
+    pair<0>(load);
+    pair<1>(load);
+  }
+  template <int I, int N, class LoadF>  // before MFMA I of N (even)
+  __device__ __forceinline__ void advance(LoadF load) {
+    if constexpr (I % 2 == 0 && I + 4 < N) pair<I / 2 + 2>(load);
+  }
+  template <class IC>
+  __device__ __forceinline__ bf16x8 at(IC) const {
+    return x[IC::value % (2 * PAIRS)];
+  }
+};
+
 }  // namespace fa

@@ -147,6 +147,29 @@ def test_small_and_large_workgroups_agree_bitwise(N, Hq, Hkv, d, causal):
             assert torch.equal(x[s], y[0]), name
 
 
+# (both sides of every edge of the four-wavefront forward kernel: blocks of 128 rows, 64 keys, wavefronts of 32 rows that see
+# fewer blocks than their workgroup; B sequences take the form of eight wavefronts, one alone that of four, and d = 64
+# causal with `grow` = 8 so that the reference of the softmax moves in the middle of a row)
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("N,Nk,B,Hq,Hkv,d,grow", [(129, 129, 72, 8, 8, 64, 1), (192, 192, 72, 8, 4, 128, 1), (257, 257, 48, 8, 8, 128, 8),
+                                                 (320, 320, 48, 8, 2, 64, 8), (449, 449, 40, 8, 8, 128, 1),
+                                                 (130, 511, 72, 8, 8, 128, 1), (200, 263, 72, 8, 8, 64, 1)])
+def test_forms_of_the_forward_pass_agree_bitwise(N, Nk, B, Hq, Hkv, d, grow, dtype, causal):
+    """The form of the forward kernel is chosen by the size of the grid; a sequence's results do not depend on it."""
+    small = -(-N // 128) * Hq
+    assert small <= 256 and B * small > (768 if d == 64 or not causal else 512)
+    g = torch.Generator(device="cuda").manual_seed(9370 + N + Nk)
+    et = torch.bfloat16 if dtype == "bf16" else torch.float16
+    Q, K, V = (torch.randn(s, generator=g, device="cuda", dtype=et) for s in ((B, N, Hq, d), (B, Nk, Hkv, d), (B, Nk, Hkv, d)))
+    K *= torch.linspace(1, grow, Nk, device="cuda").view(1, Nk, 1, 1).to(et)
+    V[:, Nk - 1] = float("inf")  # the last key: rows that do not see it stay clear of it in the same places
+    O, L = binding.fa_cross_fwd(Q, K, V, d ** -0.5, causal)
+    for s in (0, B // 2, B - 1):
+        o, l = binding.fa_cross_fwd(Q[s:s + 1].contiguous(), K[s:s + 1].contiguous(), V[s:s + 1].contiguous(), d ** -0.5, causal)
+        assert torch.equal(O[s].view(torch.int16), o[0].view(torch.int16)) and torch.equal(L[s], l[0])
+
+
 def large_workgroups(n, pairs, short_too):
     """Whether a backward kernel at d = 64 takes its form of eight wavefronts: n rows (keys), (sequence, head) pairs;
     short_too in the causal dK/dV kernel."""

@@ -36,7 +36,7 @@ def resource_remarks(source):
 @pytest.fixture(scope="module")
 def remarks():
     with concurrent.futures.ThreadPoolExecutor(4) as ex:
-        parts = list(ex.map(resource_remarks, ["fa_fwd.hip", "fa_bwd.hip", "fa_d256.hip", "fa_fp8.hip", "fa_decode.hip"]))
+        parts = list(ex.map(resource_remarks, ["fa_fwd.hip", "fa_stream.hip", "fa_bwd.hip", "fa_d256.hip", "fa_fp8.hip", "fa_decode.hip"]))
     return {k: v for part in parts for k, v in part.items()}
 
 
@@ -279,13 +279,14 @@ def mfma_hazards(lines):
     return mfmas, bad
 
 
-def test_hand_placed_products_keep_their_wait_states():
+@pytest.mark.parametrize("source,kernels", [("fa_d256.hip", 26), ("fa_stream.hip", 16)])
+def test_hand_placed_products_keep_their_wait_states(source, kernels):
     seen = 0
-    for name, lines in whole_assembly("fa_d256.hip").items():
+    for name, lines in whole_assembly(source).items():
         mfmas, bad = mfma_hazards(lines)
         seen += mfmas > 0
         assert not bad, (name, bad[:5])
-    assert seen >= 18  # forward, dK/dV and dQ kernels
+    assert seen == kernels
 
 
 @pytest.mark.parametrize("between,caught", [

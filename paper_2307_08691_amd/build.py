@@ -14,7 +14,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libfa_gfx950.so")
-SOURCES = ["fa_api.hip", "fa_fwd.hip", "fa_stream.hip", "fa_bwd.hip", "fa_d256.hip", "fa_fp8.hip", "fa_decode.hip", "fa_probe.hip"]
+SOURCES = ["fa_api.hip", "fa_fwd.hip", "fa_stream.hip", "fa_bwd.hip", "fa_short.hip", "fa_d256.hip", "fa_fp8.hip", "fa_decode.hip", "fa_probe.hip"]
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

@@ -1,6 +1,6 @@
 // Backward pass of exact attention for gfx950 (Algorithm 2 of the paper).
 //
-// Three launches on the caller's stream (the plain full backward folds the first into the
+// (Short sequences at d = 64: one kernel, fa_short.hip.) Three launches on the caller's stream (the plain full backward folds the first into the
 // third, which then runs before the second: two launches, see OWN_D):
 //   1. prep:  D = rowsum(dO o O) (Algorithm 2, line 4)
 //   2. dK/dV: one workgroup per block of 256 keys of one (sequence, key/value head)
@@ -1451,6 +1451,9 @@ template <int D, bool F16>
 static hipError_t launch_bwd_d(const BwdArgs& a, int causal, int stages, hipStream_t st) {
   // The whole backward is two launches: the dQ kernel goes first and computes D on the way, the dK/dV kernel
   // follows and reads it.
+  if constexpr (D == 64)
+    if (stages == 7 && a.p.d == D && !a.p.mask && !a.p.bmask && !windowed(a.p) && !a.p.drop_thr && bwd_short_form(a.p, causal))
+      return launch_bwd_short(a, causal, st);
   if (stages == 7 && a.p.cu_seqlens) {
     if (hipError_t e = launch_dq<D, F16, true, true>(a, causal, st)) return e;
     return launch_dkdv<D, F16, true>(a, causal, st);

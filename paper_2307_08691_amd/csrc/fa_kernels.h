@@ -104,6 +104,9 @@ struct Fp8Args {
 hipError_t launch_fwd(const FwdArgs& a, int d, int causal, hipStream_t st);
 // forward in workgroups of four wavefronts for grids that leave wavefront slots empty (fa_stream.hip); d in {64, 128}
 hipError_t launch_fwd_stream(const FwdArgs& a, int d, int causal, hipStream_t st);
+// the whole backward of short sequences as one kernel (fa_short.hip): d = 64, no options; whether a problem takes it
+bool bwd_short_form(const Problem& p, int causal);
+hipError_t launch_bwd_short(const BwdArgs& a, int causal, hipStream_t st);
 // split forward for at most 32 (query row, head of the group) pairs per key/value head (fa_decode.hip):
 // writes the shares' partial results like the split kernel; d in {64, 128}
 hipError_t launch_fwd_decode(const FwdArgs& a, int d, int causal, hipStream_t st);

@@ -200,6 +200,47 @@ def test_forms_of_the_backward_agree_bitwise(B, part, N, Hq, Hkv, causal, dq, dk
         assert torch.equal(x[:part], y), name
 
 
+# (lengths on either side of the pieces of 32 keys, the row tiles of 64 and the three sizes of workgroup; 256 pairs or more take the
+# one-kernel form, a few with shared heads, or beyond 256 tokens, the two kernels; without shared heads and up to 192 tokens
+# every grid takes the former, which the oracle judges above)
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("packed", [False, True])
+@pytest.mark.parametrize("N,B,Hq,Hkv", [(1, 32, 16, 8), (33, 32, 16, 8), (64, 64, 8, 4), (127, 64, 32, 4), (129, 32, 16, 8),
+                                        (256, 64, 32, 4), (257, 32, 8, 8), (415, 32, 8, 8), (512, 32, 8, 8)])
+def test_one_kernel_backward_agrees_bitwise(N, B, Hq, Hkv, packed, dtype, causal):
+    """The backward of short sequences at d = 64 is one kernel or two by the size of the grid; a sequence's gradients do not
+    depend on it."""
+    g = torch.Generator(device="cuda").manual_seed(9390 + N)
+    et = torch.bfloat16 if dtype == "bf16" else torch.float16
+    lens = [N] * B
+    if packed:  # uneven, empty ones among them, the longest as long as the bound
+        lens = [N] + torch.randint(0, N + 1, (B - 1,), generator=torch.Generator().manual_seed(N)).tolist()
+    cu = [0]
+    for n in lens:
+        cu.append(cu[-1] + n)
+    Q, K, V, dO = (torch.randn((cu[-1], h, 64), generator=g, device="cuda", dtype=et) for h in (Hq, Hkv, Hkv, Hq))
+    if packed:
+        cut = torch.tensor(cu, dtype=torch.int32, device="cuda")
+        O, L = binding.fa_varlen_fwd(Q, K, V, cut, N, 0.125, causal)
+        grads = binding.fa_varlen_bwd(Q, K, V, O, dO, L, cut, N, 0.125, causal)
+        L = L.transpose(0, 1)
+    else:
+        dense = lambda x: x.view(B, N, -1, 64)
+        O, L = binding.fa_cross_fwd(*map(dense, (Q, K, V)), 0.125, causal)
+        grads = [x.view(B * N, -1, 64) for x in binding.fa_cross_bwd(*map(dense, (Q, K, V, O, dO)), L, 0.125, causal)]
+        O, L = O.view(B * N, Hq, 64), L.transpose(1, 2).reshape(B * N, Hq)
+    assert all(torch.isfinite(x).all() for x in grads)
+    for s in (0, 1, B // 2, B - 1):
+        a, e = cu[s], cu[s + 1]
+        if a == e:
+            continue
+        q, k, v, o, do = (x[a:e].unsqueeze(0).contiguous() for x in (Q, K, V, O, dO))
+        alone = binding.fa_cross_bwd(q, k, v, o, do, L[a:e].transpose(0, 1).unsqueeze(0).contiguous(), 0.125, causal)
+        for name, x, y in zip(("dQ", "dK", "dV"), grads, alone):
+            assert torch.equal(x[a:e].view(torch.int16), y[0].view(torch.int16)), (name, s, e - a)
+
+
 # (the grids on which each form of the two kernels is chosen: every small one, the small dK/dV form beside the large dQ
 # form, both large ones; every product width of a padded head dimension and d = 256)
 @pytest.mark.parametrize("order", [(1, 6), (1, 2, 4), (1, 4, 2), (3, 4), (5, 2)])

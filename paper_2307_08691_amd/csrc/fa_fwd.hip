@@ -135,9 +135,10 @@ __global__ __launch_bounds__(512)
   if (!bc.valid) return;
   const int split = SPLIT ? bc.blk % nsplit : 0;
   const int rowblk = SPLIT ? bc.blk / nsplit : bc.blk;
-  const int s = SPLIT ? cache_sequence(a, bc.seq) : bc.seq;  // (uneven cache lengths: longest first)
+  const CacheSequence cseq = SPLIT ? cache_sequence(a, bc.seq) : CacheSequence{bc.seq, 0};  // (uneven cache lengths: longest first)
+  const int s = cseq.s;
   const SeqInfo si = seq_info(p, s);
-  const int n = si.n, nk = SPLIT && a.seqlens_k ? cache_length(a, s) : si.nk;  // query rows, key rows
+  const int n = si.n, nk = SPLIT ? cseq.len : si.nk;  // query rows, key rows
   const int off = nk - n;          // position of query 0 among the keys (causal alignment)
   const int nrows = SPLIT ? n * p.G : n;  // rows of the (packed) row dimension
   const int i0 = rowblk * BR;
@@ -946,9 +947,19 @@ __global__ __launch_bounds__(256) void fwd_merge_kernel(FwdArgs a) {
     nshare = (ncol + per - 1) / per;
     if (nshare == 1) return;  // the split kernel wrote O and LSE
   }
+  // Few threads per row and a handful of shares: the time is the chain of loads, so those of four shares are requested
+  // together (a share without keys for this row may have written no partial O: what is read in its place is not used).
+  constexpr int FLY = 4;
+  auto part_lse = [&](int k) { return a.Lpart[(long)(k < nshare ? k : nshare - 1) * nrows + li]; };
   float mx = -INFINITY;
   if (ncol > 0)
-    for (int k = 0; k < nshare; ++k) mx = fmaxf(mx, a.Lpart[(long)k * nrows + li]);
+    for (int k0 = 0; k0 < nshare; k0 += FLY) {
+      float lp[FLY];
+#pragma unroll
+      for (int u = 0; u < FLY; ++u) lp[u] = part_lse(k0 + u);
+#pragma unroll
+      for (int u = 0; u < FLY; ++u) mx = fmaxf(mx, lp[u]);
+    }
   if (mx == -INFINITY) {  // no share holds a key that this row sees: P = 0, so O = 0 and L = -inf
     *(u32x2*)(a.O + r * D + 4 * c) = (u32x2){0u, 0u};
     if (c == 0) a.LSE[li] = -INFINITY;
@@ -956,13 +967,21 @@ __global__ __launch_bounds__(256) void fwd_merge_kernel(FwdArgs a) {
   }
   float z = 0.f;
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  for (int k = 0; k < nshare; ++k) {
-    const float lp = a.Lpart[(long)k * nrows + li];
-    if (lp == -INFINITY) continue;  // a share without keys for this row (it may have written no partial O at all)
-    const float wgt = __expf(lp - mx);
-    const f32x4 o = *(const f32x4*)(a.Opart + ((long)k * nrows + r) * D + 4 * c);
-    z += wgt;
-    acc += o * wgt;
+  for (int k0 = 0; k0 < nshare; k0 += FLY) {
+    float lp[FLY];
+    f32x4 o[FLY];
+#pragma unroll
+    for (int u = 0; u < FLY; ++u) {
+      lp[u] = part_lse(k0 + u);
+      o[u] = *(const f32x4*)(a.Opart + ((long)(k0 + u < nshare ? k0 + u : nshare - 1) * nrows + r) * D + 4 * c);
+    }
+#pragma unroll
+    for (int u = 0; u < FLY; ++u) {
+      if (k0 + u >= nshare || lp[u] == -INFINITY) continue;
+      const float wgt = __expf(lp[u] - mx);
+      z += wgt;
+      acc += o[u] * wgt;
+    }
   }
   const float inv = 1.f / z;  // some share holds a visible key
   u32x2 o;

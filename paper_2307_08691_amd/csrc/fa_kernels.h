@@ -35,25 +35,41 @@ __device__ __forceinline__ int cache_length(const FwdArgs& a, int s) {
 // their (sequence, head) pairs in launch order, and a long sequence that starts last leaves the
 // other compute units idle at the end. The sequence index of the launch order is therefore read as a
 // RANK, and the sequence of that rank (by length, ties by index) is found here: lane c counts the
-// sequences that come before candidate c. Done by every wavefront for itself (a few hundred scalar
-// loads that hit L2); batches of more than kRankMax sequences keep the launch order.
+// sequences that come before candidate c. Done by every wavefront for itself, from one load of all lengths whose lanes
+// are then read in turn (a scalar load per sequence instead, each waited for, makes a chain of them before the first request
+// of a key); batches of more than kRankMax sequences keep the launch order.
 constexpr int kRankMax = 128;
-__device__ __forceinline__ int cache_sequence(const FwdArgs& a, int rank) {
+struct CacheSequence {
+  int s, len;  // the sequence, and its number of keys
+};
+__device__ __forceinline__ CacheSequence cache_sequence(const FwdArgs& a, int rank) {
   const int nseq = a.p.nseq, lane = threadIdx.x & 63;
-  if (!a.seqlens_k || nseq <= 1 || nseq > kRankMax) return rank;
-  int found = 0;
-  for (int c0 = 0; c0 < nseq; c0 += 64) {
-    const int c = c0 + lane;
-    const int lc = c < nseq ? cache_length(a, c) : -1;
-    int before = 0;
-    for (int j = 0; j < nseq; ++j) {
-      const int lj = __builtin_amdgcn_readfirstlane(cache_length(a, j));
-      before += (lj > lc || (lj == lc && j < c)) ? 1 : 0;
+  if (!a.seqlens_k) return {rank, a.p.Nk};
+  if (nseq <= 1 || nseq > kRankMax) return {rank, cache_length(a, rank)};
+  static_assert(kRankMax == 128, "two candidates per lane, and seven bits of an index in a key");
+  const int c0 = lane, c1 = 64 + lane;
+  const int len0 = cache_length(a, c0 < nseq ? c0 : 0), len1 = nseq > 64 ? cache_length(a, c1 < nseq ? c1 : 0) : 0;
+  // (all keys differ, and a larger one goes first; where a length outgrows 25 bits the order is another one, but still an order)
+  const unsigned key0 = ((unsigned)len0 << 7) | (unsigned)(127 - c0), key1 = ((unsigned)len1 << 7) | (unsigned)(127 - c1);
+  int before0 = 0, before1 = 0;
+  if (nseq <= 64) {
+    for (int j = 0; j < nseq; ++j) before0 += (unsigned)__builtin_amdgcn_readlane((int)key0, j) > key0 ? 1 : 0;
+  } else {
+    for (int j = 0; j < 64; ++j) {
+      const unsigned k = (unsigned)__builtin_amdgcn_readlane((int)key0, j);
+      before0 += k > key0 ? 1 : 0;
+      before1 += k > key1 ? 1 : 0;
     }
-    const unsigned long long hit = __builtin_amdgcn_ballot_w64(c < nseq && before == rank);
-    if (hit) found = c0 + __builtin_ctzll(hit);
+    for (int j = 64; j < nseq; ++j) {
+      const unsigned k = (unsigned)__builtin_amdgcn_readlane((int)key1, j - 64);
+      before0 += k > key0 ? 1 : 0;
+      before1 += k > key1 ? 1 : 0;
+    }
   }
-  return __builtin_amdgcn_readfirstlane(found);
+  const unsigned long long hit0 = __builtin_amdgcn_ballot_w64(c0 < nseq && before0 == rank);
+  const unsigned long long hit1 = __builtin_amdgcn_ballot_w64(c1 < nseq && before1 == rank);
+  const int l = hit0 ? __builtin_ctzll(hit0) : (hit1 ? __builtin_ctzll(hit1) : 0);
+  return {hit0 ? l : 64 + l, __builtin_amdgcn_readlane(hit0 ? len0 : len1, l)};
 }
 
 // Shares of the row-block split kernel, in blocks of 64 keys: a sequence of `ncol` blocks is cut into at

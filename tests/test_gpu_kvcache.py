@@ -209,6 +209,21 @@ def test_many_sequences_with_equal_and_uneven_lengths(B):
     check_contiguous(draw(18701 + B, B, 1, cap, Hq, Hkv, d), lens, True, 2)
 
 
+# (a wavefront of the decode kernel holds the pages of 64 of its tiles, 8 x 32 keys apart: more than 16384 keys in a share
+# make it load them again; the lengths end a tile before, at and after that)
+@pytest.mark.parametrize("num_splits", [1, 2])
+def test_paged_shares_of_more_keys_than_one_load_of_the_table_covers(num_splits):
+    lens = [40000, 16384, 16385 + 256, 32768 + 300, 16384 - 40]
+    g = torch.Generator(device="cuda").manual_seed(18750)
+    Q = torch.randn((len(lens), 1, 4, 64), generator=g, device="cuda", dtype=torch.bfloat16)
+    Kc, Vc = (torch.randn((len(lens), 40064, 1, 64), generator=g, device="cuda", dtype=torch.bfloat16) for _ in range(2))
+    Kp, Vp, table = page_out(Kc, Vc, lens, 64, 18751)
+    sl = torch.tensor(lens, dtype=torch.int32, device="cuda")
+    O, L = binding.fa_kvcache_fwd(Q, Kp, Vp, 0.125, True, seqlens_k=sl, block_table=table, num_splits=num_splits)
+    O2, L2 = binding.fa_kvcache_fwd(Q, Kc, Vc, 0.125, True, seqlens_k=sl, num_splits=num_splits)
+    assert torch.isfinite(O).all() and torch.equal(O, O2) and torch.equal(L, L2)
+
+
 def test_decoding_steps_replay_from_a_captured_graph():
     """A serving loop captures one decoding step into a HIP graph and replays it while the cache grows:
     the lengths, the page table and the cache contents live in device buffers that change between

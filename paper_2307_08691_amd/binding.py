@@ -106,6 +106,7 @@ SIGNATURES = {
 }
 
 _lib = None
+_host = None  # the native marshalling (csrc/fa_host.cpp): the module once a tensor-level call has looked for it, False without one
 
 
 class FaError(RuntimeError):
@@ -149,10 +150,24 @@ def _ptr(t) -> int:
     return t.data_ptr()
 
 
+def _load_host():
+    """Look for the native form of the usual calls, which takes the library's entry points by address (fa_host.cpp)."""
+    global _host
+    import torch
+    _host = False
+    if hasattr(torch._C, "_cuda_getCurrentRawStream") and os.path.exists(os.path.join(HERE, "_host.so")):
+        from . import _host as host
+        addresses = {n: ctypes.cast(getattr(load(), n), _c_void_p).value for n in host.entry_names()}
+        host.init(torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream, torch.nn.Parameter, addresses)
+        _host = host
+
+
 def _stream() -> int:
     """Handle of the current device's current stream. (Short calls are bound by the host: building the Stream object of
     torch.cuda.current_stream() takes about 3 us of the 18 us a forward call needs there.)"""
     import torch
+    if _host is None:
+        _load_host()
     if not hasattr(torch._C, "_cuda_getCurrentRawStream"):
         return torch.cuda.current_stream().cuda_stream
     return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
@@ -345,6 +360,9 @@ def fa_mfma_probe_raw(iters, random_operands, scratch, stream=0) -> int:
 # The C ABI sees raw pointers and sizes; a tensor of the wrong shape, type or device would become
 # an out-of-bounds device access there. Every tensor is therefore checked here, before the call:
 # device, contiguity, element type and the exact shape its role implies.
+#
+# The usual calls go through `_host` first, which makes the same checks natively and returns None for whatever it
+# does not recognise as an ordinary call; the Python below then has the say, and raises the errors.
 # ---------------------------------------------------------------------------
 
 def _need(t, name, dtype=None, shape=None, device=None):
@@ -457,6 +475,10 @@ def _bwd_tensors(x, O, dO, LSE, dQ, dK, dV):
 
 def fa_fwd(Q, K, V, scale: float, causal: bool, O=None, LSE=None) -> Tuple["torch.Tensor", "torch.Tensor"]:
     """Dense forward. Q [B,N,Hq,d], K,V [B,N,Hkv,d] bf16 -> O [B,N,Hq,d] bf16, LSE [B,Hq,N] fp32."""
+    if _host and O is None and LSE is None:
+        r = _host.dense_fwd(0, Q, K, V, scale, causal)
+        if r is not None:
+            return r
     import torch
     x = _dense(Q, K, V, (torch.bfloat16,), one_length=True)
     O, LSE = _fwd_outputs(x, O, LSE)
@@ -466,6 +488,10 @@ def fa_fwd(Q, K, V, scale: float, causal: bool, O=None, LSE=None) -> Tuple["torc
 
 def fa_bwd(Q, K, V, O, dO, LSE, scale: float, causal: bool, dQ=None, dK=None, dV=None, workspace=None):
     """Dense backward. Returns dQ [B,N,Hq,d], dK, dV [B,N,Hkv,d] (bf16)."""
+    if _host and dQ is None and dK is None and dV is None and workspace is None:
+        r = _host.dense_bwd(0, Q, K, V, O, dO, LSE, scale, causal)
+        if r is not None:
+            return r
     import torch
     x = _dense(Q, K, V, (torch.bfloat16,), one_length=True)
     dQ, dK, dV = _bwd_tensors(x, O, dO, LSE, dQ, dK, dV)
@@ -504,6 +530,10 @@ def fa_bwd_stages(Q, K, V, O, dO, LSE, scale: float, causal: bool, stages: int, 
 def fa_varlen_fwd(Q, K, V, cu_seqlens, max_seqlen: int, scale: float, causal: bool, O=None, LSE=None):
     """Packed ragged forward. Q [T,Hq,d], K,V [T,Hkv,d] bf16, cu_seqlens int32 on the GPU.
     Returns O [T,Hq,d] bf16 and LSE [Hq,T] fp32."""
+    if _host and O is None and LSE is None:
+        r = _host.varlen_fwd(Q, K, V, cu_seqlens, max_seqlen, scale, causal)
+        if r is not None:
+            return r
     import torch
     x = _packed(Q, K, V, cu_seqlens, allowed=(torch.bfloat16, torch.float16))
     O, LSE = _fwd_outputs(x, O, LSE)
@@ -515,6 +545,10 @@ def fa_varlen_fwd(Q, K, V, cu_seqlens, max_seqlen: int, scale: float, causal: bo
 def fa_varlen_bwd(Q, K, V, O, dO, LSE, cu_seqlens, max_seqlen: int, scale: float, causal: bool,
                   dQ=None, dK=None, dV=None, workspace=None):
     """Packed ragged backward. Returns dQ [T,Hq,d], dK, dV [T,Hkv,d] (bf16)."""
+    if _host and dQ is None and dK is None and dV is None and workspace is None:
+        r = _host.varlen_bwd(Q, K, V, O, dO, LSE, cu_seqlens, max_seqlen, scale, causal)
+        if r is not None:
+            return r
     import torch
     x = _packed(Q, K, V, cu_seqlens, allowed=(torch.bfloat16, torch.float16))
     dQ, dK, dV = _bwd_tensors(x, O, dO, LSE, dQ, dK, dV)
@@ -528,6 +562,10 @@ def fa_varlen_bwd(Q, K, V, O, dO, LSE, cu_seqlens, max_seqlen: int, scale: float
 def fa_cross_fwd(Q, K, V, scale: float, causal: bool, O=None, LSE=None):
     """Two lengths. Q [B,Nq,Hq,d], K,V [B,Nk,Hkv,d] bf16 (fa_cross_fwd) or fp16 (fa_cross_fwd_f16)
     -> O [B,Nq,Hq,d] of the same type, LSE [B,Hq,Nq] fp32."""
+    if _host and O is None and LSE is None:
+        r = _host.dense_fwd(1, Q, K, V, scale, causal)
+        if r is not None:
+            return r
     import torch
     x = _dense(Q, K, V)
     O, LSE = _fwd_outputs(x, O, LSE)
@@ -538,6 +576,10 @@ def fa_cross_fwd(Q, K, V, scale: float, causal: bool, O=None, LSE=None):
 
 def fa_cross_bwd(Q, K, V, O, dO, LSE, scale: float, causal: bool, dQ=None, dK=None, dV=None, workspace=None):
     """Two lengths, backward (bf16 or fp16 by the tensors' type). Returns dQ [B,Nq,Hq,d], dK, dV [B,Nk,Hkv,d]."""
+    if _host and dQ is None and dK is None and dV is None and workspace is None:
+        r = _host.dense_bwd(1, Q, K, V, O, dO, LSE, scale, causal)
+        if r is not None:
+            return r
     import torch
     x = _dense(Q, K, V)
     dQ, dK, dV = _bwd_tensors(x, O, dO, LSE, dQ, dK, dV)
@@ -550,6 +592,10 @@ def fa_cross_bwd(Q, K, V, O, dO, LSE, scale: float, causal: bool, dQ=None, dK=No
 
 def fa_dropout_fwd(Q, K, V, scale: float, causal: bool, p_drop: float, seed: int, O=None, LSE=None):
     """Forward with dropout on P. Q [B,Nq,Hq,d], K,V [B,Nk,Hkv,d] bf16 or fp16."""
+    if _host and O is None and LSE is None:
+        r = _host.dense_fwd(2, Q, K, V, scale, causal, p_drop, seed)
+        if r is not None:
+            return r
     import torch
     x = _dense(Q, K, V)
     O, LSE = _fwd_outputs(x, O, LSE)
@@ -561,6 +607,10 @@ def fa_dropout_fwd(Q, K, V, scale: float, causal: bool, p_drop: float, seed: int
 def fa_dropout_bwd(Q, K, V, O, dO, LSE, scale: float, causal: bool, p_drop: float, seed: int, dQ=None, dK=None,
                    dV=None, workspace=None):
     """Backward with the dropout mask of fa_dropout_fwd for the same p_drop and seed."""
+    if _host and dQ is None and dK is None and dV is None and workspace is None:
+        r = _host.dense_bwd(2, Q, K, V, O, dO, LSE, scale, causal, p_drop, seed)
+        if r is not None:
+            return r
     import torch
     x = _dense(Q, K, V)
     dQ, dK, dV = _bwd_tensors(x, O, dO, LSE, dQ, dK, dV)
@@ -663,6 +713,10 @@ def fa_mask_bwd_dmask(Q, K, V, M, O, dO, LSE, scale: float, causal: bool, dQ=Non
 def fa_local_fwd(Q, K, V, scale: float, window_left: int, window_right: int, O=None, LSE=None):
     """Sliding window: the query at position q = r + Nk - Nq sees keys q - window_left .. q + window_right
     (a negative bound: none). Q [B,Nq,Hq,d], K,V [B,Nk,Hkv,d] bf16 or fp16."""
+    if _host and O is None and LSE is None:
+        r = _host.dense_fwd(3, Q, K, V, scale, window_left, window_right)
+        if r is not None:
+            return r
     import torch
     x = _dense(Q, K, V)
     O, LSE = _fwd_outputs(x, O, LSE)
@@ -674,6 +728,10 @@ def fa_local_fwd(Q, K, V, scale: float, window_left: int, window_right: int, O=N
 def fa_local_bwd(Q, K, V, O, dO, LSE, scale: float, window_left: int, window_right: int, dQ=None, dK=None, dV=None,
                  workspace=None):
     """Backward of fa_local_fwd for the same window."""
+    if _host and dQ is None and dK is None and dV is None and workspace is None:
+        r = _host.dense_bwd(3, Q, K, V, O, dO, LSE, scale, window_left, window_right)
+        if r is not None:
+            return r
     import torch
     x = _dense(Q, K, V)
     dQ, dK, dV = _bwd_tensors(x, O, dO, LSE, dQ, dK, dV)
@@ -865,6 +923,10 @@ def fa_kvcache_fwd(Q, Kcache, Vcache, scale: float, causal: bool, seqlens_k=None
     [B,Nk,Hkv,d]. Paged: Kcache, Vcache [pages,page_size,Hkv,d] and block_table [B,pages_per_seq]
     int32 on the GPU; max_seqlen_k (0: pages_per_seq * page_size) bounds the lengths.
     Returns O [B,Nq,Hq,d] of that type and LSE [B,Hq,Nq] fp32. num_splits = 0 picks a default."""
+    if _host and num_splits == 0 and O is None and LSE is None and workspace is None:
+        r = _host.kvcache_fwd(Q, Kcache, Vcache, scale, causal, seqlens_k, block_table, max_seqlen_k)
+        if r is not None:
+            return r
     import torch
     et = _elem_type(Q)
     _need(Q, "Q", et)

@@ -1,8 +1,8 @@
-"""Build the gfx950 attention library in-tree with hipcc.
+"""Build the gfx950 attention library in-tree with hipcc, and the native marshalling of its binding with the C++ compiler.
 
     python -m paper_2307_08691_amd.build
 
-produces paper_2307_08691_amd/libfa_gfx950.so from csrc/*.hip. hipcc
+produces paper_2307_08691_amd/libfa_gfx950.so from csrc/*.hip and paper_2307_08691_amd/_host.so from csrc/fa_host.cpp. hipcc
 cross-compiles for gfx950 without a GPU.
 """
 from __future__ import annotations
@@ -14,6 +14,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libfa_gfx950.so")
+HOST_LIB = os.path.join(HERE, "_host.so")  # (a Python extension module)
 SOURCES = ["fa_api.hip", "fa_fwd.hip", "fa_stream.hip", "fa_bwd.hip", "fa_short.hip", "fa_d256.hip", "fa_fp8.hip", "fa_decode.hip", "fa_probe.hip"]
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
@@ -39,6 +40,21 @@ def _compile(source: str, obj: str) -> str:
     return err
 
 
+def build_host() -> None:
+    """Compile the extension module against the installed torch."""
+    import sysconfig
+    import torch
+    from torch.utils import cpp_extension
+    lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           *(f"-I{d}" for d in cpp_extension.include_paths() + [sysconfig.get_paths()["include"]]),
+           "-o", HOST_LIB, os.path.join(CSRC, "fa_host.cpp"), f"-L{lib}", "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("the C++ compiler failed on fa_host.cpp:\n" + r.stderr)
+
+
 def build(verbose: bool = False) -> str:
     """Compile every HIP source (in parallel, one object each) and link the shared library.
     Always recompiles."""
@@ -48,10 +64,12 @@ def build(verbose: bool = False) -> str:
         objs = [os.path.join(tmp, s.replace(".hip", ".o")) for s in SOURCES]
         if verbose:
             print(" ".join([hipcc(), *FLAGS, "-c"]), *SOURCES, flush=True)
-        with concurrent.futures.ThreadPoolExecutor(len(SOURCES)) as ex:
+        with concurrent.futures.ThreadPoolExecutor(len(SOURCES) + 1) as ex:
+            host = ex.submit(build_host)
             for err in ex.map(_compile, SOURCES, objs):
                 if verbose and err:
                     print(err, file=sys.stderr)
+            host.result()
         r = subprocess.run([hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs], capture_output=True, text=True)
         if r.returncode != 0:
             raise RuntimeError("link failed:\n" + r.stderr)

@@ -950,7 +950,7 @@ __global__ __launch_bounds__(256) void fwd_merge_kernel(FwdArgs a) {
   // Few threads per row and a handful of shares: the time is the chain of loads, so those of four shares are requested
   // together (a share without keys for this row may have written no partial O: what is read in its place is not used).
   constexpr int FLY = 4;
-  auto part_lse = [&](int k) { return a.Lpart[(long)(k < nshare ? k : nshare - 1) * nrows + li]; };
+  auto part_lse = [&](int k) { return k < nshare ? a.Lpart[(long)k * nrows + li] : -INFINITY; };
   float mx = -INFINITY;
   if (ncol > 0)
     for (int k0 = 0; k0 < nshare; k0 += FLY) {
@@ -973,11 +973,11 @@ __global__ __launch_bounds__(256) void fwd_merge_kernel(FwdArgs a) {
 #pragma unroll
     for (int u = 0; u < FLY; ++u) {
       lp[u] = part_lse(k0 + u);
-      o[u] = *(const f32x4*)(a.Opart + ((long)(k0 + u < nshare ? k0 + u : nshare - 1) * nrows + r) * D + 4 * c);
+      if (k0 + u < nshare) o[u] = *(const f32x4*)(a.Opart + ((long)(k0 + u) * nrows + r) * D + 4 * c);
     }
 #pragma unroll
     for (int u = 0; u < FLY; ++u) {
-      if (k0 + u >= nshare || lp[u] == -INFINITY) continue;
+      if (lp[u] == -INFINITY) continue;
       const float wgt = __expf(lp[u] - mx);
       z += wgt;
       acc += o[u] * wgt;

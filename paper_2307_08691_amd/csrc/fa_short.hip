@@ -5,8 +5,8 @@
 // its accumulators, so nothing is summed across workgroups: it visits the rows in tiles of 32, every wavefront forms P
 // and dS of its own 32 (KW = 1) or 2 x 32 (KW = 2) keys, adds to its dK_j, dV_j (lines 12, 16) and leaves dS in LDS, where
 // one phase later two wavefronts, in turn, form the tile's dQ_i = dS K over all keys (line 15; K is in LDS for the whole kernel).
-// Measured (MI355X, bfloat16, 32 x 512, 32 heads, causal, us of the backward): 270 -> 224; 64 x 256: 216 -> 182; 128 x 128: 194 -> 144. What
-// bounds it: 120 of the 224 pass with the row tiles left out (a workgroup's K, V, O, dO arrive before its first tile, and beyond
+// Measured (MI355X, bfloat16, 32 x 512, 32 heads, causal, us of the backward): 270 -> 215; 64 x 256: 216 -> 171; 128 x 128: 194 -> 133. What
+// bounds it: half of the time passes with the row tiles left out (a workgroup's K, V, O, dO arrive before its first tile, and beyond
 // 128 tokens there is no second workgroup on the compute unit to fill that time); the rest is the chain of a phase, LDS reads, MFMAs,
 // exponentials, barrier (the exponentials left out: 2 us less, dQ left out: 42).
 // The arithmetic is that of the two kernels operation by operation and in their order, so the results are the same bits
@@ -28,7 +28,9 @@ struct ShortPlan {
   static constexpr int STG_OFF = RING_OFF + RING * SLOTB;      // two 32 x 32 pieces of dQ on their way out
   static constexpr int L_OFF = STG_OFF + 2 * 2048;
   static constexpr int STATS = KW == 2 ? 512 : 2048;           // rows (over the group's query heads) whose L, D fit
-  static constexpr int SMEM = L_OFF + 8 * STATS;
+  // where O_i and dO_i pass through at the start: dS^T's place, and for 256 keys (one workgroup per compute unit either way) more
+  static constexpr int EXTRA_OFF = L_OFF + 8 * STATS, EXTRA = KW == 1 && NW == 8 ? NW * TILEB : 0;
+  static constexpr int SMEM = EXTRA_OFF + EXTRA;
 };
 
 template <int KW, int NW, bool CAUSAL, bool F16>
@@ -110,16 +112,35 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
     for (int ks = 0; ks < KS; ++ks) Vf[u][ks] = *(const bf16x8*)(vp + 16 * ks);
   }
   // ---- L and D = rowsum(dO o O) (line 4) of all rows, as the dQ kernel sums it: a lane takes half a row
+  // (O_i, and dO_i where there is room, come through a piece of the idle dS^T area as whole rows: straight into registers a
+  // request touches 16 bytes of each of 32 rows twice: 32 x 512 causal 224 -> 215 us, 128 x 128 144 -> 133)
+  constexpr bool BOTH = KW == 2 || Plan::EXTRA;
+  const char* const stage = smem + Plan::DS_OFF + w * (KW * Plan::TILEB);
+  const char* const stage2 = KW == 2 ? stage + Plan::TILEB : smem + Plan::EXTRA_OFF + w * Plan::TILEB;
+  const int orow = lq * ROWB + 16 * (hh ^ swz<ROWB>(lq));
   for (int q = w; q < p.G * (rows64 / 32); q += NW) {
     const int hi = q / (rows64 / 32), row = 32 * (q - hi * (rows64 / 32)) + lq, rowc = row < n ? row : n - 1;
     const int h = g * p.G + hi;
     const long o = ((si.tok0 + rowc) * p.Hq + h) * D + 8 * hh;
     const float lse = a.LSE[s * p.lse_seq_stride + (long)h * p.lse_head_stride + (p.cu_seqlens ? si.tok0 : 0) + rowc];
     bf16x8 ov[KS], gv[KS];
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // (the rows before these have been read)
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int sr = 8 * u + lane / 8, r = row - lq + sr < n ? row - lq + sr : n - 1;
+      const long so = ((si.tok0 + r) * p.Hq + h) * D + 8 * ((lane % 8) ^ swz<ROWB>(sr));
+      dma16(a.O + so, stage + 1024 * u);
+      if (BOTH) dma16(a.dO + so, stage2 + 1024 * u);
+    }
+    if (!BOTH) {
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) gv[ks] = *(const bf16x8*)(a.dO + o + 16 * ks);
+    }
+    wait_vmem();
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
-      ov[ks] = *(const bf16x8*)(a.O + o + 16 * ks);
-      gv[ks] = *(const bf16x8*)(a.dO + o + 16 * ks);
+      ov[ks] = lds_b128(stage, orow ^ (32 * ks));
+      if (BOTH) gv[ks] = lds_b128(stage2, orow ^ (32 * ks));
     }
     float part = 0.f;
 #pragma unroll
@@ -336,7 +357,7 @@ static hipError_t launch_short(const BwdArgs& a, int causal, hipStream_t st) {
 //    (1 x 128: 20.9 -> 18.1, 16 x 192: 24.5 -> 20.9, 4 x 256 causal 22.7 -> 19.5, without the mask 21.4 -> 22.7).
 //  * up to 256 tokens: from 192 pairs on (64 x 128: 49.7 -> 35.7; 64 x 256, 32 heads on 4: 160 -> 120; 17 x 256: 272 pairs, 49.7 ->
 //    46.4; 32 x 256, 32 heads on 4: 128 pairs, 101 -> 111).
-//  * beyond: rounds of 256 that are three quarters full (32 x 512, 32 heads, causal 270 -> 224; 12 x 512: 192 pairs, 58.7 -> 50.2;
+//  * beyond: rounds of 256 that are three quarters full (32 x 512, 32 heads, causal 270 -> 215; 12 x 512: 192 pairs, 58.7 -> 50.2;
 //    24 x 512: 384, 102 -> 94; 33 x 512: 528, 143 -> 141; 4 x 512: 64, 32.4 -> 44.3), without the mask, where the chains are longer
 //    still and there is more than one round, seven eighths (32 x 512, 32 heads: 330 -> 288; 24 x 512: 384, 125 -> 127).
 bool bwd_short_form(const Problem& p, int causal) {

@@ -963,8 +963,9 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
   const int wrow0 = i0 + 32 * w;
   const int row = wrow0 + lq;
   const int rowc = row < n ? row : n - 1;
+  constexpr bool QROWS = !PAD;  // whole rows through LDS, below
   bf16x8 Qf[KS], dOf[KS];
-  {
+  if constexpr (!QROWS) {
     const __bf16* qp = a.Q + ((si.tok0 + rowc) * p.Hq + h) * dh + 8 * hh;
     const __bf16* gp = a.dO + ((si.tok0 + rowc) * p.Hq + h) * dh + 8 * hh;
 #pragma unroll
@@ -1082,6 +1083,21 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
       }
     }
   };
+  // Q_i and dO_i come through the ring before the first tiles do, O_i through the half of it that these leave idle. (Two memory
+  // latencies where straight loads had one, and a quarter of the address unit's work.)
+  static_assert(RING == 4 && BUFB / 4 == 32 * ROWB, "a piece of 32 rows is a quarter of a ring slot");
+  char* const st_a = smem + ((tb + 2 + grp) % RING) * BUFB + (w & 3) * (BUFB / 4);
+  if constexpr (QROWS) {
+    char* const st_b = smem + ((tb + grp) % RING) * BUFB + (w & 3) * (BUFB / 4);
+    const long rstride = (long)p.Hq * D, r0 = (si.tok0 * p.Hq + h) * D;
+    rows_request<D>(st_b, a.Q + r0, rstride, wrow0, n - 1, lane);
+    rows_request<D>(st_a, a.dO + r0, rstride, wrow0, n - 1, lane);
+    wait_vmem();
+    row_operands<D>(Qf, st_b, lane);
+    row_operands<D>(dOf, st_a, lane);
+    lds_barrier();
+    if constexpr (OWN_D) rows_request<D>(st_a, a.O + r0, rstride, wrow0, n - 1, lane);
+  }
   issue_tile(tb);
   issue_tile(tb + 1);
   issue_mask(jb);
@@ -1092,10 +1108,17 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
     // multiplied and summed, and the other half from the partner lane
     const __bf16* op = a.O + ((si.tok0 + rowc) * p.Hq + h) * dh + 8 * hh;
     float part = 0.f;
+    bf16x8 Of[KS];
+    if constexpr (QROWS) {
+      wait_vmem_upto<2 * TPW + MPW>();  // everything but the tiles (and M)
+      row_operands<D>(Of, st_a, lane);
+    }
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks)
       if (!PAD || 16 * ks + 8 * hh < dh) {
-        const bf16x8 o = *(const bf16x8*)(op + 16 * ks);
+        bf16x8 o;
+        if constexpr (QROWS) o = Of[ks];
+        else o = *(const bf16x8*)(op + 16 * ks);
 #pragma unroll
         for (int t = 0; t < 8; ++t) part += widen<F16>(o, t) * widen<F16>(dOf[ks], t);
       }

@@ -121,12 +121,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     advance(next_v);
   };
   copy_k();
-  bf16x8 Qf[KS];
-  {
-    const __bf16* qp = a.Q + ((si.tok0 + rowc) * p.Hq + h) * D + 8 * hh;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) Qf[ks] = *(const bf16x8*)(qp + 16 * ks);
-  }
+  char* const qst = smem + V_OFF + w * (32 * ROWB);  // (no V tile is on its way yet)
+  rows_request<D>(qst, a.Q + (si.tok0 * p.Hq + h) * D, (long)p.Hq * D, prow0, n - 1, lane);
   copy_k();
   copy_k();
   f32x16 O[DT];
@@ -172,9 +168,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     for (int r = 4; r < 16; r += 2) mx = max3s(mx, S[1][r], S[1][r + 1]);
     return max_with_partner32(mx);
   };
-#pragma unroll
-  for (int ks = 0; ks < KS; ++ks) touch(Qf[ks]);
   wait_vmem_upto<2 * CPT>();
+  bf16x8 Qf[KS];
+  row_operands<D>(Qf, qst, lane);
   lds_barrier();  // K_0 has landed
   {
     OperandRing ring;

@@ -963,7 +963,9 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
   const int wrow0 = i0 + 32 * w;
   const int row = wrow0 + lq;
   const int rowc = row < n ? row : n - 1;
-  constexpr bool QROWS = !PAD;  // whole rows through LDS, below
+  // whole rows through LDS, below (not for windows at d = 64, whose short walks are all start-up and feel the second latency more:
+  // 2 x 6997, window of 223, 32 heads on 16, forward + backward 361 us without, 363.5 with it)
+  constexpr bool QROWS = !PAD && !(LOCAL == kWindow && D == 64);
   bf16x8 Qf[KS], dOf[KS];
   if constexpr (!QROWS) {
     const __bf16* qp = a.Q + ((si.tok0 + rowc) * p.Hq + h) * dh + 8 * hh;

@@ -49,22 +49,24 @@ __device__ __forceinline__ CacheSequence cache_sequence(const FwdArgs& a, int ra
   static_assert(kRankMax == 128, "two candidates per lane, and seven bits of an index in a key");
   const int c0 = lane, c1 = 64 + lane;
   const int len0 = cache_length(a, c0 < nseq ? c0 : 0), len1 = nseq > 64 ? cache_length(a, c1 < nseq ? c1 : 0) : 0;
-  // (all keys differ, and a larger one goes first; where a length outgrows 25 bits the order is another one, but still an order)
-  const unsigned key0 = ((unsigned)len0 << 7) | (unsigned)(127 - c0), key1 = ((unsigned)len1 << 7) | (unsigned)(127 - c1);
+  // (all keys differ, and a larger one goes first; where a length outgrows 25 bits the order is another one, but still an
+  // order. Lanes without a sequence hold 0, which is larger than none.)
+  const unsigned key0 = c0 < nseq ? ((unsigned)len0 << 7) | (unsigned)(127 - c0) : 0u;
+  const unsigned key1 = c1 < nseq ? ((unsigned)len1 << 7) | (unsigned)(127 - c1) : 0u;
   int before0 = 0, before1 = 0;
-  if (nseq <= 64) {
-    for (int j = 0; j < nseq; ++j) before0 += (unsigned)__builtin_amdgcn_readlane((int)key0, j) > key0 ? 1 : 0;
-  } else {
-    for (int j = 0; j < 64; ++j) {
-      const unsigned k = (unsigned)__builtin_amdgcn_readlane((int)key0, j);
-      before0 += k > key0 ? 1 : 0;
-      before1 += k > key1 ? 1 : 0;
-    }
-    for (int j = 64; j < nseq; ++j) {
-      const unsigned k = (unsigned)__builtin_amdgcn_readlane((int)key1, j - 64);
-      before0 += k > key0 ? 1 : 0;
-      before1 += k > key1 ? 1 : 0;
-    }
+  const int n0 = nseq < 64 ? nseq : 64;
+  for (int j = 0; j < n0; j += 4) {
+    unsigned k[4];
+    for (int u = 0; u < 4; ++u) k[u] = (unsigned)__builtin_amdgcn_readlane((int)key0, j + u);
+    for (int u = 0; u < 4; ++u) before0 += k[u] > key0 ? 1 : 0;
+    if (nseq > 64)
+      for (int u = 0; u < 4; ++u) before1 += k[u] > key1 ? 1 : 0;
+  }
+  for (int j = 0; j < nseq - 64; j += 4) {
+    unsigned k[4];
+    for (int u = 0; u < 4; ++u) k[u] = (unsigned)__builtin_amdgcn_readlane((int)key1, j + u);
+    for (int u = 0; u < 4; ++u) before0 += k[u] > key0 ? 1 : 0;
+    for (int u = 0; u < 4; ++u) before1 += k[u] > key1 ? 1 : 0;
   }
   const unsigned long long hit0 = __builtin_amdgcn_ballot_w64(c0 < nseq && before0 == rank);
   const unsigned long long hit1 = __builtin_amdgcn_ballot_w64(c1 < nseq && before1 == rank);

@@ -102,10 +102,10 @@ int fa_bwd(const void* Q, const void* K, const void* V, const void* O, const voi
  * Profiling aid: the backward as three launches (D pre-pass, dK/dV kernel, dQ kernel)
  * restricted to a subset of them, so that each can be timed on its own. `stages`
  * is a bit mask; all three bits give the results of fa_bwd (which itself folds the
- * pre-pass into the dQ kernel: one launch and one pass over dO fewer). Both later stages read the D
- * the prep stage writes, so results are correct only if it ran first on the
- * same arguments. Same validation and errors as fa_bwd; stages == 0 or bits
- * outside the mask return FA_ERR_SHAPE.
+ * pre-pass into the dQ kernel: one launch and one pass over dO fewer) and leave D in the
+ * workspace like the prep stage alone. Both later stages read the D the prep stage writes, so
+ * results are correct only if it ran first on the same arguments. Same validation and errors as
+ * fa_bwd; stages == 0 or bits outside the mask return FA_ERR_SHAPE.
  */
 #define FA_STAGE_PREP 1 /* D = rowsum(dO o O) (Algorithm 2, line 4) */
 #define FA_STAGE_DKDV 2 /* column-block loop: dK, dV (Algorithm 2, lines 5-19 without line 15) */

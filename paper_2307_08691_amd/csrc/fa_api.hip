@@ -138,6 +138,7 @@ struct Options {
   int page_log2 = 0, table_stride = 0;
   void* dM = nullptr;                    // masked backward: where the gradient of the mask goes, with its strides
   long long dm_bs = 0, dm_hs = 0, dm_rs = 0;
+  bool keep_d = false;                   // backward: D has to be in the workspace afterwards (fa_bwd_stages)
 };
 
 Options half_precision(int f16) {
@@ -247,6 +248,7 @@ int run_bwd(const void* Q, const void* K, const void* V, const void* O, const vo
   a.dK = (__bf16*)dK;
   a.dV = (__bf16*)dV;
   a.Dvec = (float*)ws;
+  a.keep_d = opt.keep_d;
   a.dM = (__bf16*)opt.dM;
   a.dm_bs = (long)opt.dm_bs;
   a.dm_hs = (long)opt.dm_hs;
@@ -298,9 +300,9 @@ size_t fa_bwd_workspace_bytes(int B, int Hq, int Hkv, int N, int d) {
   return ws_bytes((long)B * N, Hq, d);
 }
 
-int fa_bwd_stages(const void* Q, const void* K, const void* V, const void* O, const void* dO, const float* LSE,
-                  void* dQ, void* dK, void* dV, void* workspace, size_t workspace_bytes, int B, int Hq, int Hkv, int N,
-                  int d, float scale, int causal, int stages, void* stream) {
+static int dense_bwd(const void* Q, const void* K, const void* V, const void* O, const void* dO, const float* LSE,
+                     void* dQ, void* dK, void* dV, void* workspace, size_t workspace_bytes, int B, int Hq, int Hkv, int N,
+                     int d, float scale, int causal, int stages, void* stream, const Options& opt = Options()) {
   if (!Q || !K || !V || !O || !dO || !LSE || !dQ || !dK || !dV || !workspace) return FA_ERR_NULL;
   if (B <= 0 || N <= 0) return FA_ERR_SHAPE;
   if (int e = check_common(Hq, Hkv, d, scale)) return e;
@@ -311,14 +313,23 @@ int fa_bwd_stages(const void* Q, const void* K, const void* V, const void* O, co
   if (workspace_bytes < ws_bytes((long)B * N, Hq, d)) return FA_ERR_WORKSPACE;
   if (stages <= 0 || (stages & ~7)) return FA_ERR_SHAPE;
   return run_bwd(Q, K, V, O, dO, LSE, dQ, dK, dV, workspace, nullptr, B, N, N, (long)B * N, Hq, Hkv, d, scale, causal,
-                 stages, stream);
+                 stages, stream, nullptr, opt);
+}
+
+int fa_bwd_stages(const void* Q, const void* K, const void* V, const void* O, const void* dO, const float* LSE,
+                  void* dQ, void* dK, void* dV, void* workspace, size_t workspace_bytes, int B, int Hq, int Hkv, int N,
+                  int d, float scale, int causal, int stages, void* stream) {
+  Options opt;
+  opt.keep_d = true;
+  return dense_bwd(Q, K, V, O, dO, LSE, dQ, dK, dV, workspace, workspace_bytes, B, Hq, Hkv, N, d, scale, causal, stages,
+                   stream, opt);
 }
 
 int fa_bwd(const void* Q, const void* K, const void* V, const void* O, const void* dO, const float* LSE, void* dQ,
            void* dK, void* dV, void* workspace, size_t workspace_bytes, int B, int Hq, int Hkv, int N, int d,
            float scale, int causal, void* stream) {
-  return fa_bwd_stages(Q, K, V, O, dO, LSE, dQ, dK, dV, workspace, workspace_bytes, B, Hq, Hkv, N, d, scale, causal,
-                       FA_STAGE_PREP | FA_STAGE_DKDV | FA_STAGE_DQ, stream);
+  return dense_bwd(Q, K, V, O, dO, LSE, dQ, dK, dV, workspace, workspace_bytes, B, Hq, Hkv, N, d, scale, causal,
+                   FA_STAGE_PREP | FA_STAGE_DKDV | FA_STAGE_DQ, stream);
 }
 
 int fa_bwd_noalloc(const void* Q, const void* K, const void* V, const void* O, const void* dO, const float* LSE,
@@ -328,8 +339,8 @@ int fa_bwd_noalloc(const void* Q, const void* K, const void* V, const void* O, c
   if (B > 0 && Hq > 0 && N > 0 && (long long)B * N * Hq > (long long)FA_NOALLOC_MAX_ROWS) return FA_ERR_WORKSPACE;
   float* ws = nullptr;
   if (int e = scratch_on_current_device(&ws, &g_last_hip_error)) return e;
-  return fa_bwd_stages(Q, K, V, O, dO, LSE, dQ, dK, dV, ws, sizeof(float) * (size_t)FA_NOALLOC_MAX_ROWS, B, Hq, Hkv, N,
-                       d, scale, causal, FA_STAGE_PREP | FA_STAGE_DKDV | FA_STAGE_DQ, stream);
+  return dense_bwd(Q, K, V, O, dO, LSE, dQ, dK, dV, ws, sizeof(float) * (size_t)FA_NOALLOC_MAX_ROWS, B, Hq, Hkv, N, d,
+                   scale, causal, FA_STAGE_PREP | FA_STAGE_DKDV | FA_STAGE_DQ, stream);
 }
 
 static int check_varlen(const int32_t* cu, int nseq, int total_tokens, int max_seqlen) {

@@ -100,6 +100,7 @@ struct BwdArgs {
   __bf16* dK;
   __bf16* dV;
   float* Dvec;   // workspace: rowsum(dO o O), laid out like LSE
+  bool keep_d;   // whoever asked for all three stages may run single ones on the same workspace: D has to be left there
   // gradient of the elementwise mask (mask instantiation of the dQ kernel only; nullptr: not asked for):
   // dM = dS in the element type, entry (s, h, r, c) at dM[s * dm_bs + h * dm_hs + r * dm_rs + c]
   __bf16* dM;

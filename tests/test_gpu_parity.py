@@ -268,6 +268,27 @@ def test_any_split_of_the_backward_into_stages(B, N, Hq, Hkv, d, causal, order):
         assert pu.maxdiff(pu.to_f64(x), pu.to_f64(y)) <= pu.ulp(pu.maxabs(pu.to_f64(y))), name
 
 
+# (shapes that fa_bwd hands to one kernel, to two of four and of eight wavefronts, d = 128, padded heads, d = 256)
+@pytest.mark.parametrize("B,N,Hq,Hkv,d,causal", [(1, 100, 2, 2, 64, False), (64, 100, 8, 4, 64, True), (40, 200, 8, 8, 64, False),
+                                                 (25, 450, 8, 8, 64, True), (1, 450, 4, 2, 64, True), (8, 1100, 8, 8, 64, False),
+                                                 (2, 300, 4, 2, 128, True), (1, 200, 2, 1, 96, False), (1, 200, 2, 1, 256, True)])
+def test_single_stages_after_a_whole_backward(B, N, Hq, Hkv, d, causal):
+    """Asked for all three stages, fa_bwd_stages leaves D in the workspace as well: a later stage on the same arguments reads
+    it there and repeats its part of the results, which are those of fa_bwd, bit for bit."""
+    prob = inputs.make_dense(B=B, N=N, Hq=Hq, Hkv=Hkv, d=d, causal=causal, seed=9450 + N + d)
+    Q, K, V, dO = (pu.to_gpu(x, prob.dtype) for x in (prob.Q, prob.K, prob.V, prob.dO))
+    O, L = binding.fa_fwd(Q, K, V, prob.scale, causal)
+    ws = torch.full((binding.fa_bwd_workspace_bytes(B, Hq, Hkv, N, d),), 255, dtype=torch.uint8, device="cuda")  # NaN as float32
+    want = binding.fa_bwd(Q, K, V, O, dO, L, prob.scale, causal)
+    whole = [torch.empty_like(x) for x in (Q, K, V)]
+    binding.fa_bwd_stages(Q, K, V, O, dO, L, prob.scale, causal, 7, *whole, ws)
+    got = [torch.full_like(x, float("nan")) for x in (Q, K, V)]
+    for stages in (2, 4):
+        binding.fa_bwd_stages(Q, K, V, O, dO, L, prob.scale, causal, stages, *got, ws)
+    for name, x, y, z in zip(("dQ", "dK", "dV"), got, whole, want):
+        assert torch.isfinite(z).all() and torch.equal(x, z) and torch.equal(y, z), name
+
+
 @pytest.mark.parametrize("d", [64, 128])
 def test_every_output_is_bit_reproducible(d):
     """No output is accumulated by atomic adds (dQ comes from a row-block pass of its own instead

@@ -88,6 +88,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const int c = ((i0 + BR < n ? i0 + BR : n) - 1 + off) / BC + 1, cw = (prow0 + 31 + off) / BC + 1;
     ncol = c < ncol_all ? c : ncol_all;
     ncolw = cw < ncol ? cw : ncol;
+    // A packed sequence may hold fewer keys than queries, which the host cannot see; its first rows then see none. All wavefronts
+    // visit a block all the same: they share the barriers and the copies, and each has to make as many of both.
+    if (RAGGED && ncol < 1) ncol = 1;
+    if (RAGGED && ncolw < 1) ncolw = 1;
   }
 
   StreamCopier<D> copier;

@@ -215,6 +215,36 @@ def test_a_sequence_with_queries_but_no_keys(d):
         assert not bool(O[a:e].any()) and not bool(dQ[a:e].any()) and bool(torch.isneginf(L[:, a:e]).all())
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("d,copies", [(64, 1), (128, 1), (64, 80), (128, 60), (256, 1)])
+def test_fewer_keys_than_queries_under_the_mask_do_no_harm(d, copies, dtype):
+    """Packed causal batch with sequences of fewer keys than queries: lengths that the host cannot see and whose first rows see
+    no key. What these rows hold is open; every other row is right, and nothing outside the outputs is written. (One copy
+    of the batch takes the forward kernel of four wavefronts at d <= 128, many copies that of eight.)"""
+    lq, lk, Hq, Hkv = [256, 129, 300, 70, 128], [150, 129, 20, 64, 1], 4, 2
+    cu_q, cu_k, Qb, Kb, Vb, _ = ragged_cross(lq, lk, Hq, Hkv, d, 4300 + d)
+    et = torch.bfloat16 if dtype == "bf16" else torch.float16
+    Q, K, V = (pu.to_gpu(x).to(et).repeat(copies, 1, 1) for x in (Qb, Kb, Vb))
+    offsets = lambda l: torch.tensor([0] + l * copies, dtype=torch.int32).cumsum(0, dtype=torch.int32).cuda()
+    T = sum(lq) * copies
+    O = torch.full((T + 16, Hq, d), 7.5, device="cuda", dtype=et)
+    L = torch.full((Hq * T + 64,), 7.5, device="cuda")
+    binding.fa_varlen_cross_fwd(Q, K, V, offsets(lq), offsets(lk), max(lq), max(lk), d ** -0.5, True, O=O[8:-8],
+                                LSE=L[32:-32].view(Hq, T))
+    torch.cuda.synchronize()
+    for guard in (O[:8], O[-8:], L[:32], L[-32:]):
+        assert bool((guard == 7.5).all())
+    q, k, v = (pu.to_f64(x) for x in (Q, K, V))
+    for i, (n, nk) in enumerate(zip(lq, lk)):
+        a, b = cu_q[i] + max(0, n - nk), cu_k[i]  # the rows that see keys: the square problem at the end
+        eO, eL = orc.attention_forward(q[None, a:cu_q[i + 1]], k[None, b:cu_k[i + 1]], v[None, b:cu_k[i + 1]], d ** -0.5, True)
+        for c in (0, copies - 1):
+            got = pu.to_f64(O[8:-8][c * sum(lq) + a:c * sum(lq) + cu_q[i + 1]])
+            assert pu.maxdiff(got, eO[0]) <= pu.TOL_O, (i, c)
+            gotL = pu.to_f64(L[32:-32].view(Hq, T)[:, c * sum(lq) + a:c * sum(lq) + cu_q[i + 1]])
+            assert pu.maxdiff(gotL, eL[0]) <= pu.TOL_LSE, (i, c)
+
+
 def test_ragged_two_lengths_with_equal_offsets_reproduce_the_one_length_entry_points():
     prob = inputs.make_varlen([100, 257, 31], Hq=4, Hkv=2, d=128, causal=True, seed=4100)
     Q, K, V, dO = (pu.to_gpu(x) for x in (prob.Q, prob.K, prob.V, prob.dO))

@@ -140,16 +140,50 @@ def test_small_and_large_workgroups_agree_bitwise(N, Hq, Hkv, d, causal):
     prob = inputs.make_dense(B=36, N=N, Hq=Hq, Hkv=Hkv, d=d, causal=causal, seed=9300 + N)
     Q, K, V, dO = (pu.to_gpu(x, prob.dtype) for x in (prob.Q, prob.K, prob.V, prob.dO))
     O, L = binding.fa_fwd(Q, K, V, prob.scale, causal)
-    grads = binding.fa_bwd(Q, K, V, O, dO, L, prob.scale, causal)
+
+    def two_kernels(q, k, v, o, do, lse):  # (fa_bwd may take one kernel for short sequences; this entry point does not)
+        grads = [torch.empty_like(x) for x in (q, k, v)]
+        ws = torch.empty(binding.fa_bwd_workspace_bytes(q.shape[0], Hq, Hkv, N, d), dtype=torch.uint8, device="cuda")
+        binding.fa_bwd_stages(q, k, v, o, do, lse, prob.scale, causal, 7, *grads, ws)
+        return grads
+
+    if d == 64:
+        assert (large_workgroups(N, 36 * Hq, False) != large_workgroups(N, Hq, False)) == (N not in (257, 640))
+        assert causal or (large_workgroups(N, 36 * Hkv, False) != large_workgroups(N, Hkv, False)) == (N != 640)
+    grads = two_kernels(Q, K, V, O, dO, L)
     for s in (0, 17, 35):
-        alone = binding.fa_bwd(*(x[s:s + 1].contiguous() for x in (Q, K, V, O, dO, L)), prob.scale, causal)
+        alone = two_kernels(*(x[s:s + 1].contiguous() for x in (Q, K, V, O, dO, L)))
         for name, x, y in zip(("dQ", "dK", "dV"), grads, alone):
             assert torch.equal(x[s], y[0]), name
 
 
+def four_wavefronts(N, Nk, pairs, d, causal):
+    """Whether the plain forward pass takes its form of four wavefronts: N queries on Nk keys, (sequence, query head) pairs."""
+    small = -(-N // 128) * pairs
+    if N <= 128 or small <= 256:
+        return True
+    if causal:
+        return small <= (768 if d == 64 else 512)
+    return 512 < small <= 768
+
+
+def whole_and_single(N, Nk, B, Hq, Hkv, d, grow, dtype, causal, last_value=None):
+    """B sequences, which take the forward form of eight wavefronts, and some of them alone, which take that of four:
+    [(O, L of the sequence in the batch, O, L alone)]."""
+    assert four_wavefronts(N, Nk, Hq, d, causal) and not four_wavefronts(N, Nk, B * Hq, d, causal)
+    g = torch.Generator(device="cuda").manual_seed(9370 + N + Nk)
+    et = torch.bfloat16 if dtype == "bf16" else torch.float16
+    Q, K, V = (torch.randn(s, generator=g, device="cuda", dtype=et) for s in ((B, N, Hq, d), (B, Nk, Hkv, d), (B, Nk, Hkv, d)))
+    K *= torch.linspace(1, grow, Nk, device="cuda").view(1, Nk, 1, 1).to(et)
+    if last_value is not None:
+        V[:, Nk - 1] = last_value
+    O, L = binding.fa_cross_fwd(Q, K, V, d ** -0.5, causal)
+    alone = lambda s: binding.fa_cross_fwd(*(x[s:s + 1].contiguous() for x in (Q, K, V)), d ** -0.5, causal)
+    return [(O[s], L[s], *(x[0] for x in alone(s))) for s in (0, B // 2, B - 1)]
+
+
 # (both sides of every edge of the four-wavefront forward kernel: blocks of 128 rows, 64 keys, wavefronts of 32 rows that see
-# fewer blocks than their workgroup; B sequences take the form of eight wavefronts, one alone that of four, and d = 64
-# causal with `grow` = 8 so that the reference of the softmax moves in the middle of a row)
+# fewer blocks than their workgroup; `grow` = 8 so that the reference of the softmax moves in the middle of a row)
 @pytest.mark.parametrize("causal", [False, True])
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 @pytest.mark.parametrize("N,Nk,B,Hq,Hkv,d,grow", [(129, 129, 72, 8, 8, 64, 1), (192, 192, 72, 8, 4, 128, 1), (257, 257, 48, 8, 8, 128, 8),
@@ -157,17 +191,18 @@ def test_small_and_large_workgroups_agree_bitwise(N, Hq, Hkv, d, causal):
                                                  (130, 511, 72, 8, 8, 128, 1), (200, 263, 72, 8, 8, 64, 1)])
 def test_forms_of_the_forward_pass_agree_bitwise(N, Nk, B, Hq, Hkv, d, grow, dtype, causal):
     """The form of the forward kernel is chosen by the size of the grid; a sequence's results do not depend on it."""
-    small = -(-N // 128) * Hq
-    assert small <= 256 and B * small > (768 if d == 64 or not causal else 512)
-    g = torch.Generator(device="cuda").manual_seed(9370 + N + Nk)
-    et = torch.bfloat16 if dtype == "bf16" else torch.float16
-    Q, K, V = (torch.randn(s, generator=g, device="cuda", dtype=et) for s in ((B, N, Hq, d), (B, Nk, Hkv, d), (B, Nk, Hkv, d)))
-    K *= torch.linspace(1, grow, Nk, device="cuda").view(1, Nk, 1, 1).to(et)
-    V[:, Nk - 1] = float("inf")  # the last key: rows that do not see it stay clear of it in the same places
-    O, L = binding.fa_cross_fwd(Q, K, V, d ** -0.5, causal)
-    for s in (0, B // 2, B - 1):
-        o, l = binding.fa_cross_fwd(Q[s:s + 1].contiguous(), K[s:s + 1].contiguous(), V[s:s + 1].contiguous(), d ** -0.5, causal)
-        assert torch.equal(O[s].view(torch.int16), o[0].view(torch.int16)) and torch.equal(L[s], l[0])
+    for O, L, o, l in whole_and_single(N, Nk, B, Hq, Hkv, d, grow, dtype, causal):
+        assert torch.isfinite(O).all() and torch.isfinite(L).all() and torch.equal(O, o) and torch.equal(L, l)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("N,Nk,B,Hq,Hkv,d", [(257, 257, 48, 8, 8, 128), (320, 320, 48, 8, 2, 64)])
+def test_forms_of_the_forward_pass_keep_an_infinite_value_to_the_same_rows(N, Nk, B, Hq, Hkv, d, dtype):
+    """The last key's value is infinite: under the causal rule the rows that visit no block of 64 keys with it stay clear of
+    it, and both forms agree on which rows those are."""
+    for O, L, o, l in whole_and_single(N, Nk, B, Hq, Hkv, d, 1, dtype, True, float("inf")):
+        assert torch.isfinite(O[:(Nk - 1) // 64 * 64]).all() and not torch.isfinite(O[-1]).any()
+        assert torch.equal(O.view(torch.int16), o.view(torch.int16)) and torch.equal(L, l)
 
 
 def large_workgroups(n, pairs, short_too):

@@ -1038,17 +1038,24 @@ static hipError_t launch_fwd_split(const FwdArgs& a, int causal, hipStream_t st)
 // Whether the plain forward pass takes the four-wavefront form (fa_stream.hip) with its blocks of 128 rows. Same bits; the line is
 // where it was measured to win (MI355X, bfloat16, us from 256-row blocks to 128-row ones):
 //  * one block of 128 rows or less: the other half of a 256-row block is padding (128 x 128, 8 heads of 128: 41.9 -> 24.8).
-//  * causal: up to 512 workgroups of 128 rows, two per compute unit (1 x 1024, 64 heads of 128: 512 workgroups, 30.0 -> 26.5;
-//    5 x 1024, 16 heads: 640, 31.9 -> 32.5); at d = 64 up to 768 (6 x 1024, 16 heads: 27.3 -> 24.5; 8 x 1024: 1024,
-//    29.7 -> 29.1, 16 x 256, 32 heads: 1024, 18.0 -> 18.2).
-//  * without the mask all chains are equally long: up to 256 workgroups, one per compute unit (1 x 1024, 32 heads of 128:
-//    26.5 -> 22.0; 3 x 1024, 16 heads: 384, 30.5 -> 33.4), and from 513 to 768, where 256-row blocks need a second
-//    round for a few (5 x 1024, 16 heads: 58.0 -> 50.9; 6 x 1024: 768, 60.8 -> 54.8; 8 x 1024: 1024, 65.9 -> 69.9).
-static bool stream_form(int d, int causal, int n, int pairs) {
-  const long small = (long)((n + 127) / 128) * pairs;
-  if (n <= 128) return true;
-  if (causal) return small <= (d == 64 ? 768 : 512);
-  return small <= 256 || (small > 512 && small <= 768);
+//  * up to 256 workgroups of 128 rows, one per compute unit (1 x 1024, 32 heads of 128, no mask: 26.5 -> 22.0; 2 x 256 on 8192 keys,
+//    64 heads: 171 -> 166).
+//  * causal, where the chains are of uneven length: up to 512 workgroups, two per compute unit (1 x 1024, 64 heads of 128: 512
+//    workgroups, 30.0 -> 26.5; 5 x 1024, 16 heads: 640, 31.9 -> 32.5); at d = 64 up to 768 (6 x 1024, 16 heads: 27.3 ->
+//    24.5; 8 x 1024: 1024, 29.7 -> 29.1, 16 x 256, 32 heads: 1024, 18.0 -> 18.2). Queries at the end of many more keys than
+//    they are make chains of nearly equal length, so this holds up to twice as many keys as queries (3 x 1024, 16 heads
+//    of 128, on 2048 keys 49.7 -> 48.1, on 4096 92.0 -> 99.3, on 16384 373 -> 424; 4 x 256, 64 heads, on 1024: 37.1 -> 42.4), at
+//    d = 64 up to four times (3 x 1024, 16 heads, on 4096 keys 71.0 -> 66.0, on 8192 132 -> 134, on 32768 511 -> 546).
+//  * equally long chains (no mask, or d = 64 and more keys than that): also from 513 to 768 workgroups, where 256-row blocks
+//    need a second round for a few (5 x 1024, 16 heads of 128: 58.0 -> 50.9; 6 x 1024: 768, 60.8 -> 54.8; 8 x 1024: 1024, 65.9 ->
+//    69.9; 3 x 1024: 384, 30.5 -> 33.4), up to sixteen times as many keys as queries (5 x 1024, 16 heads of 128, on 16384 keys 710 ->
+//    677, 6 x 1024 738 -> 747; 6 x 256, 64 heads, on 4096 226 -> 229, on 8192 433 -> 449), causal up to eight times (d = 64,
+//    6 x 256, 64 heads, on 2048 66.7 -> 66.1, on 4096 141 -> 152; 5 x 1024, 16 heads, on 16384 449 -> 435).
+static bool stream_form(int d, int causal, int n, int nk, int pairs) {
+  const long small = (long)((n + 127) / 128) * pairs, keys = nk, rows = n;
+  if (n <= 128 || small <= 256) return true;
+  if (causal && keys <= (d == 64 ? 4 : 2) * rows) return small <= (d == 64 ? 768 : 512);
+  return !(causal && d == 128) && small > 512 && small <= 768 && keys <= (causal ? 8 : 16) * rows;
 }
 
 // RAGGED: a.p.cu_seqlens is set.
@@ -1086,7 +1093,7 @@ static hipError_t launch_fwd_d(const FwdArgs& a, int causal, hipStream_t st) {
     else hipLaunchKernelGGL((fwd_kernel<D, false, false, F16, true, false, false, kNoPattern, D, RAGGED>), grid, block, 0, st, a);
     return hipGetLastError();
   }
-  if (stream_form(D, causal, a.p.N, a.p.Hq * a.p.nseq)) return launch_fwd_stream(a, D, causal, st);
+  if (stream_form(D, causal, a.p.N, a.p.Nk, a.p.Hq * a.p.nseq)) return launch_fwd_stream(a, D, causal, st);
   if constexpr (D == 128 && !RAGGED) {
     // chained items (fwd_chain_kernel): dense batches of short sequences (at most 16 key blocks:
     // +15% at N = 512; from N = 2048 on the start-up no longer matters and the fixed assignment

@@ -162,9 +162,9 @@ def four_wavefronts(N, Nk, pairs, d, causal):
     small = -(-N // 128) * pairs
     if N <= 128 or small <= 256:
         return True
-    if causal:
+    if causal and Nk <= (4 if d == 64 else 2) * N:
         return small <= (768 if d == 64 else 512)
-    return 512 < small <= 768
+    return not (causal and d == 128) and 512 < small <= 768 and Nk <= (8 if causal else 16) * N
 
 
 def whole_and_single(N, Nk, B, Hq, Hkv, d, grow, dtype, causal, last_value=None):
@@ -183,12 +183,15 @@ def whole_and_single(N, Nk, B, Hq, Hkv, d, grow, dtype, causal, last_value=None)
 
 
 # (both sides of every edge of the four-wavefront forward kernel: blocks of 128 rows, 64 keys, wavefronts of 32 rows that see
-# fewer blocks than their workgroup; `grow` = 8 so that the reference of the softmax moves in the middle of a row)
+# fewer blocks than their workgroup; `grow` = 8 so that the reference of the softmax moves in the middle of a row; two lengths,
+# on either side of the ratios that the choice of the form goes by: with 2, 4, 8 and 16 times as many keys as queries, and more)
 @pytest.mark.parametrize("causal", [False, True])
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 @pytest.mark.parametrize("N,Nk,B,Hq,Hkv,d,grow", [(129, 129, 72, 8, 8, 64, 1), (192, 192, 72, 8, 4, 128, 1), (257, 257, 48, 8, 8, 128, 8),
                                                  (320, 320, 48, 8, 2, 64, 8), (449, 449, 40, 8, 8, 128, 1),
-                                                 (130, 511, 72, 8, 8, 128, 1), (200, 263, 72, 8, 8, 64, 1)])
+                                                 (130, 511, 72, 8, 8, 128, 1), (200, 263, 72, 8, 8, 64, 1),
+                                                 (129, 259, 24, 8, 8, 128, 1), (160, 641, 24, 8, 4, 64, 8),
+                                                 (129, 2065, 40, 8, 2, 64, 1)])
 def test_forms_of_the_forward_pass_agree_bitwise(N, Nk, B, Hq, Hkv, d, grow, dtype, causal):
     """The form of the forward kernel is chosen by the size of the grid; a sequence's results do not depend on it."""
     for O, L, o, l in whole_and_single(N, Nk, B, Hq, Hkv, d, grow, dtype, causal):

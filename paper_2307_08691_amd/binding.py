@@ -7,7 +7,9 @@ is no fallback: if the shared library is missing, loading raises.
 from __future__ import annotations
 
 import ctypes
+import importlib
 import os
+import warnings
 from typing import Optional, Tuple
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -151,15 +153,20 @@ def _ptr(t) -> int:
 
 
 def _load_host():
-    """Look for the native form of the usual calls, which takes the library's entry points by address (fa_host.cpp)."""
+    """Look for the native form of the usual calls, which takes the library's entry points by address (fa_host.cpp). It is
+    optional: one that does not load (built against another torch or Python) is reported, and the calls are made in Python."""
     global _host
     import torch
-    _host = False
+    host = False
     if hasattr(torch._C, "_cuda_getCurrentRawStream") and os.path.exists(os.path.join(HERE, "_host.so")):
-        from . import _host as host
-        addresses = {n: ctypes.cast(getattr(load(), n), _c_void_p).value for n in host.entry_names()}
-        host.init(torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream, torch.nn.Parameter, addresses)
-        _host = host
+        try:
+            host = importlib.import_module(__package__ + "._host")
+        except ImportError as e:
+            warnings.warn(f"the native form of the usual calls does not load, they are made in Python: {e}", RuntimeWarning, stacklevel=2)
+        else:
+            addresses = {n: ctypes.cast(getattr(load(), n), _c_void_p).value for n in host.entry_names()}
+            host.init(torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream, torch.nn.Parameter, addresses)
+    _host = host
 
 
 def _stream() -> int:

@@ -1,6 +1,7 @@
 """The native marshalling of the usual calls (csrc/fa_host.cpp): it makes the call that binding.py would make, and leaves
 whatever is not an ordinary call to it."""
 import itertools
+import sys
 
 import pytest
 
@@ -32,6 +33,14 @@ def test_host_tensors_and_other_objects_are_left_to_the_binding(host):
     assert host.varlen_bwd() is None and host.kvcache_fwd() is None
     with pytest.raises(ValueError):
         binding.fa_fwd(x, x, x, 0.125, True)
+
+
+def test_an_extension_that_does_not_load_is_reported_and_left_alone(host, monkeypatch):
+    monkeypatch.setitem(sys.modules, binding.__package__ + "._host", None)  # its import raises ImportError
+    monkeypatch.setattr(binding, "_host", None)
+    with pytest.warns(RuntimeWarning, match="does not load"):
+        binding._load_host()
+    assert binding._host is False  # looked for once; the calls are made in Python
 
 
 def _calls(dtype):

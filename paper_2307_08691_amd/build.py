@@ -57,7 +57,8 @@ def build_host() -> None:
 
 def build(verbose: bool = False) -> str:
     """Compile every HIP source (in parallel, one object each) and link the shared library.
-    Always recompiles."""
+    Always recompiles. The extension module is optional: without torch or a C++ compiler that takes it the library is built all
+    the same, the reason is printed, and none is left from an earlier build (it would be older than the library)."""
     import concurrent.futures
     import tempfile
     with tempfile.TemporaryDirectory(prefix="fa_build_") as tmp:
@@ -69,7 +70,12 @@ def build(verbose: bool = False) -> str:
             for err in ex.map(_compile, SOURCES, objs):
                 if verbose and err:
                     print(err, file=sys.stderr)
-            host.result()
+            try:
+                host.result()
+            except Exception as e:
+                print(f"no {os.path.basename(HOST_LIB)}, the usual calls will be made in Python: {e}", file=sys.stderr)
+                if os.path.exists(HOST_LIB):
+                    os.remove(HOST_LIB)
         r = subprocess.run([hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs], capture_output=True, text=True)
         if r.returncode != 0:
             raise RuntimeError("link failed:\n" + r.stderr)

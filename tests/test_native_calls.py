@@ -2,6 +2,7 @@
 whatever is not an ordinary call to it."""
 import itertools
 import sys
+import types
 
 import pytest
 
@@ -41,6 +42,23 @@ def test_an_extension_that_does_not_load_is_reported_and_left_alone(host, monkey
     with pytest.warns(RuntimeWarning, match="does not load"):
         binding._load_host()
     assert binding._host is False  # looked for once; the calls are made in Python
+
+
+def test_a_build_without_the_extension_still_makes_the_library(monkeypatch, tmp_path, capsys):
+    from paper_2307_08691_amd import build as fa_build
+    stale = tmp_path / "_host.so"
+    stale.write_bytes(b"of an earlier build")
+
+    def no_compiler():
+        raise RuntimeError("no C++ compiler")
+
+    linked = []
+    monkeypatch.setattr(fa_build, "HOST_LIB", str(stale))
+    monkeypatch.setattr(fa_build, "build_host", no_compiler)
+    monkeypatch.setattr(fa_build, "_compile", lambda source, obj: "")
+    monkeypatch.setattr(fa_build.subprocess, "run", lambda cmd, **kw: linked.append(cmd) or types.SimpleNamespace(returncode=0, stderr=""))
+    assert fa_build.build() == fa_build.LIB and len(linked) == 1
+    assert not stale.exists() and "no C++ compiler" in capsys.readouterr().err
 
 
 def _calls(dtype):

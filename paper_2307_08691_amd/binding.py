@@ -134,6 +134,12 @@ def load() -> ctypes.CDLL:
     return _lib
 
 
+def forget() -> None:
+    """Drop the loaded library, and the native calls that hold its addresses: the next call loads what has been built since."""
+    global _lib, _host
+    _lib = _host = None
+
+
 def status_string(status: int) -> str:
     return load().fa_status_string(status).decode()
 

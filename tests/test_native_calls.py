@@ -61,6 +61,15 @@ def test_a_build_without_the_extension_still_makes_the_library(monkeypatch, tmp_
     assert not stale.exists() and "no C++ compiler" in capsys.readouterr().err
 
 
+def test_after_a_build_nothing_of_the_old_library_is_called(host, monkeypatch):
+    import __graft_entry__
+    from paper_2307_08691_amd import build as fa_build
+    monkeypatch.setattr(fa_build, "build", lambda verbose=False: fa_build.LIB)
+    old = binding.load()
+    __graft_entry__.build()
+    assert binding._host is None and binding.load() is not old
+
+
 def _calls(dtype):
     """name -> (native call, the same through the Python of the binding: outputs passed in)."""
     g = torch.Generator(device="cuda").manual_seed(22000)

@@ -360,6 +360,32 @@ __device__ __forceinline__ float max_with_partner32(float x) {
   return fmaxf(__builtin_bit_cast(float, (int)sw[0]), __builtin_bit_cast(float, (int)sw[1]));
 }
 
+__device__ __forceinline__ float max3(float a, float b, float c) { return __builtin_fmaxf(__builtin_fmaxf(a, b), c); }
+// Largest score of this lane's row in a block of 64 keys (S^T: two accumulators of 32 keys, the row's other half in the partner lane).
+__device__ __forceinline__ float row_maximum(const f32x16 (&S)[2]) {
+  float mx = max3(S[0][0], S[0][1], S[1][0]);
+#pragma unroll
+  for (int r = 2; r < 16; r += 2) mx = max3(mx, S[0][r], S[0][r + 1]);
+  mx = max3(mx, S[1][1], S[1][2]);
+  mx = fmaxf(mx, S[1][3]);
+#pragma unroll
+  for (int r = 4; r < 16; r += 2) mx = max3(mx, S[1][r], S[1][r + 1]);
+  return max_with_partner32(mx);
+}
+// The reference of the running softmax is only advanced (and O, l rescaled) when a lane's share
+// of a block's row sum exceeds 2^kLazyLog2 (instantiations without the fast path: when some
+// row's maximum outgrew the reference by that factor); until then exponentials are taken against
+// the older reference and may reach 2^kLazyLog2. Half precision operands end at 65504 = 2^16;
+// bfloat16 has float32's range, and the wider margin saves most of the remaining advances when the
+// scores spread widely (3x the usual range: the row maximum grows by some 20 bits over 16k keys).
+// All 16-bit forward kernels go by these: the size of the grid chooses between forms whose results are the same bits.
+template <bool F16>
+constexpr int kLazyLog2 = F16 ? 8 : 20;
+template <bool F16>
+__device__ __forceinline__ bool reference_outgrown(float share) {
+  return __builtin_amdgcn_ballot_w64(share > (float)(1 << kLazyLog2<F16>)) != 0;
+}
+
 __device__ __forceinline__ float sum_with_partner32(float x) {
   int xi = __builtin_bit_cast(int, x);
   auto sw = __builtin_amdgcn_permlane32_swap(xi, xi, false, false);

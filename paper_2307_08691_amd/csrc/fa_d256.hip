@@ -26,7 +26,6 @@ namespace {
 
 constexpr int kHalf = 128;          // columns of one half tile
 constexpr int kRowB = 2 * kHalf;    // its row bytes
-constexpr int kLazyLog2Half = 8, kLazyLog2Bf16 = 20;  // see kFwdLazyLog2Half in fa_fwd.hip
 
 // Copies of a 256-wide tile of ROWS rows (left | right half) by NW wavefronts: one wavefront instruction fetches four rows of a
 // half tile. The lane offsets of an interior tile are computed once; at the end of a sequence rows past the last repeat it.
@@ -66,8 +65,6 @@ struct TileCopier {
     dma16_uniform(t.base + half * kHalf, t.off[u], dst + half * HALFB + (wave + NW * u) * 1024);
   }
 };
-
-__device__ __forceinline__ float max3f(float a, float b, float c) { return __builtin_fmaxf(__builtin_fmaxf(a, b), c); }
 
 // lane constants of the operand addressing inside one half tile (fa_lds.h)
 struct LaneAddr {
@@ -177,16 +174,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
         for (int r = 0; r < 16; ++r) S[kt][r] = 32 * kt + acc_row(r, 0) > lim ? -INFINITY : S[kt][r];
     }
   };
-  auto row_maximum = [&]() {
-    float mx = max3f(S[0][0], S[0][1], S[1][0]);
-#pragma unroll
-    for (int r = 2; r < 16; r += 2) mx = max3f(mx, S[0][r], S[0][r + 1]);
-    mx = max3f(mx, S[1][1], S[1][2]);
-    mx = fmaxf(mx, S[1][3]);
-#pragma unroll
-    for (int r = 4; r < 16; r += 2) mx = max3f(mx, S[1][r], S[1][r + 1]);
-    return max_with_partner32(mx);
-  };
 
   // S_0
   wait_vmem_upto<2 * CPT>();
@@ -204,7 +191,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   }
   settled(S[0], S[1]);
   mask(0);
-  m = row_maximum();
+  m = row_maximum(S);
 
   // One wavefront per SIMD has to overlap its own matrix and vector work. Iteration j:
   //   O^T += V_{j-1}^T P_{j-1}^T (line 10)     with the exponentials of block j between the MFMAs (line 9)
@@ -259,8 +246,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     });
     consume(std::integral_constant<int, NPV - 1>{});
     asm volatile("" ::: "memory");  // (the operands requested for the next stream are not to be requested later)
-    if (__builtin_amdgcn_ballot_w64(rs0 + rs1 > (float)(1 << (F16 ? kLazyLog2Half : kLazyLog2Bf16))) != 0) {
-      const float m_new = fmaxf(m, row_maximum());
+    if (reference_outgrown<F16>(rs0 + rs1)) {
+      const float m_new = fmaxf(m, row_maximum(S));
       const float alpha = fast_exp2((m - m_new) * c2);
       l *= alpha;
       m = m_new;

@@ -43,13 +43,6 @@ constexpr int kFwdAheadQK = 4, kFwdAheadPV = 3;
 // Wave priority of a matrix phase: the MFMA stream must not wait behind the other group's
 // vector work (measured: 3-5% slower at d = 128 without it).
 #define FA_FWD_MATRIX_PRIO 2
-// The reference of the running softmax is only advanced (and O, l rescaled) when a lane's share
-// of a block's row sum exceeds 2^kFwdLazyLog2 (instantiations without the fast path: when some
-// row's maximum outgrew the reference by that factor); until then exponentials are taken against
-// the older reference and may reach 2^kFwdLazyLog2. Half precision operands end at 65504 = 2^16;
-// bfloat16 has float32's range, and the wider margin saves most of the remaining advances when the
-// scores spread widely (3x the usual range: the row maximum grows by some 20 bits over 16k keys).
-constexpr int kFwdLazyLog2Half = 8, kFwdLazyLog2Bf16 = 20;
 // d = 128: workgroups that take several items in a row and overlap an item's start-up with the
 // end of the one before (fwd_chain_kernel), for sequences of at most kFwdChainMaxN keys
 constexpr int kFwdChainMaxN = 1024;
@@ -62,8 +55,6 @@ constexpr int kFwdChainMaxN = 1024;
 // without row maxima, whose second copy of the scores does not fit (fp16, 4 x 1777 tokens, 16 heads, MI355X:
 // 109 -> 98 us all the same). Not for the elementwise mask (more LDS).
 constexpr bool fwd_two_per_cu(int D, bool mask) { return D == 64 && !mask; }
-
-__device__ __forceinline__ float max3(float a, float b, float c) { return __builtin_fmaxf(__builtin_fmaxf(a, b), c); }
 
 // SPLIT (forward only, few query rows against many keys): the workgroups of one (sequence,
 // key/value head) also split the KEY sequence, each writing a normalised partial O and its
@@ -466,7 +457,7 @@ __global__ __launch_bounds__(512)
     // the same reference whatever it is, and rescaling O (line 10) by exp(m_old - m_new) only
     // matters for the range of the numbers. So the row maximum is NOT computed for every block.
     // The block's exponentials are taken against the reference as it stands; only if some lane's
-    // share of a row sum then exceeds 2^kFwdLazyLog2 (which also catches an overflow to inf)
+    // share of a row sum then exceeds 2^kLazyLog2 (which also catches an overflow to inf)
     // is the maximum of the block found, the reference advanced to it, O and l rescaled, and the
     // exponentials taken again. After the first few blocks that is rare: the fast path saves the
     // 16 three-way maxima, the exchange with the partner lane and the comparison per block.
@@ -476,23 +467,16 @@ __global__ __launch_bounds__(512)
     bool advance = !FAST || t == tb || (GUARD && __builtin_amdgcn_ballot_w64(m == -INFINITY) != 0);
     if (!advance) {
       exponentials(m * cs);
-      advance = __builtin_amdgcn_ballot_w64(rs0 + rs1 > (float)(1 << (F16 ? kFwdLazyLog2Half : kFwdLazyLog2Bf16))) != 0;
+      advance = reference_outgrown<F16>(rs0 + rs1);
     }
     if (advance) {
-      float mx = max3(S[0][0], S[0][1], S[1][0]);
-#pragma unroll
-      for (int r = 2; r < 16; r += 2) mx = max3(mx, S[0][r], S[0][r + 1]);
-      mx = max3(mx, S[1][1], S[1][2]);
-      mx = fmaxf(mx, S[1][3]);
-#pragma unroll
-      for (int r = 4; r < 16; r += 2) mx = max3(mx, S[1][r], S[1][r + 1]);
-      mx = max_with_partner32(mx);
-      const float m_new = fmaxf(m, mx);
+      const float m_new = fmaxf(m, row_maximum(S));
       // column 0 is visible to every row and blocks are walked in ascending order, so m_new is
       // finite from the first block on and exp2(-inf) = 0 covers the start (not so with split
       // keys or a mask: GUARD). Without the fast path the reference is advanced only when some
-      // row's maximum outgrew it by a factor 2^kFwdLazyLog2.
-      if (FAST ? !GUARD || __builtin_amdgcn_ballot_w64(m_new > m) != 0 : __builtin_amdgcn_ballot_w64((m_new - m) * cs > (float)(F16 ? kFwdLazyLog2Half : kFwdLazyLog2Bf16)) != 0) {
+      // row's maximum outgrew it by a factor 2^kLazyLog2.
+      if (FAST ? !GUARD || __builtin_amdgcn_ballot_w64(m_new > m) != 0
+               : __builtin_amdgcn_ballot_w64((m_new - m) * cs > (float)kLazyLog2<F16>) != 0) {
         // (split, mask: a row that has still seen no key has m = m_new = -inf and nothing to rescale)
         const float alpha = GUARD && m_new == -INFINITY ? 1.f : fast_exp2((m - m_new) * cs);
         l *= alpha;
@@ -822,18 +806,10 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     bool advance = j == 0;
     if (!advance) {
       exponentials(m * c2);
-      advance = __builtin_amdgcn_ballot_w64(rs0 + rs1 > (float)(1 << (F16 ? kFwdLazyLog2Half : kFwdLazyLog2Bf16))) != 0;
+      advance = reference_outgrown<F16>(rs0 + rs1);
     }
     if (advance) {
-      float mx = max3(S[0][0], S[0][1], S[1][0]);
-#pragma unroll
-      for (int r = 2; r < 16; r += 2) mx = max3(mx, S[0][r], S[0][r + 1]);
-      mx = max3(mx, S[1][1], S[1][2]);
-      mx = fmaxf(mx, S[1][3]);
-#pragma unroll
-      for (int r = 4; r < 16; r += 2) mx = max3(mx, S[1][r], S[1][r + 1]);
-      mx = max_with_partner32(mx);
-      const float m_new = fmaxf(m, mx);
+      const float m_new = fmaxf(m, row_maximum(S));
       const float alpha = fast_exp2((m - m_new) * c2);
       l *= alpha;
 #pragma unroll

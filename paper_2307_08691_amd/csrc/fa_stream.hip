@@ -18,9 +18,6 @@
 namespace fa {
 
 namespace {
-constexpr int kLazyLog2Half = 8, kLazyLog2Bf16 = 20;  // see kFwdLazyLog2Half in fa_fwd.hip
-__device__ __forceinline__ float max3s(float a, float b, float c) { return __builtin_fmaxf(__builtin_fmaxf(a, b), c); }
-
 // Copies of a tile of 64 rows of D elements by four wavefronts.
 template <int D>
 struct StreamCopier {
@@ -162,16 +159,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         for (int r = 0; r < 16; ++r) S[kt][r] = 32 * kt + acc_row(r, 0) > lim ? -INFINITY : S[kt][r];
     }
   };
-  auto row_maximum = [&]() {
-    float mx = max3s(S[0][0], S[0][1], S[1][0]);
-#pragma unroll
-    for (int r = 2; r < 16; r += 2) mx = max3s(mx, S[0][r], S[0][r + 1]);
-    mx = max3s(mx, S[1][1], S[1][2]);
-    mx = fmaxf(mx, S[1][3]);
-#pragma unroll
-    for (int r = 4; r < 16; r += 2) mx = max3s(mx, S[1][r], S[1][r + 1]);
-    return max_with_partner32(mx);
-  };
   wait_vmem_upto<2 * CPT>();
   bf16x8 Qf[KS];
   row_operands<D>(Qf, qst, lane);
@@ -188,7 +175,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   }
   settled(S[0], S[1]);
   mask(0);
-  m = row_maximum();
+  m = row_maximum(S);
 
   // Iteration j:
   //   O^T += V_{j-1}^T P_{j-1}^T (line 10)     with the exponentials of block j between the MFMAs (line 9)
@@ -251,8 +238,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     });
     consume(std::integral_constant<int, NPV - 1>{});
     asm volatile("" ::: "memory");  // (the operands requested for the next stream are not to be requested later)
-    if (__builtin_amdgcn_ballot_w64(rs0 + rs1 > (float)(1 << (F16 ? kLazyLog2Half : kLazyLog2Bf16))) != 0) {
-      const float m_new = fmaxf(m, row_maximum());
+    if (reference_outgrown<F16>(rs0 + rs1)) {
+      const float m_new = fmaxf(m, row_maximum(S));
       const float alpha = fast_exp2((m - m_new) * c2);
       l *= alpha;
       m = m_new;

@@ -963,9 +963,10 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
   const int wrow0 = i0 + 32 * w;
   const int row = wrow0 + lq;
   const int rowc = row < n ? row : n - 1;
-  // whole rows through LDS, below (not for windows at d = 64, whose short walks are all start-up and feel the second latency more:
-  // 2 x 6997, window of 223, 32 heads on 16, forward + backward 361 us without, 363.5 with it)
-  constexpr bool QROWS = !PAD && !(LOCAL == kWindow && D == 64);
+  // Whole rows through LDS, below: for windows too, whose short walks are mostly start-up (backward of windows of 128 to 2048 keys,
+  // nine shapes per head dimension: d = 128 0.1 to 5% faster with it, 2 x 8192, 16 heads, 128 keys 247.7 -> 245.0 us; d = 64 within 0.5%,
+  // 2 x 6997, 32 heads on 16, 223 keys 278.2 -> 279.4, 1 x 1500, 8 heads, 101 keys 33.4 -> 32.7).
+  constexpr bool QROWS = !PAD;
   bf16x8 Qf[KS], dOf[KS];
   if constexpr (!QROWS) {
     const __bf16* qp = a.Q + ((si.tok0 + rowc) * p.Hq + h) * dh + 8 * hh;

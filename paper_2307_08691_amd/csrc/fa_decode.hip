@@ -103,8 +103,10 @@ __global__ __launch_bounds__(512) void fwd_decode_kernel(FwdArgs a) {
   u32x4 Kr[2][KS];
   const int pmask = a.block_table ? (1 << a.page_log2) - 1 : 0;
   // Pages of this wavefront's tiles t_begin + w + 8 i: lane i % 64 holds the one of tile i. (Looked up one by one each was a
-  // memory latency in front of its tile's requests. The first two, which the start waits for, go the shorter way of a
-  // scalar load all the same: 44 sequences of up to 768 keys, 16 heads of 64: 25.5 us so, 26.6 without.)
+  // memory latency in front of its tile's requests: 50 sequences of up to 7680 keys, 32 heads on 8 of 64: 123 us so, 104 now.)
+  // The first two, which the start waits for, go the shorter way of a scalar load. That is even on average: without it 30 paged
+  // batches of 1 .. 96 sequences took 0.96 to 1.04 of the time (44 of up to 768 keys, 16 heads of 64: 23.4 us so, 24.2 without;
+  // 4 of up to 2048, 32 heads on 8 of 128: 14.1 and 13.7).
   int pages = 0;
   auto load_pages = [&](int t0) {
     const int t = t0 + 8 * lane < t_end ? t0 + 8 * lane : t_end - 1;

@@ -2,10 +2,9 @@
 """Benchmark of the attention hot path on one MI355X.
 
 One "step" is one pass of the whole hot path over one batch of synthetic input, through the
-entry points a user calls: the forward (Algorithm 1) followed by the backward (Algorithm 2: D
-pre-pass, dK/dV kernel, dQ kernel) of the workload named in `config.workload`, inputs resident
-in HBM. Dense workloads run fa_fwd + fa_bwd, packed ragged ones fa_varlen_fwd + fa_varlen_bwd,
-workloads with two lengths fa_cross_*, half precision fa_cross_*_f16, dropout and mask workloads
+entry points a user calls: the forward (Algorithm 1) followed by the backward (Algorithm 2)
+of the workload named in `config.workload`, inputs resident in HBM. Dense workloads run
+fa_fwd + fa_bwd, packed ragged ones fa_varlen_fwd + fa_varlen_bwd, workloads with two lengths fa_cross_*, half precision fa_cross_*_f16, dropout and mask workloads
 their own entry points; a handful of query rows against a long cache runs fa_splitkv_fwd alone
 and reports GB/s of compulsory traffic against the HBM roofline. Throughput is counted with the
 paper's formula (section 4.1): forward 4*N^2*d FLOPs per head and sequence, halved under the
@@ -58,21 +57,21 @@ PEAK_HBM_GBS = 8000.0      # MI355X HBM3E peak
 # the kernel sources are the ones they were measured on (`sources`: kernel_sources_id() at the time
 # of the measurement); otherwise `traffic` is null and the stale figure moves to `traffic_recorded`.
 MEASURED_TRAFFIC = {
-    "sources": "1275c74f5718",
-    "d128_n8k_causal": {"fwd_kernel": 687892647, "bwd_dkdv_kernel": 900573335, "bwd_dq_kernel": 755300878},
-    "sweep_d128_n8192_full": {"fwd_kernel": 269782498, "bwd_dkdv_kernel": 405144627, "bwd_dq_kernel": 337872473},
-    "sweep_d64_n8192_causal": {"fwd_kernel": 885046153, "bwd_dkdv_kernel": 882182574, "bwd_dq_kernel": 831279353},
-    "decode_b8_on_8k": {"fwd_decode_kernel": 269298586},
-    "decode_paged_b64_to_8k": {"fwd_decode_kernel": 1019798805},
+    "sources": "b8afe3af4935",
+    "d128_n8k_causal": {"fwd_kernel": 659152324, "bwd_dkdv_kernel": 864215058, "bwd_dq_kernel": 762745717},
+    "sweep_d128_n8192_full": {"fwd_kernel": 269796386, "bwd_dkdv_kernel": 405298506, "bwd_dq_kernel": 337902929},
+    "sweep_d64_n8192_causal": {"fwd_kernel": 882302946, "bwd_dkdv_kernel": 882353737, "bwd_dq_kernel": 831636651},
+    "decode_b8_on_8k": {"fwd_decode_kernel": 271323269},
+    "decode_paged_b64_to_8k": {"fwd_decode_kernel": 1019511473},
 }
 
 
 def kernel_sources_id() -> str:
-    """Short hash of the sources of the bf16 forward, backward and decode kernels (the ones the counter
-    passes cover): identifies what a counter pass measured."""
+    """Short hash of the sources of the bf16 forward, backward and decode kernels at d <= 128 (the ones the counter
+    passes below and the sweep run): identifies what a counter pass measured."""
     d = os.path.join(ROOT, "paper_2307_08691_amd", "csrc")
     h = hashlib.sha1()
-    for f in ("fa_bwd.hip", "fa_common.h", "fa_decode.hip", "fa_fwd.hip", "fa_kernels.h", "fa_lds.h"):
+    for f in ("fa_bwd.hip", "fa_common.h", "fa_decode.hip", "fa_fwd.hip", "fa_kernels.h", "fa_lds.h", "fa_short.hip", "fa_stream.hip"):
         h.update(f.encode())
         h.update(open(os.path.join(d, f), "rb").read())
     return h.hexdigest()[:12]
@@ -82,9 +81,11 @@ def traffic_fields(workload: str, kernel: str) -> dict:
     rec = MEASURED_TRAFFIC.get(workload, {}).get(kernel)
     if rec is None:
         return {"traffic": None}
+    decode = workload.startswith("decode")
+    profile = f"profiles/{'bench' if decode else 'pmc'}_{workload}_{'kernel_stats' if decode else 'kernels'}.md"
     if MEASURED_TRAFFIC["sources"] == kernel_sources_id():
-        return {"traffic": rec, "traffic_from": f"profiles/{'bench' if workload.startswith('decode') else 'pmc'}_{workload}_{'kernel_stats' if workload.startswith('decode') else 'kernels'}.md"}
-    return {"traffic": None, "traffic_recorded": {"bytes": rec, "profile": f"profiles/pmc_{workload}_kernels.md",
+        return {"traffic": rec, "traffic_from": profile}
+    return {"traffic": None, "traffic_recorded": {"bytes": rec, "profile": profile,
                                                   "kernel_sources": MEASURED_TRAFFIC["sources"],
                                                   "note": "measured on other kernel sources than this run's"}}
 
@@ -569,9 +570,9 @@ def main() -> int:
         out["roofline_dq"] = roof(1.5 * fwd_fl, dq_ms, "bwd_dq_kernel")
         out["bwd"]["prep_ms"] = prep_ms  # (a launch of its own only here: fa_bwd computes D inside the dQ kernel)
     else:
-        # no per-kernel entry point for this workload: the backward launches together (with a D pre-pass
-        # only at d = 256), against the 3.5 x forward FLOPs they execute (7 products)
-        out["roofline"] = roof(3.5 * fwd_fl, bwd_ms, ("bwd_prep_kernel + " if prob.d == 256 else "") + "bwd_dkdv_kernel + bwd_dq_kernel")
+        # no per-kernel entry point for this workload: the backward launches together, against the 3.5 x
+        # forward FLOPs they execute (7 products)
+        out["roofline"] = roof(3.5 * fwd_fl, bwd_ms, "bwd_dkdv_kernel + bwd_dq_kernel")
     # what the matrix pipe sustains on this machine with every operand in registers (outside the timed region)
     out["mfma_loop"] = {}
     for key, rnd in (("constant_operands", False), ("random_operands", True)):

@@ -84,13 +84,14 @@ int fa_fwd(const void* Q, const void* K, const void* V, void* O, float* LSE,
  * Backward pass (Algorithm 2). Needs the O and LSE that fa_fwd produced for the
  * same Q, K, V, scale and causal flag. Writes dQ, dK, dV (bfloat16).
  * `workspace` is device scratch of at least fa_bwd_workspace_bytes() bytes,
- * 16-byte aligned; its contents are undefined on entry and on return. It holds
- * D = rowsum(dO o O) (Algorithm 2, line 4). Two kernels are enqueued: a row-block
- * kernel that computes D for its rows and produces dQ by recomputing the
- * probabilities (instead of accumulating dQ across workgroups with atomic adds),
- * then a column-block kernel that produces dK and dV (section 3.2, "Backward
- * pass"). Head dimension 256 runs the D pre-pass as a launch of its own first.
- * All three outputs are bit-reproducible.
+ * 16-byte aligned; its contents are undefined on entry and on return. It is where
+ * D = rowsum(dO o O) (Algorithm 2, line 4) passes from one kernel to the next. Two
+ * kernels are enqueued: a row-block kernel that computes D for its rows and produces
+ * dQ by recomputing the probabilities (instead of accumulating dQ across workgroups
+ * with atomic adds), then a column-block kernel that produces dK and dV (section 3.2,
+ * "Backward pass"). Where it is faster, short sequences (up to 512 tokens, d = 64,
+ * without dropout, window or mask) take ONE kernel instead, with the same bits; it
+ * leaves the workspace untouched. All three outputs are bit-reproducible.
  */
 size_t fa_bwd_workspace_bytes(int B, int Hq, int Hkv, int N, int d);
 int fa_bwd(const void* Q, const void* K, const void* V, const void* O, const void* dO,

@@ -1,7 +1,7 @@
 // Backward pass of exact attention for gfx950 (Algorithm 2 of the paper).
 //
-// (Short sequences at d = 64: one kernel, fa_short.hip.) Three launches on the caller's stream (the plain full backward folds the first into the
-// third, which then runs before the second: two launches, see OWN_D):
+// (Short sequences at d = 64: one kernel, fa_short.hip.) Three launches on the caller's stream (the plain full backward
+// folds the first into the third, which then runs before the second: two launches, see OWN_D):
 //   1. prep:  D = rowsum(dO o O) (Algorithm 2, line 4)
 //   2. dK/dV: one workgroup per block of 256 keys of one (sequence, key/value head)
 //             (section 3.2 "Backward pass"); it loops over the query heads that share the

@@ -6,9 +6,9 @@
 // dQ) or 128 keys (dK/dV) each, and no second wavefront on the SIMD to run the softmax
 // while the first one multiplies. Every kernel is therefore ONE instruction stream in which the vector work of a block
 // stands between MFMAs that do not need it (the order of the source, held by scheduling fences), with one barrier
-// per block. What bounds such a stream is first the number of its instructions (a wavefront alone on its SIMD issues one in
-// about five cycles: six beside an MFMA of 32), then the chip's power: at N = 8192 without the mask the forward kernel
-// keeps the matrix pipe busy 59% of the cycles at 1.73 GHz. Accumulators and operands are placed in the two register
+// per block. What bounds such a stream is the number of its instructions (a wavefront alone on its SIMD issues one in
+// about five cycles: six beside an MFMA of 32): at N = 8192, causal, 2.7 to 3.6 vector instructions per MFMA, and the matrix pipe is
+// busy 52% (forward), 59% (dQ) and 48% (dK/dV) of the cycles at about 2 GHz. Accumulators and operands are placed in the two register
 // files by hand (mfma32_agpr and its kin, fa_common.h). Measured (MI355X, bfloat16, 16k tokens in 8 heads, us, plain
 // loops around the builtin product -> these): forward N = 2048 causal 179 -> 154, N = 8192 without the mask 1111 -> 944;
 // backward 581 -> 521 (25 of them the D pre-pass, now inside the dQ kernel) and 3575 -> 3284.
@@ -229,7 +229,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     static_for<NPV>([&](auto I) {
       constexpr int i = I.value;
       if constexpr (pv) {
-        if constexpr (next) ring.template advance<i, NPV + NS>([&](auto J) { if constexpr (J.value < NPV) return v_operand(vst, J.value); else return k_operand(kst, J.value - NPV); });
+        if constexpr (next)
+          ring.template advance<i, NPV + NS>([&](auto J) {
+            if constexpr (J.value < NPV) return v_operand(vst, J.value);
+            else return k_operand(kst, J.value - NPV);
+          });
         else ring.template advance<i, NPV>([&](auto J) { return v_operand(vst, J.value); });
         mfma32_agpr<F16>(O[i >> 2], ring.at(I), Pp[(i >> 1) & 1][i & 1]);
       }

@@ -144,10 +144,11 @@ struct TileLoader {
 
 // A wavefront's 32 rows of Q (or dO, O) on their way into its registers as whole rows: a lane that loads its own row straight
 // from memory makes every request touch 16 bytes in 64 places, four times the address unit's work, and that, not the
-// memory, is what the start of a workgroup waited for (MI355X, us: backward of 16 x 1024, 32 heads of 64, 362 -> 351, of 2 x 8192, 16 heads
-// of 128, 1555 -> 1546; forward of 1 x 1531, 32 heads on 8 of 128, 32.6 -> 31.7. In fwd_kernel, where Q_i alone comes that way and the first
-// tiles have to be waited for in any case, it gained nothing at d = 128 and lost 4% at d = 64). rows_request() copies the rows into a private piece of LDS that is idle
-// (32 * 2 D bytes); once a hand-written wait covers the copies, row_operands() reads what the lane holds of its row for every MFMA.
+// memory, is what the start of a workgroup waited for (MI355X, us: backward of 16 x 1024, 32 heads of 64, 362 -> 351, of 2 x 8192,
+// 16 heads of 128, 1555 -> 1546; forward of 1 x 1531, 32 heads on 8 of 128, 32.6 -> 31.7. In fwd_kernel, where Q_i alone comes that
+// way and the first tiles have to be waited for in any case, it gained nothing at d = 128 and lost 4% at d = 64). rows_request() copies
+// the rows into a private piece of LDS that is idle (32 * 2 D bytes); once a hand-written wait covers the copies, row_operands() reads
+// what the lane holds of its row for every MFMA.
 template <int D>
 __device__ __forceinline__ void rows_request(char* stage, const __bf16* row0, long stride, int first, int last, int lane) {
   tile_load_async<D, 32, 1>(stage, row0, stride, first, last, 0, lane);

@@ -5,10 +5,11 @@
 // its accumulators, so nothing is summed across workgroups: it visits the rows in tiles of 32, every wavefront forms P
 // and dS of its own 32 (KW = 1) or 2 x 32 (KW = 2) keys, adds to its dK_j, dV_j (lines 12, 16) and leaves dS in LDS, where
 // one phase later two wavefronts, in turn, form the tile's dQ_i = dS K over all keys (line 15; K is in LDS for the whole kernel).
-// Measured (MI355X, bfloat16, 32 x 512, 32 heads, causal, us of the backward): 270 -> 215; 64 x 256: 216 -> 171; 128 x 128: 194 -> 133. What
-// bounds it: half of the time passes with the row tiles left out (a workgroup's K, V, O, dO arrive before its first tile, and beyond
-// 128 tokens there is no second workgroup on the compute unit to fill that time); the rest is the chain of a phase, LDS reads, MFMAs,
-// exponentials, barrier (the exponentials left out: 2 us less, dQ left out: 42).
+// Measured (MI355X, bfloat16, 32 x 512, 32 heads, causal, us of the backward): 270 -> 215; 64 x 256: 216 -> 171; 128 x 128: 194 -> 133.
+// What bounds it: waiting (at 32 x 512 the matrix pipe is busy 18% of the time, LDS 23%, and the wavefronts wait 43% of theirs). Half
+// of the time passed with the row tiles left out (a workgroup's K, V, O, dO arrive before its first tile, and beyond 128 tokens there
+// is no second workgroup on the compute unit to fill that time); the rest is the chain of a phase, LDS reads, MFMAs, exponentials,
+// barrier (the exponentials left out: 2 us less, dQ left out: 42).
 // The arithmetic is that of the two kernels operation by operation and in their order, so the results are the same bits
 // and the size of the grid may choose the form (short_form).
 #include "fa_common.h"

@@ -4,11 +4,12 @@
 One "step" is one pass of the whole hot path over one batch of synthetic input, through the
 entry points a user calls: the forward (Algorithm 1) followed by the backward (Algorithm 2)
 of the workload named in `config.workload`, inputs resident in HBM. Dense workloads run
-fa_fwd + fa_bwd, packed ragged ones fa_varlen_fwd + fa_varlen_bwd, workloads with two lengths fa_cross_*, half precision fa_cross_*_f16, dropout and mask workloads
-their own entry points; a handful of query rows against a long cache runs fa_splitkv_fwd alone
-and reports GB/s of compulsory traffic against the HBM roofline. Throughput is counted with the
-paper's formula (section 4.1): forward 4*N^2*d FLOPs per head and sequence, halved under the
-causal mask, backward 2.5x that.
+fa_fwd + fa_bwd, packed ragged ones fa_varlen_fwd + fa_varlen_bwd, workloads with two lengths
+fa_cross_*, half precision fa_cross_*_f16, dropout and mask workloads their own entry points; a
+handful of query rows against a long cache runs fa_splitkv_fwd alone and reports GB/s of
+compulsory traffic against the HBM roofline. Throughput is counted with the paper's formula
+(section 4.1): forward 4*N^2*d FLOPs per head and sequence, halved under the causal mask,
+backward 2.5x that.
 
 Before the `--warmup` steps the same step runs untimed for `--settle` seconds (a fresh process on
 an idle GPU otherwise measures the clock ramp). The timed region holds exactly `--steps` steps and
@@ -57,7 +58,7 @@ PEAK_HBM_GBS = 8000.0      # MI355X HBM3E peak
 # the kernel sources are the ones they were measured on (`sources`: kernel_sources_id() at the time
 # of the measurement); otherwise `traffic` is null and the stale figure moves to `traffic_recorded`.
 MEASURED_TRAFFIC = {
-    "sources": "b8afe3af4935",
+    "sources": "9063f8016545",
     "d128_n8k_causal": {"fwd_kernel": 659152324, "bwd_dkdv_kernel": 864215058, "bwd_dq_kernel": 762745717},
     "sweep_d128_n8192_full": {"fwd_kernel": 269796386, "bwd_dkdv_kernel": 405298506, "bwd_dq_kernel": 337902929},
     "sweep_d64_n8192_causal": {"fwd_kernel": 882302946, "bwd_dkdv_kernel": 882353737, "bwd_dq_kernel": 831636651},

@@ -963,10 +963,11 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
   const int wrow0 = i0 + 32 * w;
   const int row = wrow0 + lq;
   const int rowc = row < n ? row : n - 1;
-  // Whole rows through LDS, below: for windows too, whose short walks are mostly start-up (backward of windows of 128 to 2048 keys,
-  // nine shapes per head dimension: d = 128 0.1 to 5% faster with it, 2 x 8192, 16 heads, 128 keys 247.7 -> 245.0 us; d = 64 within 0.5%,
-  // 2 x 6997, 32 heads on 16, 223 keys 278.2 -> 279.4, 1 x 1500, 8 heads, 101 keys 33.4 -> 32.7).
-  constexpr bool QROWS = !PAD;
+  // Whole rows through LDS, below. Windows, whose short walks are mostly start-up, gain by it at d = 128 (backward, nine shapes with
+  // windows of 100 to 2048 keys: 0.1 to 5% faster; 2 x 8192, 16 heads, 128 keys 247.7 -> 245.0 us) and feel the second latency at
+  // d = 64: on grids of 32 heads 0.2 to 0.8% slower (3 x 1664, 32 heads on 16, 677 keys, forward and backward 212.6 -> 214.2; 2 x
+  // 6997, 223 keys 278.2 -> 279.4), on smaller ones within 0.5% either way but for 1 x 1500, 8 heads, 101 keys: 33.4 -> 32.7.
+  constexpr bool QROWS = !PAD && !(LOCAL == kWindow && D == 64);
   bf16x8 Qf[KS], dOf[KS];
   if constexpr (!QROWS) {
     const __bf16* qp = a.Q + ((si.tok0 + rowc) * p.Hq + h) * dh + 8 * hh;

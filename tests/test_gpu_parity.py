@@ -287,7 +287,8 @@ def test_one_kernel_backward_agrees_bitwise(N, B, Hq, Hkv, packed, dtype, causal
                                                  (36, 256, 8, 8, 64, False), (40, 256, 8, 8, 128, True),
                                                  (1, 200, 2, 1, 96, True), (1, 200, 2, 1, 96, False), (1, 200, 2, 1, 32, True),
                                                  (1, 200, 2, 1, 32, False), (1, 200, 2, 1, 48, True), (1, 200, 2, 1, 48, False),
-                                                 (1, 200, 2, 1, 104, True), (1, 200, 2, 1, 104, False), (1, 200, 2, 1, 256, True)])
+                                                 (1, 200, 2, 1, 104, True), (1, 200, 2, 1, 104, False), (1, 200, 2, 1, 256, True),
+                                                 (1, 200, 2, 1, 256, False)])
 def test_any_split_of_the_backward_into_stages(B, N, Hq, Hkv, d, causal, order):
     """fa_bwd_stages runs whatever subset of the three stages it is asked for: the pre-pass first and the two
     kernels together, apart or in either order write all of dQ, dK and dV. (fa_bwd sums D inside the dQ kernel,

@@ -58,7 +58,7 @@ PEAK_HBM_GBS = 8000.0      # MI355X HBM3E peak
 # the kernel sources are the ones they were measured on (`sources`: kernel_sources_id() at the time
 # of the measurement); otherwise `traffic` is null and the stale figure moves to `traffic_recorded`.
 MEASURED_TRAFFIC = {
-    "sources": "9063f8016545",
+    "sources": "7ca42f6df36d",
     "d128_n8k_causal": {"fwd_kernel": 659152324, "bwd_dkdv_kernel": 864215058, "bwd_dq_kernel": 762745717},
     "sweep_d128_n8192_full": {"fwd_kernel": 269796386, "bwd_dkdv_kernel": 405298506, "bwd_dq_kernel": 337902929},
     "sweep_d64_n8192_causal": {"fwd_kernel": 882302946, "bwd_dkdv_kernel": 882353737, "bwd_dq_kernel": 831636651},

@@ -385,6 +385,13 @@ template <bool F16>
 __device__ __forceinline__ bool reference_outgrown(float share) {
   return __builtin_amdgcn_ballot_w64(share > (float)(1 << kLazyLog2<F16>)) != 0;
 }
+// Keys of a block (row_maximum) past `lim`, the last one that the row sees, counted from this lane's first, leave the softmax.
+__device__ __forceinline__ void mask_past(f32x16 (&S)[2], int lim) {
+#pragma unroll
+  for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) S[kt][r] = 32 * kt + acc_row(r, 0) > lim ? -INFINITY : S[kt][r];
+}
 
 __device__ __forceinline__ float sum_with_partner32(float x) {
   int xi = __builtin_bit_cast(int, x);
@@ -414,6 +421,29 @@ __device__ __forceinline__ bf16x8 pack8(const f32x16& v, int s) {
   r[2] = pack2<F16>(v[8 * s + 4], v[8 * s + 5]);
   r[3] = pack2<F16>(v[8 * s + 6], v[8 * s + 7]);
   return __builtin_bit_cast(bf16x8, r);
+}
+
+__device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
+__device__ __forceinline__ float fast_log2(float x) { return __builtin_amdgcn_logf(x); }
+
+// The exponentials of a block (row_maximum) against the reference -nref, in the exponent's base, rounded into the operands
+// of the second product, and this lane's two shares of the row sum.
+template <bool F16>
+__device__ __forceinline__ void block_exponentials(const f32x16 (&S)[2], float c2, float nref, bf16x8 (&P)[2][2], float& rs0, float& rs1) {
+  rs0 = rs1 = 0.f;
+#pragma unroll
+  for (int kt = 0; kt < 2; ++kt) {
+    f32x16 E;
+#pragma unroll
+    for (int r = 0; r < 16; r += 2) {
+      E[r] = fast_exp2(__builtin_fmaf(S[kt][r], c2, nref));
+      E[r + 1] = fast_exp2(__builtin_fmaf(S[kt][r + 1], c2, nref));
+      rs0 += E[r];
+      rs1 += E[r + 1];
+    }
+    P[kt][0] = pack8<F16>(E, 0);
+    P[kt][1] = pack8<F16>(E, 1);
+  }
 }
 
 // Element t of 8 raw 16-bit elements, widened to float32.
@@ -453,8 +483,5 @@ __device__ __forceinline__ uint32_t quad_lane(uint32_t x, int u) {
     default: return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0xff, 0xf, 0xf, true);
   }
 }
-
-__device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
-__device__ __forceinline__ float fast_log2(float x) { return __builtin_amdgcn_logf(x); }
 
 }  // namespace fa

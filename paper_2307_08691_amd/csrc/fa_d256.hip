@@ -26,45 +26,8 @@ namespace {
 
 constexpr int kHalf = 128;          // columns of one half tile
 constexpr int kRowB = 2 * kHalf;    // its row bytes
-
-// Copies of a 256-wide tile of ROWS rows (left | right half) by NW wavefronts: one wavefront instruction fetches four rows of a
-// half tile. The lane offsets of an interior tile are computed once; at the end of a sequence rows past the last repeat it.
-template <int ROWS, int NW>
-struct TileCopier {
-  static constexpr int PER = ROWS / 4 / NW, COPIES = 2 * PER, HALFB = ROWS * kRowB;
-  unsigned voff[PER], rowb, cbyte;
-  int crow, wave;
-  struct Plan {
-    const __bf16* base;
-    unsigned off[PER];
-  };
-  __device__ __forceinline__ void init(long gstride, int w, int lane) {
-    wave = w;
-    crow = 4 * w + (lane >> 4);
-    cbyte = 16u * ((lane & 15) ^ swz<kRowB>(crow));  // (4 NW rows further on the swizzle is the same)
-    static_assert(NW == 4, "");
-    rowb = (unsigned)gstride * 2u;
-#pragma unroll
-    for (int u = 0; u < PER; ++u) voff[u] = (unsigned)(crow + 4 * NW * u) * rowb + cbyte;
-  }
-  __device__ __forceinline__ Plan plan(const __bf16* base, int last) const {
-    Plan t;
-    t.base = base;
-#pragma unroll
-    for (int u = 0; u < PER; ++u) t.off[u] = voff[u];
-    if (last < ROWS - 1) {
-      asm volatile("; keep this a branch" ::);
-#pragma unroll
-      for (int u = 0; u < PER; ++u) t.off[u] = (unsigned)(crow + 4 * NW * u < last ? crow + 4 * NW * u : last) * rowb + cbyte;
-    }
-    return t;
-  }
-  template <int Q>
-  __device__ __forceinline__ void copy(const Plan& t, char* dst) const {
-    constexpr int u = Q >> 1, half = Q & 1;
-    dma16_uniform(t.base + half * kHalf, t.off[u], dst + half * HALFB + (wave + NW * u) * 1024);
-  }
-};
+template <int ROWS>
+using Copier = TileCopier<ROWS, kRowB, 2>;
 
 // lane constants of the operand addressing inside one half tile (fa_lds.h)
 struct LaneAddr {
@@ -132,9 +95,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   }
   if (ncol < 1) ncol = 1;  // (more queries than keys is only allowed without the mask)
 
-  TileCopier<BC, 4> copier;
+  Copier<BC> copier;
   copier.init(kstride, w, lane);
-  constexpr int CPT = TileCopier<BC, 4>::COPIES;  // copies per wavefront and tile
+  constexpr int CPT = Copier<BC>::COPIES;  // copies per wavefront and tile
   auto k_stage = [&](int j) { return smem + (j % KSTAGES) * TILEB; };
   auto v_stage = [&](int j) { return smem + V_OFF + (j & 1) * TILEB; };
   // (blocks past the end fetch the last one again, never read, so that the waits can count)
@@ -167,11 +130,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   auto mask = [&](int j) {  // entries above the diagonal and columns past the end
     const int col0 = j * BC;
     if ((CAUSAL && col0 + BC - 1 > prow0 + off) || col0 + BC > nk) {
-      const int lim = lim_row - col0 - 4 * hh;
-#pragma unroll
-      for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) S[kt][r] = 32 * kt + acc_row(r, 0) > lim ? -INFINITY : S[kt][r];
+      mask_past(S, lim_row - col0 - 4 * hh);
     }
   };
 
@@ -264,20 +223,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
           asm volatile("" : "+a"(O[dt]));
         }
       }
-      rs0 = rs1 = 0.f;
-#pragma unroll
-      for (int kt = 0; kt < 2; ++kt) {
-        f32x16 E;
-#pragma unroll
-        for (int r = 0; r < 16; r += 2) {
-          E[r] = fast_exp2(__builtin_fmaf(S[kt][r], c2, -m * c2));
-          E[r + 1] = fast_exp2(__builtin_fmaf(S[kt][r + 1], c2, -m * c2));
-          rs0 += E[r];
-          rs1 += E[r + 1];
-        }
-        Pn[kt][0] = pack8<F16>(E, 0);
-        Pn[kt][1] = pack8<F16>(E, 1);
-      }
+      block_exponentials<F16>(S, c2, -m * c2, Pn, rs0, rs1);
     }
     l += rs0 + rs1;
     if constexpr (next) {
@@ -419,9 +365,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   }
   if (ncol < 1) ncol = 1;
 
-  TileCopier<BC, 4> copier;
+  Copier<BC> copier;
   copier.init(kstride, w, lane);
-  constexpr int CPT = TileCopier<BC, 4>::COPIES;  // copies per wavefront and tile
+  constexpr int CPT = Copier<BC>::COPIES;  // copies per wavefront and tile
   auto k_stage = [&](int j) { return smem + (j % KSTAGES) * TILEB; };
   auto v_stage = [&](int j) { return smem + V_OFF + (j & 1) * TILEB; };
   // (blocks past the end fetch the last one again)
@@ -628,12 +574,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   bool stat_ok = false;
   // (tiles are requested in order: the head and row tile of the next request are carried along; past the last tile it is
   // requested again, never read)
-  TileCopier<BR, 4> copier;
+  Copier<BR> copier;
   copier.init(qstride, w, lane);
-  constexpr int CPT = TileCopier<BR, 4>::COPIES;  // copies per wavefront of Q_i, as many of dO_i
+  constexpr int CPT = Copier<BR>::COPIES;  // copies per wavefront of Q_i, as many of dO_i
   int next_hq = g * p.G, next_it = i_first, next_t = 0;
   struct Request {
-    typename TileCopier<BR, 4>::Plan q, o;
+    typename Copier<BR>::Plan q, o;
     char* dst;
   };
   auto request = [&]() {  // the next tile's copies (to be issued) and its statistics (on their way)

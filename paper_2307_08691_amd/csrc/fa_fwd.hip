@@ -779,30 +779,11 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const bool need_mask = (CAUSAL && col0 + BC - 1 > cur.prow0 + off) || (col0 + BC > nk);
     if (need_mask) {
       asm volatile("; keep this a branch: the mask costs two instructions per element" ::);
-      const int lim = lim_row - col0 - 4 * hh;
-#pragma unroll
-      for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) S[kt][r] = 32 * kt + acc_row(r, 0) > lim ? -INFINITY : S[kt][r];
+      mask_past(S, lim_row - col0 - 4 * hh);
     }
     // (fast path without the row maximum, see fwd_kernel)
     float rs0, rs1;
-    auto exponentials = [&](float ref) {
-      rs0 = rs1 = 0.f;
-#pragma unroll
-      for (int kt = 0; kt < 2; ++kt) {
-        f32x16 E;
-#pragma unroll
-        for (int r = 0; r < 16; r += 2) {
-          E[r] = fast_exp2(__builtin_fmaf(S[kt][r], c2, -ref));
-          E[r + 1] = fast_exp2(__builtin_fmaf(S[kt][r + 1], c2, -ref));
-          rs0 += E[r];
-          rs1 += E[r + 1];
-        }
-        Pf[kt][0] = pack8<F16>(E, 0);
-        Pf[kt][1] = pack8<F16>(E, 1);
-      }
-    };
+    auto exponentials = [&](float ref) { block_exponentials<F16>(S, c2, -ref, Pf, rs0, rs1); };
     bool advance = j == 0;
     if (!advance) {
       exponentials(m * c2);

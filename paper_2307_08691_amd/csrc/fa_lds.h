@@ -282,6 +282,45 @@ __device__ __forceinline__ void mfma_stream(LoadF load, MmaF mma) {
   mfma_stream_run<N, AHEAD, READS>(ring, load, mma);
 }
 
+// Copies of a tile of ROWS rows by four wavefronts, for such streams. A row is kept as HALVES pieces of ROWB bytes, each the row
+// of a swizzled tile of its own (rows of 512 bytes: a left and a right half, one tile after the other). One wavefront
+// instruction fetches 1 KiB. The lane offsets of an interior tile are computed once; rows past the last valid one repeat it.
+template <int ROWS, int ROWB, int HALVES = 1>
+struct TileCopier {
+  static constexpr int CPR = ROWB / 16, RPI = 64 / CPR, PER = ROWS / RPI / 4, COPIES = HALVES * PER;
+  unsigned voff[PER], rowb, cbyte;
+  int crow, wave;
+  struct Plan {
+    const __bf16* base;
+    unsigned off[PER];
+  };
+  __device__ __forceinline__ void init(long gstride, int w, int lane) {
+    wave = w;
+    crow = RPI * w + lane / CPR;
+    cbyte = 16u * ((lane % CPR) ^ swz<ROWB>(crow));  // (4 RPI rows further on the swizzle is the same)
+    rowb = (unsigned)gstride * 2u;
+#pragma unroll
+    for (int u = 0; u < PER; ++u) voff[u] = (unsigned)(crow + 4 * RPI * u) * rowb + cbyte;
+  }
+  __device__ __forceinline__ Plan plan(const __bf16* base, int last) const {  // rows past `last` repeat it
+    Plan t;
+    t.base = base;
+#pragma unroll
+    for (int u = 0; u < PER; ++u) t.off[u] = voff[u];
+    if (last < ROWS - 1) {
+      asm volatile("; keep this a branch" ::);
+#pragma unroll
+      for (int u = 0; u < PER; ++u) t.off[u] = (unsigned)(crow + 4 * RPI * u < last ? crow + 4 * RPI * u : last) * rowb + cbyte;
+    }
+    return t;
+  }
+  template <int Q>
+  __device__ __forceinline__ void copy(const Plan& t, char* dst) const {
+    constexpr int u = Q / HALVES, half = Q % HALVES;
+    dma16_uniform(t.base + half * (ROWB / 2), t.off[u], dst + half * (ROWS * ROWB) + (wave + 4 * u) * 1024);
+  }
+};
+
 // LDS operands of a stream of MFMAs, requested in pairs two pairs ahead. The second of a pair is requested first, so that the
 // wait in front of the pair's first MFMA covers both: one wait per two MFMAs. (A wavefront alone on its SIMD issues
 // one instruction in about five cycles, six beside an MFMA of 32: every instruction of the loop counts.)

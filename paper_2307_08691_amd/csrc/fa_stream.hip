@@ -17,44 +17,6 @@
 
 namespace fa {
 
-namespace {
-// Copies of a tile of 64 rows of D elements by four wavefronts.
-template <int D>
-struct StreamCopier {
-  static constexpr int ROWB = 2 * D, CPR = ROWB / 16, RPI = 64 / CPR, COPIES = 64 / RPI / 4;
-  unsigned voff[COPIES], rowb, cbyte;
-  int crow, wave;
-  struct Plan {
-    const __bf16* base;
-    unsigned off[COPIES];
-  };
-  __device__ __forceinline__ void init(long gstride, int w, int lane) {
-    wave = w;
-    crow = RPI * w + lane / CPR;
-    cbyte = 16u * ((lane % CPR) ^ swz<ROWB>(crow));  // (4 RPI rows further on the swizzle is the same)
-    rowb = (unsigned)gstride * 2u;
-#pragma unroll
-    for (int u = 0; u < COPIES; ++u) voff[u] = (unsigned)(crow + 4 * RPI * u) * rowb + cbyte;
-  }
-  __device__ __forceinline__ Plan plan(const __bf16* base, int last) const {  // rows past `last` repeat it
-    Plan t;
-    t.base = base;
-#pragma unroll
-    for (int u = 0; u < COPIES; ++u) t.off[u] = voff[u];
-    if (last < 63) {
-      asm volatile("; keep this a branch" ::);
-#pragma unroll
-      for (int u = 0; u < COPIES; ++u) t.off[u] = (unsigned)(crow + 4 * RPI * u < last ? crow + 4 * RPI * u : last) * rowb + cbyte;
-    }
-    return t;
-  }
-  template <int Q>
-  __device__ __forceinline__ void copy(const Plan& t, char* dst) const {
-    dma16_uniform(t.base, t.off[Q], dst + (wave + 4 * Q) * 1024);
-  }
-};
-}  // namespace
-
 template <int D, bool CAUSAL, bool F16, bool RAGGED>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void fwd_stream_kernel(FwdArgs a) {
   constexpr int BR = 128, BC = 64, KS = D / 16, DT = D / 32, ROWB = 2 * D;
@@ -91,9 +53,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     if (RAGGED && ncolw < 1) ncolw = 1;
   }
 
-  StreamCopier<D> copier;
+  typedef TileCopier<BC, ROWB> Copier;
+  Copier copier;
   copier.init(kstride, w, lane);
-  constexpr int CPT = StreamCopier<D>::COPIES;  // copies per wavefront and tile
+  constexpr int CPT = Copier::COPIES;  // copies per wavefront and tile
   // The next blocks of K and V to be copied: where their rows begin, the last valid row counted from there, and where they
   // go. (Blocks past the end fetch the last one again, never read, so that the waits can count. Carried along: an
   // instruction saved is five cycles.)
@@ -152,11 +115,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const int col0 = j * BC;
     if ((CAUSAL && col0 + BC - 1 > prow0 + off) || col0 + BC > nk) {
       asm volatile("; keep this a branch: the mask costs two instructions per element" ::);
-      const int lim = lim_row - col0 - 4 * hh;
-#pragma unroll
-      for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) S[kt][r] = 32 * kt + acc_row(r, 0) > lim ? -INFINITY : S[kt][r];
+      mask_past(S, lim_row - col0 - 4 * hh);
     }
   };
   wait_vmem_upto<2 * CPT>();
@@ -250,20 +209,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
           for (int r = 0; r < 16; ++r) O[dt][r] *= alpha;
       }
-      rs0 = rs1 = 0.f;
-#pragma unroll
-      for (int kt = 0; kt < 2; ++kt) {
-        f32x16 E;
-#pragma unroll
-        for (int r = 0; r < 16; r += 2) {
-          E[r] = fast_exp2(__builtin_fmaf(S[kt][r], c2, -m * c2));
-          E[r + 1] = fast_exp2(__builtin_fmaf(S[kt][r + 1], c2, -m * c2));
-          rs0 += E[r];
-          rs1 += E[r + 1];
-        }
-        Pn[kt][0] = pack8<F16>(E, 0);
-        Pn[kt][1] = pack8<F16>(E, 1);
-      }
+      block_exponentials<F16>(S, c2, -m * c2, Pn, rs0, rs1);
     }
     l += rs0 + rs1;
     if constexpr (next) {

@@ -166,7 +166,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 12
   const int kgi = WIDE ? v : kg;  // which 32 keys of the block this wavefront owns
   const int gtid = tid & 255;  // thread index inside the group
   const int lq = lane & 31, hh = lane >> 5;
-  const BlockCoord bc = key_block_coord<CAUSAL, RAGGED>(p, BC);
+  const BlockCoord bc = key_block_coord<CAUSAL, RAGGED>(p, BC, D == 64 && NW == 4 ? 2 : 1);
   if (!bc.valid) return;
   const int g = bc.head, s = bc.seq;
   const SeqInfo si = seq_info(p, s);
@@ -944,7 +944,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int grp = w >> 2;  // 0: matrix phase on even phases, 1: on odd phases
   const int lq = lane & 31, hh = lane >> 5;
-  const BlockCoord bc = row_block_coord<CAUSAL, RAGGED, true>(p, BR);
+  const BlockCoord bc = row_block_coord<CAUSAL, RAGGED, true>(p, BR, D == 64 && NW == 4 ? 2 : 1);
   if (!bc.valid) return;
   const int rowblk = bc.blk;
   const int h = bc.head, s = bc.seq;
@@ -1362,7 +1362,7 @@ template <int D, bool F16, bool OWN_D, bool RAGGED>
 static hipError_t launch_dq(const BwdArgs& a, int causal, hipStream_t st) {
   constexpr int DN = dn_of(D);
   const int pairs = a.p.Hq * a.p.nseq;
-  const dim3 grid(grid_size((a.p.N + 255) / 256, pairs)), block(512);
+  const dim3 grid(grid_size(a.p, (a.p.N + 255) / 256, a.p.Hq)), block(512);
   if constexpr (OWN_D && !RAGGED) {
     if (a.p.bmask) {  // block-sparse pattern (perhaps with a window)
       hipLaunchKernelGGL((bwd_dq_kernel<D, false, F16, false, false, false, kBlocks, true>), grid, block, 0, st, a);
@@ -1397,7 +1397,7 @@ static hipError_t launch_dq(const BwdArgs& a, int causal, hipStream_t st) {
   }
   if constexpr (D == 64) {
     if (small_workgroups(a.p.N, pairs, false)) {
-      const dim3 sgrid(grid_size((a.p.N + 127) / 128, pairs));
+      const dim3 sgrid(grid_size(a.p, (a.p.N + 127) / 128, a.p.Hq, 2));
       if (causal) hipLaunchKernelGGL((bwd_dq_kernel<D, true, F16, false, false, false, kNoPattern, OWN_D, D, 4, RAGGED>), sgrid, dim3(256), 0, st, a);
       else hipLaunchKernelGGL((bwd_dq_kernel<D, false, F16, false, false, false, kNoPattern, OWN_D, D, 4, RAGGED>), sgrid, dim3(256), 0, st, a);
       return hipGetLastError();
@@ -1414,8 +1414,8 @@ static hipError_t launch_dkdv(const BwdArgs& a, int causal, hipStream_t st) {
   constexpr int DN = dn_of(D);
   const int pairs = a.p.Hkv * a.p.nseq;
   const int bck = dkdv_block_keys(a.p.mask != nullptr);  // keys per workgroup differ between the instantiations
-  const dim3 grid(grid_size((a.p.Nk + bck - 1) / bck, pairs)), block(512);
-  const dim3 sgrid(grid_size((a.p.Nk + 127) / 128, pairs));
+  const dim3 grid(grid_size(a.p, (a.p.Nk + bck - 1) / bck, a.p.Hkv)), block(512);
+  const dim3 sgrid(grid_size(a.p, (a.p.Nk + 127) / 128, a.p.Hkv, D == 64 ? 2 : 1));
   if constexpr (!RAGGED) {
     if (a.p.bmask) {  // block-sparse pattern (perhaps with a window)
       hipLaunchKernelGGL((bwd_dkdv_kernel<D, false, F16, false, false, false, kBlocks>), grid, block, 0, st, a);

@@ -103,15 +103,36 @@ __device__ __forceinline__ SeqInfo seq_info(const Problem& p, int s) {
 // XCD walk its pairs one after the other, so its 32 CUs share one pair's operands at a time
 // instead of thrashing L2 with eight. Under the causal mask block costs differ by up to
 // the number of blocks, so there the XCD's pairs are interleaved and all their heaviest
-// blocks are dispatched first (longest-processing-time order), lightest last. Kernels are launched on grid_size(nblk, pairs) workgroups; indices that
-// fall past the last pair return valid = false.
-constexpr int kXcds = 8;
+// blocks are dispatched first (longest-processing-time order), lightest last.
+// Pairs that do not make up a full set of eight leave XCDs without work (one head of a long sequence: seven of them).
+// Where an XCD that has one pair more than another would have more blocks than fit on it at once (per_cu on a compute
+// unit), the blocks of the pairs past the last full set, up to seven pairs' worth, are dealt to all XCDs in turn (`spread_pairs`;
+// MI355X, us: a cache of 10 pairs, 5 x 416 new queries on up to 14848 keys, 2 heads of 128: 69.9 -> 43.4; forward and backward of 25
+// packed sequences of up to 4067, 2 heads of 128: 434 -> 391, of 27 x 832, 4 heads of 128: 213 -> 206). Where all of
+// them fit they stay where they were: 1 x 5056, 2 heads of 64, spread over eight L2s took 62.7 instead of 61.2.
+// Kernels are launched on grid_size(nblk, pairs) workgroups; indices that fall past the last block return valid = false.
+constexpr int kXcds = 8, kXcdUnits = 32;
 struct BlockCoord {
   int blk, head, seq;
   bool valid;
 };
-__host__ __device__ inline unsigned grid_size(int nblk, int pairs) {
-  return (unsigned)(((pairs + kXcds - 1) / kXcds) * kXcds * nblk);
+__host__ __device__ inline int spread_pairs(int nblk, int pairs, int per_cu) {
+  return (pairs + kXcds - 1) / kXcds * nblk > kXcdUnits * per_cu ? pairs % kXcds : 0;
+}
+__host__ __device__ inline unsigned grid_size(int nblk, int pairs, int per_cu = 1) {
+  const int rest = spread_pairs(nblk, pairs, per_cu);
+  return (unsigned)(kXcds * ((pairs - rest + kXcds - 1) / kXcds * nblk + (rest * nblk + kXcds - 1) / kXcds));
+}
+// Packed batches (ragged_coord): the real blocks of all pairs are numbered through, or of the pairs of each XCD, of
+// which one may then have a pair more than another.
+__host__ __device__ inline bool packed_through(int nblk, int pairs, int per_cu) {
+  return pairs < 64 && spread_pairs(nblk, pairs, per_cu) != 0;
+}
+// The grid of a kernel that goes by row_block_coord (heads: p.Hq) or key_block_coord (p.Hkv)
+inline unsigned grid_size(const Problem& p, int nblk, int heads, int per_cu = 1) {
+  const int pairs = heads * p.nseq;
+  if (!p.cu_seqlens || packed_through(nblk, pairs, per_cu)) return grid_size(nblk, pairs, per_cu);
+  return (unsigned)((pairs + kXcds - 1) / kXcds * kXcds * nblk);
 }
 // `group` > 1 (kernels whose grid runs over QUERY heads that share key/value heads in groups of
 // that size): heads are handed out so that the heads of one group follow each other at a
@@ -119,25 +140,43 @@ __host__ __device__ inline unsigned grid_size(int nblk, int pairs) {
 // same XCD, whose L2 holds the group's K and V once instead of every XCD holding them all.
 // BACK: the pairs from the last to the first (see launch_bwd_d).
 template <bool WORK_SORTED, bool BACK = false>
-__device__ __forceinline__ BlockCoord block_coord(int nblk, int nheads, int nseq, int group = 1) {
-  const int L = blockIdx.x;
-  const int x = L % kXcds, k = L / kXcds;
-  const int ppx = gridDim.x / (kXcds * nblk);  // pairs per XCD
-  int pl;                                       // which of this XCD's pairs
+__device__ __forceinline__ BlockCoord block_coord(int nblk, int nheads, int nseq, int group = 1, int per_cu = 1) {
+  const int x = blockIdx.x % kXcds, k = blockIdx.x / kXcds;
+  const int pairs = nheads * nseq, rest = spread_pairs(nblk, pairs, per_cu);
+  const int own = (pairs - rest + kXcds - 1) / kXcds;  // pairs that one XCD has to itself
   BlockCoord c;
+  int pl;  // which of them
   if (WORK_SORTED) {  // causal: the XCD's pairs take turns, every pair's heaviest blocks first
-    c.blk = k / ppx;
-    pl = k % ppx;
+    c.blk = rest ? kXcds * k / pairs : k / own;
+    pl = k - c.blk * own;
   } else {  // one pair at a time
-    c.blk = k % nblk;
     pl = k / nblk;
+    c.blk = k - pl * nblk;
   }
-  if (BACK) pl = ppx - 1 - pl;
-  const int pr = pl * kXcds + x;
-  const int hp = pr % nheads, nkv = nheads / group;
-  c.head = (hp % nkv) * group + hp / nkv;
+  int pr = (BACK ? own - 1 - pl : pl) * kXcds + x;
+  if (rest) {
+    asm volatile("; keep this a branch: short kernels feel every division in front of their first request" ::);
+    if (WORK_SORTED) {
+      // Block b of the q-th spread pair goes to XCD (rest * b + q) % 8. before(b): blocks of this XCD that come before those with
+      // index b.
+      auto before = [&](int b) { return own * b + (rest * b + kXcds - 1 - x) / kXcds; };
+      while (before(c.blk + 1) <= k) ++c.blk;
+      while (before(c.blk) > k) --c.blk;
+      pl = k - before(c.blk);
+      pr = pl < own ? (BACK ? own - 1 - pl : pl) * kXcds + x : own * kXcds + ((x - rest * c.blk) & (kXcds - 1));
+    } else if (pl >= own) {
+      const int i = (k - own * nblk) * kXcds + x;
+      pr = own * kXcds + i / nblk;
+      c.blk = i % nblk;
+    }
+  }
   c.seq = pr / nheads;
-  c.valid = pr < nheads * nseq;
+  c.head = pr - c.seq * nheads;
+  if (group > 1) {  // (a branch: a division is a chain of some twenty instructions in front of the first request)
+    const int nkv = nheads / group, in = c.head / nkv;
+    c.head = (c.head - in * nkv) * group + in;
+  }
+  c.valid = pr < pairs && c.blk < nblk;
   return c;
 }
 
@@ -163,7 +202,7 @@ __device__ __forceinline__ int wave_sum(int x) {
 //  * else: every block of a sequence costs the same; the pairs with the most blocks first, block by block.
 // 16 sequences of 758 .. 3951 tokens (37954 in all), 32 heads on 8, d = 128, causal: the dK/dV kernel takes
 // 2.05 ms with the gaps and 1.57 ms without (the pass of three kernels 4.26 -> 3.82 ms).
-// Lane l holds the number of blocks of the pairs l, l + 64, .. of this XCD; the number of real blocks
+// Lane l holds the number of blocks of the pairs l, l + 64, .. of this XCD (or of all: packed_through); the number of real blocks
 // with at least `left` left (the number of blocks of pairs with at least that many) falls with `left`, and
 // a binary search finds where launch index k stands. Up to 64 * kRaggedChunks pairs per XCD; beyond (and for
 // dense batches, which have no gaps) block_coord's order stays.
@@ -173,16 +212,18 @@ struct RaggedCoord {
   bool valid;
 };
 template <bool LEVELS>
-__device__ __forceinline__ RaggedCoord ragged_coord(const int32_t* cu, int rows, int nblk, int nheads, int nseq, int group) {
+__device__ __forceinline__ RaggedCoord ragged_coord(const int32_t* cu, int rows, int nblk, int nheads, int nseq, int group,
+                                                    int per_cu) {
   const int lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
-  const int x = blockIdx.x % kXcds, k = blockIdx.x / kXcds;
-  const int ppx = gridDim.x / (kXcds * nblk), chunks = (ppx + 63) / 64;
+  const int pairs = nheads * nseq, lists = packed_through(nblk, pairs, per_cu) ? 1 : kXcds;  // (a list per XCD, or one for all)
+  const int x = blockIdx.x % lists, k = blockIdx.x / lists;
+  const int chunks = ((pairs + lists - 1) / lists + 63) / 64;
   int nb[kRaggedChunks];
 #pragma unroll
   for (int c = 0; c < kRaggedChunks; ++c) {
     nb[c] = 0;
-    const int pr = (64 * c + lane) * kXcds + x;
-    if (c < chunks && 64 * c + lane < ppx && pr < nheads * nseq) {
+    const int pr = (64 * c + lane) * lists + x;
+    if (c < chunks && pr < pairs) {
       const int s = pr / nheads;
       const int b = (cu[s + 1] - cu[s] + rows - 1) / rows;
       nb[c] = b < 0 ? 0 : (b < nblk ? b : nblk);
@@ -218,7 +259,7 @@ __device__ __forceinline__ RaggedCoord ragged_coord(const int32_t* cu, int rows,
     }
     which -= __builtin_popcountll(m);
   }
-  const int pr = pl * kXcds + x, hp = pr % nheads, nkv = nheads / group;
+  const int pr = pl * lists + x, hp = pr % nheads, nkv = nheads / group;
   r.left = lo;
   r.blk = LEVELS ? 0 : nth % lo;
   r.head = (hp % nkv) * group + hp / nkv;  // (as in block_coord)
@@ -226,7 +267,7 @@ __device__ __forceinline__ RaggedCoord ragged_coord(const int32_t* cu, int rows,
   r.valid = true;
   return r;
 }
-__device__ __forceinline__ bool ragged_order(int nblk) { return (int)(gridDim.x / (kXcds * nblk)) <= 64 * kRaggedChunks; }
+__device__ __forceinline__ bool ragged_order(int pairs) { return pairs <= kXcds * 64 * kRaggedChunks; }
 
 // (through the first lane: the compiler would keep the coordinates, and all that follows from them, per lane)
 __device__ __forceinline__ BlockCoord scalar_coord(BlockCoord c) {
@@ -238,13 +279,13 @@ __device__ __forceinline__ BlockCoord scalar_coord(BlockCoord c) {
 // RAGGED (p.cu_seqlens is set) is a parameter of the instantiation, not asked here: short dense batches, whose time is
 // the chain of one workgroup, feel the search even as code that they jump over.
 template <bool CAUSAL, bool RAGGED, bool BACK = false>
-__device__ __forceinline__ BlockCoord row_block_coord(const Problem& p, int rows) {
+__device__ __forceinline__ BlockCoord row_block_coord(const Problem& p, int rows, int per_cu = 1) {
   const int nblk = (p.N + rows - 1) / rows;
-  if (RAGGED && ragged_order(nblk)) {
-    const RaggedCoord r = ragged_coord<CAUSAL>(p.cu_seqlens, rows, nblk, p.Hq, p.nseq, p.G);
+  if (RAGGED && ragged_order(p.Hq * p.nseq)) {
+    const RaggedCoord r = ragged_coord<CAUSAL>(p.cu_seqlens, rows, nblk, p.Hq, p.nseq, p.G, per_cu);
     return scalar_coord({CAUSAL ? r.left - 1 : r.blk, r.head, r.seq, r.valid});
   }
-  BlockCoord c = block_coord<CAUSAL, BACK>(nblk, p.Hq, p.nseq, p.G);
+  BlockCoord c = block_coord<CAUSAL, BACK>(nblk, p.Hq, p.nseq, p.G, per_cu);
   c.blk = nblk - 1 - c.blk;
   return c;
 }
@@ -253,14 +294,14 @@ __device__ __forceinline__ BlockCoord row_block_coord(const Problem& p, int rows
 // block_coord's order (batches with very many pairs) block indices therefore count from the END of the
 // longest possible sequence, and the blocks that a shorter one does not have are not valid.
 template <bool CAUSAL, bool RAGGED>
-__device__ __forceinline__ BlockCoord key_block_coord(const Problem& p, int keys) {
+__device__ __forceinline__ BlockCoord key_block_coord(const Problem& p, int keys, int per_cu = 1) {
   const int nblk = (p.Nk + keys - 1) / keys;
-  if (RAGGED && ragged_order(nblk)) {
+  if (RAGGED && ragged_order(p.Hkv * p.nseq)) {
     const RaggedCoord r =
-        ragged_coord<CAUSAL>(p.cu_seqlens_k ? p.cu_seqlens_k : p.cu_seqlens, keys, nblk, p.Hkv, p.nseq, 1);
+        ragged_coord<CAUSAL>(p.cu_seqlens_k ? p.cu_seqlens_k : p.cu_seqlens, keys, nblk, p.Hkv, p.nseq, 1, per_cu);
     return scalar_coord({CAUSAL ? r.blocks - r.left : r.blk, r.head, r.seq, r.valid});
   }
-  BlockCoord c = block_coord<CAUSAL>(nblk, p.Hkv, p.nseq);
+  BlockCoord c = block_coord<CAUSAL>(nblk, p.Hkv, p.nseq, 1, per_cu);
   if (CAUSAL && RAGGED && c.valid) {
     c.blk -= nblk - (seq_info(p, c.seq).nk + keys - 1) / keys;
     c.valid = c.blk >= 0;

@@ -297,7 +297,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 
 template <bool RAGGED>  // a.p.cu_seqlens is set
 static hipError_t launch_fwd256_d(const FwdArgs& a, int causal, hipStream_t st) {
-  dim3 grid(grid_size((a.p.N + 127) / 128, a.p.Hq * a.p.nseq)), block(256);
+  dim3 grid(grid_size(a.p, (a.p.N + 127) / 128, a.p.Hq)), block(256);
   if (a.p.f16) {
     if (causal) hipLaunchKernelGGL((fwd256_kernel<true, true, RAGGED>), grid, block, 0, st, a);
     else hipLaunchKernelGGL((fwd256_kernel<false, true, RAGGED>), grid, block, 0, st, a);
@@ -772,7 +772,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 
 template <bool RAGGED>
 static hipError_t launch_dkdv256(const BwdArgs& a, int causal, hipStream_t st) {
-  dim3 grid(grid_size((a.p.Nk + 127) / 128, a.p.Hkv * a.p.nseq)), block(256);
+  dim3 grid(grid_size(a.p, (a.p.Nk + 127) / 128, a.p.Hkv)), block(256);
   if (a.p.f16) {
     if (causal) hipLaunchKernelGGL((dkdv256_kernel<true, true, RAGGED>), grid, block, 0, st, a);
     else hipLaunchKernelGGL((dkdv256_kernel<false, true, RAGGED>), grid, block, 0, st, a);
@@ -784,7 +784,7 @@ static hipError_t launch_dkdv256(const BwdArgs& a, int causal, hipStream_t st) {
 }
 template <bool F16, bool OWN_D, bool RAGGED>
 static hipError_t launch_dq256(const BwdArgs& a, int causal, hipStream_t st) {
-  dim3 grid(grid_size((a.p.N + 127) / 128, a.p.Hq * a.p.nseq)), block(256);
+  dim3 grid(grid_size(a.p, (a.p.N + 127) / 128, a.p.Hq)), block(256);
   if (causal) hipLaunchKernelGGL((dq256_kernel<true, F16, OWN_D, RAGGED>), grid, block, 0, st, a);
   else hipLaunchKernelGGL((dq256_kernel<false, F16, OWN_D, RAGGED>), grid, block, 0, st, a);
   return hipGetLastError();

@@ -122,7 +122,8 @@ __global__ __launch_bounds__(512)
   const int lq = lane & 31, hh = lane >> 5;
   const int nsplit = SPLIT ? a.nsplit : 1;
   const int nblk = ((SPLIT ? p.N * p.G : p.N) + BR - 1) / BR;
-  const BlockCoord bc = SPLIT ? block_coord<false>(nblk * nsplit, p.Hkv, p.nseq) : row_block_coord<CAUSAL, RAGGED>(p, BR);
+  const BlockCoord bc = SPLIT ? block_coord<false>(nblk * nsplit, p.Hkv, p.nseq, 1, TWO ? 2 : 1)
+                              : row_block_coord<CAUSAL, RAGGED>(p, BR, TWO ? 2 : 1);
   if (!bc.valid) return;
   const int split = SPLIT ? bc.blk % nsplit : 0;
   const int rowblk = SPLIT ? bc.blk / nsplit : bc.blk;
@@ -978,7 +979,7 @@ static hipError_t launch_fwd_split(const FwdArgs& a, int causal, hipStream_t st)
     if (hipError_t e = launch_fwd_decode(a, D, causal, st)) return e;
   } else {
     const int nblk = (a.p.N * a.p.G + 255) / 256;
-    dim3 grid(grid_size(nblk * a.nsplit, a.p.Hkv * a.p.nseq));
+    dim3 grid(grid_size(nblk * a.nsplit, a.p.Hkv * a.p.nseq, fwd_two_per_cu(D, false) ? 2 : 1));
     if (causal) hipLaunchKernelGGL((fwd_kernel<D, true, true, F16>), grid, block, 0, st, a);
     else hipLaunchKernelGGL((fwd_kernel<D, false, true, F16>), grid, block, 0, st, a);
     if (hipError_t e = hipGetLastError()) return e;
@@ -1018,7 +1019,7 @@ static bool stream_form(int d, int causal, int n, int nk, int pairs) {
 // RAGGED: a.p.cu_seqlens is set.
 template <int D, bool F16, bool RAGGED>
 static hipError_t launch_fwd_d(const FwdArgs& a, int causal, hipStream_t st) {
-  const dim3 grid(grid_size((a.p.N + 255) / 256, a.p.Hq * a.p.nseq)), block(512);
+  const dim3 grid(grid_size(a.p, (a.p.N + 255) / 256, a.p.Hq, fwd_two_per_cu(D, a.p.mask || a.p.bmask) ? 2 : 1)), block(512);
   if constexpr (!RAGGED) {  // the entry points keep everything else away from the elementwise mask and the block-sparse pattern
     if (a.p.mask) {
       if (causal) hipLaunchKernelGGL((fwd_kernel<D, true, false, F16, false, false, true>), grid, block, 0, st, a);

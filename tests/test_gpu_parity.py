@@ -279,6 +279,61 @@ def test_one_kernel_backward_agrees_bitwise(N, B, Hq, Hkv, packed, dtype, causal
             assert torch.equal(x[a:e].view(torch.int16), y[0].view(torch.int16)), (name, s, e - a)
 
 
+# (one pair, and three and ten: past the last full set of eight XCDs; as many blocks of 128 and of 256 rows as make an XCD that
+# holds them all hold more than fit on it at once, and fewer)
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("packed", [False, True])
+@pytest.mark.parametrize("H,N,d", [(1, 8321, 64), (3, 8321, 64), (10, 4300, 64), (10, 300, 64), (1, 8300, 128), (3, 8300, 128),
+                                   (10, 4300, 128), (3, 4300, 256)])
+def test_pairs_that_do_not_divide_over_the_xcds(H, N, d, packed, causal):
+    """The blocks of pairs past the last full set of eight are dealt to all XCDs: every block is computed, by whichever workgroup,
+    and a head's results are those of the head alone."""
+    g = torch.Generator(device="cuda").manual_seed(9500 + N + H)
+    Q, K, V, dO = (torch.randn((N, H, d), generator=g, device="cuda", dtype=torch.bfloat16) for _ in range(4))
+    cu = [0, N // 3, N // 3 + 5, N] if packed else [0, N]
+    cut = torch.tensor(cu, dtype=torch.int32, device="cuda")
+    longest = max(b - a for a, b in zip(cu, cu[1:]))
+
+    def run(h0, h1):
+        q, k, v, do = (x[:, h0:h1].contiguous() for x in (Q, K, V, dO))
+        bad = lambda x: torch.full_like(x, float("nan"))
+        lse = torch.full((h1 - h0, N), float("nan"), device="cuda")
+        if packed:
+            O, L = binding.fa_varlen_fwd(q, k, v, cut, longest, d ** -0.5, causal, O=bad(q), LSE=lse)
+            grads = binding.fa_varlen_bwd(q, k, v, O, do, L, cut, longest, d ** -0.5, causal, dQ=bad(q), dK=bad(k), dV=bad(v))
+            return (O, L.transpose(0, 1)) + tuple(grads)
+        one = lambda x: x.view(1, *x.shape)
+        O, L = binding.fa_fwd(one(q), one(k), one(v), d ** -0.5, causal, O=bad(one(q)), LSE=one(lse))
+        grads = binding.fa_bwd(one(q), one(k), one(v), O, one(do), L, d ** -0.5, causal, dQ=bad(one(q)), dK=bad(one(k)), dV=bad(one(v)))
+        return (O[0], L[0].transpose(0, 1)) + tuple(x[0] for x in grads)
+
+    whole = run(0, H)
+    assert all(torch.isfinite(x).all() for x in whole)
+    for h in {0, H // 2, H - 1}:
+        for name, x, y in zip(("O", "LSE", "dQ", "dK", "dV"), whole, run(h, h + 1)):
+            assert torch.equal(x[:, h], y[:, 0]), (name, h)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_cache_and_fp8_pairs_that_do_not_divide_over_the_xcds(d):
+    """As above for the split-key kernel (nine pairs, more shares than an XCD holds) and the FP8 kernel."""
+    g = torch.Generator(device="cuda").manual_seed(9600 + d)
+    Q, K, V = (torch.randn(s, generator=g, device="cuda", dtype=torch.bfloat16)
+               for s in ((3, 700, 3, d), (3, 1500, 3, d), (3, 1500, 3, d)))
+    lens = torch.tensor([1500, 900, 1300], dtype=torch.int32, device="cuda")
+    O, L = binding.fa_kvcache_fwd(Q, K, V, d ** -0.5, True, seqlens_k=lens, num_splits=12)
+    for s in range(3):
+        o, l = binding.fa_kvcache_fwd(*(x[s:s + 1] for x in (Q, K, V)), d ** -0.5, True, seqlens_k=lens[s:s + 1], num_splits=12)
+        assert torch.isfinite(O[s]).all() and torch.equal(O[s], o[0]) and torch.equal(L[s], l[0])
+    N = 8400 if d == 128 else 16700
+    q, k, v = ((torch.randn((1, N, 2, d), generator=g, device="cuda") * 16).to(torch.float8_e4m3fn).view(torch.uint8) for _ in range(3))
+    O, L = binding.fa_fp8_fwd(q, k, binding.fp8_key_major(v), N, d ** -0.5, 0.06, 0.06, 0.06, True)
+    for h in range(2):
+        one = [x[:, :, h:h + 1].contiguous() for x in (q, k, v)]
+        o, l = binding.fa_fp8_fwd(one[0], one[1], binding.fp8_key_major(one[2]), N, d ** -0.5, 0.06, 0.06, 0.06, True)
+        assert torch.isfinite(O).all() and torch.equal(O[:, :, h], o[:, :, 0]) and torch.equal(L[:, h], l[:, 0])
+
+
 # (the grids on which each form of the two kernels is chosen: every small one, the small dK/dV form beside the large dQ
 # form, both large ones; every product width of a padded head dimension and d = 256)
 @pytest.mark.parametrize("order", [(1, 6), (1, 2, 4), (1, 4, 2), (3, 4), (5, 2)])

@@ -155,7 +155,6 @@ __device__ __forceinline__ BlockCoord block_coord(int nblk, int nheads, int nseq
   }
   int pr = (BACK ? own - 1 - pl : pl) * kXcds + x;
   if (rest) {
-    asm volatile("; keep this a branch: short kernels feel every division in front of their first request" ::);
     if (WORK_SORTED) {
       // Block b of the q-th spread pair goes to XCD (rest * b + q) % 8. before(b): blocks of this XCD that come before those with
       // index b.

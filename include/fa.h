@@ -89,7 +89,8 @@ int fa_fwd(const void* Q, const void* K, const void* V, void* O, float* LSE,
  * kernels are enqueued: a row-block kernel that computes D for its rows and produces
  * dQ by recomputing the probabilities (instead of accumulating dQ across workgroups
  * with atomic adds), then a column-block kernel that produces dK and dV (section 3.2,
- * "Backward pass"). Where it is faster, short sequences (up to 512 tokens, d = 64,
+ * "Backward pass"); or, where that is faster, one that computes D and one whose workgroups
+ * are of both kinds, with the same bits. Where it is faster, short sequences (up to 512 tokens, d = 64,
  * without dropout, window or mask) take ONE kernel instead, with the same bits; it
  * leaves the workspace untouched. All three outputs are bit-reproducible.
  */

@@ -105,33 +105,38 @@ __device__ __forceinline__ SeqInfo seq_info(const Problem& p, int s) {
 // the number of blocks, so there the XCD's pairs are interleaved and all their heaviest
 // blocks are dispatched first (longest-processing-time order), lightest last.
 // Pairs that do not make up a full set of eight leave XCDs without work (one head of a long sequence: seven of them).
-// Where an XCD that has one pair more than another would have more blocks than fit on it at once (per_cu on a compute
-// unit), the blocks of the pairs past the last full set, up to seven pairs' worth, are dealt to all XCDs in turn (`spread_pairs`;
+// Where an XCD that has one pair more than another would have more blocks than fit on it at once (Place::slots), the blocks of the pairs past the last full set, up to seven pairs' worth, are dealt to all XCDs in turn (`spread_pairs`;
 // MI355X, us: a cache of 10 pairs, 5 x 416 new queries on up to 14848 keys, 2 heads of 128: 69.9 -> 43.4; forward and backward of 25
 // packed sequences of up to 4067, 2 heads of 128: 434 -> 391, of 27 x 832, 4 heads of 128: 213 -> 206). Where all of
 // them fit they stay where they were: 1 x 5056, 2 heads of 64, spread over eight L2s took 62.7 instead of 61.2.
 // Kernels are launched on grid_size(nblk, pairs) workgroups; indices that fall past the last block return valid = false.
-constexpr int kXcds = 8, kXcdUnits = 32;
+constexpr int kXcds = 8, kXcdUnits = 32;  // compute units of an XCD
 struct BlockCoord {
   int blk, head, seq;
   bool valid;
 };
-__host__ __device__ inline int spread_pairs(int nblk, int pairs, int per_cu) {
-  return (pairs + kXcds - 1) / kXcds * nblk > kXcdUnits * per_cu ? pairs % kXcds : 0;
+// A workgroup's place among those of its kind (the grid, or a part of it that begins at a multiple of kXcds), and how many
+// of them an XCD holds at once (beside those of another kind).
+struct Place {
+  unsigned index;
+  int slots;
+};
+__host__ __device__ inline int spread_pairs(int nblk, int pairs, int slots) {
+  return (pairs + kXcds - 1) / kXcds * nblk > slots ? pairs % kXcds : 0;
 }
-__host__ __device__ inline unsigned grid_size(int nblk, int pairs, int per_cu = 1) {
-  const int rest = spread_pairs(nblk, pairs, per_cu);
+__host__ __device__ inline unsigned grid_size(int nblk, int pairs, int slots) {
+  const int rest = spread_pairs(nblk, pairs, slots);
   return (unsigned)(kXcds * ((pairs - rest + kXcds - 1) / kXcds * nblk + (rest * nblk + kXcds - 1) / kXcds));
 }
 // Packed batches (ragged_coord): the real blocks of all pairs are numbered through, or of the pairs of each XCD, of
 // which one may then have a pair more than another.
-__host__ __device__ inline bool packed_through(int nblk, int pairs, int per_cu) {
-  return pairs < 64 && spread_pairs(nblk, pairs, per_cu) != 0;
+__host__ __device__ inline bool packed_through(int nblk, int pairs, int slots) {
+  return pairs < 64 && spread_pairs(nblk, pairs, slots) != 0;
 }
 // The grid of a kernel that goes by row_block_coord (heads: p.Hq) or key_block_coord (p.Hkv)
-inline unsigned grid_size(const Problem& p, int nblk, int heads, int per_cu = 1) {
+inline unsigned grid_size(const Problem& p, int nblk, int heads, int slots) {
   const int pairs = heads * p.nseq;
-  if (!p.cu_seqlens || packed_through(nblk, pairs, per_cu)) return grid_size(nblk, pairs, per_cu);
+  if (!p.cu_seqlens || packed_through(nblk, pairs, slots)) return grid_size(nblk, pairs, slots);
   return (unsigned)((pairs + kXcds - 1) / kXcds * kXcds * nblk);
 }
 // `group` > 1 (kernels whose grid runs over QUERY heads that share key/value heads in groups of
@@ -140,9 +145,9 @@ inline unsigned grid_size(const Problem& p, int nblk, int heads, int per_cu = 1)
 // same XCD, whose L2 holds the group's K and V once instead of every XCD holding them all.
 // BACK: the pairs from the last to the first (see launch_bwd_d).
 template <bool WORK_SORTED, bool BACK = false>
-__device__ __forceinline__ BlockCoord block_coord(int nblk, int nheads, int nseq, int group = 1, int per_cu = 1) {
-  const int x = blockIdx.x % kXcds, k = blockIdx.x / kXcds;
-  const int pairs = nheads * nseq, rest = spread_pairs(nblk, pairs, per_cu);
+__device__ __forceinline__ BlockCoord block_coord(Place at, int nblk, int nheads, int nseq, int group = 1) {
+  const int x = at.index % kXcds, k = at.index / kXcds;
+  const int pairs = nheads * nseq, rest = spread_pairs(nblk, pairs, at.slots);
   const int own = (pairs - rest + kXcds - 1) / kXcds;  // pairs that one XCD has to itself
   BlockCoord c;
   int pl;  // which of them
@@ -211,11 +216,11 @@ struct RaggedCoord {
   bool valid;
 };
 template <bool LEVELS>
-__device__ __forceinline__ RaggedCoord ragged_coord(const int32_t* cu, int rows, int nblk, int nheads, int nseq, int group,
-                                                    int per_cu) {
+__device__ __forceinline__ RaggedCoord ragged_coord(Place at, const int32_t* cu, int rows, int nblk, int nheads, int nseq,
+                                                    int group) {
   const int lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
-  const int pairs = nheads * nseq, lists = packed_through(nblk, pairs, per_cu) ? 1 : kXcds;  // (a list per XCD, or one for all)
-  const int x = blockIdx.x % lists, k = blockIdx.x / lists;
+  const int pairs = nheads * nseq, lists = packed_through(nblk, pairs, at.slots) ? 1 : kXcds;  // (a list per XCD, or one for all)
+  const int x = at.index % lists, k = at.index / lists;
   const int chunks = ((pairs + lists - 1) / lists + 63) / 64;
   int nb[kRaggedChunks];
 #pragma unroll
@@ -278,13 +283,13 @@ __device__ __forceinline__ BlockCoord scalar_coord(BlockCoord c) {
 // RAGGED (p.cu_seqlens is set) is a parameter of the instantiation, not asked here: short dense batches, whose time is
 // the chain of one workgroup, feel the search even as code that they jump over.
 template <bool CAUSAL, bool RAGGED, bool BACK = false>
-__device__ __forceinline__ BlockCoord row_block_coord(const Problem& p, int rows, int per_cu = 1) {
+__device__ __forceinline__ BlockCoord row_block_coord(Place at, const Problem& p, int rows) {
   const int nblk = (p.N + rows - 1) / rows;
   if (RAGGED && ragged_order(p.Hq * p.nseq)) {
-    const RaggedCoord r = ragged_coord<CAUSAL>(p.cu_seqlens, rows, nblk, p.Hq, p.nseq, p.G, per_cu);
+    const RaggedCoord r = ragged_coord<CAUSAL>(at, p.cu_seqlens, rows, nblk, p.Hq, p.nseq, p.G);
     return scalar_coord({CAUSAL ? r.left - 1 : r.blk, r.head, r.seq, r.valid});
   }
-  BlockCoord c = block_coord<CAUSAL, BACK>(nblk, p.Hq, p.nseq, p.G, per_cu);
+  BlockCoord c = block_coord<CAUSAL, BACK>(at, nblk, p.Hq, p.nseq, p.G);
   c.blk = nblk - 1 - c.blk;
   return c;
 }
@@ -293,14 +298,14 @@ __device__ __forceinline__ BlockCoord row_block_coord(const Problem& p, int rows
 // block_coord's order (batches with very many pairs) block indices therefore count from the END of the
 // longest possible sequence, and the blocks that a shorter one does not have are not valid.
 template <bool CAUSAL, bool RAGGED>
-__device__ __forceinline__ BlockCoord key_block_coord(const Problem& p, int keys, int per_cu = 1) {
+__device__ __forceinline__ BlockCoord key_block_coord(Place at, const Problem& p, int keys) {
   const int nblk = (p.Nk + keys - 1) / keys;
   if (RAGGED && ragged_order(p.Hkv * p.nseq)) {
     const RaggedCoord r =
-        ragged_coord<CAUSAL>(p.cu_seqlens_k ? p.cu_seqlens_k : p.cu_seqlens, keys, nblk, p.Hkv, p.nseq, 1, per_cu);
+        ragged_coord<CAUSAL>(at, p.cu_seqlens_k ? p.cu_seqlens_k : p.cu_seqlens, keys, nblk, p.Hkv, p.nseq, 1);
     return scalar_coord({CAUSAL ? r.blocks - r.left : r.blk, r.head, r.seq, r.valid});
   }
-  BlockCoord c = block_coord<CAUSAL>(nblk, p.Hkv, p.nseq, 1, per_cu);
+  BlockCoord c = block_coord<CAUSAL>(at, nblk, p.Hkv, p.nseq);
   if (CAUSAL && RAGGED && c.valid) {
     c.blk -= nblk - (seq_info(p, c.seq).nk + keys - 1) / keys;
     c.valid = c.blk >= 0;
@@ -491,6 +496,19 @@ template <bool F16>
 __device__ __forceinline__ float widen(bf16x8 v, int t) {
   if constexpr (F16) return (float)__builtin_bit_cast(f16x8, v)[t];
   else return (float)v[t];
+}
+
+// acc + the sum of the products of 8 raw 16-bit elements, one after the other. Every kernel that sums D = rowsum(dO o O) does it by
+// this chain, so that D is the same bits whoever forms it. (Held step by step: the compiler would otherwise take two products of
+// half precision together in some kernels, v_dot2c_f32_f16, and not in others.)
+template <bool F16>
+__device__ __forceinline__ float dot8(bf16x8 a, bf16x8 b, float acc) {
+#pragma unroll
+  for (int t = 0; t < 8; ++t) {
+    acc = __builtin_fmaf(widen<F16>(a, t), widen<F16>(b, t), acc);
+    if constexpr (F16) asm("" : "+v"(acc));
+  }
+  return acc;
 }
 
 // The 16-bit element in the low (hi = false) or high half of a 32-bit word, widened to float32.

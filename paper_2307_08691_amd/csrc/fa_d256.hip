@@ -59,7 +59,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lq = lane & 31, hh = lane >> 5;
-  const BlockCoord bc = row_block_coord<CAUSAL, RAGGED>(p, BR);
+  const BlockCoord bc = row_block_coord<CAUSAL, RAGGED>({blockIdx.x, kXcdUnits}, p, BR);
   if (!bc.valid) return;
   const int rowblk = bc.blk;
   const int h = bc.head, s = bc.seq;
@@ -297,7 +297,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 
 template <bool RAGGED>  // a.p.cu_seqlens is set
 static hipError_t launch_fwd256_d(const FwdArgs& a, int causal, hipStream_t st) {
-  dim3 grid(grid_size(a.p, (a.p.N + 127) / 128, a.p.Hq)), block(256);
+  dim3 grid(grid_size(a.p, (a.p.N + 127) / 128, a.p.Hq, kXcdUnits)), block(256);
   if (a.p.f16) {
     if (causal) hipLaunchKernelGGL((fwd256_kernel<true, true, RAGGED>), grid, block, 0, st, a);
     else hipLaunchKernelGGL((fwd256_kernel<false, true, RAGGED>), grid, block, 0, st, a);
@@ -326,7 +326,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lq = lane & 31, hh = lane >> 5;
-  const BlockCoord bc = row_block_coord<CAUSAL, RAGGED>(p, BR);
+  const BlockCoord bc = row_block_coord<CAUSAL, RAGGED>({blockIdx.x, kXcdUnits}, p, BR);
   if (!bc.valid) return;
   const int rowblk = bc.blk;
   const int h = bc.head, s = bc.seq;
@@ -388,8 +388,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
       const bf16x8 o = *(const bf16x8*)(op + 16 * ks);
-#pragma unroll
-      for (int t = 0; t < 8; ++t) part += widen<F16>(o, t) * widen<F16>(dOf[ks], t);
+      part = dot8<F16>(o, dOf[ks], part);
     }
     Dq = sum_with_partner32(part);
     if (row < n && hh == 0) a.Dvec[stat] = Dq;
@@ -538,7 +537,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lq = lane & 31, hh = lane >> 5;
-  const BlockCoord bc = key_block_coord<CAUSAL, RAGGED>(p, BC);
+  const BlockCoord bc = key_block_coord<CAUSAL, RAGGED>({blockIdx.x, kXcdUnits}, p, BC);
   if (!bc.valid) return;
   const int g = bc.head, s = bc.seq;
   const SeqInfo si = seq_info(p, s);
@@ -772,7 +771,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 
 template <bool RAGGED>
 static hipError_t launch_dkdv256(const BwdArgs& a, int causal, hipStream_t st) {
-  dim3 grid(grid_size(a.p, (a.p.Nk + 127) / 128, a.p.Hkv)), block(256);
+  dim3 grid(grid_size(a.p, (a.p.Nk + 127) / 128, a.p.Hkv, kXcdUnits)), block(256);
   if (a.p.f16) {
     if (causal) hipLaunchKernelGGL((dkdv256_kernel<true, true, RAGGED>), grid, block, 0, st, a);
     else hipLaunchKernelGGL((dkdv256_kernel<false, true, RAGGED>), grid, block, 0, st, a);
@@ -784,7 +783,7 @@ static hipError_t launch_dkdv256(const BwdArgs& a, int causal, hipStream_t st) {
 }
 template <bool F16, bool OWN_D, bool RAGGED>
 static hipError_t launch_dq256(const BwdArgs& a, int causal, hipStream_t st) {
-  dim3 grid(grid_size(a.p, (a.p.N + 127) / 128, a.p.Hq)), block(256);
+  dim3 grid(grid_size(a.p, (a.p.N + 127) / 128, a.p.Hq, kXcdUnits)), block(256);
   if (causal) hipLaunchKernelGGL((dq256_kernel<true, F16, OWN_D, RAGGED>), grid, block, 0, st, a);
   else hipLaunchKernelGGL((dq256_kernel<false, F16, OWN_D, RAGGED>), grid, block, 0, st, a);
   return hipGetLastError();

@@ -71,7 +71,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(D == 64 ? 4
   const int grp = w >> 2;
   const int lq = lane & 31, hh = lane >> 5;
   const int nblk = (p.N + BR - 1) / BR;
-  const BlockCoord bc = block_coord<CAUSAL>(nblk, p.Hq, p.nseq, p.G, D == 64 ? 2 : 1);
+  const BlockCoord bc = block_coord<CAUSAL>({blockIdx.x, (D == 64 ? 2 : 1) * kXcdUnits}, nblk, p.Hq, p.nseq, p.G);
   if (!bc.valid) return;
   const int rowblk = nblk - 1 - bc.blk;  // longest causal rows first
   const int s = bc.seq, h = bc.head, g = h / p.G;
@@ -300,7 +300,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(D == 64 ? 4
 }
 
 hipError_t launch_fwd_fp8(const Fp8Args& a, int d, int causal, hipStream_t st) {
-  dim3 grid(grid_size((a.p.N + 255) / 256, a.p.Hq * a.p.nseq, d == 64 ? 2 : 1)), block(512);
+  dim3 grid(grid_size((a.p.N + 255) / 256, a.p.Hq * a.p.nseq, (d == 64 ? 2 : 1) * kXcdUnits)), block(512);
   if (d == 128) {
     if (causal) hipLaunchKernelGGL((fwd_fp8_kernel<128, true>), grid, block, 0, st, a);
     else hipLaunchKernelGGL((fwd_fp8_kernel<128, false>), grid, block, 0, st, a);

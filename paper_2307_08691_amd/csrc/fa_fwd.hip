@@ -55,6 +55,7 @@ constexpr int kFwdChainMaxN = 1024;
 // without row maxima, whose second copy of the scores does not fit (fp16, 4 x 1777 tokens, 16 heads, MI355X:
 // 109 -> 98 us all the same). Not for the elementwise mask (more LDS).
 constexpr bool fwd_two_per_cu(int D, bool mask) { return D == 64 && !mask; }
+constexpr int fwd_slots(int D, bool mask) { return (fwd_two_per_cu(D, mask) ? 2 : 1) * kXcdUnits; }
 
 // SPLIT (forward only, few query rows against many keys): the workgroups of one (sequence,
 // key/value head) also split the KEY sequence, each writing a normalised partial O and its
@@ -95,6 +96,7 @@ __global__ __launch_bounds__(512)
     __attribute__((amdgpu_waves_per_eu(fwd_two_per_cu(D, MASK || LOCAL == kBlocks) ? 4 : 2, fwd_two_per_cu(D, MASK || LOCAL == kBlocks) ? 4 : 2))) void
     fwd_kernel(FwdArgs a) {
   constexpr bool TWO = fwd_two_per_cu(D, MASK || LOCAL == kBlocks);
+  constexpr int SLOTS = fwd_slots(D, MASK || LOCAL == kBlocks);
   static_assert(!LOCAL || (!CAUSAL && !SPLIT && !DROPOUT && !PAD && !MASK), "the window variant is built for the plain kernel");
   static_assert(!RAGGED || (!SPLIT && !MASK && LOCAL != kBlocks), "no entry point packs these batches");
   constexpr int AHEAD_QK = TWO ? 1 : kFwdAheadQK, AHEAD_PV = TWO ? 1 : kFwdAheadPV;
@@ -122,8 +124,8 @@ __global__ __launch_bounds__(512)
   const int lq = lane & 31, hh = lane >> 5;
   const int nsplit = SPLIT ? a.nsplit : 1;
   const int nblk = ((SPLIT ? p.N * p.G : p.N) + BR - 1) / BR;
-  const BlockCoord bc = SPLIT ? block_coord<false>(nblk * nsplit, p.Hkv, p.nseq, 1, TWO ? 2 : 1)
-                              : row_block_coord<CAUSAL, RAGGED>(p, BR, TWO ? 2 : 1);
+  const BlockCoord bc = SPLIT ? block_coord<false>({blockIdx.x, SLOTS}, nblk * nsplit, p.Hkv, p.nseq)
+                              : row_block_coord<CAUSAL, RAGGED>({blockIdx.x, SLOTS}, p, BR);
   if (!bc.valid) return;
   const int split = SPLIT ? bc.blk % nsplit : 0;
   const int rowblk = SPLIT ? bc.blk / nsplit : bc.blk;
@@ -979,7 +981,7 @@ static hipError_t launch_fwd_split(const FwdArgs& a, int causal, hipStream_t st)
     if (hipError_t e = launch_fwd_decode(a, D, causal, st)) return e;
   } else {
     const int nblk = (a.p.N * a.p.G + 255) / 256;
-    dim3 grid(grid_size(nblk * a.nsplit, a.p.Hkv * a.p.nseq, fwd_two_per_cu(D, false) ? 2 : 1));
+    dim3 grid(grid_size(nblk * a.nsplit, a.p.Hkv * a.p.nseq, fwd_slots(D, false)));
     if (causal) hipLaunchKernelGGL((fwd_kernel<D, true, true, F16>), grid, block, 0, st, a);
     else hipLaunchKernelGGL((fwd_kernel<D, false, true, F16>), grid, block, 0, st, a);
     if (hipError_t e = hipGetLastError()) return e;
@@ -1019,7 +1021,7 @@ static bool stream_form(int d, int causal, int n, int nk, int pairs) {
 // RAGGED: a.p.cu_seqlens is set.
 template <int D, bool F16, bool RAGGED>
 static hipError_t launch_fwd_d(const FwdArgs& a, int causal, hipStream_t st) {
-  const dim3 grid(grid_size(a.p, (a.p.N + 255) / 256, a.p.Hq, fwd_two_per_cu(D, a.p.mask || a.p.bmask) ? 2 : 1)), block(512);
+  const dim3 grid(grid_size(a.p, (a.p.N + 255) / 256, a.p.Hq, fwd_slots(D, a.p.mask || a.p.bmask))), block(512);
   if constexpr (!RAGGED) {  // the entry points keep everything else away from the elementwise mask and the block-sparse pattern
     if (a.p.mask) {
       if (causal) hipLaunchKernelGGL((fwd_kernel<D, true, false, F16, false, false, true>), grid, block, 0, st, a);

@@ -47,7 +47,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lq = lane & 31, hh = lane >> 5;
-  const BlockCoord bc = block_coord<false, true>(1, p.Hkv, p.nseq);  // (from the last pair to the first: see launch_bwd_d)
+  const BlockCoord bc = block_coord<false, true>({blockIdx.x, kXcdUnits}, 1, p.Hkv, p.nseq);  // (from the last pair to the first: see launch_bwd_d)
   if (!bc.valid) return;
   const int g = bc.head, s = bc.seq;
   const SeqInfo si = seq_info(p, s);
@@ -145,9 +145,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
     }
     float part = 0.f;
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks)
-#pragma unroll
-      for (int t = 0; t < 8; ++t) part += widen<F16>(ov[ks], t) * widen<F16>(gv[ks], t);
+    for (int ks = 0; ks < KS; ++ks) part = dot8<F16>(ov[ks], gv[ks], part);
     const float dsum = sum_with_partner32(part);
     if (hh == 0) {
       Ls[hi * rows64 + row] = row < n ? lse * kLog2e : INFINITY;  // rows past the end: P = 0
@@ -338,7 +336,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
 
 template <int KW, int NW>
 static hipError_t launch_short(const BwdArgs& a, int causal, hipStream_t st) {
-  const dim3 grid(grid_size(1, a.p.Hkv * a.p.nseq)), block(64 * NW);
+  const dim3 grid(grid_size(1, a.p.Hkv * a.p.nseq, kXcdUnits)), block(64 * NW);
   if (a.p.f16) {
     if (causal) hipLaunchKernelGGL((bwd_short_kernel<KW, NW, true, true>), grid, block, 0, st, a);
     else hipLaunchKernelGGL((bwd_short_kernel<KW, NW, false, true>), grid, block, 0, st, a);

@@ -28,7 +28,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lq = lane & 31, hh = lane >> 5;
-  const BlockCoord bc = row_block_coord<CAUSAL, RAGGED>(p, BR, 2);
+  const BlockCoord bc = row_block_coord<CAUSAL, RAGGED>({blockIdx.x, 2 * kXcdUnits}, p, BR);
   if (!bc.valid) return;
   const int h = bc.head, s = bc.seq;
   const SeqInfo si = seq_info(p, s);
@@ -288,7 +288,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 
 template <int D, bool F16, bool RAGGED>
 static hipError_t launch_stream_d(const FwdArgs& a, int causal, hipStream_t st) {
-  const dim3 grid(grid_size(a.p, (a.p.N + 127) / 128, a.p.Hq, 2)), block(256);
+  const dim3 grid(grid_size(a.p, (a.p.N + 127) / 128, a.p.Hq, 2 * kXcdUnits)), block(256);
   if (causal) hipLaunchKernelGGL((fwd_stream_kernel<D, true, F16, RAGGED>), grid, block, 0, st, a);
   else hipLaunchKernelGGL((fwd_stream_kernel<D, false, F16, RAGGED>), grid, block, 0, st, a);
   return hipGetLastError();

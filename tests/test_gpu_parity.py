@@ -314,6 +314,46 @@ def test_pairs_that_do_not_divide_over_the_xcds(H, N, d, packed, causal):
             assert torch.equal(x[:, h], y[:, 0]), (name, h)
 
 
+# (512 pairs: blocks of 256 rows, or of 128 in the forms of four wavefronts and among the mask's keys, that fill rounds of the chip
+# without a rest take two launches; one sequence of them takes one grid)
+@pytest.mark.parametrize("kind,d,N,causal", [("plain", 128, 300, False), ("plain", 128, 512, True), ("plain", 96, 257, True),
+                                             ("plain", 80, 400, False), ("plain", 104, 511, True), ("plain", 48, 300, False),
+                                             ("plain", 32, 510, True), ("plain", 64, 300, False), ("plain", 64, 600, True),
+                                             ("window", 128, 400, False), ("window", 64, 300, False), ("dropout", 64, 390, True),
+                                             ("dropout", 64, 512, False), ("mask", 128, 300, True), ("mask", 64, 500, False),
+                                             ("blocks", 128, 512, False), ("blocks", 64, 512, True)])
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+def test_one_grid_and_two_launches_agree_bitwise(kind, d, N, causal, dtype):
+    """The backward is a pre-pass and one grid, or two kernels, by how the blocks divide over the chip; a sequence's gradients do
+    not depend on it."""
+    B, H, scale = 64, 8, d ** -0.5
+    g = torch.Generator(device="cuda").manual_seed(9700 + N + d)
+    et = torch.bfloat16 if dtype == "bf16" else torch.float16
+    Q, K, V, dO = (torch.randn((B, N, H, d), generator=g, device="cuda", dtype=et) for _ in range(4))
+    M = binding.mask_buffer(1, 1, N, N, "cuda", et) if kind == "mask" else None
+    if kind == "mask":
+        M.copy_(torch.randn(M.shape, generator=g, device="cuda", dtype=et))
+    nb = -(-N // 64)
+    pattern = (torch.rand((1, H, nb, nb), generator=g, device="cuda") < 0.5).to(torch.uint8) if kind == "blocks" else None
+    fwd, bwd = {
+        "plain": (lambda q, k, v: binding.fa_cross_fwd(q, k, v, scale, causal),
+                  lambda q, k, v, o, do, l: binding.fa_cross_bwd(q, k, v, o, do, l, scale, causal)),
+        "window": (lambda q, k, v: binding.fa_local_fwd(q, k, v, scale, 100, 30),
+                   lambda q, k, v, o, do, l: binding.fa_local_bwd(q, k, v, o, do, l, scale, 100, 30)),
+        "dropout": (lambda q, k, v: binding.fa_dropout_fwd(q, k, v, scale, causal, 0.2, 78),
+                    lambda q, k, v, o, do, l: binding.fa_dropout_bwd(q, k, v, o, do, l, scale, causal, 0.2, 78)),
+        "mask": (lambda q, k, v: binding.fa_mask_fwd(q, k, v, M, scale, causal),
+                 lambda q, k, v, o, do, l: binding.fa_mask_bwd(q, k, v, M, o, do, l, scale, causal)),
+        "blocks": (lambda q, k, v: binding.fa_blocksparse_fwd(q, k, v, pattern, 64, scale, causal),
+                   lambda q, k, v, o, do, l: binding.fa_blocksparse_bwd(q, k, v, pattern, 64, o, do, l, scale, causal)),
+    }[kind]
+    O, L = fwd(Q, K, V)
+    whole = bwd(Q, K, V, O, dO, L)
+    alone = bwd(*(x[:1].contiguous() for x in (Q, K, V, O, dO, L)))  # (the first: the generator of dropout counts sequences)
+    for name, x, y in zip(("dQ", "dK", "dV"), whole, alone):
+        assert torch.isfinite(x).all() and torch.equal(x[0], y[0]), name
+
+
 @pytest.mark.parametrize("d", [64, 128])
 def test_cache_and_fp8_pairs_that_do_not_divide_over_the_xcds(d):
     """As above for the split-key kernel (nine pairs, more shares than an XCD holds) and the FP8 kernel."""

@@ -886,7 +886,60 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 }
 
 // Combine the partial results of the key shares: one thread per 4 output elements. DECODE: the shares are
-// those of fwd_decode_kernel (always nsplit), otherwise those of the split kernel.
+// those of fwd_decode_kernel (always nsplit, and every one has written its logsumexp), otherwise those of the split kernel.
+// Few threads per row and a handful of shares: the time is the chain of loads. FLY shares are requested together, and up to
+// FLY are all that there are: logsumexps and partial rows are then on their way at once. (A share without keys for this
+// row may have written no partial O: what is read in its place is not used.)
+template <int D, bool F16, bool DECODE, int FLY>
+__device__ __forceinline__ void merge_row(const FwdArgs& a, long r, int c, long li, int nshare, long nrows) {
+  auto lse_of = [&](int k) { return a.Lpart[(long)(k < nshare ? k : nshare - 1) * nrows + li]; };
+  auto row_of = [&](int k) { return *(const f32x4*)(a.Opart + ((long)(k < nshare ? k : nshare - 1) * nrows + r) * D + 4 * c); };
+  float lp[FLY];
+  f32x4 o[FLY];
+  float mx = -INFINITY;
+  auto request = [&](int k0) {
+#pragma unroll
+    for (int u = 0; u < FLY; ++u) lp[u] = lse_of(k0 + u);
+#pragma unroll
+    for (int u = 0; u < FLY; ++u) o[u] = row_of(k0 + u);
+  };
+  if (nshare > FLY) {
+    for (int k0 = FLY; k0 < nshare; k0 += FLY) {
+      float x[FLY];
+#pragma unroll
+      for (int u = 0; u < FLY; ++u) x[u] = lse_of(k0 + u);
+#pragma unroll
+      for (int u = 0; u < FLY; ++u) mx = fmaxf(mx, x[u]);
+    }
+  }
+  request(0);
+#pragma unroll
+  for (int u = 0; u < FLY; ++u) mx = fmaxf(mx, lp[u]);
+  if (mx == -INFINITY) {  // no share holds a key that this row sees: P = 0, so O = 0 and L = -inf
+    *(u32x2*)(a.O + r * D + 4 * c) = (u32x2){0u, 0u};
+    if (c == 0) a.LSE[li] = -INFINITY;
+    return;
+  }
+  float z = 0.f;
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  for (int k0 = 0;;) {
+#pragma unroll
+    for (int u = 0; u < FLY; ++u) {
+      if (k0 + u >= nshare || lp[u] == -INFINITY) continue;
+      const float wgt = __expf(lp[u] - mx);
+      z += wgt;
+      acc += o[u] * wgt;
+    }
+    if ((k0 += FLY) >= nshare) break;
+    request(k0);
+  }
+  const float inv = 1.f / z;  // some share holds a visible key
+  u32x2 x;
+  x[0] = pack2<F16>(acc[0] * inv, acc[1] * inv);
+  x[1] = pack2<F16>(acc[2] * inv, acc[3] * inv);
+  *(u32x2*)(a.O + r * D + 4 * c) = x;
+  if (c == 0) a.LSE[li] = mx + __logf(z);
+}
 template <int D, bool F16, bool DECODE>
 __global__ __launch_bounds__(256) void fwd_merge_kernel(FwdArgs a) {
   constexpr int TPR = D / 4;  // threads per (token, head) row
@@ -899,56 +952,22 @@ __global__ __launch_bounds__(256) void fwd_merge_kernel(FwdArgs a) {
   const int h = (int)(r - tok * p.Hq);
   const long b = tok / p.N, q = tok - b * p.N;
   const long li = b * p.lse_seq_stride + (long)h * p.lse_head_stride + q;
-  // (a cache without keys: the split kernel wrote nothing for this sequence)
-  const int ncol = ((a.seqlens_k ? cache_length(a, b) : p.Nk) + 63) / 64;
-  int nshare = a.nsplit;
-  if (!DECODE) {
+  if constexpr (DECODE) {
+    if (a.nsplit <= 4) merge_row<D, F16, DECODE, 4>(a, r, c, li, a.nsplit, nrows);
+    else if (a.nsplit <= 8) merge_row<D, F16, DECODE, 8>(a, r, c, li, a.nsplit, nrows);
+    else merge_row<D, F16, DECODE, 16>(a, r, c, li, a.nsplit, nrows);
+  } else {
+    const int ncol = ((a.seqlens_k ? cache_length(a, b) : p.Nk) + 63) / 64;
+    if (ncol == 0) {  // (a cache without keys: the split kernel wrote nothing for this sequence)
+      *(u32x2*)(a.O + r * D + 4 * c) = (u32x2){0u, 0u};
+      if (c == 0) a.LSE[li] = -INFINITY;
+      return;
+    }
     const int per = split_share_blocks(ncol, (p.Nk + 63) / 64, a.nsplit);
-    nshare = (ncol + per - 1) / per;
+    const int nshare = (ncol + per - 1) / per;
     if (nshare == 1) return;  // the split kernel wrote O and LSE
+    merge_row<D, F16, DECODE, 4>(a, r, c, li, nshare, nrows);
   }
-  // Few threads per row and a handful of shares: the time is the chain of loads, so those of four shares are requested
-  // together (a share without keys for this row may have written no partial O: what is read in its place is not used).
-  constexpr int FLY = 4;
-  auto part_lse = [&](int k) { return k < nshare ? a.Lpart[(long)k * nrows + li] : -INFINITY; };
-  float mx = -INFINITY;
-  if (ncol > 0)
-    for (int k0 = 0; k0 < nshare; k0 += FLY) {
-      float lp[FLY];
-#pragma unroll
-      for (int u = 0; u < FLY; ++u) lp[u] = part_lse(k0 + u);
-#pragma unroll
-      for (int u = 0; u < FLY; ++u) mx = fmaxf(mx, lp[u]);
-    }
-  if (mx == -INFINITY) {  // no share holds a key that this row sees: P = 0, so O = 0 and L = -inf
-    *(u32x2*)(a.O + r * D + 4 * c) = (u32x2){0u, 0u};
-    if (c == 0) a.LSE[li] = -INFINITY;
-    return;
-  }
-  float z = 0.f;
-  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  for (int k0 = 0; k0 < nshare; k0 += FLY) {
-    float lp[FLY];
-    f32x4 o[FLY];
-#pragma unroll
-    for (int u = 0; u < FLY; ++u) {
-      lp[u] = part_lse(k0 + u);
-      if (k0 + u < nshare) o[u] = *(const f32x4*)(a.Opart + ((long)(k0 + u) * nrows + r) * D + 4 * c);
-    }
-#pragma unroll
-    for (int u = 0; u < FLY; ++u) {
-      if (lp[u] == -INFINITY) continue;
-      const float wgt = __expf(lp[u] - mx);
-      z += wgt;
-      acc += o[u] * wgt;
-    }
-  }
-  const float inv = 1.f / z;  // some share holds a visible key
-  u32x2 o;
-  o[0] = pack2<F16>(acc[0] * inv, acc[1] * inv);
-  o[1] = pack2<F16>(acc[2] * inv, acc[3] * inv);
-  *(u32x2*)(a.O + r * D + 4 * c) = o;
-  if (c == 0) a.LSE[li] = mx + __logf(z);
 }
 
 // A sequence without any key (possible in ragged batches with two lengths) has no softmax. Its

@@ -60,6 +60,18 @@ def test_contiguous_cache_with_lengths(Nq, Hq, Hkv, d, num_splits, causal):
     check_contiguous(draw(18000 + Nq + d, 5, Nq, cap, Hq, Hkv, d), [cap, 1, 0, 517, 64], causal, num_splits)
 
 
+# (more workgroups than compute units and short shares: two workgroups on a compute unit; 33 sequences x 8 heads and 300 x 1, of which
+# the latter are more than are ranked by length; every remainder of a tile of 32 keys for four and eight wavefronts, empty caches)
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("B,Nq,Hq,Hkv,cap,num_splits", [(33, 1, 16, 8, 500, 1), (33, 3, 8, 8, 257, 1), (300, 1, 2, 1, 130, 1),
+                                                        (20, 1, 32, 8, 700, 3)])
+def test_many_short_caches(B, Nq, Hq, Hkv, cap, num_splits, d, causal):
+    lens = [(i * 37) % (cap + 1) for i in range(B)]
+    lens[B // 2], lens[B - 1] = cap, 0
+    check_contiguous(draw(18050 + B + d, B, Nq, cap, Hq, Hkv, d), lens, causal, num_splits)
+
+
 def page_out(Kc, Vc, lens, page, seed, spare=3):
     """Cut contiguous caches [B, cap, Hkv, d] into pages that lie shuffled in pools with `spare` pages
     nobody owns; pages that a sequence does not reach, the spare ones and the slack of every last

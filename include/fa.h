@@ -59,7 +59,7 @@ extern "C" {
                                    inconsistent ragged description */
 #define FA_ERR_UNSUPPORTED (-3) /* head dim neither a multiple of 8 in 8 .. 128 nor 256 (dropout, mask, split keys: not 64 or 128) */
 #define FA_ERR_ALIGN (-4)       /* a tensor pointer is not 16-byte aligned */
-#define FA_ERR_WORKSPACE (-5)   /* workspace smaller than fa_*_workspace_bytes() */
+#define FA_ERR_WORKSPACE (-5)   /* workspace smaller than fa_*_workspace_bytes() (backward: than D) */
 #define FA_ERR_LAUNCH (-6)      /* the HIP runtime refused a launch; see fa_last_hip_error() */
 
 /* Library version: major * 10000 + minor * 100 + patch. */
@@ -93,6 +93,12 @@ int fa_fwd(const void* Q, const void* K, const void* V, void* O, float* LSE,
  * are of both kinds, with the same bits. Where it is faster, short sequences (up to 512 tokens, d = 64,
  * without dropout, window or mask) take ONE kernel instead, with the same bits; it
  * leaves the workspace untouched. All three outputs are bit-reproducible.
+ * Groups of four and more query heads to a key/value head (more than 1200 rows with four, 320 with eight), on grids that leave compute units idle: several workgroups
+ * share a block of keys and leave float32 sums of dK and dV behind D, and a further kernel adds them; dK and dV then
+ * differ from those of a larger batch, or of the separate stages below, by the rounding of float32 sums. A workspace that
+ * holds D alone (4 * B * N * Hq bytes, rounded up to 256) is accepted too, and the pass then takes no shares: such
+ * problems are the only ones for which fa_bwd_workspace_bytes() asks for more, up to 64 MiB. The same goes
+ * for the other backward entry points but those with a mask, a block pattern or packed batches of two lengths.
  */
 size_t fa_bwd_workspace_bytes(int B, int Hq, int Hkv, int N, int d);
 int fa_bwd(const void* Q, const void* K, const void* V, const void* O, const void* dO,
@@ -121,8 +127,8 @@ int fa_bwd_stages(const void* Q, const void* K, const void* V, const void* O, co
 /*
  * fa_bwd for callers that cannot allocate device memory or pass a workspace: code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc. Same arguments, results
- * (bit for bit) and errors as fa_bwd, without `workspace`: D = rowsum(dO o O) goes to a
- * file-scope device array of FA_NOALLOC_MAX_ROWS floats (8 MiB) inside the library, which
+ * (bit for bit) and errors as fa_bwd, without `workspace`: D = rowsum(dO o O) and the sums of shares go to a
+ * file-scope device array (8 MiB for FA_NOALLOC_MAX_ROWS floats of D, 64 MiB for the sums) inside the library, which
  * every GPU the library has run on holds until the process ends. The call itself allocates
  * and frees nothing. B * N * Hq above FA_NOALLOC_MAX_ROWS returns FA_ERR_WORKSPACE and nothing
  * runs. The first call on a device looks the array's address up (hipGetSymbolAddress, with

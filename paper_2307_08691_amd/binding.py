@@ -408,11 +408,14 @@ def _out(t, name, shape, dtype, device):
     return t
 
 
-def _workspace(ws, nbytes, device):
+def _workspace(ws, nbytes, device, rows=None):
+    """rows (backward): one that holds D alone, a float for each (query row, head), is enough (the pass then takes no shares)."""
     import torch
     if ws is None:
         return torch.empty(nbytes, dtype=torch.uint8, device=device)
     _need(ws, "workspace", None, None, device)
+    if rows is not None:
+        nbytes = (4 * rows + 255) // 256 * 256
     if ws.numel() * ws.element_size() < nbytes:
         raise ValueError(f"workspace holds {ws.numel() * ws.element_size()} bytes, {nbytes} are needed")
     return ws
@@ -508,7 +511,7 @@ def fa_bwd(Q, K, V, O, dO, LSE, scale: float, causal: bool, dQ=None, dK=None, dV
     import torch
     x = _dense(Q, K, V, (torch.bfloat16,), one_length=True)
     dQ, dK, dV = _bwd_tensors(x, O, dO, LSE, dQ, dK, dV)
-    ws = _workspace(workspace, fa_bwd_workspace_bytes(x.B, x.Hq, x.Hkv, x.Nq, x.d), x.dev)
+    ws = _workspace(workspace, fa_bwd_workspace_bytes(x.B, x.Hq, x.Hkv, x.Nq, x.d), x.dev, x.B * x.Nq * x.Hq)
     _check(fa_bwd_raw(_ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(dO), _ptr(LSE), _ptr(dQ), _ptr(dK), _ptr(dV),
                       _ptr(ws), _wsbytes(ws), x.B, x.Hq, x.Hkv, x.Nq, x.d, scale, causal, _stream()))
     return dQ, dK, dV
@@ -519,7 +522,7 @@ FA_NOALLOC_MAX_ROWS = 2 * 1024 * 1024  # (query row, head) pairs that fa_bwd_noa
 
 def fa_bwd_noalloc(Q, K, V, O, dO, LSE, scale: float, causal: bool, dQ, dK, dV) -> None:
     """Dense backward into caller-supplied dQ, dK, dV without a workspace: nothing is allocated,
-    here or in the library (D lives in a static device array; at most FA_NOALLOC_MAX_ROWS
+    here or in the library (D and the sums of shares live in a static device array; at most FA_NOALLOC_MAX_ROWS
     (query row, head) pairs). Calls on one GPU must not overlap."""
     import torch
     x = _dense(Q, K, V, (torch.bfloat16,), one_length=True)
@@ -535,7 +538,7 @@ def fa_bwd_stages(Q, K, V, O, dO, LSE, scale: float, causal: bool, stages: int, 
     import torch
     x = _dense(Q, K, V, (torch.bfloat16,), one_length=True)
     _bwd_tensors(x, O, dO, LSE, dQ, dK, dV)
-    ws = _workspace(workspace, fa_bwd_workspace_bytes(x.B, x.Hq, x.Hkv, x.Nq, x.d), x.dev)
+    ws = _workspace(workspace, fa_bwd_workspace_bytes(x.B, x.Hq, x.Hkv, x.Nq, x.d), x.dev, x.B * x.Nq * x.Hq)
     _check(fa_bwd_stages_raw(_ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(dO), _ptr(LSE), _ptr(dQ), _ptr(dK), _ptr(dV),
                              _ptr(ws), _wsbytes(ws), x.B, x.Hq, x.Hkv, x.Nq, x.d, scale, causal, stages, _stream()))
 
@@ -565,7 +568,7 @@ def fa_varlen_bwd(Q, K, V, O, dO, LSE, cu_seqlens, max_seqlen: int, scale: float
     import torch
     x = _packed(Q, K, V, cu_seqlens, allowed=(torch.bfloat16, torch.float16))
     dQ, dK, dV = _bwd_tensors(x, O, dO, LSE, dQ, dK, dV)
-    ws = _workspace(workspace, fa_varlen_bwd_workspace_bytes(x.Tq, x.Hq, x.Hkv, x.d), x.dev)
+    ws = _workspace(workspace, fa_varlen_bwd_workspace_bytes(x.Tq, x.Hq, x.Hkv, x.d), x.dev, x.Tq * x.Hq)
     _check(fa_varlen_bwd_raw(_ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(dO), _ptr(LSE), _ptr(dQ), _ptr(dK), _ptr(dV),
                              _ptr(ws), _wsbytes(ws), _ptr(cu_seqlens), x.nseq, x.Tq, max_seqlen, x.Hq, x.Hkv, x.d, scale,
                              causal, _stream(), x.et == torch.float16))
@@ -596,7 +599,7 @@ def fa_cross_bwd(Q, K, V, O, dO, LSE, scale: float, causal: bool, dQ=None, dK=No
     import torch
     x = _dense(Q, K, V)
     dQ, dK, dV = _bwd_tensors(x, O, dO, LSE, dQ, dK, dV)
-    ws = _workspace(workspace, fa_cross_bwd_workspace_bytes(x.B, x.Hq, x.Hkv, x.Nq, x.Nk, x.d), x.dev)
+    ws = _workspace(workspace, fa_cross_bwd_workspace_bytes(x.B, x.Hq, x.Hkv, x.Nq, x.Nk, x.d), x.dev, x.B * x.Nq * x.Hq)
     _check(fa_cross_bwd_raw(_ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(dO), _ptr(LSE), _ptr(dQ), _ptr(dK), _ptr(dV),
                             _ptr(ws), _wsbytes(ws), x.B, x.Hq, x.Hkv, x.Nq, x.Nk, x.d, scale, causal, _stream(),
                             x.et == torch.float16))
@@ -627,7 +630,7 @@ def fa_dropout_bwd(Q, K, V, O, dO, LSE, scale: float, causal: bool, p_drop: floa
     import torch
     x = _dense(Q, K, V)
     dQ, dK, dV = _bwd_tensors(x, O, dO, LSE, dQ, dK, dV)
-    ws = _workspace(workspace, fa_cross_bwd_workspace_bytes(x.B, x.Hq, x.Hkv, x.Nq, x.Nk, x.d), x.dev)
+    ws = _workspace(workspace, fa_cross_bwd_workspace_bytes(x.B, x.Hq, x.Hkv, x.Nq, x.Nk, x.d), x.dev, x.B * x.Nq * x.Hq)
     _check(fa_dropout_bwd_raw(_ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(dO), _ptr(LSE), _ptr(dQ), _ptr(dK), _ptr(dV),
                               _ptr(ws), _wsbytes(ws), x.B, x.Hq, x.Hkv, x.Nq, x.Nk, x.d, scale, causal, p_drop, seed,
                               _stream(), x.et == torch.float16))
@@ -651,7 +654,7 @@ def fa_varlen_dropout_bwd(Q, K, V, O, dO, LSE, cu_seqlens, max_seqlen: int, scal
     import torch
     x = _packed(Q, K, V, cu_seqlens, allowed=(torch.bfloat16, torch.float16))
     dQ, dK, dV = _bwd_tensors(x, O, dO, LSE, dQ, dK, dV)
-    ws = _workspace(workspace, fa_varlen_bwd_workspace_bytes(x.Tq, x.Hq, x.Hkv, x.d), x.dev)
+    ws = _workspace(workspace, fa_varlen_bwd_workspace_bytes(x.Tq, x.Hq, x.Hkv, x.d), x.dev, x.Tq * x.Hq)
     _check(fa_varlen_dropout_bwd_raw(_ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(dO), _ptr(LSE), _ptr(dQ), _ptr(dK),
                                      _ptr(dV), _ptr(ws), _wsbytes(ws), _ptr(cu_seqlens), x.nseq, x.Tq, max_seqlen, x.Hq,
                                      x.Hkv, x.d, scale, causal, p_drop, seed, _stream(), x.et == torch.float16))
@@ -696,7 +699,7 @@ def fa_mask_bwd(Q, K, V, M, O, dO, LSE, scale: float, causal: bool, dQ=None, dK=
     x = _dense(Q, K, V)
     bs, hs, rs = _mask_strides(M, x)
     dQ, dK, dV = _bwd_tensors(x, O, dO, LSE, dQ, dK, dV)
-    ws = _workspace(workspace, fa_cross_bwd_workspace_bytes(x.B, x.Hq, x.Hkv, x.Nq, x.Nk, x.d), x.dev)
+    ws = _workspace(workspace, fa_cross_bwd_workspace_bytes(x.B, x.Hq, x.Hkv, x.Nq, x.Nk, x.d), x.dev, x.B * x.Nq * x.Hq)
     _check(fa_mask_bwd_raw(_ptr(Q), _ptr(K), _ptr(V), _ptr(M), _ptr(O), _ptr(dO), _ptr(LSE), _ptr(dQ), _ptr(dK),
                            _ptr(dV), _ptr(ws), _wsbytes(ws), x.B, x.Hq, x.Hkv, x.Nq, x.Nk, x.d, scale, causal, bs, hs, rs,
                            _stream(), x.et == torch.float16))
@@ -715,7 +718,7 @@ def fa_mask_bwd_dmask(Q, K, V, M, O, dO, LSE, scale: float, causal: bool, dQ=Non
         dM = mask_buffer(x.B, x.Hq, x.Nq, x.Nk, device=x.dev, dtype=x.et)
     if dM.dtype != x.et or dM.device != x.dev or tuple(dM.shape) != (x.B, x.Hq, x.Nq, x.Nk) or dM.stride(3) != 1:
         raise ValueError("dM must be [B, Hq, Nq, Nk] of the element type of Q, on its device, key dimension contiguous")
-    ws = _workspace(workspace, fa_cross_bwd_workspace_bytes(x.B, x.Hq, x.Hkv, x.Nq, x.Nk, x.d), x.dev)
+    ws = _workspace(workspace, fa_cross_bwd_workspace_bytes(x.B, x.Hq, x.Hkv, x.Nq, x.Nk, x.d), x.dev, x.B * x.Nq * x.Hq)
     _check(fa_mask_bwd_dmask_raw(_ptr(Q), _ptr(K), _ptr(V), _ptr(M), _ptr(O), _ptr(dO), _ptr(LSE), _ptr(dQ), _ptr(dK),
                                  _ptr(dV), _ptr(dM), _ptr(ws), _wsbytes(ws), x.B, x.Hq, x.Hkv, x.Nq, x.Nk, x.d, scale,
                                  causal, bs, hs, rs, dM.stride(0), dM.stride(1), dM.stride(2), _stream(),
@@ -748,7 +751,7 @@ def fa_local_bwd(Q, K, V, O, dO, LSE, scale: float, window_left: int, window_rig
     import torch
     x = _dense(Q, K, V)
     dQ, dK, dV = _bwd_tensors(x, O, dO, LSE, dQ, dK, dV)
-    ws = _workspace(workspace, fa_cross_bwd_workspace_bytes(x.B, x.Hq, x.Hkv, x.Nq, x.Nk, x.d), x.dev)
+    ws = _workspace(workspace, fa_cross_bwd_workspace_bytes(x.B, x.Hq, x.Hkv, x.Nq, x.Nk, x.d), x.dev, x.B * x.Nq * x.Hq)
     _check(fa_local_bwd_raw(_ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(dO), _ptr(LSE), _ptr(dQ), _ptr(dK), _ptr(dV),
                             _ptr(ws), _wsbytes(ws), x.B, x.Hq, x.Hkv, x.Nq, x.Nk, x.d, scale, window_left, window_right,
                             _stream(), x.et == torch.float16))
@@ -773,7 +776,7 @@ def fa_varlen_local_bwd(Q, K, V, O, dO, LSE, cu_seqlens, max_seqlen: int, scale:
     import torch
     x = _packed(Q, K, V, cu_seqlens, allowed=(torch.bfloat16, torch.float16))
     dQ, dK, dV = _bwd_tensors(x, O, dO, LSE, dQ, dK, dV)
-    ws = _workspace(workspace, fa_varlen_bwd_workspace_bytes(x.Tq, x.Hq, x.Hkv, x.d), x.dev)
+    ws = _workspace(workspace, fa_varlen_bwd_workspace_bytes(x.Tq, x.Hq, x.Hkv, x.d), x.dev, x.Tq * x.Hq)
     _check(fa_varlen_local_bwd_raw(_ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(dO), _ptr(LSE), _ptr(dQ), _ptr(dK),
                                    _ptr(dV), _ptr(ws), _wsbytes(ws), _ptr(cu_seqlens), x.nseq, x.Tq, max_seqlen, x.Hq,
                                    x.Hkv, x.d, scale, window_left, window_right, _stream(), x.et == torch.float16))
@@ -809,7 +812,7 @@ def fa_blocksparse_bwd(Q, K, V, block_mask, block: int, O, dO, LSE, scale: float
     x = _dense(Q, K, V)
     bs, hs = _block_mask_strides(block_mask, x, block)
     dQ, dK, dV = _bwd_tensors(x, O, dO, LSE, dQ, dK, dV)
-    ws = _workspace(workspace, fa_cross_bwd_workspace_bytes(x.B, x.Hq, x.Hkv, x.Nq, x.Nk, x.d), x.dev)
+    ws = _workspace(workspace, fa_cross_bwd_workspace_bytes(x.B, x.Hq, x.Hkv, x.Nq, x.Nk, x.d), x.dev, x.B * x.Nq * x.Hq)
     _check(fa_blocksparse_bwd_raw(_ptr(Q), _ptr(K), _ptr(V), _ptr(block_mask), _ptr(O), _ptr(dO), _ptr(LSE), _ptr(dQ),
                                   _ptr(dK), _ptr(dV), _ptr(ws), _wsbytes(ws), x.B, x.Hq, x.Hkv, x.Nq, x.Nk, x.d, scale,
                                   causal, block, bs, hs, _stream(), x.et == torch.float16))
@@ -866,7 +869,7 @@ def fa_varlen_cross_bwd(Q, K, V, O, dO, LSE, cu_seqlens_q, cu_seqlens_k, max_seq
     import torch
     x = _packed(Q, K, V, cu_seqlens_q, cu_seqlens_k, allowed=(torch.bfloat16, torch.float16))
     dQ, dK, dV = _bwd_tensors(x, O, dO, LSE, dQ, dK, dV)
-    ws = _workspace(workspace, fa_varlen_bwd_workspace_bytes(x.Tq, x.Hq, x.Hkv, x.d), x.dev)
+    ws = _workspace(workspace, fa_varlen_bwd_workspace_bytes(x.Tq, x.Hq, x.Hkv, x.d), x.dev, x.Tq * x.Hq)
     _check(fa_varlen_cross_bwd_raw(_ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(dO), _ptr(LSE), _ptr(dQ), _ptr(dK), _ptr(dV),
                                    _ptr(ws), _wsbytes(ws), _ptr(cu_seqlens_q), _ptr(cu_seqlens_k), x.nseq, x.Tq, x.Tk,
                                    max_seqlen_q, max_seqlen_k, x.Hq, x.Hkv, x.d, scale, causal, _stream(), x.et == torch.float16))

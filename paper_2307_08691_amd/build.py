@@ -15,7 +15,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libfa_gfx950.so")
 HOST_LIB = os.path.join(HERE, "_host.so")  # (a Python extension module)
-SOURCES = ["fa_api.hip", "fa_fwd.hip", "fa_stream.hip", "fa_bwd.hip", "fa_joint64.hip", "fa_joint128.hip", "fa_short.hip", "fa_d256.hip", "fa_fp8.hip", "fa_decode.hip", "fa_probe.hip"]
+SOURCES = ["fa_api.hip", "fa_fwd.hip", "fa_stream.hip", "fa_bwd.hip", "fa_joint64.hip", "fa_joint128.hip", "fa_shares64.hip", "fa_shares128.hip", "fa_short.hip", "fa_d256.hip", "fa_fp8.hip", "fa_decode.hip", "fa_probe.hip"]
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

@@ -7,9 +7,10 @@
 #include <cstdlib>
 
 // Scratch of fa_bwd_noalloc: D = rowsum(dO o O) for up to FA_NOALLOC_MAX_ROWS (query row, head)
-// pairs. Every GPU the library runs on holds its own copy of this array, at its own address,
+// pairs, and behind it the most that shares of blocks of keys leave (d = 128). Every GPU the library runs on holds its own copy of this array, at its own address,
 // until the process ends. In host code the name below is only a handle for hipGetSymbolAddress.
-static __device__ __align__(256) float scratch[FA_NOALLOC_MAX_ROWS];
+constexpr size_t kScratchFloats = FA_NOALLOC_MAX_ROWS + (size_t)fa::kShareRows * 2 * 128;
+static __device__ __align__(256) float scratch[kScratchFloats];
 
 namespace {
 
@@ -89,9 +90,12 @@ fa::Problem make_problem(const int32_t* cu, int nseq, int N, int Nk, int Hq, int
   return p;
 }
 
-size_t ws_bytes(long tokens, int Hq, int d) {
-  (void)d;
+size_t ws_bytes(long tokens, int Hq) {
   return round_up((size_t)tokens * Hq * sizeof(float), 256);  // D = rowsum(dO o O)
+}
+// ... and behind it, where blocks of keys may be taken in shares, the shares' sums of dK and dV
+size_t ws_bytes(long tokens, int Hq, int Hkv, int d, long nq, long key_rows) {
+  return ws_bytes(tokens, Hq) + (d > 128 ? 0 : round_up((size_t)fa::share_rows(key_rows, Hq, Hkv, nq) * d * 2 * sizeof(float), 256));
 }
 
 // dropout: threshold round(256 p) in 0 .. 255 (0: nothing is dropped) and the mixed seed
@@ -232,7 +236,7 @@ int run_fwd(const void* Q, const void* K, const void* V, void* O, float* LSE, co
 }
 
 int run_bwd(const void* Q, const void* K, const void* V, const void* O, const void* dO, const float* LSE, void* dQ,
-            void* dK, void* dV, void* ws, const int32_t* cu, int nseq, int N, int Nk, long total, int Hq, int Hkv, int d,
+            void* dK, void* dV, void* ws, size_t ws_size, const int32_t* cu, int nseq, int N, int Nk, long total, int Hq, int Hkv, int d,
             float scale, int causal, int stages, void* stream, const int32_t* cu_k = nullptr,
             const Options& opt = Options()) {
   fa::BwdArgs a;
@@ -249,6 +253,11 @@ int run_bwd(const void* Q, const void* K, const void* V, const void* O, const vo
   a.dV = (__bf16*)dV;
   a.Dvec = (float*)ws;
   a.keep_d = opt.keep_d;
+  a.shares = 1;
+  a.share_turn = 0;
+  a.key_rows = cu ? total : (long)nseq * Nk;
+  // (a workspace that holds D alone is enough for the backward without shares)
+  a.partial = d <= 128 && !cu_k && ws_size >= ws_bytes(total, Hq, Hkv, d, N, a.key_rows) ? (float*)((char*)ws + ws_bytes(total, Hq)) : nullptr;
   a.dM = (__bf16*)opt.dM;
   a.dm_bs = (long)opt.dm_bs;
   a.dm_hs = (long)opt.dm_hs;
@@ -295,9 +304,8 @@ int fa_fwd(const void* Q, const void* K, const void* V, void* O, float* LSE, int
 }
 
 size_t fa_bwd_workspace_bytes(int B, int Hq, int Hkv, int N, int d) {
-  (void)Hkv;
   if (B <= 0 || Hq <= 0 || N <= 0 || d <= 0) return 0;
-  return ws_bytes((long)B * N, Hq, d);
+  return ws_bytes((long)B * N, Hq, Hkv, d, N, (long)B * N);
 }
 
 static int dense_bwd(const void* Q, const void* K, const void* V, const void* O, const void* dO, const float* LSE,
@@ -310,9 +318,9 @@ static int dense_bwd(const void* Q, const void* K, const void* V, const void* O,
   if (!aligned16(Q) || !aligned16(K) || !aligned16(V) || !aligned16(O) || !aligned16(dO) || !aligned16(LSE) ||
       !aligned16(dQ) || !aligned16(dK) || !aligned16(dV) || !aligned16(workspace))
     return FA_ERR_ALIGN;
-  if (workspace_bytes < ws_bytes((long)B * N, Hq, d)) return FA_ERR_WORKSPACE;
+  if (workspace_bytes < ws_bytes((long)B * N, Hq)) return FA_ERR_WORKSPACE;
   if (stages <= 0 || (stages & ~7)) return FA_ERR_SHAPE;
-  return run_bwd(Q, K, V, O, dO, LSE, dQ, dK, dV, workspace, nullptr, B, N, N, (long)B * N, Hq, Hkv, d, scale, causal,
+  return run_bwd(Q, K, V, O, dO, LSE, dQ, dK, dV, workspace, workspace_bytes, nullptr, B, N, N, (long)B * N, Hq, Hkv, d, scale, causal,
                  stages, stream, nullptr, opt);
 }
 
@@ -339,7 +347,7 @@ int fa_bwd_noalloc(const void* Q, const void* K, const void* V, const void* O, c
   if (B > 0 && Hq > 0 && N > 0 && (long long)B * N * Hq > (long long)FA_NOALLOC_MAX_ROWS) return FA_ERR_WORKSPACE;
   float* ws = nullptr;
   if (int e = scratch_on_current_device(&ws, &g_last_hip_error)) return e;
-  return dense_bwd(Q, K, V, O, dO, LSE, dQ, dK, dV, ws, sizeof(float) * (size_t)FA_NOALLOC_MAX_ROWS, B, Hq, Hkv, N, d,
+  return dense_bwd(Q, K, V, O, dO, LSE, dQ, dK, dV, ws, sizeof(float) * kScratchFloats, B, Hq, Hkv, N, d,
                    scale, causal, FA_STAGE_PREP | FA_STAGE_DKDV | FA_STAGE_DQ, stream);
 }
 
@@ -406,9 +414,8 @@ int fa_varlen_dropout_fwd_f16(const void* Q, const void* K, const void* V, void*
 }
 
 size_t fa_varlen_bwd_workspace_bytes(int total_tokens, int Hq, int Hkv, int d) {
-  (void)Hkv;
   if (total_tokens <= 0 || Hq <= 0 || d <= 0) return 0;
-  return ws_bytes(total_tokens, Hq, d);
+  return ws_bytes(total_tokens, Hq, Hkv, d, total_tokens, total_tokens);
 }
 
 static int varlen_bwd(const void* Q, const void* K, const void* V, const void* O, const void* dO, const float* LSE,
@@ -421,8 +428,8 @@ static int varlen_bwd(const void* Q, const void* K, const void* V, const void* O
   if (!aligned16(Q) || !aligned16(K) || !aligned16(V) || !aligned16(O) || !aligned16(dO) || !aligned16(LSE) ||
       !aligned16(dQ) || !aligned16(dK) || !aligned16(dV) || !aligned16(workspace))
     return FA_ERR_ALIGN;
-  if (workspace_bytes < ws_bytes(total_tokens, Hq, d)) return FA_ERR_WORKSPACE;
-  return run_bwd(Q, K, V, O, dO, LSE, dQ, dK, dV, workspace, cu_seqlens, nseq, max_seqlen, max_seqlen, total_tokens, Hq,
+  if (workspace_bytes < ws_bytes(total_tokens, Hq)) return FA_ERR_WORKSPACE;
+  return run_bwd(Q, K, V, O, dO, LSE, dQ, dK, dV, workspace, workspace_bytes, cu_seqlens, nseq, max_seqlen, max_seqlen, total_tokens, Hq,
                  Hkv, d, scale, causal, 7, stream, nullptr, opt);
 }
 
@@ -504,8 +511,8 @@ static int cross_bwd(const void* Q, const void* K, const void* V, const void* O,
   if (!aligned16(Q) || !aligned16(K) || !aligned16(V) || !aligned16(O) || !aligned16(dO) || !aligned16(LSE) ||
       !aligned16(dQ) || !aligned16(dK) || !aligned16(dV) || !aligned16(workspace))
     return FA_ERR_ALIGN;
-  if (workspace_bytes < ws_bytes((long)B * Nq, Hq, d)) return FA_ERR_WORKSPACE;
-  return run_bwd(Q, K, V, O, dO, LSE, dQ, dK, dV, workspace, nullptr, B, Nq, Nk, (long)B * Nq, Hq, Hkv, d, scale,
+  if (workspace_bytes < ws_bytes((long)B * Nq, Hq)) return FA_ERR_WORKSPACE;
+  return run_bwd(Q, K, V, O, dO, LSE, dQ, dK, dV, workspace, workspace_bytes, nullptr, B, Nq, Nk, (long)B * Nq, Hq, Hkv, d, scale,
                  causal, FA_STAGE_PREP | FA_STAGE_DKDV | FA_STAGE_DQ, stream, nullptr, opt);
 }
 
@@ -520,9 +527,8 @@ int fa_cross_fwd_f16(const void* Q, const void* K, const void* V, void* O, float
 }
 
 size_t fa_cross_bwd_workspace_bytes(int B, int Hq, int Hkv, int Nq, int Nk, int d) {
-  (void)Hkv;
   if (B <= 0 || Hq <= 0 || Nq <= 0 || Nk <= 0 || d <= 0) return 0;
-  return ws_bytes((long)B * Nq, Hq, d);
+  return ws_bytes((long)B * Nq, Hq, Hkv, d, Nq, (long)B * Nk);
 }
 
 int fa_cross_bwd(const void* Q, const void* K, const void* V, const void* O, const void* dO, const float* LSE,
@@ -917,8 +923,8 @@ static int varlen_cross_bwd_any(int f16, const void* Q, const void* K, const voi
   if (!aligned16(Q) || !aligned16(K) || !aligned16(V) || !aligned16(O) || !aligned16(dO) || !aligned16(LSE) ||
       !aligned16(dQ) || !aligned16(dK) || !aligned16(dV) || !aligned16(workspace))
     return FA_ERR_ALIGN;
-  if (workspace_bytes < ws_bytes(total_q, Hq, d)) return FA_ERR_WORKSPACE;
-  return run_bwd(Q, K, V, O, dO, LSE, dQ, dK, dV, workspace, cu_seqlens_q, nseq, max_seqlen_q, max_seqlen_k, total_q,
+  if (workspace_bytes < ws_bytes(total_q, Hq)) return FA_ERR_WORKSPACE;
+  return run_bwd(Q, K, V, O, dO, LSE, dQ, dK, dV, workspace, workspace_bytes, cu_seqlens_q, nseq, max_seqlen_q, max_seqlen_k, total_q,
                  Hq, Hkv, d, scale, causal, 7, stream, cu_seqlens_k, half_precision(f16));
 }
 

@@ -2,7 +2,8 @@
 //
 // (Short sequences at d = 64: one kernel, fa_short.hip.) Three parts; the two kernels stand in fa_bwd_work.h. The full backward is two
 // launches on the caller's stream: the pre-pass, then the other two side by side in one grid (fa_bwd_joint.h), or, on grids that leave
-// no compute units idle either way, the third, which then sums D itself (OWN_D), and the second.
+// no compute units idle either way, the third, which then sums D itself (OWN_D), and the second. Where few blocks of keys stand
+// for long chains, several workgroups share each and a merge follows (key_shares).
 //   1. prep:  D = rowsum(dO o O) (Algorithm 2, line 4)
 //   2. dK/dV: one workgroup per block of 256 keys of one (sequence, key/value head)
 //             (section 3.2 "Backward pass"); it loops over the query heads that share the
@@ -178,6 +179,76 @@ bool joint_form(const Problem& p, int D, int causal) {
   return (causal && key_rounds <= 1) || rest(key_rounds) + rest(row_rounds) > 0.04 * (key_rounds + row_rounds);
 }
 
+// How many workgroups share the row tiles of a block of keys (1: one takes all of them). A block's chain is G * N / 32 tiles (64 at
+// d = 64) long, G times that of a block of rows, and few key/value heads make few blocks: the chip waits for a handful of
+// workgroups. Shares leave float32 sums that merge_keys_kernel adds: a write and a read of 8 bytes an element and a launch.
+// Estimated in us as in joint_small, with eight wavefronts: the longest chain, or all the work over the compute units; taken
+// where it saves a fifth. MI355X, us of forward and backward, without and with: 1 x 8192, 8 heads on 1 of 128, causal: 2793 -> 728; 1 x
+// 2048, 32 heads on 8 of 128: 391 -> 193, of 64: 231 -> 117; 2 x 817, 8 heads on 1 of 128: 273 -> 62; window of 512, 1 x 6000, 8 heads on 1 of
+// 128: 311 -> 114; dropout, 2 x 3000, 8 heads on 1 of 64: 842 -> 258; 8 packed of up to 1500, 32 heads on 4 of 64: 361 -> 233. Where
+// nothing is idle it is left: 8 x 1024, 16 heads on 4 of 128.
+// Only for groups of four heads and more, with some thousand rows to a block of keys (share_rows): the sums are rounded in another order
+// than a single chain's, and with fewer heads or shorter sequences, which gain less, a sequence has the same gradients in every batch
+// (what that leaves: 1 x 1024, 4 heads on 1 of 64: 121, with shares 45; 4 x 600 of 128: 127, with shares 53). Not for masks and patterns, nor for packed batches of two lengths (whose number of keys only the
+// device knows).
+static int key_shares(const BwdArgs& a, int D, int causal) {
+  const Problem& p = a.p;
+  if (!a.partial || p.mask || p.bmask || p.cu_seqlens_k) return 1;
+  const long room = share_rows(a.key_rows, p.Hq, p.Hkv, p.N);
+  if (!room) return 1;
+  const int most = (int)(room / (a.key_rows * p.Hkv));
+  const bool window = windowed(p) && p.win_left >= 0 && p.win_right >= 0;
+  const double seen = window ? p.win_left + p.win_right + 256. : 1e9;  // rows that see a block of keys, keys that a block of rows sees
+  const double rows = p.N < seen ? p.N : seen, keys = p.Nk < seen ? p.Nk : seen, start = 6;
+  const double chain = rows * p.G * (D == 64 ? 1.5 / 64 : 1.2 / 32), row_block = start + keys / 64 * (D == 64 ? 1.0 : 1.5);
+  const double nk = block_count(p, p.Nk, 256, p.Hkv), nq = block_count(p, p.N, 256, p.Hq);
+  const double part = (causal ? 0.55 : 1) * (p.cu_seqlens ? (double)p.total_tokens / ((double)p.nseq * p.N) : 1);  // an average one
+  const double work = part * (nk * chain + nq * row_block) / 256, merged = a.key_rows * p.Hkv * (double)p.d * 8 / 4e6;
+  int best = 1;
+  double least = (start + chain > work ? start + chain : work) * 0.8;
+  for (int z = 2; z <= most; ++z) {
+    double t = start + chain / z;
+    if (t < row_block) t = row_block;
+    const double all = work + start * z * nk / 256 + 0.5 * (nk * z + nq > 256 ? t : 0);
+    if (t < all) t = all;
+    t += 4 + z * merged;
+    if (t < least) {
+      least = t;
+      best = z;
+    }
+  }
+  return best;
+}
+
+// dK, dV from the sums of the shares: eight elements a thread, the scaling with dK. Bound by the bytes of the sums.
+template <bool F16>
+__global__ __launch_bounds__(256) void merge_keys_kernel(BwdArgs a) {
+  const long n = a.key_rows * a.p.Hkv * a.p.d, i = 8 * ((long)blockIdx.x * 256 + threadIdx.x);
+  if (i >= n) return;
+  const bool v = blockIdx.y != 0;
+  const float* src = a.partial + (v ? n : 0) + i;
+  f32x4 lo = {0, 0, 0, 0}, hi = {0, 0, 0, 0};
+#pragma unroll 4
+  for (int z = 0; z < a.shares; ++z) {
+    lo += *(const f32x4*)(src + 2 * n * z);
+    hi += *(const f32x4*)(src + 2 * n * z + 4);
+  }
+  const float mul = v ? 1.f : a.p.scale;
+  u32x4 o;
+  o[0] = pack2<F16>(lo[0] * mul, lo[1] * mul);
+  o[1] = pack2<F16>(lo[2] * mul, lo[3] * mul);
+  o[2] = pack2<F16>(hi[0] * mul, hi[1] * mul);
+  o[3] = pack2<F16>(hi[2] * mul, hi[3] * mul);
+  *(u32x4*)((v ? a.dV : a.dK) + i) = o;
+}
+hipError_t launch_merge_keys(const BwdArgs& a, hipStream_t st) {
+  const long n = a.key_rows * a.p.Hkv * a.p.d;
+  const dim3 grid((unsigned)((n / 8 + 255) / 256), 2), block(256);
+  if (a.p.f16) hipLaunchKernelGGL((merge_keys_kernel<true>), grid, block, 0, st, a);
+  else hipLaunchKernelGGL((merge_keys_kernel<false>), grid, block, 0, st, a);
+  return hipGetLastError();
+}
+
 // The dQ kernel. OWN_D: it sums D on the way (the whole backward, with every option); otherwise the pre-pass has (the
 // separate stages, which have no options). RAGGED: a.p.cu_seqlens is set (the stages and the two patterns of the mask
 // are for dense batches).
@@ -306,6 +377,12 @@ static hipError_t launch_bwd_d(const BwdArgs& a, int causal, int stages, hipStre
     if (stages == 7 && !a.keep_d && a.p.d == D && !a.p.mask && !a.p.bmask && !windowed(a.p) && !a.p.drop_thr &&
         bwd_short_form(a.p, causal))
       return launch_bwd_short(a, causal, st);
+  if (stages == 7) {
+    BwdArgs shared = a;
+    shared.shares = key_shares(a, D, causal);
+    shared.share_turn = a.p.cu_seqlens ? 3 : (int)((a.p.Nk + 255L) / 256 * a.p.Hkv * a.p.nseq % kXcds);  // (packed: nobody has counted the blocks)
+    if (shared.shares > 1) return launch_joint_shares<D, F16>(shared, causal, st);
+  }
   if (stages == 7 && joint_form(a.p, D, causal)) return launch_joint<D, F16>(a, causal, st);
   if (stages == 7 && a.p.cu_seqlens) {
     if (hipError_t e = launch_dq<D, F16, true, true>(a, causal, st)) return e;

@@ -27,6 +27,9 @@ bool joint_form(const Problem& p, int D, int causal);
 bool joint_small(const Problem& p, int D, int causal);
 template <int D, bool F16>
 hipError_t launch_joint(const BwdArgs& a, int causal, hipStream_t st);
+template <int D, bool F16>
+hipError_t launch_joint_shares(const BwdArgs& a, int causal, hipStream_t st);  // a.shares > 1
+hipError_t launch_merge_keys(const BwdArgs& a, hipStream_t st);
 
 // dK/dV kernel: 8 wavefronts in two groups of four. Two forms share the code below.
 // WIDE (every instantiation but the mask's and SHARED): 256 keys per workgroup, wavefront
@@ -87,6 +90,9 @@ constexpr int dkdv_block_keys(bool mask) { return mask ? 128 : 256; }
 // first DH columns of the D-wide tiles only (see the forward kernel).
 //
 // RAGGED: a packed batch (p.cu_seqlens); see row_block_coord.
+//
+// SHARE: the workgroup takes share `share` of a.shares of its block's tiles and leaves float32 sums, which merge_keys_kernel adds
+// (see key_shares).
 template <int D, bool MASK, int LOCAL, int NW, bool SHARED>
 struct DkdvPlan {
   static constexpr int SLOTS = (D == 64 && NW == 4 ? 2 : 1) * kXcdUnits;  // workgroups that an XCD holds at once
@@ -110,8 +116,9 @@ struct DkdvPlan {
   static_assert(VT_OFF + BC * ROWB <= 65536 && BUFB <= 32768, "immediate offsets must fit 16 bits");
   static_assert(SMEM <= 160 * 1024, "LDS of one compute unit");
 };
-template <int D, bool CAUSAL, bool F16, bool DROPOUT, bool PAD, bool MASK, int LOCAL, int DH, int NW, bool SHARED, bool RAGGED>
-__device__ __forceinline__ void dkdv_work(const BwdArgs& a, char* smem, Place at) {
+template <int D, bool CAUSAL, bool F16, bool DROPOUT, bool PAD, bool MASK, int LOCAL, int DH, int NW, bool SHARED, bool RAGGED, bool SHARE = false>
+__device__ __forceinline__ void dkdv_work(const BwdArgs& a, char* smem, Place at, int share = 0) {
+  static_assert(!SHARE || (!MASK && LOCAL != kBlocks && !SHARED && NW == 8), "shares are taken in the wide form");
   static_assert(DH == D || (PAD && DH % 32 == 0 && DH < D), "a narrower product width is for padded head dimensions");
   static_assert(!MASK || (!DROPOUT && !PAD), "the mask variant is built for the plain kernel");
   static_assert(!LOCAL || (!CAUSAL && !DROPOUT && !PAD && !MASK), "the window variant is built for the plain kernel");
@@ -160,7 +167,9 @@ __device__ __forceinline__ void dkdv_work(const BwdArgs& a, char* smem, Place at
     if (last_row / BR + 1 < i_end) i_end = (int)(last_row / BR) + 1;
     if (i_end < i_first) i_end = i_first;
   }
-  const int T = (i_end - i_first) * p.G;     // tiles this workgroup visits, over the group's query heads
+  const int T_all = (i_end - i_first) * p.G;  // tiles of the block, over the group's query heads
+  const int t_first = SHARE ? (int)((long)T_all * share / a.shares) : 0;
+  const int T = SHARE ? (int)((long)T_all * (share + 1) / a.shares) - t_first : T_all;  // tiles this workgroup visits
   const long stat_base = s * p.lse_seq_stride + (p.cu_seqlens ? si.tok0 : 0);
 
   // Position of a tile in the visiting order: row tile, query head, ring slot, and where the
@@ -188,8 +197,9 @@ __device__ __forceinline__ void dkdv_work(const BwdArgs& a, char* smem, Place at
       c.slot = c.slot + 1 == RING ? 0 : c.slot + 1;
     }
   };
-  const Cursor tile0 = {g * p.G, i_first, 0, ((si.tok0 + (long)i_first * BR) * p.Hq + g * p.G) * dh,
-                        stat_base + (long)g * p.G * p.lse_head_stride + (long)i_first * BR};
+  const int it0 = i_first + (SHARE ? t_first / p.G : 0), hq0 = g * p.G + (SHARE ? t_first % p.G : 0);
+  const Cursor tile0 = {hq0, it0, 0, ((si.tok0 + (long)it0 * BR) * p.Hq + hq0) * dh,
+                        stat_base + (long)hq0 * p.lse_head_stride + (long)it0 * BR};
   // (an entry of the visit list below: the tile's number in that order, and its row tile in the upper half)
   auto cursor_at = [&](unsigned entry, int slot) {
     const int tt = entry & 0xffff, it = entry >> 16, hq = g * p.G + tt - (it - i_first) * p.G;
@@ -200,16 +210,20 @@ __device__ __forceinline__ void dkdv_work(const BwdArgs& a, char* smem, Place at
   // (256 keys per workgroup) Leading tiles in which every score of THIS wavefront's 32 keys is
   // masked (its keys lie above the tile's last row, or past the end of the sequence), and under a
   // window trailing ones: the wavefront only keeps up with the copies and the barriers.
-  int skip = 0, t_stop = T;  // this wavefront computes on tiles skip .. t_stop - 1
-  if (j0 + 32 * kgi >= nk) skip = T;
+  int skip = 0, t_stop = T_all;  // this wavefront computes on tiles skip .. t_stop - 1
+  if (j0 + 32 * kgi >= nk) skip = T_all;
   else if ((CAUSAL || wr >= 0) && j0 + 32 * kgi > off + (LOCAL ? wr : 0)) {
     const int first_useful = (j0 + 32 * kgi - off - (LOCAL ? wr : 0)) / BR;  // first row tile that reaches this wavefront's keys
-    skip = (first_useful - i_first) * p.G < T ? (first_useful - i_first) * p.G : T;
+    skip = (first_useful - i_first) * p.G < T_all ? (first_useful - i_first) * p.G : T_all;
   }
   if (LOCAL && wl >= 0) {  // one past the last row tile whose rows still see this wavefront's last key
     const long last_row = (long)j0 + 32 * kgi + 31 - off + wl;
     const long stop = (last_row / BR + 1 - i_first) * p.G;
     if (stop < t_stop) t_stop = (int)stop;
+  }
+  if (SHARE) {  // counted from the share's first tile
+    skip = skip < t_first ? 0 : (skip - t_first < T ? skip - t_first : T);
+    t_stop = t_stop - t_first < T ? t_stop - t_first : T;
   }
   if (t_stop < skip) t_stop = skip;
 
@@ -792,6 +806,22 @@ __device__ __forceinline__ void dkdv_work(const BwdArgs& a, char* smem, Place at
       }
     }
 
+    if constexpr (SHARE) {  // the sums of this share: rows of p.d floats, dK's before dV's
+      if (key_ok) {
+        const long rows = (long)a.key_rows * p.Hkv;
+        float* const dst = a.partial + ((2 * share * rows) + (si.tok0k + key) * p.Hkv + g) * dh + 4 * hh;
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+          for (int r4 = 0; r4 < 4; ++r4)
+            if (!PAD || 32 * dt + 8 * r4 + 4 * hh < dh) {
+              *(f32x4*)(dst + 32 * dt + 8 * r4) = (f32x4){dKt[dt][4 * r4], dKt[dt][4 * r4 + 1], dKt[dt][4 * r4 + 2], dKt[dt][4 * r4 + 3]};
+              *(f32x4*)(dst + rows * dh + 32 * dt + 8 * r4) =
+                  (f32x4){dVt[dt][4 * r4], dVt[dt][4 * r4 + 1], dVt[dt][4 * r4 + 2], dVt[dt][4 * r4 + 3]};
+            }
+      }
+      return;
+    }
     // ---- write dK_j, dV_j (line 18); dK carries the scaling. The ring is idle now (no copy is
     // requested past the last tile): each wavefront stages its rows there and stores whole rows.
     {

@@ -100,12 +100,28 @@ struct BwdArgs {
   __bf16* dK;
   __bf16* dV;
   float* Dvec;   // workspace: rowsum(dO o O), laid out like LSE
+  // shares of the blocks of keys (key_shares in fa_bwd.hip): how many, and where their sums of dK, dV go, float32 [share][dK, dV][row of
+  // K][p.d], key_rows rows of K; partial = nullptr: no room, not taken
+  int shares, share_turn;  // (by how many XCDs a share's blocks are turned against those of the share before it)
+  float* partial;
+  long key_rows;
   bool keep_d;   // whoever asked for all three stages may run single ones on the same workspace: D has to be left there
   // gradient of the elementwise mask (mask instantiation of the dQ kernel only; nullptr: not asked for):
   // dM = dS in the element type, entry (s, h, r, c) at dM[s * dm_bs + h * dm_hs + r * dm_rs + c]
   __bf16* dM;
   long dm_bs, dm_hs, dm_rs;
 };
+
+// Room for the sums of the largest number of shares that key_shares takes, in rows of K (dK and dV make two of each); 0 where it takes
+// none. nq: query rows of a sequence, or an upper bound.
+constexpr long kShareRows = 65536;
+constexpr int kMostShares = 16;
+inline long share_rows(long key_rows, int Hq, int Hkv, long nq) {
+  const long rows = key_rows * Hkv, group = Hkv > 0 ? Hq / Hkv : 0;
+  if (group < 4 || group * nq <= (group < 8 ? 4800 : 2560) || rows <= 0 || 2 * rows > kShareRows) return 0;
+  const long most = kShareRows / rows;
+  return rows * (most < kMostShares ? most : kMostShares);
+}
 
 // FP8 (E4M3) forward: Q, K one byte per element in the token-major layout, V key-major
 // [B, Hkv, d, vt_stride]; p.scale is the softmax scaling times the scales of Q and K

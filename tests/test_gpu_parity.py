@@ -354,6 +354,70 @@ def test_one_grid_and_two_launches_agree_bitwise(kind, d, N, causal, dtype):
         assert torch.isfinite(x).all() and torch.equal(x[0], y[0]), name
 
 
+# (eight heads to a key/value head, or four: a block of keys is a chain of hundreds of row tiles, which several workgroups share unless the
+# workspace holds D alone; lengths off the tiles, fewer tiles than shares in a packed batch's short sequences, every product width)
+@pytest.mark.parametrize("packed", [False, True])
+@pytest.mark.parametrize("kind,d,N,Hkv,causal", [("plain", 128, 700, 1, False), ("plain", 128, 1301, 2, True), ("plain", 96, 511, 1, True),
+                                                 ("plain", 96, 640, 1, False), ("plain", 120, 600, 1, True), ("plain", 104, 513, 1, False),
+                                                 ("plain", 64, 1100, 1, True), ("plain", 64, 1250, 2, False), ("plain", 32, 900, 1, True),
+                                                 ("plain", 24, 800, 1, False), ("plain", 48, 900, 1, True), ("plain", 40, 700, 1, False),
+                                                 ("window", 128, 900, 1, False), ("window", 64, 1300, 1, False),
+                                                 ("dropout", 128, 520, 1, True), ("dropout", 128, 700, 1, False),
+                                                 ("dropout", 64, 1000, 1, True), ("dropout", 64, 800, 1, False)])
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+def test_shares_of_a_block_of_keys(kind, d, N, Hkv, causal, dtype, packed):
+    """dK and dV added from the shares' float32 sums are the single chain's, apart from the order of the sums: the same 16-bit
+    value or its neighbour (2^-7 or 2^-10 of the value apart at most; values near zero are held to the sums' rounding, 2^-24 of some
+    thousand terms below one). dQ, which has no shares, is the same."""
+    if packed and d not in (64, 128) and dtype == "f16":
+        dtype = "bf16"
+    G, scale = 8 // Hkv, d ** -0.5
+    et = torch.bfloat16 if dtype == "bf16" else torch.float16
+    g = torch.Generator(device="cuda").manual_seed(9800 + N + d)
+    cu = [0, N, N, N + 5, N + 5 + N // 3] if packed else [0, N, 2 * N]
+    T = cu[-1]
+    Q, K, V, dO = (torch.randn((T, h, d), generator=g, device="cuda", dtype=et) for h in (G * Hkv, Hkv, Hkv, G * Hkv))
+    cut = torch.tensor(cu, dtype=torch.int32, device="cuda")
+    if packed:
+        extra = {"plain": (causal,), "window": (300, 50), "dropout": (causal, 0.2, 78)}[kind]
+        fwd, bwd = {"plain": (binding.fa_varlen_fwd, binding.fa_varlen_bwd), "window": (binding.fa_varlen_local_fwd, binding.fa_varlen_local_bwd),
+                    "dropout": (binding.fa_varlen_dropout_fwd, binding.fa_varlen_dropout_bwd)}[kind]
+        shape, lengths, need = (lambda x: x), (cut, N), binding.fa_varlen_bwd_workspace_bytes(T, G * Hkv, Hkv, d)
+    else:
+        extra = {"plain": (causal,), "window": (300, 50), "dropout": (causal, 0.2, 78)}[kind]
+        fwd, bwd = {"plain": (binding.fa_cross_fwd, binding.fa_cross_bwd), "window": (binding.fa_local_fwd, binding.fa_local_bwd),
+                    "dropout": (binding.fa_dropout_fwd, binding.fa_dropout_bwd)}[kind]
+        shape, lengths, need = (lambda x: x.view(2, N, -1, d)), (), binding.fa_cross_bwd_workspace_bytes(2, G * Hkv, Hkv, N, N, d)
+    Q, K, V, dO = map(shape, (Q, K, V, dO))
+    O, L = fwd(Q, K, V, *lengths, scale, *extra)
+    just_d = (4 * T * G * Hkv + 255) // 256 * 256
+    assert need > just_d
+
+    def grads(nbytes):
+        ws = torch.full((nbytes + 256,), 255, dtype=torch.uint8, device="cuda")  # NaN as float32
+        r = bwd(Q, K, V, O, dO, L, *lengths, scale, *extra, workspace=ws[:nbytes], **{n: torch.full_like(x, float("nan")) for n, x in
+                                                                                     (("dQ", Q), ("dK", K), ("dV", V))})
+        assert (ws[nbytes:] == 255).all()
+        return r
+
+    whole, shared = grads(just_d), grads(need)
+    assert torch.equal(whole[0], shared[0]) and not torch.equal(whole[1], shared[1])
+    for x, y in zip(whole[1:], shared[1:]):
+        torch.testing.assert_close(y.float(), x.float(), rtol=2.0 ** (-7 if et == torch.bfloat16 else -10), atol=1e-3)
+
+
+def test_shares_match_the_oracle_and_need_no_workspace():
+    prob = inputs.make_dense(B=1, N=513, Hq=8, Hkv=1, d=128, causal=True, seed=9850)
+    check(prob)
+    Q, K, V, dO = (pu.to_gpu(x, prob.dtype) for x in (prob.Q, prob.K, prob.V, prob.dO))
+    O, L = binding.fa_fwd(Q, K, V, prob.scale, True)
+    want = binding.fa_bwd(Q, K, V, O, dO, L, prob.scale, True)
+    got = [torch.full_like(x, float("nan")) for x in (Q, K, V)]
+    binding.fa_bwd_noalloc(Q, K, V, O, dO, L, prob.scale, True, *got)
+    for x, y in zip(want, got):
+        assert torch.equal(x, y)
+
+
 @pytest.mark.parametrize("d", [64, 128])
 def test_cache_and_fp8_pairs_that_do_not_divide_over_the_xcds(d):
     """As above for the split-key kernel (nine pairs, more shares than an XCD holds) and the FP8 kernel."""

@@ -36,7 +36,7 @@ def resource_remarks(source):
 @pytest.fixture(scope="module")
 def remarks():
     with concurrent.futures.ThreadPoolExecutor(4) as ex:
-        parts = list(ex.map(resource_remarks, ["fa_fwd.hip", "fa_stream.hip", "fa_bwd.hip", "fa_joint64.hip", "fa_joint128.hip", "fa_short.hip", "fa_d256.hip", "fa_fp8.hip", "fa_decode.hip"]))
+        parts = list(ex.map(resource_remarks, ["fa_fwd.hip", "fa_stream.hip", "fa_bwd.hip", "fa_joint64.hip", "fa_joint128.hip", "fa_shares64.hip", "fa_shares128.hip", "fa_short.hip", "fa_d256.hip", "fa_fp8.hip", "fa_decode.hip"]))
     return {k: v for part in parts for k, v in part.items()}
 
 

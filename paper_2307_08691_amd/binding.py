@@ -882,6 +882,15 @@ FA_SPLITKV_MAX_SPLITS = 128
 def splitkv_default_splits(B, Hq, Hkv, Nq, Nk, ragged: bool = False) -> int:
     """About one workgroup per compute unit, and at least 8 blocks of 64 keys per share (measured:
     more, shorter shares cost more in prologues and in the merge than they gain in parallelism).
+    Up to 32 query rows per key/value head (the decode kernel), at least twelve blocks and room for four shares or more:
+     * shares down to two blocks, up to sixteen of them, as equal as they come: a wavefront's blocks follow each other, and the
+       merge reads sixteen shares in one go (4 sequences, 32 heads on 8, device us at 8 blocks per share and so: d = 128, 1024 keys 13.9 ->
+       9.7, 1792: 14.9 -> 11.1, 2560: 14.6 -> 12.4; d = 64: 9.9 -> 8.0, 10.4 -> 8.5, 10.3 -> 9.3). Beyond sixteen 8 blocks each as
+       elsewhere (1 sequence, 16384 keys, 16 / 32 / 64 shares: 20.1 / 18.5 / 25.1);
+     * no more workgroups than compute units, since one that is left over is a second round (3 sequences, 16 heads of 128, 5 / 6 shares:
+       4096 keys 21.6 / 28.3, 8192 keys 34.1 / 38.1; 13, 4 heads, 2560 keys, 4 / 5: 18.2 / 21.2), but where that leaves an eighth of them
+       idle and shares are long (7, 8 heads, 4352 keys, 4 / 5: 21.6 / 20.9), and on long caches (6, 16 heads on 8, 9984 keys, 5 / 6: 36.1 /
+       33.5).
     ragged (a cache with a length of its own per sequence, Nk the capacity): the same for up to 128
     sequences in decoding shapes, where the decode kernel hands the sequences out longest first
     (measured on 64 sequences of 1 .. 8192 keys: 1 share 5.0 TB/s, 4 shares 4.3, 16 shares 2.5);
@@ -895,6 +904,13 @@ def splitkv_default_splits(B, Hq, Hkv, Nq, Nk, ragged: bool = False) -> int:
     blocks = (Nk + 63) // 64
     if ragged and not (B <= 128 and Nq * (Hq // Hkv) <= 32):
         return max(1, min(FA_SPLITKV_MAX_SPLITS, blocks // 16, -(-2048 // units)))
+    if Nq * (Hq // Hkv) <= 32 and units <= 64 and blocks >= 12:
+        fit, eights = 256 // units, blocks // 8
+        if eights < -(-256 // units):
+            n = max(eights, min(fit, 16, blocks // 2))
+            return -(-blocks // -(-blocks // n)) if n <= 16 else min(n, FA_SPLITKV_MAX_SPLITS)
+        if blocks <= (128 if fit >= 5 else 63):
+            return min(fit, FA_SPLITKV_MAX_SPLITS)
     return max(1, min(FA_SPLITKV_MAX_SPLITS, blocks // 8, -(-256 // units)))
 
 
@@ -910,8 +926,11 @@ def _cache_splits(B, Hq, Hkv, Nq, Nk, d, ragged: bool) -> int:
     compute unit, and as many shares as fit there at once are best (same heads, us at 2 / 3 / 4 / 5 / 8 shares: 4 x 233
     on up to 10752 keys, 128 workgroups per share: 124 / 118 / 99 / 100 / 105; 8 x 128: 99 / 84 / 73 / 85 / 97;
     1 x 512: 98 / 75 / 63 / 73 / 62; 2 x 700, 16 heads, 96 workgroups: 178 / 144 / 122 / 108 / 116 and 6 shares
-    137). Never more than splitkv_default_splits: a workspace sized by that is large enough."""
+    137). Decoding at d = 64 keeps one share below sixteen blocks, where the merge is a launch for nothing (4 sequences, 32 heads on 8, 768
+    keys: 7.9 us, in 6 shares 9.8; at d = 128 12.7 and 10.2). Never more than splitkv_default_splits: a workspace sized by that is large enough."""
     rows = Nq * (Hq // Hkv)
+    if d == 64 and rows <= 32 and Nk <= 15 * 64:
+        return 1
     if not ragged or rows <= 32:
         return splitkv_default_splits(B, Hq, Hkv, Nq, Nk, ragged)
     units = B * Hkv * ((rows + 255) // 256)

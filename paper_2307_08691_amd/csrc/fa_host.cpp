@@ -283,6 +283,16 @@ int cache_splits_of(long B, long Hq, long Hkv, long Nq, long Nk, long d, bool ra
   long want, least;
   if (!ragged || rows <= 32) {
     const bool many = ragged && !(B <= 128 && rows <= 32);
+    if (d == 64 && rows <= 32 && blocks < 16) return 1;
+    if (!many && rows <= 32 && units <= 64 && blocks >= 12) {
+      const long fit = 256 / units, eights = blocks / 8;
+      auto least_of = [](long a, long b) { return a < b ? a : b; };
+      if (eights < up(256, units)) {
+        const long small = least_of(least_of(fit, 16), blocks / 2), n = small > eights ? small : eights;
+        return (int)(n <= 16 ? up(blocks, up(blocks, n)) : least_of(n, FA_SPLITKV_MAX_SPLITS));
+      }
+      if (blocks <= (fit >= 5 ? 128 : 63)) return (int)least_of(fit, FA_SPLITKV_MAX_SPLITS);
+    }
     want = up(many ? 2048 : 256, units), least = many ? 16 : 8;
   } else {
     want = d == 64 ? 512 / units : up(B > 1 ? 384 : 256, units), least = 16;

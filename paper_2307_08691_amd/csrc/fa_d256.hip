@@ -67,7 +67,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   const int n = si.n, nk = si.nk, off = nk - n;
   const int i0 = rowblk * BR;
   if (i0 >= n || nk == 0) return;  // (a sequence without keys: see keyless_rows_kernel)
-  const int g = h / p.G;
+  const int g = __builtin_amdgcn_readfirstlane(h / p.G);  // (else the tile copies keep their addresses per lane)
   const long kstride = (long)p.Hkv * D;
   const __bf16* Kb = a.K + (si.tok0k * p.Hkv + g) * D;
   const __bf16* Vb = a.V + (si.tok0k * p.Hkv + g) * D;
@@ -258,6 +258,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   constexpr std::false_type no{};
   if (ncol > 1) {
     iteration(0, no, yes);
+    // (where the loop begins is worth 4% to a wavefront alone on its SIMD, see fa_stream.hip: causal, 1 x 4000, 16 heads, us at 0, 8, .. 56 past
+    // a multiple of 64: 134.2, 138.5, 136.3, 138.4, 135.7, 139.2, 135.4, 139.6; grids that fill the chip within 1%)
+    asm volatile(".p2align 6");
     for (int j = 1; j < ncol - 1; ++j) iteration(j, yes, yes);
     iteration(ncol - 1, yes, no);
   } else {
@@ -334,7 +337,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   const int n = si.n, nk = si.nk, off = nk - n;
   const int i0 = rowblk * BR;
   if (i0 >= n || nk == 0) return;  // (a sequence without keys: see keyless_rows_kernel)
-  const int g = h / p.G;
+  const int g = __builtin_amdgcn_readfirstlane(h / p.G);  // (else the tile copies keep their addresses per lane)
   const long kstride = (long)p.Hkv * D;
   const __bf16* Kb = a.K + (si.tok0k * p.Hkv + g) * D;
   const __bf16* Vb = a.V + (si.tok0k * p.Hkv + g) * D;

@@ -512,6 +512,10 @@ __global__ __launch_bounds__(512)
   // at once instead of waiting for the other group (+2% at d = 128; with two workgroups per compute
   // unit, four wavefronts per SIMD, it measured 3% slower and stays).
   constexpr bool MID = TWO;
+  // Where the loops begin: split keys at d = 64 feel it, every 32 bytes alike, and the compiler lays them wherever the code before them
+  // ends. At 0 and at 24 past a multiple of 32 (MI355X, us): 3 x 893 new queries on up to 6656 keys, 32 heads on 16: 140.3 and
+  // 146.8; 1 x 65 on 5632, 32 on 4: 34.6 and 36.1. d = 128 and the forward pass without a cache: 1% at most between any two places.
+  if constexpr (SPLIT && D == 64) asm volatile(".p2align 6");
   if (grp == 0) {
     for (int j = tb; j <= tend; ++j) {
       matrix_phase(j);

@@ -34,6 +34,9 @@ struct ShortPlan {
   static constexpr int SMEM = EXTRA_OFF + EXTRA;
 };
 
+// (one block a pair: the pairs go round the XCDs by themselves, and a short step's time is the chain that its workgroup starts with)
+constexpr int kAnyNumber = 0x7fffffff;
+
 template <int KW, int NW, bool CAUSAL, bool F16>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2))) void bwd_short_kernel(BwdArgs a) {
   typedef ShortPlan<KW, NW> Plan;
@@ -47,7 +50,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lq = lane & 31, hh = lane >> 5;
-  const BlockCoord bc = block_coord<false, true>({blockIdx.x, kXcdUnits}, 1, p.Hkv, p.nseq);  // (from the last pair to the first: see launch_bwd_d)
+  const BlockCoord bc = block_coord<false, true>({blockIdx.x, kAnyNumber}, 1, p.Hkv, p.nseq);  // (from the last pair to the first: see launch_bwd_d)
   if (!bc.valid) return;
   const int g = bc.head, s = bc.seq;
   const SeqInfo si = seq_info(p, s);
@@ -336,7 +339,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
 
 template <int KW, int NW>
 static hipError_t launch_short(const BwdArgs& a, int causal, hipStream_t st) {
-  const dim3 grid(grid_size(1, a.p.Hkv * a.p.nseq, kXcdUnits)), block(64 * NW);
+  const dim3 grid(grid_size(1, a.p.Hkv * a.p.nseq, kAnyNumber)), block(64 * NW);
   if (a.p.f16) {
     if (causal) hipLaunchKernelGGL((bwd_short_kernel<KW, NW, true, true>), grid, block, 0, st, a);
     else hipLaunchKernelGGL((bwd_short_kernel<KW, NW, false, true>), grid, block, 0, st, a);

@@ -340,11 +340,12 @@ static hipError_t launch_dkdv(const BwdArgs& a, int causal, hipStream_t st) {
     // Dropout at d = 64 takes the four-wavefront form by the same rule (bfloat16, 14 x 353
     // causal, 8 heads on 4, forward + backward: 66.6 us in blocks of 256 keys, 61.5 so).
     if constexpr (D == 128) {
-      if (dropout_shared(a.p, causal)) {
-        if (causal) hipLaunchKernelGGL((bwd_dkdv_kernel<D, true, F16, true, false, false, kNoPattern, D, 8, true, RAGGED>), sgrid, block, 0, st, a);
-        else hipLaunchKernelGGL((bwd_dkdv_kernel<D, false, F16, true, false, false, kNoPattern, D, 8, true, RAGGED>), sgrid, block, 0, st, a);
-        return hipGetLastError();
-      }
+      // (causal or packed, grids as small as that are joint ones: joint_form)
+      if constexpr (!RAGGED)
+        if (!causal && dropout_shared(a.p, causal)) {
+          hipLaunchKernelGGL((bwd_dkdv_kernel<D, false, F16, true, false, false, kNoPattern, D, 8, true, false>), sgrid, block, 0, st, a);
+          return hipGetLastError();
+        }
     } else if (small) {
       if (causal) hipLaunchKernelGGL((bwd_dkdv_kernel<D, true, F16, true, false, false, kNoPattern, D, 4, false, RAGGED>), sgrid, dim3(256), 0, st, a);
       else hipLaunchKernelGGL((bwd_dkdv_kernel<D, false, F16, true, false, false, kNoPattern, D, 4, false, RAGGED>), sgrid, dim3(256), 0, st, a);
@@ -354,11 +355,12 @@ static hipError_t launch_dkdv(const BwdArgs& a, int causal, hipStream_t st) {
     else hipLaunchKernelGGL((bwd_dkdv_kernel<D, false, F16, true, false, false, kNoPattern, D, 8, false, RAGGED>), grid, block, 0, st, a);
     return hipGetLastError();
   }
-  if (small) {
-    if (causal) hipLaunchKernelGGL((bwd_dkdv_kernel<D, true, F16, false, false, false, kNoPattern, D, 4, false, RAGGED>), sgrid, dim3(256), 0, st, a);
-    else hipLaunchKernelGGL((bwd_dkdv_kernel<D, false, F16, false, false, false, kNoPattern, D, 4, false, RAGGED>), sgrid, dim3(256), 0, st, a);
-    return hipGetLastError();
-  }
+  if constexpr (D == 64 || !RAGGED)  // (packed at d = 128, a grid as small as that is a joint one)
+    if (small) {
+      if (causal) hipLaunchKernelGGL((bwd_dkdv_kernel<D, true, F16, false, false, false, kNoPattern, D, 4, false, RAGGED>), sgrid, dim3(256), 0, st, a);
+      else hipLaunchKernelGGL((bwd_dkdv_kernel<D, false, F16, false, false, false, kNoPattern, D, 4, false, RAGGED>), sgrid, dim3(256), 0, st, a);
+      return hipGetLastError();
+    }
   if (causal) hipLaunchKernelGGL((bwd_dkdv_kernel<D, true, F16, false, false, false, kNoPattern, D, 8, false, RAGGED>), grid, block, 0, st, a);
   else hipLaunchKernelGGL((bwd_dkdv_kernel<D, false, F16, false, false, false, kNoPattern, D, 8, false, RAGGED>), grid, block, 0, st, a);
   return hipGetLastError();

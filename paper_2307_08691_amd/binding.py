@@ -915,7 +915,7 @@ def splitkv_default_splits(B, Hq, Hkv, Nq, Nk, ragged: bool = False) -> int:
 
 
 def _cache_splits(B, Hq, Hkv, Nq, Nk, d, ragged: bool) -> int:
-    """Shares of fa_kvcache_fwd when the caller names none: splitkv_default_splits, but fewer where more than 32
+    """Shares of fa_kvcache_fwd and fa_splitkv_fwd when the caller names none: splitkv_default_splits, but fewer where more than 32
     query rows meet caches with lengths of their own (the row-block kernel; longest sequence first). Sequences of
     different lengths then want half as many workgroups again as there are compute units, and shares of at
     least 16 blocks (d = 128, 32 heads on 8, lengths up to 8192; us at 1 / 2 / 3 / 4 / 8 shares: 4 x 512
@@ -943,7 +943,7 @@ def fa_splitkv_fwd(Q, K, V, scale: float, causal: bool, num_splits: int = 0, O=N
     import torch
     x = _dense(Q, K, V)
     if num_splits <= 0:
-        num_splits = splitkv_default_splits(x.B, x.Hq, x.Hkv, x.Nq, x.Nk)
+        num_splits = _cache_splits(x.B, x.Hq, x.Hkv, x.Nq, x.Nk, x.d, False)
     O, LSE = _fwd_outputs(x, O, LSE)
     ws = _workspace(workspace, fa_splitkv_fwd_workspace_bytes(x.B, x.Hq, x.Nq, x.d, num_splits), x.dev)
     _check(fa_splitkv_fwd_raw(_ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(LSE), _ptr(ws), _wsbytes(ws), x.B, x.Hq, x.Hkv,

@@ -222,22 +222,45 @@ def test_split_key_entry_point_rejects_bad_arguments():
 
 
 def test_default_shares_of_cache_attention_fit_the_public_workspace():
-    """fa_kvcache_fwd's own rule: the public one where lengths are equal or the query rows fit the decode kernel, never
-    more than it elsewhere, so a workspace sized by splitkv_default_splits is always large enough."""
+    """The rule of fa_kvcache_fwd and fa_splitkv_fwd: the public one where lengths are equal or the query rows fit the decode
+    kernel (which keeps one share of fewer than sixteen blocks at d = 64), never more than it elsewhere, so a workspace sized by
+    splitkv_default_splits is always large enough."""
     public, own = binding.splitkv_default_splits, binding._cache_splits
     for B in (1, 2, 3, 4, 7, 8, 16, 33, 64, 128, 129, 300):
         for Hq, Hkv in ((1, 1), (4, 4), (8, 1), (32, 8), (32, 32), (64, 8)):
             for Nq in (1, 2, 8, 33, 70, 128, 233, 512, 1000, 4096):
-                for Nk in (1, 64, 65, 700, 1024, 2048, 8191, 8192, 10752, 131072):
+                for Nk in (1, 64, 65, 700, 768, 960, 961, 1024, 2048, 8191, 8192, 10752, 131072):
                     for d in (64, 128):
                         n, most = own(B, Hq, Hkv, Nq, Nk, d, True), public(B, Hq, Hkv, Nq, Nk, ragged=True)
                         assert 1 <= n <= most <= binding.FA_SPLITKV_MAX_SPLITS, (B, Hq, Hkv, Nq, Nk, d)
-                        assert Nq * (Hq // Hkv) > 32 or n == most
-                        assert own(B, Hq, Hkv, Nq, Nk, d, False) == public(B, Hq, Hkv, Nq, Nk)
+                        alone = d == 64 and Nq * (Hq // Hkv) <= 32 and Nk <= 960
+                        assert Nq * (Hq // Hkv) > 32 or n == (1 if alone else most)
+                        assert own(B, Hq, Hkv, Nq, Nk, d, False) == (1 if alone else public(B, Hq, Hkv, Nq, Nk))
     assert own(4, 32, 8, 512, 8192, 128, True) == 2
     assert own(8, 32, 8, 128, 8192, 128, True) == 3
     assert own(1, 32, 8, 512, 8192, 128, True) == 4
     assert own(4, 32, 8, 233, 10752, 64, True) == 4
+
+
+@pytest.fixture
+def shares_asked_for(monkeypatch):
+    """num_splits as the two split-key entry points hand it to the library, called on host tensors."""
+    asked = []
+    monkeypatch.setattr(binding, "_ptr", lambda t: P)
+    monkeypatch.setattr(binding, "_stream", lambda: 0)
+    monkeypatch.setattr(binding, "_host", False)
+    monkeypatch.setattr(binding, "fa_splitkv_fwd_raw", lambda *a: asked.append(a[15]) or 0)
+    monkeypatch.setattr(binding, "fa_kvcache_fwd_raw", lambda *a: asked.append(a[19]) or 0)
+    return asked
+
+
+@pytest.mark.parametrize("d,Nk,want", [(64, 768, 1), (64, 960, 1), (64, 1024, 8), (128, 768, 6), (128, 1024, 8)])
+def test_both_split_key_entry_points_take_the_same_shares(d, Nk, want, shares_asked_for):
+    torch = pytest.importorskip("torch")
+    Q, K = torch.zeros(4, 1, 32, d, dtype=torch.bfloat16), torch.zeros(4, Nk, 8, d, dtype=torch.bfloat16)
+    binding.fa_splitkv_fwd(Q, K, K, 0.1, True)
+    binding.fa_kvcache_fwd(Q, K, K, 0.1, True)
+    assert shares_asked_for == [want, want]
 
 
 def test_window_pattern_cache_fp8_and_mask_gradient_entry_points_reject_bad_arguments():

@@ -238,7 +238,7 @@ int run_fwd(const void* Q, const void* K, const void* V, void* O, float* LSE, co
 int run_bwd(const void* Q, const void* K, const void* V, const void* O, const void* dO, const float* LSE, void* dQ,
             void* dK, void* dV, void* ws, size_t ws_size, const int32_t* cu, int nseq, int N, int Nk, long total, int Hq, int Hkv, int d,
             float scale, int causal, int stages, void* stream, const int32_t* cu_k = nullptr,
-            const Options& opt = Options()) {
+            const Options& opt = Options(), long total_k = 0) {
   fa::BwdArgs a;
   a.p = make_problem(cu, nseq, N, Nk, Hq, Hkv, d, total, scale, cu_k, opt.f16);
   if (int e = apply_options(a.p, opt)) return e;
@@ -255,7 +255,7 @@ int run_bwd(const void* Q, const void* K, const void* V, const void* O, const vo
   a.keep_d = opt.keep_d;
   a.shares = 1;
   a.share_turn = 0;
-  a.key_rows = cu ? total : (long)nseq * Nk;
+  a.key_rows = cu_k ? total_k : cu ? total : (long)nseq * Nk;
   // (a workspace that holds D alone is enough for the backward without shares)
   a.partial = d <= 128 && !cu_k && ws_size >= ws_bytes(total, Hq, Hkv, d, N, a.key_rows) ? (float*)((char*)ws + ws_bytes(total, Hq)) : nullptr;
   a.dM = (__bf16*)opt.dM;
@@ -925,7 +925,7 @@ static int varlen_cross_bwd_any(int f16, const void* Q, const void* K, const voi
     return FA_ERR_ALIGN;
   if (workspace_bytes < ws_bytes(total_q, Hq)) return FA_ERR_WORKSPACE;
   return run_bwd(Q, K, V, O, dO, LSE, dQ, dK, dV, workspace, workspace_bytes, cu_seqlens_q, nseq, max_seqlen_q, max_seqlen_k, total_q,
-                 Hq, Hkv, d, scale, causal, 7, stream, cu_seqlens_k, half_precision(f16));
+                 Hq, Hkv, d, scale, causal, 7, stream, cu_seqlens_k, half_precision(f16), total_k);
 }
 
 int fa_varlen_cross_bwd(const void* Q, const void* K, const void* V, const void* O, const void* dO, const float* LSE,

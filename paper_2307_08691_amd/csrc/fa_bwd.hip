@@ -132,11 +132,15 @@ static bool small_workgroups(int n, int pairs, bool short_too, bool two = true) 
   return large >= 512 && 2 * large * 5 >= 6 * small;
 }
 
-// Blocks of `rows` rows (keys) over all pairs of a problem with `heads` heads: those that exist, on average in a packed batch.
-static double block_count(const Problem& p, int n, int rows, int heads) {
-  if (p.cu_seqlens) return ((double)p.total_tokens / rows + 0.5 * p.nseq) * heads;
+// Blocks of `rows` rows (keys) over all pairs of a problem: those that exist, on average in a packed batch.
+static double block_count(const Problem& p, int n, long total, int rows, int heads) {
+  if (p.cu_seqlens) return ((double)total / rows + 0.5 * p.nseq) * heads;
   return (double)((n + rows - 1) / rows) * heads * p.nseq;
 }
+static double row_blocks(const BwdArgs& a, int rows) { return block_count(a.p, a.p.N, a.p.total_tokens, rows, a.p.Hq); }
+static double key_blocks(const BwdArgs& a, int keys) { return block_count(a.p, a.p.Nk, a.key_rows, keys, a.p.Hkv); }
+// An average sequence's length over the longest's.
+static double average_part(const Problem& p, int n, long total) { return p.cu_seqlens ? (double)total / ((double)p.nseq * n) : 1; }
 
 // Whether the plain kernels (and dropout's at d = 64) of a joint grid take four wavefronts, blocks of 128 rows and keys.
 //  * d = 64, two such workgroups on a compute unit: while the blocks of keys are at most two rounds (MI355X, us of forward and
@@ -147,19 +151,20 @@ static double block_count(const Problem& p, int n, int rows, int heads) {
 //    1.2, 1.2 a key block of a block of rows instead of 1.5, about 6 to start), but four wavefronts get through less. The longest
 //    chain, or all the work over the compute units and half of a last block, whichever is longer, is within 3% of the better form on
 //    44 shapes (1 x 2048, 8 heads: 123 and 115; 3 x 700, 8 heads: 54.5 and 73.0; 2 x 1024, 32 heads on 8: 218 and 198).
-bool joint_small(const Problem& p, int D, int causal) {
-  const double keys4 = block_count(p, p.Nk, 128, p.Hkv);
+bool joint_small(const BwdArgs& a, int D, int causal) {
+  const Problem& p = a.p;
+  const double keys4 = key_blocks(a, 128);
   if (D == 64) return keys4 <= 1024 || (causal && p.Nk <= 4096);
   const double tiles = (double)((p.N + 31) / 32) * p.G, blocks = (p.Nk + 63) / 64, start = 6;  // of the longest chains
-  const double part = (causal ? 0.55 : 1) * (p.cu_seqlens ? (double)p.total_tokens / ((double)p.nseq * p.N) : 1);  // an average one
+  const double seen = causal ? 0.55 : 1;  // an average block's part of them
+  const double part_rows = seen * average_part(p, p.N, p.total_tokens), part_keys = seen * average_part(p, p.Nk, a.key_rows);
   auto estimate = [&](double nk, double nq, double per_tile, double per_block) {
     const double chain = start + tiles * per_tile, row_block = start + blocks * per_block;
-    double all = (part * (nk * tiles * per_tile + nq * blocks * per_block) + start * (nk + nq)) / 256;
+    double all = (part_rows * nk * tiles * per_tile + part_keys * nq * blocks * per_block + start * (nk + nq)) / 256;
     if (nk + nq > 256) all += 0.5 * (causal ? 0.2 : 1) * row_block;
     return chain > all ? chain : all;
   };
-  return estimate(keys4, block_count(p, p.N, 128, p.Hq), 1.06, 1.2) <
-         estimate(block_count(p, p.Nk, 256, p.Hkv), block_count(p, p.N, 256, p.Hq), 1.2, 1.5);
+  return estimate(keys4, row_blocks(a, 128), 1.06, 1.2) < estimate(key_blocks(a, 256), row_blocks(a, 256), 1.2, 1.5);
 }
 
 // Whether the backward is one grid (fa_bwd_joint.h) or two launches. The one grid costs the pre-pass (a pass over O and dO, 1 to 4% of
@@ -169,11 +174,13 @@ bool joint_small(const Problem& p, int D, int causal) {
 // 128, window of 95: 103 -> 87; 7 x 1152, 16 heads on 8 of 128: 436 -> 362; 16 x 1024, 16 heads on 4 of 128: 413 -> 361; 27 x 600, 16
 // heads of 128: 515 -> 492. Rounds without a rest are better off as they were: 8 x 2048, 32 heads of 64: 732 and 750; 4 x 1024, 16 heads
 // of 128, window of 129: 77.8 and 81.0; 32 x 256, 16 heads of 96: 125 and 129. Packed batches, whose blocks nobody has counted: up to
-// four rounds of blocks of keys (9 of up to 2077, 16 heads on 8 of 64: 286 -> 266; 16 of up to 4096, 32 heads on 8 of 128: even).
-bool joint_form(const Problem& p, int D, int causal) {
-  const bool small = D == 64 && p.d == D && !p.mask && !p.bmask && !windowed(p) && joint_small(p, D, causal);
+// four rounds of blocks of keys (9 of up to 2077, 16 heads on 8 of 64: 286 -> 266; 16 of up to 4096, 32 heads on 8 of 128: even; of two lengths, the backward: 16 x 4096 on 128, 16 heads of 64: 214 -> 168; 10 of up to 382
+// on up to 8030, 4 heads of 128, causal, five rounds, one grid and two launches: 356 -> 278).
+bool joint_form(const BwdArgs& a, int D, int causal) {
+  const Problem& p = a.p;
+  const bool small = D == 64 && p.d == D && !p.mask && !p.bmask && !windowed(p) && joint_small(a, D, causal);
   const int rows = small ? 128 : 256, keys = p.mask ? 128 : rows, slots = small ? 512 : 256;
-  const double key_rounds = block_count(p, p.Nk, keys, p.Hkv) / slots, row_rounds = block_count(p, p.N, rows, p.Hq) / slots;
+  const double key_rounds = key_blocks(a, keys) / slots, row_rounds = row_blocks(a, rows) / slots;
   if (p.cu_seqlens) return key_rounds < 4;
   auto rest = [](double rounds) { return __builtin_ceil(rounds) - rounds; };
   return (causal && key_rounds <= 1) || rest(key_rounds) + rest(row_rounds) > 0.04 * (key_rounds + row_rounds);
@@ -189,8 +196,8 @@ bool joint_form(const Problem& p, int D, int causal) {
 // nothing is idle it is left: 8 x 1024, 16 heads on 4 of 128.
 // Only for groups of four heads and more, with some thousand rows to a block of keys (share_rows): the sums are rounded in another order
 // than a single chain's, and with fewer heads or shorter sequences, which gain less, a sequence has the same gradients in every batch
-// (what that leaves: 1 x 1024, 4 heads on 1 of 64: 121, with shares 45; 4 x 600 of 128: 127, with shares 53). Not for masks and patterns, nor for packed batches of two lengths (whose number of keys only the
-// device knows).
+// (what that leaves: 1 x 1024, 4 heads on 1 of 64: 121, with shares 45; 4 x 600 of 128: 127, with shares 53). Not for masks and
+// patterns, nor for packed batches of two lengths.
 static int key_shares(const BwdArgs& a, int D, int causal) {
   const Problem& p = a.p;
   if (!a.partial || p.mask || p.bmask || p.cu_seqlens_k) return 1;
@@ -201,8 +208,8 @@ static int key_shares(const BwdArgs& a, int D, int causal) {
   const double seen = window ? p.win_left + p.win_right + 256. : 1e9;  // rows that see a block of keys, keys that a block of rows sees
   const double rows = p.N < seen ? p.N : seen, keys = p.Nk < seen ? p.Nk : seen, start = 6;
   const double chain = rows * p.G * (D == 64 ? 1.5 / 64 : 1.2 / 32), row_block = start + keys / 64 * (D == 64 ? 1.0 : 1.5);
-  const double nk = block_count(p, p.Nk, 256, p.Hkv), nq = block_count(p, p.N, 256, p.Hq);
-  const double part = (causal ? 0.55 : 1) * (p.cu_seqlens ? (double)p.total_tokens / ((double)p.nseq * p.N) : 1);  // an average one
+  const double nk = key_blocks(a, 256), nq = row_blocks(a, 256);
+  const double part = (causal ? 0.55 : 1) * average_part(p, p.N, p.total_tokens);  // an average one
   const double work = part * (nk * chain + nq * row_block) / 256, merged = a.key_rows * p.Hkv * (double)p.d * 8 / 4e6;
   int best = 1;
   double least = (start + chain > work ? start + chain : work) * 0.8;
@@ -385,7 +392,7 @@ static hipError_t launch_bwd_d(const BwdArgs& a, int causal, int stages, hipStre
     shared.share_turn = a.p.cu_seqlens ? 3 : (int)((a.p.Nk + 255L) / 256 * a.p.Hkv * a.p.nseq % kXcds);  // (packed: nobody has counted the blocks)
     if (shared.shares > 1) return launch_joint_shares<D, F16>(shared, causal, st);
   }
-  if (stages == 7 && joint_form(a.p, D, causal)) return launch_joint<D, F16>(a, causal, st);
+  if (stages == 7 && joint_form(a, D, causal)) return launch_joint<D, F16>(a, causal, st);
   if (stages == 7 && a.p.cu_seqlens) {
     if (hipError_t e = launch_dq<D, F16, true, true>(a, causal, st)) return e;
     return launch_dkdv<D, F16, true>(a, causal, st);

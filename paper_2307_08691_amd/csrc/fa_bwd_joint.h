@@ -57,7 +57,7 @@ static hipError_t launch_joint_d(const BwdArgs& a, int causal, hipStream_t st) {
     if (a.p.drop_thr) return launch_joint_rule<D, F16, true, false, false, D, 8, false, RAGGED, true>(a, causal, st);
     return launch_joint_rule<D, F16, false, false, false, D, 8, false, RAGGED, true>(a, causal, st);
   } else {
-    const bool small = joint_small(a.p, D, causal);
+    const bool small = joint_small(a, D, causal);
     if (a.p.drop_thr) {
       if constexpr (D == 128) {  // by the rule of the two launches: which form sums a key's rows does not depend on the grid being a joint one
         if (dropout_shared(a.p, causal)) return launch_joint_rule<D, F16, true, false, false, D, 8, true, RAGGED, SHARE>(a, causal, st);

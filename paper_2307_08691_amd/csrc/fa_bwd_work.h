@@ -23,8 +23,8 @@ template <int D, bool F16>
 hipError_t launch_prep(const BwdArgs& a, hipStream_t st);
 // the whole backward as one grid behind the pre-pass (fa_bwd_joint.h): whether a problem takes it, whether in workgroups of four
 // wavefronts (plain kernels and dropout at d = 64)
-bool joint_form(const Problem& p, int D, int causal);
-bool joint_small(const Problem& p, int D, int causal);
+bool joint_form(const BwdArgs& a, int D, int causal);
+bool joint_small(const BwdArgs& a, int D, int causal);
 template <int D, bool F16>
 hipError_t launch_joint(const BwdArgs& a, int causal, hipStream_t st);
 template <int D, bool F16>

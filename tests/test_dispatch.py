@@ -1,0 +1,24 @@
+"""The rules that choose a kernel, on the CPU (launches.py)."""
+import pytest
+
+from launches import launches, varlen_cross_bwd
+
+
+@pytest.mark.parametrize("nseq,nq,nk,Hq,Hkv,d", [(16, 4096, 128, 16, 16, 128), (16, 4096, 128, 16, 16, 64), (6, 382, 8030, 4, 4, 128),
+                                                 (15, 387, 6909, 1, 1, 128), (3, 700, 900, 8, 4, 64), (40, 2000, 60, 8, 8, 128)])
+@pytest.mark.parametrize("f16", [False, True])
+def test_packed_batches_of_two_lengths_count_their_keys(nseq, nq, nk, Hq, Hkv, d, f16):
+    """The blocks of keys of a packed batch are counted by its keys, not by its queries: under four rounds of them on the compute units
+    the backward is one grid (joint_form), whatever the number of queries."""
+    packed, more = launches([varlen_cross_bwd(nseq, nseq * nq, nseq * nk, nq, nk, Hq, Hkv, d, False, f16),
+                             varlen_cross_bwd(nseq, nseq * nq * 64, nseq * nk, nq * 64, nk, Hq, Hkv, d, False, f16)])
+    assert (nk / 256 + 0.5) * nseq * Hkv / 256 < 4
+    for kernels in (packed, more):
+        assert ["keyless" in kernels[0][0], "bwd_prep" in kernels[1][0], "bwd_joint" in kernels[2][0]] == [True] * 3 and len(kernels) == 3
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_many_rounds_of_keys_are_two_launches_for_few_queries_too(d):
+    few, many = launches([varlen_cross_bwd(64, 64 * 16, 64 * 8192, 16, 8192, 8, 8, d), varlen_cross_bwd(64, 64 * 8192, 64 * 8192, 8192, 8192, 8, 8, d)])
+    for kernels in (few, many):
+        assert [k[0].split("<")[0].split()[-1] for k in kernels[1:]] == ["bwd_dq_kernel", "bwd_dkdv_kernel"]

@@ -885,7 +885,9 @@ def splitkv_default_splits(B, Hq, Hkv, Nq, Nk, ragged: bool = False) -> int:
     Up to 32 query rows per key/value head (the decode kernel), at least twelve blocks and room for four shares or more:
      * shares down to two blocks, up to sixteen of them, as equal as they come: a wavefront's blocks follow each other, and the
        merge reads sixteen shares in one go (4 sequences, 32 heads on 8, device us at 8 blocks per share and so: d = 128, 1024 keys 13.9 ->
-       9.7, 1792: 14.9 -> 11.1, 2560: 14.6 -> 12.4; d = 64: 9.9 -> 8.0, 10.4 -> 8.5, 10.3 -> 9.3). Beyond sixteen 8 blocks each as
+       9.7, 1792: 14.9 -> 11.1, 2560: 14.6 -> 12.4; d = 64: 9.9 -> 8.0, 10.4 -> 8.5, 10.3 -> 9.3). More of them than that makes, some of
+       them empty, would not fall again at longer caches, but costs the merge (1 sequence, 32 heads on 8, 1216 keys, 7 / 9 shares: d = 64
+       7.6 / 8.4, d = 128 9.9 / 10.6). Beyond sixteen 8 blocks each as
        elsewhere (1 sequence, 16384 keys, 16 / 32 / 64 shares: 20.1 / 18.5 / 25.1);
      * no more workgroups than compute units, since one that is left over is a second round (3 sequences, 16 heads of 128, 5 / 6 shares:
        4096 keys 21.6 / 28.3, 8192 keys 34.1 / 38.1; 13, 4 heads, 2560 keys, 4 / 5: 18.2 / 21.2), but where that leaves an eighth of them
@@ -908,9 +910,13 @@ def splitkv_default_splits(B, Hq, Hkv, Nq, Nk, ragged: bool = False) -> int:
         fit, eights = 256 // units, blocks // 8
         if eights < -(-256 // units):
             n = max(eights, min(fit, 16, blocks // 2))
-            return -(-blocks // -(-blocks // n)) if n <= 16 else min(n, FA_SPLITKV_MAX_SPLITS)
+            return max(eights, -(-blocks // -(-blocks // n))) if n <= 16 else min(n, FA_SPLITKV_MAX_SPLITS)
         if blocks <= (128 if fit >= 5 else 63):
             return min(fit, FA_SPLITKV_MAX_SPLITS)
+    return _least_splits(units, blocks)
+
+
+def _least_splits(units, blocks) -> int:
     return max(1, min(FA_SPLITKV_MAX_SPLITS, blocks // 8, -(-256 // units)))
 
 
@@ -938,12 +944,25 @@ def _cache_splits(B, Hq, Hkv, Nq, Nk, d, ragged: bool) -> int:
     return max(1, min(FA_SPLITKV_MAX_SPLITS, (Nk + 63) // 64 // 16, want))
 
 
+def _own_splits(x, ragged: bool, workspace) -> int:
+    """_cache_splits, or as many shares as the caller's workspace holds where those are fewer: as equal as they come, the shares of a
+    longer cache may be fewer than those of a shorter one (d = 128, 1 sequence, 8 heads: 12 at 2304 keys, 16 at 2048), and a
+    workspace that was sized for the longest takes every shorter one. Not below shares of 8 blocks, which never get fewer."""
+    n = _cache_splits(x.B, x.Hq, x.Hkv, x.Nq, x.Nk, x.d, ragged)
+    if workspace is None or n == 1 or x.Nq * (x.Hq // x.Hkv) > 32:
+        return n
+    held, least = _wsbytes(workspace), _least_splits(x.B * x.Hkv, (x.Nk + 63) // 64)
+    while n > least and fa_splitkv_fwd_workspace_bytes(x.B, x.Hq, x.Nq, x.d, n) > held:
+        n -= 1
+    return n
+
+
 def fa_splitkv_fwd(Q, K, V, scale: float, causal: bool, num_splits: int = 0, O=None, LSE=None, workspace=None):
     """Few query rows against many keys; layouts and results as fa_cross_fwd. num_splits = 0 picks a default."""
     import torch
     x = _dense(Q, K, V)
     if num_splits <= 0:
-        num_splits = _cache_splits(x.B, x.Hq, x.Hkv, x.Nq, x.Nk, x.d, False)
+        num_splits = _own_splits(x, False, workspace)
     O, LSE = _fwd_outputs(x, O, LSE)
     ws = _workspace(workspace, fa_splitkv_fwd_workspace_bytes(x.B, x.Hq, x.Nq, x.d, num_splits), x.dev)
     _check(fa_splitkv_fwd_raw(_ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(LSE), _ptr(ws), _wsbytes(ws), x.B, x.Hq, x.Hkv,
@@ -989,7 +1008,7 @@ def fa_kvcache_fwd(Q, Kcache, Vcache, scale: float, causal: bool, seqlens_k=None
         _need(seqlens_k, "seqlens_k", torch.int32, (x.B,), x.dev)
     x.q_shape, x.l_shape = (x.B, x.Nq, x.Hq, x.d), (x.B, x.Hq, x.Nq)
     if num_splits <= 0:
-        num_splits = _cache_splits(x.B, x.Hq, x.Hkv, x.Nq, x.Nk, x.d, seqlens_k is not None)
+        num_splits = _own_splits(x, seqlens_k is not None, workspace)
     O, LSE = _fwd_outputs(x, O, LSE)
     ws = _workspace(workspace, fa_splitkv_fwd_workspace_bytes(x.B, x.Hq, x.Nq, x.d, num_splits), x.dev)
     _check(fa_kvcache_fwd_raw(_ptr(Q), _ptr(Kcache), _ptr(Vcache), _ptr(seqlens_k) if seqlens_k is not None else 0,

@@ -174,8 +174,9 @@ bool joint_small(const BwdArgs& a, int D, int causal) {
 // 128, window of 95: 103 -> 87; 7 x 1152, 16 heads on 8 of 128: 436 -> 362; 16 x 1024, 16 heads on 4 of 128: 413 -> 361; 27 x 600, 16
 // heads of 128: 515 -> 492. Rounds without a rest are better off as they were: 8 x 2048, 32 heads of 64: 732 and 750; 4 x 1024, 16 heads
 // of 128, window of 129: 77.8 and 81.0; 32 x 256, 16 heads of 96: 125 and 129. Packed batches, whose blocks nobody has counted: up to
-// four rounds of blocks of keys (9 of up to 2077, 16 heads on 8 of 64: 286 -> 266; 16 of up to 4096, 32 heads on 8 of 128: even; of two lengths, the backward: 16 x 4096 on 128, 16 heads of 64: 214 -> 168; 10 of up to 382
-// on up to 8030, 4 heads of 128, causal, five rounds, one grid and two launches: 356 -> 278).
+// four rounds of blocks of keys (9 of up to 2077, 16 heads on 8 of 64: 286 -> 266; 16 of up to 4096, 32 heads on 8 of 128: even;
+// the backward alone, of two lengths: 16 x 4096 on 128, 16 heads of 64: 214 -> 168; 10 of up to 382 on up to 8030, 4 heads of 128, causal, five
+// rounds: 278 in two launches, 356).
 bool joint_form(const BwdArgs& a, int D, int causal) {
   const Problem& p = a.p;
   const bool small = D == 64 && p.d == D && !p.mask && !p.bmask && !windowed(p) && joint_small(a, D, causal);

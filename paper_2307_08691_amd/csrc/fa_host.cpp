@@ -289,7 +289,8 @@ int cache_splits_of(long B, long Hq, long Hkv, long Nq, long Nk, long d, bool ra
       auto least_of = [](long a, long b) { return a < b ? a : b; };
       if (eights < up(256, units)) {
         const long small = least_of(least_of(fit, 16), blocks / 2), n = small > eights ? small : eights;
-        return (int)(n <= 16 ? up(blocks, up(blocks, n)) : least_of(n, FA_SPLITKV_MAX_SPLITS));
+        const long equal = up(blocks, up(blocks, n));
+        return (int)(n > 16 ? least_of(n, FA_SPLITKV_MAX_SPLITS) : equal > eights ? equal : eights);
       }
       if (blocks <= (fit >= 5 ? 128 : 63)) return (int)least_of(fit, FA_SPLITKV_MAX_SPLITS);
     }

@@ -263,6 +263,28 @@ def test_both_split_key_entry_points_take_the_same_shares(d, Nk, want, shares_as
     assert shares_asked_for == [want, want]
 
 
+@pytest.mark.parametrize("entry", [binding.fa_splitkv_fwd, binding.fa_kvcache_fwd])
+@pytest.mark.parametrize("B,Hq,Hkv,d,cap", [(1, 32, 8, 128, 2304), (1, 32, 8, 64, 2304), (2, 32, 8, 128, 2304), (3, 32, 8, 128, 1536),
+                                            (4, 32, 8, 128, 1792)])
+def test_a_workspace_for_the_longest_cache_takes_every_shorter_one(entry, B, Hq, Hkv, d, cap, shares_asked_for):
+    """The number of shares may fall as the cache grows: a workspace of splitkv_default_splits at the capacity is large enough for every
+    length below, whatever the rule says there. One that is too small for shares of eight blocks is refused."""
+    torch = pytest.importorskip("torch")
+    size = lambda n: binding.fa_splitkv_fwd_workspace_bytes(B, Hq, 1, d, n)
+    ws = torch.zeros(size(binding.splitkv_default_splits(B, Hq, Hkv, 1, cap)), dtype=torch.uint8)
+    Q, K = torch.zeros(B, 1, Hq, d, dtype=torch.bfloat16), torch.zeros(B, cap, Hkv, d, dtype=torch.bfloat16)
+    fewer = 0
+    for Nk in range(64, cap + 1, 64):
+        k = K[:, :Nk].contiguous()
+        entry(Q, k, k, 0.1, True, workspace=ws)
+        n, rule = shares_asked_for.pop(), binding._cache_splits(B, Hq, Hkv, 1, Nk, d, False)
+        assert n == rule or (n < rule and size(n) <= ws.numel() < size(n + 1)), Nk
+        fewer += n < rule
+    assert fewer
+    with pytest.raises(ValueError, match="are needed"):
+        entry(Q, K, K, 0.1, True, workspace=ws[:size(cap // 64 // 8) - 1])
+
+
 def test_window_pattern_cache_fp8_and_mask_gradient_entry_points_reject_bad_arguments():
     def local(Nq=64, Nk=64, d=128, left=10, right=0, Q=P):
         return binding.fa_local_fwd_raw(Q, P, P, P, P, 1, 4, 2, Nq, Nk, d, 0.1, left, right, 0)

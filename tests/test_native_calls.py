@@ -21,7 +21,7 @@ def host():
 def test_shares_of_a_cache_are_those_of_the_binding(host):
     for B, (Hq, Hkv), Nq, Nk, d, ragged in itertools.product(
             (1, 2, 5, 64, 128, 129, 500), ((1, 1), (8, 2), (32, 8), (32, 1)), (1, 2, 32, 33, 70, 512, 1000),
-            (1, 64, 1023, 1024, 5000, 8192, 70000), (64, 96, 128), (False, True)):
+            (1, 64, 768, 960, 1023, 1024, 1216, 2304, 5000, 8192, 8300, 70000), (64, 96, 128), (False, True)):
         want = binding._cache_splits(B, Hq, Hkv, Nq, Nk, d, ragged)
         assert host.cache_splits(B, Hq, Hkv, Nq, Nk, d, ragged) == want, (B, Hq, Hkv, Nq, Nk, d, ragged)
 

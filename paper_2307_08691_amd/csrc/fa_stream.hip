@@ -240,12 +240,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   if (ncolw > 1) {
     iteration(0, no, yes);
     // Where the loop begins: a wavefront alone on its SIMD waits for instructions that straddle a fetch, and the compiler lays the loop
-    // wherever the code before it ends. 40 bytes past a multiple of 64 (d = 64 without a mask 48) is the best of sixteen places, 0 the
-    // worst (MI355X, us, at 0 and here: causal, d = 64, 1 x 1292, 4 heads 19.0 and 18.4, 2 x 2112 27.6 and 26.6; 2 heads of 128, 3119: 52.2 and
-    // 50.4; no mask, d = 64, 1 x 1777, 8 heads 24.9 and 22.6; grids that fill the chip: no difference).
-    if constexpr (D == 64 && !CAUSAL) asm volatile(".p2align 6\n.rept 12\ns_nop 0\n.endr");
-    else asm volatile(".p2align 6\n.rept 10\ns_nop 0\n.endr");
-    for (int j = 1; j < ncolw - 1; ++j) iteration(j, yes, yes);
+    // wherever the code before it ends. Bytes past a multiple of 64, the best of sixteen places (MI355X, us, at the worst and here:
+    // causal, d = 64, 1 x 1292, 4 heads 19.0 and 18.4, 2 x 2112 27.6 and 26.6; 2 heads of 128, 3119: 52.2 and 50.4; no mask, d = 64, 1 x 1777, 8
+    // heads 24.9 and 22.6; grids that fill the chip: no difference). Under a condition of its own: the loop is then entered without a
+    // test, which the compiler would lay in between, longer or shorter by instantiation (packed batches, causal, d = 128, 6 of up to 68
+    // on 2377: 42.3 so and 41.3 here), and who does not loop does not go through the filling (1 x 128, 2 heads of 64: 4.56 and 4.50).
+    if (ncolw > 2) {
+      if constexpr (D == 64 && !CAUSAL) asm volatile(".p2align 6\n.rept 7\ns_nop 0\n.endr");
+      else if constexpr (D == 64) asm volatile(".p2align 6\n.rept 1\ns_nop 0\n.endr");
+      else if constexpr (!CAUSAL) asm volatile(".p2align 6\n.rept 6\ns_nop 0\n.endr");
+      else asm volatile(".p2align 6\n.rept 2\ns_nop 0\n.endr");
+      for (int j = 1; j < ncolw - 1; ++j) iteration(j, yes, yes);
+    }
     iteration(ncolw - 1, yes, no);
   } else {
     iteration(0, no, no);

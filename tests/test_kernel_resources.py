@@ -7,6 +7,7 @@ out of order with respect to loads and would make such a count pass early, and a
 makes the compiler wait for every copy in flight. The check compiles the kernel files for
 gfx950 with the flags of the build and reads the compiler's resource remarks (no GPU needed)."""
 import concurrent.futures
+import functools
 import os
 import re
 import subprocess
@@ -185,6 +186,7 @@ def test_the_in_flight_check_sees_a_planted_copy():
 #  * its accumulator is not touched by anything but another MFMA that accumulates into exactly the same registers for 12
 #    wait states (a product of 8 passes; the next MFMA cannot issue before those 8 passes are over).
 
+@functools.lru_cache(None)
 def whole_assembly(source):
     """kernel -> all lines up to its end (kernel_assembly stops at the first s_endpgm)."""
     cmd = [fa_build.hipcc(), *[f for f in fa_build.FLAGS if f not in ("-shared", "-fPIC")], "--cuda-device-only", "-S",
@@ -287,6 +289,16 @@ def test_hand_placed_products_keep_their_wait_states(source, kernels):
         seen += mfmas > 0
         assert not bad, (name, bad[:5])
     assert seen == kernels
+
+
+def test_the_four_wavefront_forward_loops_where_it_is_placed():
+    """The main loop's place against the instruction fetch is measured and filled up to (fa_stream.hip). The loop's first instruction
+    follows at once, in every instantiation: what the compiler puts in between would move it."""
+    for name, lines in whole_assembly("fa_stream.hip").items():
+        fills = [i for i, l in enumerate(lines) if l.split() == [".p2align", "6"]]
+        assert len(fills) == 1, name
+        end = next(i for i in range(fills[0], len(lines)) if "#ASMEND" in lines[i])
+        assert re.match(r"\.LBB\w+:.*Loop Header", lines[end + 1]), (name, lines[end + 1])
 
 
 @pytest.mark.parametrize("between,caught", [

@@ -514,8 +514,12 @@ __global__ __launch_bounds__(512)
   constexpr bool MID = TWO;
   // Where the loops begin: split keys at d = 64 feel it, every 32 bytes alike, and the compiler lays them wherever the code before them
   // ends. At 0 and at 24 past a multiple of 32 (MI355X, us): 3 x 893 new queries on up to 6656 keys, 32 heads on 16: 140.3 and
-  // 146.8; 1 x 65 on 5632, 32 on 4: 34.6 and 36.1. d = 128 and the forward pass without a cache: 1% at most between any two places.
+  // 146.8; 1 x 65 on 5632, 32 on 4: 34.6 and 36.1. The elementwise mask at d = 128 too: causal, 3 x 253 queries on 3022 keys, 8 heads, at 0,
+  // 8, 16 and 24 past a multiple of 32: 92.1, 92.1, 93.1, 90.7, where the compiler had laid them 100.8; without, 2 x 600 on 3000: 91.7, 91.3, 88.0,
+  // 89.5. d = 128 and the forward pass without a cache or a mask: 1% at most between any two places.
   if constexpr (SPLIT && D == 64) asm volatile(".p2align 6");
+  if constexpr (MASK && D == 128 && CAUSAL) asm volatile(".p2align 5\n.rept 6\ns_nop 0\n.endr");
+  if constexpr (MASK && D == 128 && !CAUSAL) asm volatile(".p2align 5\n.rept 4\ns_nop 0\n.endr");
   if (grp == 0) {
     for (int j = tb; j <= tend; ++j) {
       matrix_phase(j);

@@ -167,6 +167,57 @@ bool joint_small(const BwdArgs& a, int D, int causal) {
   return estimate(keys4, row_blocks(a, 128), 1.06, 1.2) < estimate(key_blocks(a, 256), row_blocks(a, 256), 1.2, 1.5);
 }
 
+// How long `first` equal blocks of t1 and then `second` of t2 take when `places` workgroups are resident and the next block goes to
+// whichever ends first.
+static double two_kinds(double first, double t1, double second, double t2, double places) {
+  const double full = __builtin_floor(first / places), late = first - full * places;  // late: places that take one more of the first kind
+  const double free[2] = {full * t1, late > 0 ? (full + 1) * t1 : full * t1};
+  auto done = [&](double t) {  // blocks of the second kind that have ended
+    auto of_a_place = [&](double from) { return t < from ? 0. : __builtin_floor((t - from) / t2 + 1e-6); };
+    return (places - late) * of_a_place(free[0]) + late * of_a_place(free[1]);
+  };
+  if (done(free[1]) >= second) return free[1];
+  // no earlier than if blocks could be divided, and a whole number of blocks after some place was free
+  const double least = (second * t2 + (places - late) * free[0] + late * free[1]) / places;
+  double end = free[1] + __builtin_ceil(second / places) * t2;
+  for (double from : free)
+    for (double i = __builtin_ceil((least - from) / t2 - 1e-6); from + i * t2 < end; ++i)
+      if (done(from + i * t2) >= second) end = from + i * t2;
+  return end;
+}
+
+// Where all blocks of a kind take as long (dense batches without a mask of the causal kind): whether the one grid ends before the two
+// launches do. Rests alone do not say so: two kinds of half a round and more make two rounds either way, and blocks of 256 rows of which
+// few exist may be the longer part. Blocks take what joint_small says they do (d = 64: 1.5 us a row tile, 1 a key block, 6 to start),
+// with dropout 1.6 times as long, and there 5% less in the four wavefronts that only the one grid has for both kinds at d = 64; 2 us lie
+// between two launches; the pre-pass takes 3.5 and the part of its bytes that the dQ kernel does not save. Against the better of the
+// two forms on 551 random shapes (MI355X, the backward, queries and keys of one length and of two, masks, patterns, dropout) this takes
+// 0.3% longer on average, the rests alone 1.3% (us, one grid and two launches: 32 x 44 queries on 3127 keys, 16 heads on 2 of 64: 196 and
+// 147; 18 x 103 on 585, 32 on 16 of 64: 84.5 and 74.7; 25 x 268, 32 heads of 64: 158 and 125; 2 x 199 on 8152, 8 heads of 128, mask: 362 and
+// 329; where it stays: 10 x 934 on 54, 32 on 16 of 64, mask: 91.5 and 107; half precision, dropout, 4 x 1777, 16 heads of 64: 263 and 274).
+static bool joint_sooner(const BwdArgs& a, int D, bool small) {
+  const Problem& p = a.p;
+  const bool plain = p.d == D && !p.mask && !p.bmask;
+  if (D == 128 && plain && !p.drop_thr) small = joint_small(a, D, false);
+  const double rows = (double)p.N, keys = (double)p.Nk, slower = p.drop_thr ? 1.6 : 1;
+  auto key_time = [&](bool four) {
+    return 6 + slower * p.G * (D == 64 ? 1.5 * __builtin_ceil(rows / 64) : (four ? 1.06 : 1.2) * __builtin_ceil(rows / 32));
+  };
+  auto row_time = [&](bool four) { return 6 + slower * (D == 64 ? 1. : four ? 1.2 : 1.5) * __builtin_ceil(keys / 64); };
+  auto places = [&](bool four) { return D == 64 && four ? 512 : 256; };
+  const bool shared = D == 128 && p.drop_thr && dropout_shared(p, false);
+  auto blocks_of_keys = [&](bool four) { return key_blocks(a, four || p.mask || shared ? 128 : 256); };
+  auto blocks_of_rows = [&](bool four) { return row_blocks(a, four ? 128 : 256); };
+  const double pre_pass = 3.5 + 0.6 * p.total_tokens * (double)p.Hq * p.d * 4 / 4e6;  // (bytes at 4 TB/s)
+  const double one = two_kinds(blocks_of_keys(small), key_time(small), blocks_of_rows(small), row_time(small), places(small)) + pre_pass;
+  // (the forms that launch_dq and launch_dkdv take)
+  const bool four_q = D == 64 && plain && !p.drop_thr && small_workgroups(p.N, p.Hq * p.nseq, false);
+  const bool four_k = plain && (D == 64 || !p.drop_thr) && small_workgroups(p.Nk, p.Hkv * p.nseq, false, D == 64);
+  const double two = __builtin_ceil(blocks_of_rows(four_q) / places(four_q)) * row_time(four_q) +
+                     __builtin_ceil(blocks_of_keys(four_k) / places(four_k)) * key_time(four_k) + 2;
+  return (small && D == 64 && p.drop_thr ? 0.95 : 1) * one < two;
+}
+
 // Whether the backward is one grid (fa_bwd_joint.h) or two launches. The one grid costs the pre-pass (a pass over O and dO, 1 to 4% of
 // the backward, part of which the dQ kernel saves) and gains what the two launches leave idle: the rest of their last rounds, and
 // under the causal mask, whose blocks are uneven, whatever a grid of one round does not fill. MI355X, us of forward and backward, two
@@ -184,7 +235,8 @@ bool joint_form(const BwdArgs& a, int D, int causal) {
   const double key_rounds = key_blocks(a, keys) / slots, row_rounds = row_blocks(a, rows) / slots;
   if (p.cu_seqlens) return key_rounds < 4;
   auto rest = [](double rounds) { return __builtin_ceil(rounds) - rounds; };
-  return (causal && key_rounds <= 1) || rest(key_rounds) + rest(row_rounds) > 0.04 * (key_rounds + row_rounds);
+  const bool idle = (causal && key_rounds <= 1) || rest(key_rounds) + rest(row_rounds) > 0.04 * (key_rounds + row_rounds);
+  return idle && (causal || windowed(p) || joint_sooner(a, D, small));
 }
 
 // How many workgroups share the row tiles of a block of keys (1: one takes all of them). A block's chain is G * N / 32 tiles (64 at

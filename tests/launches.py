@@ -49,3 +49,11 @@ def varlen_cross_bwd(nseq, total_q, total_k, max_q, max_k, Hq, Hkv, d, causal=Fa
 
 def cross_bwd(B, Hq, Hkv, Nq, Nk, d, causal=False, f16=False):
     return "fa_cross_bwd", [P] * 10 + [1 << 40, B, Hq, Hkv, Nq, Nk, d, 0.1, causal, 0, f16]
+
+
+def mask_bwd(B, Hq, Hkv, Nq, Nk, d, causal=False, f16=False):
+    return "fa_mask_bwd", [P] * 11 + [1 << 40, B, Hq, Hkv, Nq, Nk, d, 0.1, causal, 0, 0, (Nk + 7) // 8 * 8, 0, f16]
+
+
+def dropout_bwd(B, Hq, Hkv, Nq, Nk, d, causal=False, f16=False):
+    return "fa_dropout_bwd", [P] * 10 + [1 << 40, B, Hq, Hkv, Nq, Nk, d, 0.1, causal, 0.1, 7, 0, f16]

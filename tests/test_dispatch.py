@@ -1,7 +1,7 @@
 """The rules that choose a kernel, on the CPU (launches.py)."""
 import pytest
 
-from launches import launches, varlen_cross_bwd
+from launches import cross_bwd, dropout_bwd, launches, mask_bwd, varlen_cross_bwd
 
 
 @pytest.mark.parametrize("nseq,nq,nk,Hq,Hkv,d", [(16, 4096, 128, 16, 16, 128), (16, 4096, 128, 16, 16, 64), (6, 382, 8030, 4, 4, 128),
@@ -22,3 +22,20 @@ def test_many_rounds_of_keys_are_two_launches_for_few_queries_too(d):
     few, many = launches([varlen_cross_bwd(64, 64 * 16, 64 * 8192, 16, 8192, 8, 8, d), varlen_cross_bwd(64, 64 * 8192, 64 * 8192, 8192, 8192, 8, 8, d)])
     for kernels in (few, many):
         assert [k[0].split("<")[0].split()[-1] for k in kernels[1:]] == ["bwd_dq_kernel", "bwd_dkdv_kernel"]
+
+
+def form(kernels):
+    return "one grid" if any("bwd_joint" in k[0] for k in kernels) else "two launches"
+
+
+@pytest.mark.parametrize("call,want", [
+    (cross_bwd(32, 16, 2, 44, 3127, 64), "two launches"), (cross_bwd(18, 32, 16, 103, 585, 64), "two launches"),
+    (cross_bwd(18, 32, 16, 631, 631, 64, f16=True), "two launches"), (mask_bwd(2, 8, 8, 199, 8152, 128, f16=True), "two launches"),
+    (mask_bwd(1, 32, 8, 123, 7714, 128), "two launches"), (cross_bwd(12, 8, 8, 900, 900, 80), "one grid"),
+    (mask_bwd(10, 32, 16, 934, 54, 64), "one grid"), (cross_bwd(2, 1, 1, 2304, 2304, 128), "one grid"), (cross_bwd(1, 8, 4, 448, 448, 64, True), "one grid"),
+    (cross_bwd(27, 16, 16, 600, 600, 128), "one grid"), (cross_bwd(25, 32, 32, 268, 268, 64), "two launches"),
+    (dropout_bwd(4, 16, 16, 1777, 1777, 64, f16=True), "one grid"),
+    (cross_bwd(16, 16, 16, 1024, 1024, 128), "two launches"), (cross_bwd(8, 32, 32, 2048, 2048, 64), "two launches")])
+def test_the_backward_is_one_grid_where_that_ends_sooner(call, want):
+    """Shapes whose two forms were measured (joint_sooner, joint_form): rests of rounds alone do not make one grid the sooner form."""
+    assert form(launches([call])[0]) == want

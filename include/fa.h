@@ -96,9 +96,11 @@ int fa_fwd(const void* Q, const void* K, const void* V, void* O, float* LSE,
  * Groups of four and more query heads to a key/value head (more than 1200 rows with four, 320 with eight), on grids that leave compute units idle: several workgroups
  * share a block of keys and leave float32 sums of dK and dV behind D, and a further kernel adds them; dK and dV then
  * differ from those of a larger batch, or of the separate stages below, by the rounding of float32 sums. A workspace that
- * holds D alone (4 * B * N * Hq bytes, rounded up to 256) is accepted too, and the pass then takes no shares: such
- * problems are the only ones for which fa_bwd_workspace_bytes() asks for more, up to 64 MiB. The same goes
- * for the other backward entry points but those with a mask, a block pattern or packed batches of two lengths.
+ * holds D alone (4 * B * N * Hq bytes, rounded up to 256) is accepted too, and the pass then takes no shares. For
+ * groups and lengths as above fa_bwd_workspace_bytes() asks for more, up to 64 MiB, also where the pass then takes no shares
+ * (which further depends on how full the grid is); fa_varlen_bwd_workspace_bytes(), which does not know the longest sequence, for
+ * groups as above and as many tokens. The same goes for the other backward entry points but those with a mask, a block pattern or packed
+ * batches of two lengths, which take no shares and use D alone.
  */
 size_t fa_bwd_workspace_bytes(int B, int Hq, int Hkv, int N, int d);
 int fa_bwd(const void* Q, const void* K, const void* V, const void* O, const void* dO,

@@ -408,14 +408,28 @@ def _out(t, name, shape, dtype, device):
     return t
 
 
+def _d_bytes(rows) -> int:
+    """D alone, a float for each (query row, head): the least workspace of a backward pass, and all that one uses which takes no shares."""
+    return (4 * rows + 255) // 256 * 256
+
+
+def _packed_bwd_bytes(x, max_seqlen) -> int:
+    """What a packed backward uses. fa_varlen_bwd_workspace_bytes, which does not know the longest sequence, asks for shares' room also where
+    no sequence is long enough for shares; the dense function says what a longest sequence and this many keys need behind its D."""
+    if not 0 < max_seqlen <= x.Tq:
+        return fa_varlen_bwd_workspace_bytes(x.Tq, x.Hq, x.Hkv, x.d)
+    return (_d_bytes(x.Tq * x.Hq) - _d_bytes(max_seqlen * x.Hq) +
+            fa_cross_bwd_workspace_bytes(1, x.Hq, x.Hkv, max_seqlen, x.Tq, x.d))
+
+
 def _workspace(ws, nbytes, device, rows=None):
-    """rows (backward): one that holds D alone, a float for each (query row, head), is enough (the pass then takes no shares)."""
+    """rows (backward): one that holds D alone is enough (the pass then takes no shares)."""
     import torch
     if ws is None:
         return torch.empty(nbytes, dtype=torch.uint8, device=device)
     _need(ws, "workspace", None, None, device)
     if rows is not None:
-        nbytes = (4 * rows + 255) // 256 * 256
+        nbytes = _d_bytes(rows)
     if ws.numel() * ws.element_size() < nbytes:
         raise ValueError(f"workspace holds {ws.numel() * ws.element_size()} bytes, {nbytes} are needed")
     return ws
@@ -568,7 +582,7 @@ def fa_varlen_bwd(Q, K, V, O, dO, LSE, cu_seqlens, max_seqlen: int, scale: float
     import torch
     x = _packed(Q, K, V, cu_seqlens, allowed=(torch.bfloat16, torch.float16))
     dQ, dK, dV = _bwd_tensors(x, O, dO, LSE, dQ, dK, dV)
-    ws = _workspace(workspace, fa_varlen_bwd_workspace_bytes(x.Tq, x.Hq, x.Hkv, x.d), x.dev, x.Tq * x.Hq)
+    ws = _workspace(workspace, _packed_bwd_bytes(x, max_seqlen), x.dev, x.Tq * x.Hq)
     _check(fa_varlen_bwd_raw(_ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(dO), _ptr(LSE), _ptr(dQ), _ptr(dK), _ptr(dV),
                              _ptr(ws), _wsbytes(ws), _ptr(cu_seqlens), x.nseq, x.Tq, max_seqlen, x.Hq, x.Hkv, x.d, scale,
                              causal, _stream(), x.et == torch.float16))
@@ -654,7 +668,7 @@ def fa_varlen_dropout_bwd(Q, K, V, O, dO, LSE, cu_seqlens, max_seqlen: int, scal
     import torch
     x = _packed(Q, K, V, cu_seqlens, allowed=(torch.bfloat16, torch.float16))
     dQ, dK, dV = _bwd_tensors(x, O, dO, LSE, dQ, dK, dV)
-    ws = _workspace(workspace, fa_varlen_bwd_workspace_bytes(x.Tq, x.Hq, x.Hkv, x.d), x.dev, x.Tq * x.Hq)
+    ws = _workspace(workspace, _packed_bwd_bytes(x, max_seqlen), x.dev, x.Tq * x.Hq)
     _check(fa_varlen_dropout_bwd_raw(_ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(dO), _ptr(LSE), _ptr(dQ), _ptr(dK),
                                      _ptr(dV), _ptr(ws), _wsbytes(ws), _ptr(cu_seqlens), x.nseq, x.Tq, max_seqlen, x.Hq,
                                      x.Hkv, x.d, scale, causal, p_drop, seed, _stream(), x.et == torch.float16))
@@ -699,7 +713,7 @@ def fa_mask_bwd(Q, K, V, M, O, dO, LSE, scale: float, causal: bool, dQ=None, dK=
     x = _dense(Q, K, V)
     bs, hs, rs = _mask_strides(M, x)
     dQ, dK, dV = _bwd_tensors(x, O, dO, LSE, dQ, dK, dV)
-    ws = _workspace(workspace, fa_cross_bwd_workspace_bytes(x.B, x.Hq, x.Hkv, x.Nq, x.Nk, x.d), x.dev, x.B * x.Nq * x.Hq)
+    ws = _workspace(workspace, _d_bytes(x.B * x.Nq * x.Hq), x.dev)
     _check(fa_mask_bwd_raw(_ptr(Q), _ptr(K), _ptr(V), _ptr(M), _ptr(O), _ptr(dO), _ptr(LSE), _ptr(dQ), _ptr(dK),
                            _ptr(dV), _ptr(ws), _wsbytes(ws), x.B, x.Hq, x.Hkv, x.Nq, x.Nk, x.d, scale, causal, bs, hs, rs,
                            _stream(), x.et == torch.float16))
@@ -718,7 +732,7 @@ def fa_mask_bwd_dmask(Q, K, V, M, O, dO, LSE, scale: float, causal: bool, dQ=Non
         dM = mask_buffer(x.B, x.Hq, x.Nq, x.Nk, device=x.dev, dtype=x.et)
     if dM.dtype != x.et or dM.device != x.dev or tuple(dM.shape) != (x.B, x.Hq, x.Nq, x.Nk) or dM.stride(3) != 1:
         raise ValueError("dM must be [B, Hq, Nq, Nk] of the element type of Q, on its device, key dimension contiguous")
-    ws = _workspace(workspace, fa_cross_bwd_workspace_bytes(x.B, x.Hq, x.Hkv, x.Nq, x.Nk, x.d), x.dev, x.B * x.Nq * x.Hq)
+    ws = _workspace(workspace, _d_bytes(x.B * x.Nq * x.Hq), x.dev)
     _check(fa_mask_bwd_dmask_raw(_ptr(Q), _ptr(K), _ptr(V), _ptr(M), _ptr(O), _ptr(dO), _ptr(LSE), _ptr(dQ), _ptr(dK),
                                  _ptr(dV), _ptr(dM), _ptr(ws), _wsbytes(ws), x.B, x.Hq, x.Hkv, x.Nq, x.Nk, x.d, scale,
                                  causal, bs, hs, rs, dM.stride(0), dM.stride(1), dM.stride(2), _stream(),
@@ -776,7 +790,7 @@ def fa_varlen_local_bwd(Q, K, V, O, dO, LSE, cu_seqlens, max_seqlen: int, scale:
     import torch
     x = _packed(Q, K, V, cu_seqlens, allowed=(torch.bfloat16, torch.float16))
     dQ, dK, dV = _bwd_tensors(x, O, dO, LSE, dQ, dK, dV)
-    ws = _workspace(workspace, fa_varlen_bwd_workspace_bytes(x.Tq, x.Hq, x.Hkv, x.d), x.dev, x.Tq * x.Hq)
+    ws = _workspace(workspace, _packed_bwd_bytes(x, max_seqlen), x.dev, x.Tq * x.Hq)
     _check(fa_varlen_local_bwd_raw(_ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(dO), _ptr(LSE), _ptr(dQ), _ptr(dK),
                                    _ptr(dV), _ptr(ws), _wsbytes(ws), _ptr(cu_seqlens), x.nseq, x.Tq, max_seqlen, x.Hq,
                                    x.Hkv, x.d, scale, window_left, window_right, _stream(), x.et == torch.float16))
@@ -812,7 +826,7 @@ def fa_blocksparse_bwd(Q, K, V, block_mask, block: int, O, dO, LSE, scale: float
     x = _dense(Q, K, V)
     bs, hs = _block_mask_strides(block_mask, x, block)
     dQ, dK, dV = _bwd_tensors(x, O, dO, LSE, dQ, dK, dV)
-    ws = _workspace(workspace, fa_cross_bwd_workspace_bytes(x.B, x.Hq, x.Hkv, x.Nq, x.Nk, x.d), x.dev, x.B * x.Nq * x.Hq)
+    ws = _workspace(workspace, _d_bytes(x.B * x.Nq * x.Hq), x.dev)
     _check(fa_blocksparse_bwd_raw(_ptr(Q), _ptr(K), _ptr(V), _ptr(block_mask), _ptr(O), _ptr(dO), _ptr(LSE), _ptr(dQ),
                                   _ptr(dK), _ptr(dV), _ptr(ws), _wsbytes(ws), x.B, x.Hq, x.Hkv, x.Nq, x.Nk, x.d, scale,
                                   causal, block, bs, hs, _stream(), x.et == torch.float16))
@@ -869,7 +883,7 @@ def fa_varlen_cross_bwd(Q, K, V, O, dO, LSE, cu_seqlens_q, cu_seqlens_k, max_seq
     import torch
     x = _packed(Q, K, V, cu_seqlens_q, cu_seqlens_k, allowed=(torch.bfloat16, torch.float16))
     dQ, dK, dV = _bwd_tensors(x, O, dO, LSE, dQ, dK, dV)
-    ws = _workspace(workspace, fa_varlen_bwd_workspace_bytes(x.Tq, x.Hq, x.Hkv, x.d), x.dev, x.Tq * x.Hq)
+    ws = _workspace(workspace, _d_bytes(x.Tq * x.Hq), x.dev)
     _check(fa_varlen_cross_bwd_raw(_ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(dO), _ptr(LSE), _ptr(dQ), _ptr(dK), _ptr(dV),
                                    _ptr(ws), _wsbytes(ws), _ptr(cu_seqlens_q), _ptr(cu_seqlens_k), x.nseq, x.Tq, x.Tk,
                                    max_seqlen_q, max_seqlen_k, x.Hq, x.Hkv, x.d, scale, causal, _stream(), x.et == torch.float16))

@@ -259,7 +259,11 @@ PyObject* varlen_bwd(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
     Py_RETURN_NONE;
   if (!current_stream(st)) return nullptr;
   at::Tensor dQ = make(x.Q->sizes(), x.et, x.dev), dK = make(x.K->sizes(), x.et, x.dev), dV = make(x.K->sizes(), x.et, x.dev);
-  const size_t nb = lib.fa_varlen_bwd_workspace_bytes(x.T, x.Hq, x.Hkv, x.d);
+  // (binding._packed_bwd_bytes)
+  auto d_bytes = [&](long rows) { return (size_t)(4 * rows * x.Hq + 255) / 256 * 256; };
+  const size_t nb = x.longest > 0 && x.longest <= x.T
+                        ? d_bytes(x.T) - d_bytes(x.longest) + lib.fa_cross_bwd_workspace_bytes(1, x.Hq, x.Hkv, x.longest, x.T, x.d)
+                        : lib.fa_varlen_bwd_workspace_bytes(x.T, x.Hq, x.Hkv, x.d);
   at::Tensor W = make({(int64_t)nb}, at::kByte, x.dev);
   const void *q = in(x.Q), *k = in(x.K), *v = in(x.V), *o = in(O), *g = in(dO);
   const float* l = stat(L);

@@ -57,3 +57,7 @@ def mask_bwd(B, Hq, Hkv, Nq, Nk, d, causal=False, f16=False):
 
 def dropout_bwd(B, Hq, Hkv, Nq, Nk, d, causal=False, f16=False):
     return "fa_dropout_bwd", [P] * 10 + [1 << 40, B, Hq, Hkv, Nq, Nk, d, 0.1, causal, 0.1, 7, 0, f16]
+
+
+def varlen_bwd(nseq, total, longest, Hq, Hkv, d, workspace=1 << 40, causal=False):
+    return "fa_varlen_bwd", [P] * 10 + [workspace, P, nseq, total, longest, Hq, Hkv, d, 0.1, causal, 0, False]

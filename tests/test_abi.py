@@ -100,6 +100,45 @@ def test_workspace_size_formula():
     assert binding.fa_bwd_workspace_bytes(1, 8, 2, 16, 128) >= 16 * 8 * 4
 
 
+@pytest.fixture
+def workspace_asked_for(monkeypatch):
+    """Bytes of workspace that the backward entry points allocate, called on host tensors."""
+    asked = []
+    monkeypatch.setattr(binding, "_ptr", lambda t: P)
+    monkeypatch.setattr(binding, "_stream", lambda: 0)
+    monkeypatch.setattr(binding, "_host", False)
+    monkeypatch.setattr(binding, "_wsbytes", lambda ws: asked.append(ws.numel()) or ws.numel())
+    for name in ("fa_mask_bwd", "fa_mask_bwd_dmask", "fa_blocksparse_bwd", "fa_varlen_cross_bwd", "fa_varlen_bwd", "fa_varlen_local_bwd",
+                 "fa_varlen_dropout_bwd"):
+        monkeypatch.setattr(binding, name + "_raw", lambda *a: 0)
+    return asked
+
+
+def test_calls_that_take_no_shares_allocate_no_room_for_them(workspace_asked_for):
+    """A mask, a block pattern, packed batches of two lengths, and packed batches of short sequences: a float for each (row, head), while
+    the same numbers of rows in a long sequence ask for the shares' sums too."""
+    torch = pytest.importorskip("torch")
+    t = lambda *s: torch.zeros(s, dtype=torch.bfloat16)
+    B, N, Hq, Hkv, d = 1, 2048, 32, 4, 64
+    Q, K, L = t(B, N, Hq, d), t(B, N, Hkv, d), torch.zeros(B, Hq, N)
+    M, blocks = binding.mask_buffer(1, 1, N, N, "cpu", torch.bfloat16), torch.ones(1, 1, N // 64, N // 64, dtype=torch.uint8)
+    only_d = 4 * B * N * Hq
+    assert binding.fa_cross_bwd_workspace_bytes(B, Hq, Hkv, N, N, d) > only_d
+    binding.fa_mask_bwd(Q, K, K, M, Q, Q, L, 0.1, True)
+    binding.fa_mask_bwd_dmask(Q, K, K, M, Q, Q, L, 0.1, False)
+    binding.fa_blocksparse_bwd(Q, K, K, blocks, 64, Q, Q, L, 0.1, True)
+    q, k, l = Q[0], K[0], L[0]
+    short = torch.arange(0, N + 1, 128, dtype=torch.int32)
+    binding.fa_varlen_cross_bwd(q, k, k, q, q, l, short, short, 128, 128, 0.1, True)
+    binding.fa_varlen_bwd(q, k, k, q, q, l, short, 128, 0.1, True)
+    binding.fa_varlen_local_bwd(q, k, k, q, q, l, short, 128, 0.1, 64, 0)
+    binding.fa_varlen_dropout_bwd(q, k, k, q, q, l, short, 128, 0.1, True, 0.1, 7)
+    assert workspace_asked_for == [only_d] * 7
+    one = torch.tensor([0, N], dtype=torch.int32)
+    binding.fa_varlen_bwd(q, k, k, q, q, l, one, N, 0.1, True)
+    assert workspace_asked_for[-1] == binding.fa_varlen_bwd_workspace_bytes(N, Hq, Hkv, d) > only_d
+
+
 def test_varlen_rejects_bad_arguments():
     def vf(cu=P, nseq=4, total=1000, mx=400, Hq=4, Hkv=2, d=128, scale=0.1, Q=P):
         return binding.fa_varlen_fwd_raw(Q, P, P, P, P, cu, nseq, total, mx, Hq, Hkv, d, scale, 1, 0)

@@ -1,7 +1,10 @@
 """The rules that choose a kernel, on the CPU (launches.py)."""
+import types
+
 import pytest
 
-from launches import cross_bwd, dropout_bwd, launches, mask_bwd, varlen_cross_bwd
+from launches import cross_bwd, dropout_bwd, launches, mask_bwd, varlen_bwd, varlen_cross_bwd
+from paper_2307_08691_amd import binding
 
 
 @pytest.mark.parametrize("nseq,nq,nk,Hq,Hkv,d", [(16, 4096, 128, 16, 16, 128), (16, 4096, 128, 16, 16, 64), (6, 382, 8030, 4, 4, 128),
@@ -39,3 +42,16 @@ def form(kernels):
 def test_the_backward_is_one_grid_where_that_ends_sooner(call, want):
     """Shapes whose two forms were measured (joint_sooner, joint_form): rests of rounds alone do not make one grid the sooner form."""
     assert form(launches([call])[0]) == want
+
+
+@pytest.mark.parametrize("lens,Hq,Hkv,d", [([3000], 8, 1, 64), ([700, 1, 0, 233], 8, 1, 128), ([1500] * 8, 32, 4, 64), ([321, 100], 8, 1, 128),
+                                           ([128] * 16, 32, 8, 128), ([1201], 4, 1, 128), ([4000, 12], 16, 4, 96)])
+def test_packed_batches_get_the_workspace_that_they_use(lens, Hq, Hkv, d):
+    """The workspace that the binding allocates for a packed batch, which knows the longest sequence, is as good as the larger one of
+    fa_varlen_bwd_workspace_bytes, which does not."""
+    x = types.SimpleNamespace(Tq=sum(lens), Hq=Hq, Hkv=Hkv, d=d)
+    used, bound = binding._packed_bwd_bytes(x, max(lens)), binding.fa_varlen_bwd_workspace_bytes(x.Tq, Hq, Hkv, d)
+    assert used <= bound
+    a, b = launches([varlen_bwd(len(lens), x.Tq, max(lens), Hq, Hkv, d, w) for w in (used, bound)])
+    assert a == b
+    assert any("merge" in k[0] for k in a) <= (used > 4 * x.Tq * Hq + 255)

@@ -415,11 +415,16 @@ static hipError_t launch_dkdv(const BwdArgs& a, int causal, hipStream_t st) {
     else hipLaunchKernelGGL((bwd_dkdv_kernel<D, false, F16, true, false, false, kNoPattern, D, 8, false, RAGGED>), grid, block, 0, st, a);
     return hipGetLastError();
   }
-  if constexpr (D == 64 || !RAGGED)  // (packed at d = 128, a grid as small as that is a joint one)
+  if constexpr (D == 64 || !RAGGED)  // (at d = 128, packed or causal, a grid as small as that is a joint one; single stages are for bfloat16)
     if (small) {
-      if (causal) hipLaunchKernelGGL((bwd_dkdv_kernel<D, true, F16, false, false, false, kNoPattern, D, 4, false, RAGGED>), sgrid, dim3(256), 0, st, a);
-      else hipLaunchKernelGGL((bwd_dkdv_kernel<D, false, F16, false, false, false, kNoPattern, D, 4, false, RAGGED>), sgrid, dim3(256), 0, st, a);
-      return hipGetLastError();
+      if (!causal) {
+        hipLaunchKernelGGL((bwd_dkdv_kernel<D, false, F16, false, false, false, kNoPattern, D, 4, false, RAGGED>), sgrid, dim3(256), 0, st, a);
+        return hipGetLastError();
+      }
+      if constexpr (D == 64 || !F16) {
+        hipLaunchKernelGGL((bwd_dkdv_kernel<D, true, F16, false, false, false, kNoPattern, D, 4, false, RAGGED>), sgrid, dim3(256), 0, st, a);
+        return hipGetLastError();
+      }
     }
   if (causal) hipLaunchKernelGGL((bwd_dkdv_kernel<D, true, F16, false, false, false, kNoPattern, D, 8, false, RAGGED>), grid, block, 0, st, a);
   else hipLaunchKernelGGL((bwd_dkdv_kernel<D, false, F16, false, false, false, kNoPattern, D, 8, false, RAGGED>), grid, block, 0, st, a);

@@ -898,7 +898,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 // Few threads per row and a handful of shares: the time is the chain of loads. FLY shares are requested together, and up to
 // FLY are all that there are: logsumexps and partial rows are then on their way at once. (A share without keys for this
 // row may have written no partial O: what is read in its place is not used.)
-template <int D, bool F16, bool DECODE, int FLY>
+template <int D, bool F16, int FLY>
 __device__ __forceinline__ void merge_row(const FwdArgs& a, long r, int c, long li, int nshare, long nrows) {
   auto lse_of = [&](int k) { return a.Lpart[(long)(k < nshare ? k : nshare - 1) * nrows + li]; };
   auto row_of = [&](int k) { return *(const f32x4*)(a.Opart + ((long)(k < nshare ? k : nshare - 1) * nrows + r) * D + 4 * c); };
@@ -961,9 +961,9 @@ __global__ __launch_bounds__(256) void fwd_merge_kernel(FwdArgs a) {
   const long b = tok / p.N, q = tok - b * p.N;
   const long li = b * p.lse_seq_stride + (long)h * p.lse_head_stride + q;
   if constexpr (DECODE) {
-    if (a.nsplit <= 4) merge_row<D, F16, DECODE, 4>(a, r, c, li, a.nsplit, nrows);
-    else if (a.nsplit <= 8) merge_row<D, F16, DECODE, 8>(a, r, c, li, a.nsplit, nrows);
-    else merge_row<D, F16, DECODE, 16>(a, r, c, li, a.nsplit, nrows);
+    if (a.nsplit <= 4) merge_row<D, F16, 4>(a, r, c, li, a.nsplit, nrows);
+    else if (a.nsplit <= 8) merge_row<D, F16, 8>(a, r, c, li, a.nsplit, nrows);
+    else merge_row<D, F16, 16>(a, r, c, li, a.nsplit, nrows);
   } else {
     const int ncol = ((a.seqlens_k ? cache_length(a, b) : p.Nk) + 63) / 64;
     if (ncol == 0) {  // (a cache without keys: the split kernel wrote nothing for this sequence)
@@ -974,7 +974,7 @@ __global__ __launch_bounds__(256) void fwd_merge_kernel(FwdArgs a) {
     const int per = split_share_blocks(ncol, (p.Nk + 63) / 64, a.nsplit);
     const int nshare = (ncol + per - 1) / per;
     if (nshare == 1) return;  // the split kernel wrote O and LSE
-    merge_row<D, F16, DECODE, 4>(a, r, c, li, nshare, nrows);
+    merge_row<D, F16, 4>(a, r, c, li, nshare, nrows);
   }
 }
 

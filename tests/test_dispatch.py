@@ -1,9 +1,13 @@
 """The rules that choose a kernel, on the CPU (launches.py)."""
+import shutil
+import subprocess
 import types
 
 import pytest
 
-from launches import cross_bwd, dropout_bwd, launches, mask_bwd, varlen_bwd, varlen_cross_bwd
+import forms
+
+from launches import P, cross_bwd, dropout_bwd, launches, mask_bwd, varlen_bwd, varlen_cross_bwd
 from paper_2307_08691_amd import binding
 
 
@@ -55,3 +59,29 @@ def test_packed_batches_get_the_workspace_that_they_use(lens, Hq, Hkv, d):
     a, b = launches([varlen_bwd(len(lens), x.Tq, max(lens), Hq, Hkv, d, w) for w in (used, bound)])
     assert a == b
     assert any("merge" in k[0] for k in a) <= (used > 4 * x.Tq * Hq + 255)
+
+
+def test_every_backward_kernel_is_launched_by_a_problem_that_runs_on_the_gpu():
+    """The problems of forms.py reach every instantiation of the two-launch kernels, of the one grid and of the short form. Not counted:
+    those that only single stages take (fa_bwd_stages: a dQ kernel that is given D; 128-key blocks at d = 128 under the causal
+    rule) and the grids with shares (test_shares_of_a_block_of_keys)."""
+    if not shutil.which("nm"):
+        pytest.skip("lists the library's kernels with nm")
+    names = subprocess.run(["nm", "-DC", binding.LIB_PATH], capture_output=True, text=True, check=True).stdout.splitlines()
+    kernels = {n.split("fa::", 1)[1].rsplit("(", 1)[0] for n in names if " V " in n and "fa::" in n}
+    args = lambda k: k[k.index("<") + 1:-1].split(", ")
+    want = {k for k in kernels if k.startswith(("bwd_dkdv_kernel", "bwd_short_kernel")) or (k.startswith("bwd_dq_kernel") and args(k)[7] == "true") or
+            (k.startswith("bwd_joint_kernel") and args(k)[11] == "false")}
+    want -= {k for k in want if k.startswith("bwd_dkdv_kernel<128, true, false") and args(k)[8] == "4"}
+    assert len(want) > 300
+    reached = launches([forms.backward_call(*c, f16) for c in forms.cases() for f16 in (False, True)])
+    assert not want - {k[0] for call in reached for k in call}
+
+
+@pytest.mark.parametrize("B,Hkv,d,cap,num_splits", [(33, 8, 64, 512, 1), (33, 8, 128, 512, 1), (11, 8, 128, 1536, 3), (21, 8, 64, 1280, 2)])
+@pytest.mark.parametrize("f16", [False, True])
+def test_many_short_caches_share_a_compute_unit(B, Hkv, d, cap, num_splits, f16):
+    """The problems of test_many_short_paged_caches take the form of two workgroups on a compute unit."""
+    for causal in (False, True):
+        kernels = launches([("fa_kvcache_fwd", [P] * 8 + [1 << 40, B, Hkv, Hkv, 1, cap, d, 64, cap // 64, 0.1, causal, num_splits, 0, f16])])[0]
+        assert kernels[0][0] == f"fwd_decode_kernel<{d}, {str(causal).lower()}, {str(f16).lower()}, true>"

@@ -15,8 +15,8 @@ torch = pytest.importorskip("torch")
 import parity_util as pu  # noqa: E402
 
 
-def draw(seed, B, Nq, cap, Hq, Hkv, d):
-    prob = inputs.make_cross(B=B, Nq=Nq, Nk=cap, Hq=Hq, Hkv=Hkv, d=d, causal=False, seed=seed)
+def draw(seed, B, Nq, cap, Hq, Hkv, d, dtype="bf16"):
+    prob = inputs.make_cross(B=B, Nq=Nq, Nk=cap, Hq=Hq, Hkv=Hkv, d=d, causal=False, seed=seed, dtype=dtype)
     return prob
 
 
@@ -36,7 +36,7 @@ def reference(Q, K_of, V_of, lens, scale, causal, Hq, Hkv):
 
 
 def check_contiguous(prob, lens, causal, num_splits, standard=True):
-    Q, Kc, Vc = (pu.to_gpu(x) for x in (prob.Q, prob.K, prob.V))
+    Q, Kc, Vc = (pu.to_gpu(x, prob.dtype) for x in (prob.Q, prob.K, prob.V))
     cap = Kc.shape[1]
     for b, n in enumerate(lens):  # what lies past a sequence's length is not part of it
         Kc[b, n:] = float("nan")
@@ -44,11 +44,12 @@ def check_contiguous(prob, lens, causal, num_splits, standard=True):
     sl = torch.tensor(lens, dtype=torch.int32, device="cuda")
     O, L = binding.fa_kvcache_fwd(Q, Kc, Vc, prob.scale, causal, seqlens_k=sl, num_splits=num_splits)
     torch.cuda.synchronize()
-    Qf, Kf, Vf = (orc.widen_bf16(x) for x in (prob.Q, prob.K, prob.V))
+    widen = orc.widen_f16 if prob.dtype == "f16" else orc.widen_bf16
+    Qf, Kf, Vf = (widen(x) for x in (prob.Q, prob.K, prob.V))
     eO, eL = orc.kvcache_forward(Qf, Kf, Vf, prob.scale, causal, np.asarray(lens))
     ref = reference(Q, lambda b: Kc[b, :lens[b]], lambda b: Vc[b, :lens[b]], lens, prob.scale, causal, prob.Hq, prob.Hkv)
     pu.judge(f"cache {lens} of {cap} Nq{prob.N} H{prob.Hq}/{prob.Hkv} d{prob.d} {'c' if causal else 'f'} x{num_splits}",
-             {"O": pu.to_f64(O), "LSE": pu.to_f64(L)}, {"O": eO, "LSE": eL}, ref, standard=standard, d=prob.d)
+             {"O": pu.to_f64(O), "LSE": pu.to_f64(L)}, {"O": eO, "LSE": eL}, ref, standard=standard, dtype=prob.dtype, d=prob.d)
     return O, L
 
 
@@ -70,6 +71,25 @@ def test_many_short_caches(B, Nq, Hq, Hkv, cap, num_splits, d, causal):
     lens = [(i * 37) % (cap + 1) for i in range(B)]
     lens[B // 2], lens[B - 1] = cap, 0
     check_contiguous(draw(18050 + B + d, B, Nq, cap, Hq, Hkv, d), lens, causal, num_splits)
+
+
+# (two workgroups on a compute unit, as above, and up to 20 tiles of 32 keys in a share: a wavefront's third tile is the first whose page
+# comes from the lanes; every way of a page lookup with four and eight wavefronts)
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("page", [64, 256])
+@pytest.mark.parametrize("B,Hq,Hkv,d,cap,num_splits", [(33, 16, 8, 64, 512, 1), (33, 16, 8, 128, 512, 1), (11, 16, 8, 128, 1536, 3),
+                                                       (21, 8, 8, 64, 1280, 2)])
+def test_many_short_paged_caches(B, Hq, Hkv, d, cap, num_splits, page, dtype, causal):
+    lens = [(i * 137) % (cap + 1) for i in range(B)]
+    lens[B // 2], lens[B - 1] = cap, 0
+    prob = draw(18070 + B + d, B, 1, cap, Hq, Hkv, d, dtype)
+    O, L = check_contiguous(prob, lens, causal, num_splits)
+    Q, Kc, Vc = (pu.to_gpu(x, dtype) for x in (prob.Q, prob.K, prob.V))
+    Kp, Vp, table = page_out(Kc, Vc, lens, page, 18080 + page)
+    sl = torch.tensor(lens, dtype=torch.int32, device="cuda")
+    O2, L2 = binding.fa_kvcache_fwd(Q, Kp, Vp, prob.scale, causal, seqlens_k=sl, block_table=table, num_splits=num_splits)
+    assert torch.equal(O, O2) and torch.equal(L, L2)
 
 
 def page_out(Kc, Vc, lens, page, seed, spare=3):

@@ -94,8 +94,9 @@ int fa_fwd(const void* Q, const void* K, const void* V, void* O, float* LSE,
  * without dropout, window or mask) take ONE kernel instead, with the same bits; it
  * leaves the workspace untouched. All three outputs are bit-reproducible.
  * Groups of four and more query heads to a key/value head (more than 1200 rows with four, 320 with eight), on grids that leave compute units idle: several workgroups
- * share a block of keys and leave float32 sums of dK and dV behind D, and a further kernel adds them; dK and dV then
- * differ from those of a larger batch, or of the separate stages below, by the rounding of float32 sums. A workspace that
+ * share a block of keys and leave float32 sums of dK and dV behind D, and a further kernel adds them. How many do depends on the
+ * whole call: dK and dV of a sequence then differ by the rounding of float32 sums from those in another batch, beside other
+ * sequences of a pack, with another max_seqlen, with a workspace of D alone or by the separate stages below. A workspace that
  * holds D alone (4 * B * N * Hq bytes, rounded up to 256) is accepted too, and the pass then takes no shares. For
  * groups and lengths as above fa_bwd_workspace_bytes() asks for more, up to 64 MiB, also where the pass then takes no shares
  * (which further depends on how full the grid is); fa_varlen_bwd_workspace_bytes(), which does not know the longest sequence, for
@@ -111,8 +112,7 @@ int fa_bwd(const void* Q, const void* K, const void* V, const void* O, const voi
 /*
  * Profiling aid: the backward as three launches (D pre-pass, dK/dV kernel, dQ kernel)
  * restricted to a subset of them, so that each can be timed on its own. `stages`
- * is a bit mask; all three bits give the results of fa_bwd (which itself folds the
- * pre-pass into the dQ kernel: one launch and one pass over dO fewer) and leave D in the
+ * is a bit mask; all three bits give the results of fa_bwd, by whichever of its forms, and leave D in the
  * workspace like the prep stage alone. Both later stages read the D the prep stage writes, so
  * results are correct only if it ran first on the same arguments. Same validation and errors as
  * fa_bwd; stages == 0 or bits outside the mask return FA_ERR_SHAPE.
@@ -129,9 +129,9 @@ int fa_bwd_stages(const void* Q, const void* K, const void* V, const void* O, co
 /*
  * fa_bwd for callers that cannot allocate device memory or pass a workspace: code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc. Same arguments, results
- * (bit for bit) and errors as fa_bwd, without `workspace`: D = rowsum(dO o O) and the sums of shares go to a
- * file-scope device array (8 MiB for FA_NOALLOC_MAX_ROWS floats of D, 64 MiB for the sums) inside the library, which
- * every GPU the library has run on holds until the process ends. The call itself allocates
+ * (bit for bit) and errors as fa_bwd with a workspace of fa_bwd_workspace_bytes(), without `workspace`: D = rowsum(dO o O) and the
+ * sums of shares go to a file-scope device array (8 MiB for FA_NOALLOC_MAX_ROWS floats of D, 64 MiB for the sums) inside the library.
+ * The runtime loads it with the first such call on a GPU, which holds it until the process ends. The call itself allocates
  * and frees nothing. B * N * Hq above FA_NOALLOC_MAX_ROWS returns FA_ERR_WORKSPACE and nothing
  * runs. The first call on a device looks the array's address up (hipGetSymbolAddress, with
  * that device current; a failure returns FA_ERR_LAUNCH, see fa_last_hip_error()): make that
@@ -218,10 +218,10 @@ int fa_cross_bwd_f16(const void* Q, const void* K, const void* V, const void* O,
  *     keep = byte (key mod 4) of x  >=  round(256 * p_drop)       (threshold capped at 255)
  * so the effective drop probability is a multiple of 1/256, and 1 / (1 - p) uses that
  * multiple. 0 <= p_drop < 1, otherwise FA_ERR_SHAPE; a threshold of 0 runs the plain kernels.
- * Workspace: fa_cross_bwd_workspace_bytes. All outputs are bit-reproducible. Unlike those of the
- * plain entry points, dK and dV at d = 128 are not independent of the batch a sequence is in: on
+ * Workspace: fa_cross_bwd_workspace_bytes. All outputs are bit-reproducible. Beside the
+ * shares of fa_bwd (see there), dK and dV at d = 128 are not independent of the batch a sequence is in: on
  * grids that fit the GPU at once a key's float32 sum is taken in two halves, on larger ones in a
- * single chain, so a 16-bit entry may come out as its neighbour (O, LSE, dQ and d = 64 are
+ * single chain, so a 16-bit entry may come out as its neighbour (O, LSE, dQ and, without shares, d = 64 are
  * independent of it).
  */
 int fa_dropout_fwd(const void* Q, const void* K, const void* V, void* O, float* LSE,

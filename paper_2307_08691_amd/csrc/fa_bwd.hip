@@ -436,8 +436,8 @@ static hipError_t launch_dkdv(const BwdArgs& a, int causal, hipStream_t st) {
 // MI355X, backward: N = 256 250 -> 235 us, N = 512 without the mask 337 -> 326 us, N >= 1024 -1% .. 0).
 template <int D, bool F16>
 static hipError_t launch_bwd_d(const BwdArgs& a, int causal, int stages, hipStream_t st) {
-  // The whole backward is two launches: the dQ kernel goes first and computes D on the way, the dK/dV kernel
-  // follows and reads it.
+  // The whole backward: one launch (short sequences), shares, one grid behind the pre-pass, or two launches, of which the dQ
+  // kernel goes first and computes D on the way and the dK/dV kernel reads it.
   // Short sequences at d = 64 are one launch, which keeps D to itself (its store costs 1% of a short step: 14.4 -> 14.5 us for the
   // forward and backward of 1 x 128, 2 heads): not for a caller that may read D afterwards.
   if constexpr (D == 64)

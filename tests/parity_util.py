@@ -302,7 +302,8 @@ def run_reference(prob: AttnProblem, backward: bool = True):
 
 def large_varlen(d, causal, seed, dtype="bf16") -> AttnProblem:
     """A ragged batch small enough for the oracle whose grids (sized by the longest sequence) hold more than 256 workgroups of
-    256 rows or keys: the kernels take their largest form, in the causal dK/dV kernel at d = 64 past 4096 keys."""
+    256 rows or keys: the forward kernel takes its largest form. (The backward counts the blocks that exist and takes such a batch as one
+    grid; the largest forms of its kernels are in forms.py.)"""
     short = [257, 1, 100, 0, 511, 64, 300, 31, 129, 256, 513, 2, 128, 33, 255]
     longest, Hkv = (4150, 1) if d == 64 and causal else (1100, 4)
     return make_varlen(short[:7] + [longest] + short[7:], Hq=2 * Hkv, Hkv=Hkv, d=d, causal=causal, seed=seed, dtype=dtype)

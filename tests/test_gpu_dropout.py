@@ -199,8 +199,7 @@ def test_ragged_batches_with_dropout(d, Hq, Hkv, causal, dtype):
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 @pytest.mark.parametrize("d", [64, 128])
 def test_ragged_batches_with_dropout_on_large_grids(d, causal, dtype):
-    """The same where the dK/dV kernel has blocks of 256 keys (more than 256 workgroups; past 4096 keys at d = 64 with
-    the mask)."""
+    """The same on grids of more than 256 workgroups by the longest sequence (forms.py has batches whose blocks themselves are as many)."""
     check_ragged_dropout(pu.large_varlen(d=d, causal=causal, seed=6900 + d, dtype=dtype))
 
 
